@@ -180,6 +180,8 @@ void fill_common(Params& p, WorkspaceHead* h, const void* grad, float* residual,
     p.ntiles = (uint32_t)((d + kTile - 1) / kTile);
     p.nfull = (uint32_t)(d / kTile);
     p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;
+    p.tq = p.ntiles / p.nwaves;
+    p.tr = p.ntiles % p.nwaves;
     p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
     p.vec_ok = (gt == kGradF32 ? aligned16(grad) : ((uintptr_t)grad & 7u) == 0) && aligned16(residual);
     p.dist = dist;
@@ -423,9 +425,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
                 cand = theta > 0.0;
             }
         } else {
-            // one source list per wave: the kernel is a chain of dependent round trips per list, and
-            // fewer, longer chains were slower than more blocks (measured: 128 blocks 18 us, 512 blocks 14 us)
-            launch_lists(p, p.nblocks, s);
+            launch_lists(p, s);
             ++k;
             mark("k_lists");
             list_frac = cum * ratios[m - 1];
@@ -823,7 +823,9 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         ds.out_offset = out_offsets[t];
         ds.out_cap = out_offsets[t + 1] - out_offsets[t];
         ds.index = (uint32_t)t;
-        ds.reserved = 0;
+        ds.nwaves = (uint32_t)nwaves;
+        ds.tq = (uint32_t)(ntiles / nwaves);
+        ds.tr = (uint32_t)(ntiles % nwaves);
         for (uint32_t i = 0; i < ds.nblocks; ++i) pl.map[fb + i] = (uint16_t)t;
         for (uint32_t i = 0; i < ds.nfinal; ++i) pl.fmap[ff + i] = (uint16_t)t;
         fb += ds.nblocks;
@@ -1004,20 +1006,6 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     for (int m = 0; m < M; ++m) a.L[m] = log(1.0 / ratios[m]);
     a.use_hint = same_shape ? 1 : 0;
 
-    // The dense stages may prefetch (see launch_compact) if that is safe for every vector: its accumulated values
-    // start on a 16-byte boundary (and its gradient on the boundary the vector path needs), each of its blocks
-    // runs all its waves, and every wave owns the prefetched tiles complete.
-    bool prefetch = true;
-    for (int t = 0; t < n && prefetch; ++t) {
-        const TensorDesc& ds = pl.desc[t];
-        const uint64_t ntiles = (uint64_t)((ds.d + kTile - 1) / kTile), nfull = (uint64_t)(ds.d / kTile);
-        const uint64_t nwaves = (uint64_t)ds.nblocks * kWavesPerBlock;
-        const uintptr_t g = (uintptr_t)grad + (uintptr_t)ds.offset * (gt == kGradF32 ? 4u : 2u);
-        const float* accp = residual ? residual + ds.offset : (a.acc_own ? a.acc_own + ds.offset : nullptr);
-        prefetch = nwaves <= ntiles && nfull / nwaves >= (uint64_t)(kCompactPrefetch * 4 + 1) &&
-                   (g & (gt == kGradF32 ? 15u : 7u)) == 0 && ((uintptr_t)accp & 15u) == 0;
-    }
-
     // same sequence as a single call (see run), every kernel once for all vectors
     a.in = 1;
     a.out = 0;
@@ -1044,7 +1032,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
             }
             a.reverse = reverse ? 1 : 0;
             reverse = !reverse;
-            launch_compact_batched(a, /*stats=*/true, write, prefetch, pl.blocks, s);
+            launch_compact_batched(a, /*stats=*/true, write, pl.blocks, s);
             if (write) {
                 lists = true;
                 cand = theta > 0.0;
@@ -1058,7 +1046,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     bind(M);
     if (!lists) {
         a.reverse = reverse ? 1 : 0;
-        launch_compact_batched(a, /*stats=*/false, /*write=*/true, prefetch, pl.blocks, s);
+        launch_compact_batched(a, /*stats=*/false, /*write=*/true, pl.blocks, s);
         a.in = sel;  // the gather reads what the compaction just wrote
         launch_gather_batched(a, pl.blocks, s);
     } else {

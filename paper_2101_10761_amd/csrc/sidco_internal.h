@@ -90,9 +90,10 @@ struct Params {
     uint32_t ntiles;        // ceil(d / kTile)
     uint32_t nfull;         // d / kTile: tiles below this index are complete
     uint32_t nwaves;        // waves that own tiles
+    uint32_t tq, tr;        // ntiles / nwaves and ntiles % nwaves (see WaveTiles)
     uint32_t nblocks;       // grid size of the kernels that read the dense vector or write partial sums
     int vec_ok;             // all dense buffers aligned for 4-element accesses (16 bytes; 8 for a 16-bit gradient)
-    int reverse;            // a dense stage kernel walks every wave's tiles from the last to the first
+    int reverse;            // a dense stage kernel walks the tiles from the last to the first
     int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
     unsigned long long owner;  // id of the stage controller that makes the call, 0 otherwise
     int dist;
@@ -110,7 +111,7 @@ struct Params {
     uint32_t* cnt_out;
     const uint32_t* blk_in; // [kMaxBlocks] per-block sums of cnt
     uint32_t* blk_out;
-    const int2* seg_in;     // survivor lists (index, value bits); wave w's list starts at tile_begin(w)*kTile
+    const int2* seg_in;     // survivor lists (index, value bits); wave w's list starts at seg_begin(w)
     int2* seg_out;
     int32_t* out_idx;
     float* out_val;
@@ -217,7 +218,8 @@ struct TensorDesc {
     uint32_t first_final;   // ... and in the last stage's grid
     uint32_t nfinal;
     uint32_t index;         // position in out_counts / out_etas
-    uint32_t reserved;
+    uint32_t nwaves;        // waves that own tiles of the vector, and tiles / nwaves, tiles % nwaves
+    uint32_t tq, tr;
 };
 
 struct BatchTable {
@@ -250,7 +252,7 @@ struct BatchArgs {
 };
 
 void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, double* scratch, hipStream_t s);
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool prefetch, uint32_t blocks, hipStream_t s);
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s);
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
 void launch_final_lists_batched(const BatchArgs& a, uint32_t final_blocks, hipStream_t s);
 void launch_gather_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
@@ -258,9 +260,6 @@ void launch_gather_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
 void launch_clear_u32(uint32_t* p, hipStream_t s);
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s);
-// batches of 4 tiles that a dense stage's waves load before their threshold is known and then stay ahead of
-// the batch they process (long vectors only; see compact_dense)
-constexpr int kCompactPrefetch = 1;
 // k_fit's shape for large vectors (see k_fit_flat): one float4 per thread, 256-thread blocks; from the
 // length at which the faster sweep pays for the extra kernel that folds its partial sums
 constexpr int kFlatBlock = 256;
@@ -269,7 +268,7 @@ inline bool fit_uses_flat(int64_t d, bool vec_ok) { return vec_ok && d >= kFlatM
 inline uint32_t fit_flat_blocks(int64_t d) { return (uint32_t)((d / 4 + kFlatBlock - 1) / kFlatBlock); }
 void launch_fit(const Params& p, double* scratch, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, hipStream_t s);
-void launch_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);
+void launch_lists(const Params& p, hipStream_t s);
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);
 void launch_gather(const Params& p, hipStream_t s);
 

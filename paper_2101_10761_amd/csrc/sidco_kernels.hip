@@ -4,7 +4,7 @@
 //
 //   k_fit        acc = g + residual, stored back to residual; per-block fp64 partial sums of
 //                |acc|, acc^2, log2|acc| (whichever the chosen law needs)       [reads 8 B, writes 4 B / element]
-//                Two launch shapes: every wave walks its own contiguous range (short vectors), or
+//                Two launch shapes: every wave walks its own tiles (short vectors), or
 //                k_fit_flat, one float4 per thread in address order, followed by k_fit_reduce, which
 //                folds the per-block sums into the 512 slots the next kernel expects (long vectors,
 //                whose operands come from HBM: that shape streams 15 % faster there).
@@ -17,8 +17,8 @@
 //                (|x| - eta_m) and its square over the exceedances for the next stage's fit, and writes
 //                per-wave lists of the entries above a candidate threshold at or above eta_m - high enough
 //                that the lists stay short, low enough (judged from the fit and from where the previous
-//                call's next threshold fell) that the next stage can select from them alone.  On long
-//                vectors a wave requests tiles before its threshold is known and stays a batch ahead.
+//                call's next threshold fell) that the next stage can select from them alone.  A wave requests
+//                its first tile before its threshold is known and stays a tile ahead.
 //                k_lists: a middle stage whose source is those lists (or, if they turn out not to reach
 //                down to its threshold, the dense acc again): same sums, exact exceedance lists out.
 //                k_final_lists: the last stage for M >= 2; it selects, writes the contiguous
@@ -29,9 +29,9 @@
 //
 // Design rules, from measurement on this chip: same-address atomics serialise at ~11 ns each and a
 // device-scope fence in a write-heavy kernel forces an L2 write-back, so the big kernels have
-// neither.  Kernel boundaries are the only global synchronisation; every wave owns a contiguous
-// range of 256-element tiles and a survivor list at the same offset, so list positions need no
-// atomics, and thresholds, selected set and values are deterministic.
+// neither.  Kernel boundaries are the only global synchronisation; every wave owns every nwaves-th
+// 256-element tile and a survivor list with room for all of them, so list positions need no atomics,
+// and thresholds, selected set and values are deterministic.
 // The *_batched kernels run the same bodies for the vectors of a batch, each block on the vector that a
 // table on the device assigns to it.
 //
@@ -446,27 +446,47 @@ __device__ __forceinline__ float fit_one(const Params& p, int64_t i, double& s1,
     return c;
 }
 
-// One wave's tiles.
+// One wave's tiles.  The wave requests its next tile before it adds up the one it has: one tile (1 KB of each
+// operand) per wave in flight is what 16 waves per CU need to keep HBM busy, and more only widens the window of
+// addresses that the chip works in (see WaveTiles).
 template <int DIST, bool EC, int GT>
 __device__ __forceinline__ void fit_wave(const Params& p, uint32_t w, int lane, double& s1, double& s2, double& sl,
                                          int& se)
 {
-    const uint32_t t0 = tile_begin(w, p.ntiles, p.nwaves), t1 = tile_begin(w + 1, p.ntiles, p.nwaves);
-    const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;  // tiles [t0,tf) are complete
-    uint32_t t = t0;
-    if (p.vec_ok) {
+    constexpr bool WRITE = EC || GT != kGradF32;
+    const WaveTiles wt = wave_tiles(p, w);
+    uint32_t k = 0;
+    if (p.vec_ok && wt.full > 0) {
         f4* a4 = reinterpret_cast<f4*>(p.acc_w);
-        // no second register buffer: with 16 waves per CU in flight it gained nothing (measured)
+        size_t i = (size_t)w * 64 + lane;
+        const size_t step = (size_t)wt.W * 64;
+        f4 g = load_grad4<GT, WRITE>(p.grad, i), r = {};
+        if (EC) r = a4[i];
+        auto add_up = [&](f4 c) {
+            fit_accum<DIST>(c.x, s1, s2, sl, se);
+            fit_accum<DIST>(c.y, s1, s2, sl, se);
+            fit_accum<DIST>(c.z, s1, s2, sl, se);
+            fit_accum<DIST>(c.w, s1, s2, sl, se);
+        };
 #pragma unroll 1
-        for (; t + 4 <= tf; t += 4) fit_tiles<DIST, EC, GT, 4>(p.grad, a4, t, lane, s1, s2, sl, se);
-#pragma unroll 1
-        for (; t < tf; ++t) fit_tiles<DIST, EC, GT, 1>(p.grad, a4, t, lane, s1, s2, sl, se);
+        for (k = 1; k < wt.full; ++k) {
+            f4 c = g;
+            if (EC) c = g + r;
+            g = load_grad4<GT, WRITE>(p.grad, i + step);
+            if (EC) r = a4[i + step];
+            if (WRITE) a4[i] = c;
+            add_up(c);
+            i += step;
+        }
+        if (EC) g = g + r;
+        if (WRITE) a4[i] = g;
+        add_up(g);
     }
     // unaligned buffers and the ragged last tile: guarded scalar accesses
-    for (; t < t1; ++t) {
+    for (; k < wt.n; ++k) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t i = (int64_t)t * kTile + lane * 4 + j;
+            const int64_t i = (int64_t)(w + k * wt.W) * kTile + lane * 4 + j;
             if (i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
         }
     }
@@ -503,7 +523,7 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b)
 // ---------------------------------------------------------------------------------------------
 // k_fit_flat + k_fit_reduce: the same pass for large vectors.  One float4 per thread and a grid that
 // covers the vector in address order: the blocks in flight at any time touch one narrow window of each
-// buffer, which DRAM serves better than the 3 x 4096 separate streams of the per-wave ranges when
+// buffer, which DRAM serves better than the 3 x 4096 separate streams of contiguous per-wave ranges when
 // the operands come from HBM (measured with a gradient and a residual that no cache holds: 52.9 us
 // against 62.5 us at d = 25.6 M, 129 us against 156 us at 66 M, i.e. what a plain in-place add reaches;
 // with a residual that is still in the memory-side cache from the previous call the per-wave shape is
@@ -600,95 +620,79 @@ __device__ __forceinline__ void emit(bool valid, float x, int32_t idx, float eta
     }
 }
 
-// U complete tiles of the dense vector, already loaded
-template <bool STATS, bool WRITE, int U>
-__device__ __forceinline__ void compact_loaded(const f4* a, uint32_t t, int lane, float eta_s, float eta_w,
-                                               ListWriter& lw, uint32_t& ns, double& sy, double& syy)
+// one complete tile of the dense vector, already loaded
+template <bool STATS, bool WRITE>
+__device__ __forceinline__ void compact_tile(f4 a, uint32_t t, int lane, float eta_s, float eta_w, ListWriter& lw,
+                                             uint32_t& ns, double& sy, double& syy)
 {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int32_t i0 = (int32_t)((t + u) * kTile + lane * 4);
-        emit<STATS, WRITE>(true, a[u].x, i0 + 0, eta_s, eta_w, lw, lane, ns, sy, syy);
-        emit<STATS, WRITE>(true, a[u].y, i0 + 1, eta_s, eta_w, lw, lane, ns, sy, syy);
-        emit<STATS, WRITE>(true, a[u].z, i0 + 2, eta_s, eta_w, lw, lane, ns, sy, syy);
-        emit<STATS, WRITE>(true, a[u].w, i0 + 3, eta_s, eta_w, lw, lane, ns, sy, syy);
-        if (WRITE) list_flush(lw, lane);
-    }
+    const int32_t i0 = (int32_t)(t * kTile + lane * 4);
+    emit<STATS, WRITE>(true, a.x, i0 + 0, eta_s, eta_w, lw, lane, ns, sy, syy);
+    emit<STATS, WRITE>(true, a.y, i0 + 1, eta_s, eta_w, lw, lane, ns, sy, syy);
+    emit<STATS, WRITE>(true, a.z, i0 + 2, eta_s, eta_w, lw, lane, ns, sy, syy);
+    emit<STATS, WRITE>(true, a.w, i0 + 3, eta_s, eta_w, lw, lane, ns, sy, syy);
+    if (WRITE) list_flush(lw, lane);
 }
 
-// Plain (L2-allocating) loads: the next pass over the dense vector, if any, starts with what this one read last.
-template <int U>
-__device__ __forceinline__ void load_tiles(f4 (&a)[U], const f4* __restrict__ x4, uint32_t t, int lane)
+// The sweep of one wave over its tiles of the dense vector.  p.reverse walks them from the last to the first: the
+// kernel before this one left the end of what it touched last in the caches, and the host alternates the
+// direction from pass to pass so that each pass starts where the one before it stopped.
+// The loads are non-temporal: the vector has just been written by k_fit and much of it is still dirty in the
+// memory-side cache; reads that do not allocate behind it neither push those lines out early nor wait for them
+// (k_fit_flat and a statistics-only sweep together, plain against non-temporal loads: 65.7 and 63.9 us at 25.6 M
+// elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).
+struct DenseSweep {
+    const f4* x4;     // the dense vector, or a readable stand-in if the wave has no complete tile
+    uint32_t nb;      // complete tiles of the wave
+    uint32_t first;   // the first tile in walking order
+    int32_t step;     // from one tile to the next in walking order
+};
+
+__device__ __forceinline__ DenseSweep dense_sweep(const Params& p, const WaveTiles& wt)
 {
-#pragma unroll
-    for (int u = 0; u < U; ++u) a[u] = x4[(size_t)(t + u) * 64 + lane];
+    DenseSweep d;
+    d.nb = p.vec_ok ? wt.full : 0;
+    d.x4 = d.nb > 0 ? reinterpret_cast<const f4*>(p.acc) : reinterpret_cast<const f4*>(p.seg_out);
+    d.first = d.nb > 0 ? (p.reverse ? wt.w + (d.nb - 1) * wt.W : wt.w) : 0u;
+    d.step = p.reverse ? -(int32_t)wt.W : (int32_t)wt.W;
+    return d;
 }
 
-// Tiles [t0, t1) of the dense vector (complete below tf).  p.reverse walks them from the last to the
-// first: the kernel before this one left the end of what it touched last in L2 (32 MB over the chip),
-// and the host alternates the direction from pass to pass so that each pass starts where the one
-// before it stopped (measured: 15.5 us instead of 18.3 us for 102 MB right after k_fit).
-// Batches of U tiles.  The caller has loaded the first PRE batches already, into a[0 .. PRE*U), while it
-// still waited for its threshold: a stage kernel's prologue is a cold round trip for the partial sums
-// plus a few hundred dependent fp64 instructions, 4-5 us in which the memory pipes would otherwise run
-// dry after the first batch.  PRE is a template parameter and the caller's loads are unconditional:
-// loads under a run-time condition come with copies that the compiler waits for on the spot.
-// After them the wave stays PRE batches ahead: the request for batch k + PRE goes out
-// before batch k is processed, into the last register batch, and the batches move up by register copies
-// once batch k is done - one copy of the loop body (two inlined copies cost more in code size and
-// registers than they gained).  Measured against load-then-process steps with two prefetched batches:
-// 1-2 us less per dense stage at 14.7 M to 66 M elements, nothing at 138 M, where the stage is bound by
-// what the memory system still has to write back for the pass before it.
-__device__ __forceinline__ uint32_t dense_batch_tile(const Params& p, uint32_t t0, uint32_t tf, uint32_t U, uint32_t k)
+// Tile number j in walking order.  Past the wave's last tile the same tile 0 for every wave: the load is
+// unconditional (loads under a run-time condition come with waits on the spot), but costs no HBM traffic.
+__device__ __forceinline__ f4 dense_load(const DenseSweep& d, uint32_t j, int lane)
 {
-    return p.reverse ? tf - (k + 1) * U : t0 + k * U;
+    const uint32_t t = j < d.nb ? d.first + (uint32_t)((int32_t)j * d.step) : 0u;
+    return __builtin_nontemporal_load(d.x4 + (size_t)t * 64 + lane);
 }
 
-// register batches a wave holds: the PRE prefetched ones and the one in flight behind them
-constexpr int dense_batches(int PRE) { return PRE > 0 ? PRE + 1 : 1; }
+// `a` holds the wave's first kAhead tiles, requested before the threshold was known: a stage kernel's prologue is
+// a cold round trip for the partial sums plus a few hundred dependent fp64 instructions in which the memory pipes
+// would otherwise run dry.  From then on tile j + kAhead is requested before tile j is processed.
+// One tile (1 KB per wave, 16 KB per CU) is enough: 1, 2 and 4 measured alike at 14.7 M, 25.6 M and 138 M elements.
+constexpr int kAhead = 1;
 
-template <bool STATS, bool WRITE, int U, int PRE>
-__device__ __forceinline__ void compact_dense(const Params& p, f4 (&a)[dense_batches(PRE) * U], uint32_t t0, uint32_t t1,
-                                              uint32_t tf, int lane, float eta_s, float eta_w, ListWriter& lw,
-                                              uint32_t& ns, double& sy, double& syy)
+template <bool STATS, bool WRITE>
+__device__ __forceinline__ void compact_dense(const Params& p, const WaveTiles& wt, const DenseSweep& d, f4 (&a)[kAhead],
+                                              int lane, float eta_s, float eta_w, ListWriter& lw, uint32_t& ns, double& sy,
+                                              double& syy)
 {
-    const f4* __restrict__ x4 = reinterpret_cast<const f4*>(p.acc);
-    uint32_t ts = t0;  // tiles [ts, t1) take guarded scalar loads: unaligned buffers, the ragged last tile
-    if (p.vec_ok) {
-        const uint32_t nb = (tf - t0) / U, rem = (tf - t0) - nb * U;
-#pragma unroll 1  // unrolled, the batches' loads pile up in registers and halve the occupancy
-        for (uint32_t k = 0; k < nb; ++k) {
-            const uint32_t t = dense_batch_tile(p, t0, tf, U, k);
-            if constexpr (PRE > 0) {
-                // Batch k + PRE is requested before batch k is processed, so the wave keeps a batch in flight
-                // while it computes (per-wave time max(latency, arithmetic) instead of their sum).  The load is
-                // unconditional - the last batches are requested again, from L2, instead of a load under a
-                // condition - and lands in the last register batch; the batches move up once batch k is done.
-                const uint32_t kn = k + PRE < nb ? k + PRE : nb - 1;
-                const uint32_t tn = dense_batch_tile(p, t0, tf, U, kn);
+#pragma unroll 1
+    for (uint32_t j = 0; j < d.nb; j += kAhead) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) a[PRE * U + u] = x4[(size_t)(tn + u) * 64 + lane];
-                compact_loaded<STATS, WRITE, U>(a, t, lane, eta_s, eta_w, lw, ns, sy, syy);
-#pragma unroll
-                for (int u = 0; u < PRE * U; ++u) a[u] = a[u + U];
-            } else {
-#pragma unroll
-                for (int u = 0; u < U; ++u) a[u] = x4[(size_t)(t + u) * 64 + lane];
-                compact_loaded<STATS, WRITE, U>(a, t, lane, eta_s, eta_w, lw, ns, sy, syy);
+        for (int u = 0; u < kAhead; ++u) {
+            if (j + u < d.nb) {  // wave-uniform
+                const f4 c = a[u];
+                a[u] = dense_load(d, j + u + kAhead, lane);
+                compact_tile<STATS, WRITE>(c, d.first + (uint32_t)((int32_t)(j + u) * d.step), lane, eta_s, eta_w, lw, ns, sy,
+                                           syy);
             }
         }
-        const uint32_t tr = p.reverse ? t0 : t0 + nb * U;
-        for (uint32_t t = tr; t < tr + rem; ++t) {
-            f4 one[1];
-            load_tiles<1>(one, x4, t, lane);
-            compact_loaded<STATS, WRITE, 1>(one, t, lane, eta_s, eta_w, lw, ns, sy, syy);
-        }
-        ts = tf;
     }
-    for (uint32_t t = ts; t < t1; ++t) {
+    // unaligned buffers and the ragged last tile: guarded scalar accesses
+    for (uint32_t k = d.nb; k < wt.n; ++k) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t i = (int64_t)t * kTile + lane * 4 + j;
+            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + lane * 4 + j;
             const bool valid = i < p.d;
             const float v = valid ? p.acc[i] : 0.0f;
             emit<STATS, WRITE>(valid, v, (int32_t)i, eta_s, eta_w, lw, lane, ns, sy, syy);
@@ -760,37 +764,26 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
 // k_compact: a stage that reads the dense vector.  STATS: form the sums for the next stage's fit.
 // WRITE: append the entries above eta_w to this stage's lists (eta_w = eta_m, or a candidate threshold
 // above it); a stage whose candidates would still be a large fraction only counts and sums.
-// PRE: batches of U tiles that every wave loads before the prologue; the host picks PRE > 0 only when the
-// vector is aligned for 4-element accesses and every wave owns at least PRE * U complete tiles.
-template <bool STATS, bool WRITE, int PRE>
+template <bool STATS, bool WRITE>
 __device__ __forceinline__ void compact_body(const Params& p, Blk b)
 {
     __shared__ double sh[kWavesPerBlock][4];
     __shared__ uint32_t sh_cnt[kWavesPerBlock];
     __shared__ int2 ring[WRITE ? kWavesPerBlock : 1][kRingSize];
-    constexpr int U = 4;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     const uint32_t w = b.id * kWavesPerBlock + wib;
     const bool active = w < p.nwaves;
-    const uint32_t t0 = active ? tile_begin(w, p.ntiles, p.nwaves) : 0;
-    const uint32_t t1 = active ? tile_begin(w + 1, p.ntiles, p.nwaves) : 0;
-    const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;  // tiles [t0,tf) are complete
+    const WaveTiles wt = wave_tiles(p, active ? w : 0);
 
     // Neither the prologue's own loads nor the first loads of the body depend on the threshold.  The
     // prologue's go first (the memory counter retires in order: behind the tiles they would wait for
-    // them), then the first batches of tiles, so that the stream runs while the partial sums are reduced
-    // and the closed form is evaluated.
+    // them), then the first tiles, so that the stream runs while the partial sums are reduced and the
+    // closed form is evaluated.
     PrologueLoads g = prologue_load(p, b, false);
-    f4 a0[dense_batches(PRE) * U];
-    if constexpr (PRE > 0) {
-        const f4* __restrict__ x4 = reinterpret_cast<const f4*>(p.acc);
+    const DenseSweep d = dense_sweep(p, wt);
+    f4 a[kAhead];
 #pragma unroll
-        for (int k = 0; k < PRE; ++k) {
-            const uint32_t t = dense_batch_tile(p, t0, tf, U, k);
-#pragma unroll
-            for (int u = 0; u < U; ++u) a0[k * U + u] = x4[(size_t)(t + u) * 64 + lane];
-        }
-    }
+    for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
 
     const StageEta se = prologue_finish(p, b, false, g, sh);
 
@@ -798,10 +791,10 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b)
     double sy = 0.0, syy = 0.0;
     if (active) {
         ListWriter lw;
-        lw.list = p.seg_out + (size_t)t0 * kTile;  // room for every element of the wave's tiles
+        lw.list = p.seg_out + seg_begin(p, w);  // room for every element of the wave's tiles
         lw.ring = ring[WRITE ? wib : 0];
         lw.run = lw.fill = 0;
-        compact_dense<STATS, WRITE, U, PRE>(p, a0, t0, t1, tf, lane, se.eta, se.eta_w, lw, ns, sy, syy);
+        compact_dense<STATS, WRITE>(p, wt, d, a, lane, se.eta, se.eta_w, lw, ns, sy, syy);
         if (WRITE) run = list_finish(lw, lane);
         if (lane == 0) p.cnt_out[w] = run;
     }
@@ -812,81 +805,57 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b)
 // k_lists: a stage m < M whose source is the producer's survivor lists, or, if those are candidate
 // lists that do not reach down to this stage's threshold (see stage_prologue), the dense vector.
 // The lists are short (a few per cent of the vector at most) and the kernel is bound by latency and
-// by the launch itself, so the host sizes the grid to the expected list volume: block b takes the
-// source lists [b * per_block, (b + 1) * per_block), wave i of it every 8th of those, and writes one
-// output list per source list, in the same per-wave segments.  The first 128 entries of a wave's
-// first kListGroup lists are loaded before the prologue.
+// by the launch itself: every wave takes the list of the same wave of the kernel before it, and its
+// first 128 entries are loaded before the prologue.
 // ---------------------------------------------------------------------------------------------
-constexpr int kListGroup = 4;
-
 __device__ __forceinline__ void lists_body(const Params& p, Blk b)
 {
     __shared__ double sh[kWavesPerBlock][4];
     __shared__ uint32_t sh_cnt[kWavesPerBlock];
     __shared__ int2 ring[kWavesPerBlock][kRingSize];
-    constexpr int K = kListGroup, U = 4;
+    constexpr int U = 4;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const uint32_t per_block = (p.nwaves + b.n - 1) / b.n;
-    const uint32_t first = b.id * per_block + wib;
-    const uint32_t last = min(p.nwaves, (b.id + 1) * per_block);
-
-    uint32_t n0[K];
-    int4 q0[K];
-#pragma unroll
-    for (int k = 0; k < K; ++k) {
-        const uint32_t sw = first + k * kWavesPerBlock;
-        const bool valid = sw < last;
-        const uint32_t t0 = valid ? tile_begin(sw, p.ntiles, p.nwaves) : 0;
-        const uint32_t t1 = valid ? tile_begin(sw + 1, p.ntiles, p.nwaves) : 0;
-        n0[k] = valid ? p.cnt_in[sw] : 0u;
-        q0[k] = (uint32_t)lane < (t1 - t0) * (kTile / 2)
-                    ? reinterpret_cast<const int4*>(p.seg_in + (size_t)t0 * kTile)[lane]
-                    : make_int4(0, 0, 0, 0);
-    }
+    const uint32_t w = b.id * kWavesPerBlock + wib;
+    const bool active = w < p.nwaves;
+    const size_t seg = seg_begin(p, active ? w : 0);
+    const int4* __restrict__ src4 = reinterpret_cast<const int4*>(p.seg_in + seg);
+    const uint32_t cap2 = seg_slots(p, active ? w : 0) / 2;  // at least 128: a wave owns a tile
+    uint32_t n_in = active ? p.cnt_in[w] : 0u;
+    const int4 q0 = src4[lane];
 
     const StageEta se = stage_prologue(p, b, true, sh);
     const float eta = se.eta;
 
     uint32_t ns = 0;
     double sy = 0.0, syy = 0.0;
-    for (uint32_t g = first, grp = 0; g < last; g += K * kWavesPerBlock, ++grp) {
+    if (active) {
+        ListWriter lw;
+        lw.list = p.seg_out + seg;
+        lw.ring = ring[wib];
+        lw.run = lw.fill = 0;
+        if (!se.lists_ok) {
+            // this stage's exceedances straight from the dense vector
+            const WaveTiles wt = wave_tiles(p, w);
+            const DenseSweep d = dense_sweep(p, wt);
+            f4 a[kAhead];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const uint32_t sw = g + k * kWavesPerBlock;
-            if (sw >= last) break;  // wave-uniform
-            const uint32_t t0 = tile_begin(sw, p.ntiles, p.nwaves), t1 = tile_begin(sw + 1, p.ntiles, p.nwaves);
-            ListWriter lw;
-            lw.list = p.seg_out + (size_t)t0 * kTile;
-            lw.ring = ring[wib];
-            lw.run = lw.fill = 0;
-            if (!se.lists_ok) {
-                // this stage's exceedances straight from the dense vector
-                f4 unused[U];
-                const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;
-                compact_dense<true, true, U, 0>(p, unused, t0, t1, tf, lane, eta, eta, lw, ns, sy, syy);
-            } else {
-                const int4* __restrict__ src4 = reinterpret_cast<const int4*>(p.seg_in + (size_t)t0 * kTile);
-                const uint32_t cap2 = (t1 - t0) * (kTile / 2);
-                const uint32_t n_in = __builtin_amdgcn_readfirstlane(grp == 0 ? n0[k] : p.cnt_in[sw]);
-                const uint32_t nslot = (n_in + 1) / 2;
-                // slots [0, 64): prefetched for the first group
-                {
-                    int4 q = q0[k];
-                    if (grp != 0) q = (uint32_t)lane < cap2 ? src4[lane] : make_int4(0, 0, 0, 0);
-                    const uint32_t e = 2 * lane;
-                    emit<true, true>(e < n_in, __int_as_float(q.y), q.x, eta, eta, lw, lane, ns, sy, syy);
-                    emit<true, true>(e + 1 < n_in, __int_as_float(q.w), q.z, eta, eta, lw, lane, ns, sy, syy);
-                }
-                // the rest, 256 slots per step
-                for (uint32_t c = 64; c < nslot; c += 64 * U) {
-                    int4 q[U];
-                    load_slots<U>(q, src4, c, cap2, lane);
-                    compact_slots<true, U>(q, c, n_in, lane, eta, lw, ns, sy, syy);
-                }
+            for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
+            compact_dense<true, true>(p, wt, d, a, lane, eta, eta, lw, ns, sy, syy);
+        } else {
+            n_in = __builtin_amdgcn_readfirstlane(n_in);
+            const uint32_t nslot = (n_in + 1) / 2;
+            const uint32_t e = 2 * lane;
+            emit<true, true>(e < n_in, __int_as_float(q0.y), q0.x, eta, eta, lw, lane, ns, sy, syy);
+            emit<true, true>(e + 1 < n_in, __int_as_float(q0.w), q0.z, eta, eta, lw, lane, ns, sy, syy);
+            // the rest, 256 slots per step
+            for (uint32_t c = 64; c < nslot; c += 64 * U) {
+                int4 q[U];
+                load_slots<U>(q, src4, c, cap2, lane);
+                compact_slots<true, U>(q, c, n_in, lane, eta, lw, ns, sy, syy);
             }
-            const uint32_t n_out = list_finish(lw, lane);
-            if (lane == 0) p.cnt_out[sw] = n_out;
         }
+        const uint32_t n_out = list_finish(lw, lane);
+        if (lane == 0) p.cnt_out[w] = n_out;
     }
     stage_epilogue<true>(p, b, lane, wib, ns, sy, syy, sh, sh_cnt);
 }
@@ -914,11 +883,10 @@ struct FinalList {
 __device__ __forceinline__ FinalList final_list(const Params& p, uint32_t sw, bool valid)
 {
     FinalList l;
-    const uint32_t t0 = valid ? tile_begin(sw, p.ntiles, p.nwaves) : 0;
-    const uint32_t t1 = valid ? tile_begin(sw + 1, p.ntiles, p.nwaves) : 0;
-    l.src4 = reinterpret_cast<const int4*>(p.seg_in + (size_t)t0 * kTile);
-    l.cap2 = (t1 - t0) * (kTile / 2);
-    l.n = valid ? p.cnt_in[sw] : 0u;
+    const uint32_t w = valid ? sw : 0;
+    l.src4 = reinterpret_cast<const int4*>(p.seg_in + seg_begin(p, w));
+    l.cap2 = seg_slots(p, w) / 2;
+    l.n = valid ? p.cnt_in[w] : 0u;
     return l;
 }
 
@@ -955,13 +923,14 @@ __device__ __forceinline__ void final_emit(const Params& p, int4 q, uint32_t slo
 // Dense fallback of the two passes: the elements of source wave sw's tiles, 64 consecutive ones per step.
 __device__ __forceinline__ uint32_t final_count_dense(const Params& p, uint32_t sw, int lane, float eta)
 {
-    const int64_t b0 = (int64_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
-    const int64_t b1 = (int64_t)tile_begin(sw + 1, p.ntiles, p.nwaves) * kTile;
+    const WaveTiles wt = wave_tiles(p, sw);
     uint32_t c = 0;
-    for (int64_t b = b0; b < b1 && b < p.d; b += 64) {
-        const int64_t i = b + lane;
-        const bool sel = i < p.d && __builtin_fabsf(p.acc[i < p.d ? i : 0]) > eta;
-        c += (uint32_t)__popcll(__ballot(sel));
+    for (uint32_t k = 0; k < wt.n; ++k) {
+        for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
+            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane;
+            const bool sel = i < p.d && __builtin_fabsf(p.acc[i < p.d ? i : 0]) > eta;
+            c += (uint32_t)__popcll(__ballot(sel));
+        }
     }
     return c;
 }
@@ -969,20 +938,21 @@ __device__ __forceinline__ uint32_t final_count_dense(const Params& p, uint32_t 
 __device__ __forceinline__ void final_emit_dense(const Params& p, uint32_t sw, int lane, float eta,
                                                  unsigned long long cap, unsigned long long& pos)
 {
-    const int64_t b0 = (int64_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
-    const int64_t b1 = (int64_t)tile_begin(sw + 1, p.ntiles, p.nwaves) * kTile;
-    for (int64_t b = b0; b < b1 && b < p.d; b += 64) {
-        const int64_t i = b + lane;
-        const float x = i < p.d ? p.acc[i] : 0.0f;
-        const bool sel = i < p.d && __builtin_fabsf(x) > eta;
-        const unsigned long long mask = __ballot(sel);
-        const unsigned long long at = pos + lane_prefix(mask);
-        if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
-            p.out_idx[at] = (int32_t)i;
-            p.out_val[at] = x;
-            if (p.residual) p.residual[i] = 0.0f;
+    const WaveTiles wt = wave_tiles(p, sw);
+    for (uint32_t k = 0; k < wt.n; ++k) {
+        for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
+            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane;
+            const float x = i < p.d ? p.acc[i] : 0.0f;
+            const bool sel = i < p.d && __builtin_fabsf(x) > eta;
+            const unsigned long long mask = __ballot(sel);
+            const unsigned long long at = pos + lane_prefix(mask);
+            if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
+                p.out_idx[at] = (int32_t)i;
+                p.out_val[at] = x;
+                if (p.residual) p.residual[i] = 0.0f;
+            }
+            pos += (unsigned long long)__popcll(mask);
         }
-        pos += (unsigned long long)__popcll(mask);
     }
 }
 
@@ -1090,10 +1060,8 @@ __device__ __forceinline__ void gather_body(const Params& p, Blk b)
     const unsigned long long c = t < p.nblocks ? (unsigned long long)p.blk_in[t] : 0ull;
     uint32_t mine = (lane < wib && w0 + lane < p.nwaves) ? p.cnt_in[w0 + lane] : 0u;
     uint32_t n_in = active ? p.cnt_in[w] : 0u;
-    const int2* __restrict__ src = p.seg_in + (size_t)(active ? tile_begin(w, p.ntiles, p.nwaves) : 0) * kTile;
-    const uint32_t cap_w = active ? (tile_begin(w + 1, p.ntiles, p.nwaves) - tile_begin(w, p.ntiles, p.nwaves)) * kTile : 0;
-    int2 first = make_int2(0, 0);
-    if ((uint32_t)lane < cap_w) first = src[lane];
+    const int2* __restrict__ src = p.seg_in + seg_begin(p, active ? w : 0);
+    const int2 first = src[lane];
 
     // exclusive prefix of the per-block counts at this block, and their total
     unsigned long long below = wave_sum_u64(t < b.id ? c : 0ull);
@@ -1198,7 +1166,9 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.d = ds.d;
     p.ntiles = (uint32_t)((ds.d + kTile - 1) / kTile);
     p.nfull = (uint32_t)(ds.d / kTile);
-    p.nwaves = ds.nblocks * kWavesPerBlock < p.ntiles ? ds.nblocks * kWavesPerBlock : p.ntiles;
+    p.nwaves = ds.nwaves;
+    p.tq = ds.tq;
+    p.tr = ds.tr;
     p.nblocks = ds.nblocks;
     p.vec_ok = ((uintptr_t)p.grad & (a.gt == kGradF32 ? 15u : 7u)) == 0 && ((uintptr_t)p.acc_w & 15u) == 0;
     p.reverse = a.reverse;
@@ -1242,8 +1212,8 @@ __device__ __forceinline__ void block_tiles(const Params& p, Blk b, uint32_t& T0
 
 template <int DIST, bool EC, int GT>
 __global__ __launch_bounds__(kBlock, 4) void k_fit(Params p) { fit_body<DIST, EC, GT>(p, whole_grid()); }
-template <bool STATS, bool WRITE, int PRE>
-__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p) { compact_body<STATS, WRITE, PRE>(p, whole_grid()); }
+template <bool STATS, bool WRITE>
+__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p) { compact_body<STATS, WRITE>(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock, 4) void k_lists(Params p) { lists_body(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock) void k_final_lists(Params p) { final_body(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock) void k_gather(Params p) { gather_body(p, whole_grid()); }
@@ -1336,12 +1306,12 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a, cons
     }
 }
 
-template <bool STATS, bool WRITE, int PRE>
+template <bool STATS, bool WRITE>
 __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
 {
     Blk b;
     const Params p = batch_params(a, false, b);
-    compact_body<STATS, WRITE, PRE>(p, b);
+    compact_body<STATS, WRITE>(p, b);
 }
 __global__ __launch_bounds__(kBlock, 4) void k_lists_batched(BatchArgs a)
 {
@@ -1421,30 +1391,17 @@ void launch_fit(const Params& p, double* scratch, hipStream_t s)
     }
 }
 
-template <int PRE>
-static void launch_compact_pre(const Params& p, bool stats, bool write, hipStream_t s)
-{
-    const dim3 grid(p.nblocks), block(kBlock);
-    if (stats && write) hipLaunchKernelGGL((k_compact<true, true, PRE>), grid, block, 0, s, p);
-    else if (stats) hipLaunchKernelGGL((k_compact<true, false, PRE>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_compact<false, true, PRE>), grid, block, 0, s, p);
-}
-
 void launch_compact(const Params& p, bool stats, bool write, hipStream_t s)
 {
-    // Prefetch before the prologue only where every wave has that many complete tiles to itself: a wave owns
-    // at least floor(nfull / nwaves) tiles, and the last wave's last tile may be the incomplete one, which a
-    // whole-tile load must not touch - hence one tile more than the prefetched batches hold.
-    const uint32_t per_wave = p.nwaves ? p.nfull / p.nwaves : 0;
-    if (p.vec_ok && p.nwaves == (uint32_t)kMaxWaves && per_wave >= (uint32_t)(kCompactPrefetch * 4 + 1))
-        launch_compact_pre<kCompactPrefetch>(p, stats, write, s);
-    else
-        launch_compact_pre<0>(p, stats, write, s);
+    const dim3 grid(p.nblocks), block(kBlock);
+    if (stats && write) hipLaunchKernelGGL((k_compact<true, true>), grid, block, 0, s, p);
+    else if (stats) hipLaunchKernelGGL((k_compact<true, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_compact<false, true>), grid, block, 0, s, p);
 }
 
-void launch_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
+void launch_lists(const Params& p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_lists, dim3(grid_blocks), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_lists, dim3(p.nblocks), dim3(kBlock), 0, s, p);
 }
 
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
@@ -1509,21 +1466,12 @@ void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t f
     }
 }
 
-template <int PRE>
-static void launch_compact_batched_pre(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s)
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s)
 {
     const dim3 grid(blocks), block(kBlock);
-    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true, PRE>), grid, block, 0, s, a);
-    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, PRE>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_compact_batched<false, true, PRE>), grid, block, 0, s, a);
-}
-
-// `prefetch`: every vector of the batch meets launch_compact's condition (aligned, all waves of its blocks in
-// use, enough complete tiles per wave), so the dense stage may request tiles before its threshold is known
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool prefetch, uint32_t blocks, hipStream_t s)
-{
-    if (prefetch) launch_compact_batched_pre<kCompactPrefetch>(a, stats, write, blocks, s);
-    else launch_compact_batched_pre<0>(a, stats, write, blocks, s);
+    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true>), grid, block, 0, s, a);
+    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_compact_batched<false, true>), grid, block, 0, s, a);
 }
 
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s)

@@ -1,0 +1,40 @@
+"""GPU parity where the split of the vector into waves' tiles changes shape: fewer tiles than waves, one tile, a tile
+more or less than a whole round of 4096 waves, an incomplete last tile owned by the first, a middle or the last wave."""
+import numpy as np
+import pytest
+
+from gpu_harness import check_parity, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+ROUND = 4096 * 256  # elements of one tile for every wave
+
+
+@pytest.mark.parametrize("d", [1, 255, 256, 257, 8 * 256 + 1, ROUND - 256, ROUND - 1, ROUND, ROUND + 1, ROUND + 257,
+                               2 * ROUND + 100, 3 * ROUND - 255])
+@pytest.mark.parametrize("dist,delta,stages", [(0, 0.02, 1), (2, 0.01, 3), (1, 0.002, 2)])
+def test_edges_of_the_tile_split(oracle, d, dist, delta, stages):
+    rng = np.random.default_rng(d + dist)
+    ratios = oracle.schedule(delta, stages, 0.25)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual in (r, None):
+        out = run_gpu(g, residual, dist, ratios)
+        check_parity(oracle, g, residual, dist, ratios, out, label=f"d={d} dist={dist} M={stages} ec={residual is not None}")
+
+
+@pytest.mark.parametrize("d", [ROUND + 257, 2 * ROUND - 1])
+@pytest.mark.parametrize("stages", [2, 3])
+def test_dense_fallback_walks_the_same_tiles(oracle, d, stages):
+    """Candidate lists that start above the next threshold: the stages behind the dense one read the vector again."""
+    import paper_2101_10761_amd as sidco
+    rng = np.random.default_rng(d + stages)
+    g = rng.uniform(-1e-3, 1e-3, size=d).astype(np.float32)   # far lighter tail than the fitted law
+    ratios = oracle.schedule(0.001, stages, 0.25)
+    sidco.sidco_set_speculation(1.0)
+    try:
+        out = run_gpu(g, None, 0, ratios)
+    finally:
+        sidco.sidco_set_speculation(0.5)
+    assert out.status & sidco.ST_FALLBACK
+    check_parity(oracle, g, None, 0, ratios, out, label=f"fallback d={d} M={stages}")
