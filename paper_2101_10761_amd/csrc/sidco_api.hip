@@ -23,9 +23,9 @@ constexpr uint32_t kFinalLists = 32;  // source lists per block of the last stag
 // Fixed-size head of the workspace; the two survivor-list buffers follow it.
 struct WorkspaceHead {
     DevState st;
-    alignas(256) double part[2][4 * kMaxBlocks];
-    alignas(256) uint32_t cnt[2][kMaxWaves];
-    alignas(256) uint32_t blk[2][kMaxBlocks];
+    alignas(256) double part[2][4 * kBatchBlocks];
+    alignas(256) uint32_t cnt[2][kBatchBlocks * kWavesPerBlock];
+    alignas(256) uint32_t blk[2][kBatchBlocks];
     alignas(256) uint32_t topk_hist[3 * kTopkBins];
     alignas(256) TopkState topk;
     alignas(256) uint32_t dgc_hist[2][3 * kTopkBins];
@@ -791,7 +791,10 @@ struct BatchPlan {
     uint32_t flat_gx = 0;  // > 0: the first pass runs in the flat shape with this many chunks per block (see below)
 };
 
-// Splits the 512 blocks of a launch over the vectors in proportion to their lengths (at least one each).
+// Splits a launch over the vectors so that no block has more tiles than one of 512 blocks would have if all
+// tiles were one vector's.  Many short vectors then add blocks to the launch instead of taking them away from
+// the long ones, whose blocks decide how long it lasts: with 512 blocks shared out in proportion, at least one
+// each, 161 tensors of 64 elements to 1.8 million left the long ones two thirds of the chip.
 int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchPlan& pl)
 {
     if (n < 1 || n > kMaxBatch) return SIDCO_ERR_SIZE;
@@ -803,15 +806,17 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         tiles_total += (uint64_t)((d + kTile - 1) / kTile);
     }
     pl.desc.assign(n, TensorDesc());
-    pl.map.assign(kMaxBlocks, 0);
-    pl.fmap.assign(kMaxBlocks, 0);
+    pl.map.assign(kBatchBlocks, 0);
+    pl.fmap.assign(kBatchBlocks, 0);
+    uint64_t per_block = (tiles_total + kMaxBlocks - 1) / kMaxBlocks;
+    if (per_block < kWavesPerBlock) per_block = kWavesPerBlock;  // a tile for every wave
     uint32_t fb = 0, ff = 0;
     uint64_t slot = 0;
     for (int t = 0; t < n; ++t) {
         TensorDesc& ds = pl.desc[t];
         const int64_t d = offsets[t + 1] - offsets[t];
         const uint64_t ntiles = (uint64_t)((d + kTile - 1) / kTile);
-        uint64_t share = 1 + ((uint64_t)(kMaxBlocks - n) * ntiles) / tiles_total;
+        uint64_t share = (ntiles + per_block - 1) / per_block;
         uint64_t nwaves = share * kWavesPerBlock < ntiles ? share * kWavesPerBlock : ntiles;
         ds.offset = offsets[t];
         ds.d = d;
@@ -949,9 +954,9 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     std::vector<unsigned char> image(table_bytes, 0);
     memcpy(image.data(), pl.desc.data(), (size_t)n * sizeof(TensorDesc));
     memcpy(image.data() + (offsetof(BatchTable, map) - offsetof(BatchTable, desc)), pl.map.data(),
-           kMaxBlocks * sizeof(uint16_t));
+           kBatchBlocks * sizeof(uint16_t));
     memcpy(image.data() + (offsetof(BatchTable, fmap) - offsetof(BatchTable, desc)), pl.fmap.data(),
-           kMaxBlocks * sizeof(uint16_t));
+           kBatchBlocks * sizeof(uint16_t));
     const bool same_table = c.batch_cur >= 0 && image == *c.batch_images[(size_t)c.batch_cur];
     const bool same_shape = same_table && c.batch_delta == delta && c.batch_theta == theta && c.batch_dist == dist &&
                             c.batch_M == M;
@@ -1393,7 +1398,7 @@ int sidco_fit_result(void* stream, double* host_sums)
     int rc = pick_ws(stream, false, &cp);
     if (rc != SIDCO_OK) return rc;
     if (!cp->ws || cp->fit_nblocks == 0) return SIDCO_ERR_WORKSPACE;
-    static thread_local double part[4 * kMaxBlocks];
+    static thread_local double part[4 * kBatchBlocks];
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemcpyAsync(part, ((WorkspaceHead*)cp->ws)->part[0], sizeof(part), hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_fail(e, "hipMemcpyAsync(partials)");
@@ -1401,7 +1406,7 @@ int sidco_fit_result(void* stream, double* host_sums)
     if (e != hipSuccess) return hip_fail(e, "hipStreamSynchronize");
     double sum[3] = {0.0, 0.0, 0.0};
     for (int q = 0; q < 3; ++q)
-        for (uint32_t b = 0; b < cp->fit_nblocks; ++b) sum[q] += part[q * kMaxBlocks + b];
+        for (uint32_t b = 0; b < cp->fit_nblocks; ++b) sum[q] += part[q * kBatchBlocks + b];
     host_sums[0] = sum[0];
     host_sums[1] = cp->fit_dist == SIDCO_DIST_GPD ? sum[1] : 0.0;
     host_sums[2] = cp->fit_dist == SIDCO_DIST_GAMMA_GPD ? sum[2] * 0.6931471805599453094 : 0.0;

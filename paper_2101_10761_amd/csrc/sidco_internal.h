@@ -14,6 +14,10 @@ constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kTile = 256;                        // elements per wave step: 64 lanes x float4
 constexpr int kMaxBlocks = 512;                   // 2 blocks per CU on 256 CUs
 constexpr int kMaxWaves = kMaxBlocks * kWavesPerBlock;
+// A batch's launch: its vectors share kMaxBlocks blocks' worth of tiles evenly, and each may leave one block
+// that is not full, so up to twice as many.
+constexpr int kMaxBatch = kMaxBlocks;  // vectors per batch
+constexpr int kBatchBlocks = kMaxBlocks + kMaxBatch;
 // A non-final stage whose source is still the dense vector writes survivor lists only if the expected
 // fraction of the vector that goes into them is at most this; otherwise it only counts and sums, and
 // the next stage scans the dense vector again (4 B/element read, against 16 B per list entry written
@@ -105,7 +109,7 @@ struct Params {
     int use_hint;           // the previous call on the device had this call's shape: theta_seen applies
     int prev_cand;          // the producer of this kernel's source lists wrote candidate lists
     DevState* st;
-    const double* part_in;  // [4][kMaxBlocks] partial sums written by the previous kernel
+    const double* part_in;  // [4][kBatchBlocks] partial sums written by the previous kernel
     double* part_out;
     const uint32_t* cnt_in; // [kMaxWaves] survivor-list lengths written by the previous kernel
     uint32_t* cnt_out;
@@ -203,8 +207,6 @@ struct Blk {
 };
 
 // ---- batched calls: several vectors (the tensors of one flat buffer) in one launch sequence ----
-constexpr int kMaxBatch = kMaxBlocks;  // every vector owns at least one block of the 512-block launches
-
 // One vector of a batch, relative to the call's base pointers (so that the table on the device depends on
 // the layout alone and survives a change of buffers).
 struct TensorDesc {
@@ -225,8 +227,8 @@ struct TensorDesc {
 struct BatchTable {
     DevState st[kMaxBatch];
     TensorDesc desc[kMaxBatch];
-    uint16_t map[kMaxBlocks];   // block of a dense grid -> vector
-    uint16_t fmap[kMaxBlocks];  // block of the last stage's grid -> vector
+    uint16_t map[kBatchBlocks];   // block of a dense grid -> vector
+    uint16_t fmap[kBatchBlocks];  // block of the last stage's grid -> vector
 };
 
 // Kernel arguments of a batched launch (by value): what all vectors share.

@@ -213,12 +213,12 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
     g.status = 0;
     g.frozen = false;
     if (m == 1) {
-        g.v[0] = have ? p.part_in[0 * kMaxBlocks + t] : 0.0;
-        g.v[1] = (have && p.dist == kDistGpd) ? p.part_in[1 * kMaxBlocks + t] : 0.0;
-        g.v[2] = (have && p.dist == kDistGamma) ? p.part_in[2 * kMaxBlocks + t] : 0.0;
+        g.v[0] = have ? p.part_in[0 * kBatchBlocks + t] : 0.0;
+        g.v[1] = (have && p.dist == kDistGpd) ? p.part_in[1 * kBatchBlocks + t] : 0.0;
+        g.v[2] = (have && p.dist == kDistGamma) ? p.part_in[2 * kBatchBlocks + t] : 0.0;
     } else {
-        g.v[0] = have ? p.part_in[0 * kMaxBlocks + t] : 0.0;
-        g.v[1] = (have && p.dist != kDistExp) ? p.part_in[1 * kMaxBlocks + t] : 0.0;
+        g.v[0] = have ? p.part_in[0 * kBatchBlocks + t] : 0.0;
+        g.v[1] = (have && p.dist != kDistExp) ? p.part_in[1 * kBatchBlocks + t] : 0.0;
         g.v[2] = have ? (double)p.blk_in[t] : 0.0;  // counts < 2^31: exact in fp64
         g.eta_prev = p.st->diag.eta[m - 2];
         g.status = p.st->status_after[m - 1];
@@ -515,7 +515,7 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b)
         double tot = 0.0;
 #pragma unroll
         for (int i = 0; i < kWavesPerBlock; ++i) tot += sh[i][threadIdx.x];
-        p.part_out[threadIdx.x * kMaxBlocks + b.id] = tot;
+        p.part_out[threadIdx.x * kBatchBlocks + b.id] = tot;
     }
     if (b.id == 0 && threadIdx.x == 0) fit_reset_state(p);
 }
@@ -590,9 +590,9 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
     v[1] = wave_sum(v[1]);
     v[2] = wave_sum(v[2]);
     if (lane == 0 && slot < (uint32_t)kMaxBlocks) {
-        p.part_out[0 * kMaxBlocks + slot] = v[0];
-        p.part_out[1 * kMaxBlocks + slot] = v[1];
-        p.part_out[2 * kMaxBlocks + slot] = v[2];
+        p.part_out[0 * kBatchBlocks + slot] = v[0];
+        p.part_out[1 * kBatchBlocks + slot] = v[1];
+        p.part_out[2 * kBatchBlocks + slot] = v[2];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) fit_reset_state(p);
 }
@@ -757,7 +757,7 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
         double tot = 0.0;
 #pragma unroll
         for (int i = 0; i < kWavesPerBlock; ++i) tot += sh[i][threadIdx.x];
-        p.part_out[threadIdx.x * kMaxBlocks + b.id] = tot;
+        p.part_out[threadIdx.x * kBatchBlocks + b.id] = tot;
     }
 }
 
@@ -1299,9 +1299,9 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a, cons
     v[1] = wave_sum(v[1]);
     v[2] = wave_sum(v[2]);
     if (lane == 0) {
-        p.part_out[0 * kMaxBlocks + b.id] = v[0];
-        p.part_out[1 * kMaxBlocks + b.id] = v[1];
-        p.part_out[2 * kMaxBlocks + b.id] = v[2];
+        p.part_out[0 * kBatchBlocks + b.id] = v[0];
+        p.part_out[1 * kBatchBlocks + b.id] = v[1];
+        p.part_out[2 * kBatchBlocks + b.id] = v[2];
         if (b.id == 0) fit_reset_state(p);
     }
 }

@@ -38,3 +38,18 @@ def test_dense_fallback_walks_the_same_tiles(oracle, d, stages):
         sidco.sidco_set_speculation(0.5)
     assert out.status & sidco.ST_FALLBACK
     check_parity(oracle, g, None, 0, ratios, out, label=f"fallback d={d} M={stages}")
+
+
+@pytest.mark.parametrize("n_short,n_long", [(500, 12), (400, 112), (0, 512), (511, 1), (3, 1)])
+def test_batch_of_more_blocks_than_one_vector_uses(oracle, n_short, n_long):
+    """Many short vectors beside long ones: the short ones' blocks come on top of the long ones' 512."""
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(n_short + 3 * n_long)
+    sizes = np.concatenate([rng.integers(1, 700, n_short), rng.integers(9_000, 60_000 if n_long > 12 else 400_000, n_long)])
+    rng.shuffle(sizes)
+    offs = [0] + [int(v) for v in np.cumsum(sizes)]
+    g = (rng.standard_t(3.0, size=offs[-1]) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
+    for dist, delta, stages in ((2, 0.01, 3), (0, 0.02, 1)):
+        out = run_batched(g, r, offs, delta, dist, stages, repeat=2)
+        check_batched(oracle, g, r, offs, delta, dist, stages, out, f"{n_short} short, {n_long} long, M={stages}")
