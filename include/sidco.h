@@ -181,7 +181,7 @@ int sidco_compress_ex(void *stream, const float *grad, float *residual, int64_t 
  * residual in fp32, fits in fp64, fp32 thresholds, fp32 residual and values.
  *
  *  grad        device, d elements of grad_dtype, read only, aligned to its
- *              element size (8-byte alignment enables the vector path)
+ *              element size
  *  grad_dtype  SIDCO_GRAD_F32 (then this is sidco_compress), _F16 or _BF16
  *  residual    device, d floats, in/out, or NULL.  Without a residual the
  *              widened vector is kept in the workspace, which then needs

@@ -35,11 +35,11 @@ struct WorkspaceHead {
 
 constexpr size_t head_bytes() { return (sizeof(WorkspaceHead) + kAlign - 1) / kAlign * kAlign; }
 
-size_t seg_bytes(int64_t d)
-{
-    const size_t ntiles = (size_t)((d + kTile - 1) / kTile);
-    return ntiles * kTile * sizeof(int2);  // one slot per element: no list can overflow
-}
+// Tiles of a vector of d elements if it starts right before a 16-byte boundary, the most it can have (see
+// WaveTiles): workspaces must not depend on where the caller's buffers start.
+constexpr uint64_t max_tiles(int64_t d) { return ((uint64_t)d + 3 + kTile - 1) / kTile; }
+
+constexpr size_t seg_bytes(int64_t d) { return max_tiles(d) * kTile * sizeof(int2); }  // one slot per element: no list can overflow
 
 // One workspace and the host's record of the calls made with it.  Library-owned workspaces are per
 // (device, stream): calls on different streams of a device use different ones and may overlap.
@@ -92,7 +92,7 @@ struct WsCtx {
 // and that pointer is what kernels and copies get.
 constexpr int64_t kStaticMaxD = 2097152;
 constexpr size_t kStaticBytes =
-    (sizeof(WorkspaceHead) + kAlign - 1) / kAlign * kAlign + 2 * (size_t)kStaticMaxD * sizeof(int2);
+    (sizeof(WorkspaceHead) + kAlign - 1) / kAlign * kAlign + 2 * seg_bytes(kStaticMaxD);
 static __device__ __align__(256) __attribute__((used)) unsigned char scratch[kStaticBytes];
 
 struct DeviceCtx {
@@ -165,6 +165,18 @@ int ensure_workspace(WsCtx& c, size_t need)
     return SIDCO_OK;
 }
 
+// Launch geometry of the comparators' kernels, which start their tiles at the vector's first element and use
+// 16-byte accesses only where all buffers allow them.
+template <typename P>
+void fill_plain(P& p, const void* grad, const float* residual, int64_t d, int gt)
+{
+    p.ntiles = (uint32_t)((d + kTile - 1) / kTile);
+    p.nfull = (uint32_t)(d / kTile);
+    p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;
+    p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
+    p.vec_ok = (gt == kGradF32 ? aligned16(grad) : ((uintptr_t)grad & 7u) == 0) && aligned16(residual);
+}
+
 // Fills the launch geometry and buffer pointers that every kernel of a call shares.
 // `acc_scratch`: fp32 buffer of the workspace that receives acc when the gradient is 16-bit and there is no residual.
 void fill_common(Params& p, WorkspaceHead* h, const void* grad, float* residual, int64_t d, int dist,
@@ -177,13 +189,13 @@ void fill_common(Params& p, WorkspaceHead* h, const void* grad, float* residual,
     p.acc_w = residual ? residual : (gt != kGradF32 ? acc_scratch : nullptr);
     p.acc = p.acc_w ? p.acc_w : (const float*)grad;
     p.d = d;
-    p.ntiles = (uint32_t)((d + kTile - 1) / kTile);
-    p.nfull = (uint32_t)(d / kTile);
+    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & 3u;
+    p.ntiles = (uint32_t)((d + p.shift + kTile - 1) / kTile);
+    p.nfull = (uint32_t)((d + p.shift) / kTile);
     p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;
     p.tq = p.ntiles / p.nwaves;
     p.tr = p.ntiles % p.nwaves;
     p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
-    p.vec_ok = (gt == kGradF32 ? aligned16(grad) : ((uintptr_t)grad & 7u) == 0) && aligned16(residual);
     p.dist = dist;
     p.st = &h->st;
 }
@@ -803,7 +815,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         const int64_t d = offsets[t + 1] - offsets[t];
         if (offsets[t] < 0 || d < 1 || d > (int64_t)INT32_MAX) return SIDCO_ERR_SIZE;
         if (out_offsets[t] < 0 || out_offsets[t + 1] - out_offsets[t] < 1) return SIDCO_ERR_SIZE;
-        tiles_total += (uint64_t)((d + kTile - 1) / kTile);
+        tiles_total += max_tiles(d);
     }
     pl.desc.assign(n, TensorDesc());
     pl.map.assign(kBatchBlocks, 0);
@@ -815,7 +827,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     for (int t = 0; t < n; ++t) {
         TensorDesc& ds = pl.desc[t];
         const int64_t d = offsets[t + 1] - offsets[t];
-        const uint64_t ntiles = (uint64_t)((d + kTile - 1) / kTile);
+        const uint64_t ntiles = max_tiles(d);
         uint64_t share = (ntiles + per_block - 1) / per_block;
         uint64_t nwaves = share * kWavesPerBlock < ntiles ? share * kWavesPerBlock : ntiles;
         ds.offset = offsets[t];
@@ -828,9 +840,11 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         ds.out_offset = out_offsets[t];
         ds.out_cap = out_offsets[t + 1] - out_offsets[t];
         ds.index = (uint32_t)t;
+        ds.ntiles = (uint32_t)ntiles;
         ds.nwaves = (uint32_t)nwaves;
         ds.tq = (uint32_t)(ntiles / nwaves);
         ds.tr = (uint32_t)(ntiles % nwaves);
+        ds.reserved = 0;
         for (uint32_t i = 0; i < ds.nblocks; ++i) pl.map[fb + i] = (uint16_t)t;
         for (uint32_t i = 0; i < ds.nfinal; ++i) pl.fmap[ff + i] = (uint16_t)t;
         fb += ds.nblocks;
@@ -847,8 +861,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     uint64_t total = 0, chunks = 0, most = 0;
     for (int t = 0; t < n; ++t) {
         const TensorDesc& ds = pl.desc[t];
-        const uint64_t ntiles = (uint64_t)((ds.d + kTile - 1) / kTile);
-        const uint64_t nwaves = (uint64_t)ds.nblocks * kWavesPerBlock < ntiles ? (uint64_t)ds.nblocks * kWavesPerBlock : ntiles;
+        const uint64_t ntiles = ds.ntiles, nwaves = ds.nwaves;
         total += (uint64_t)ds.d;
         for (uint32_t b = 0; b < ds.nblocks; ++b) {
             const uint64_t w0 = (uint64_t)b * kWavesPerBlock;
@@ -889,7 +902,7 @@ size_t sidco_workspace_bytes_batched(const int64_t* offsets, int n)
     for (int t = 0; t < n; ++t) {
         const int64_t d = offsets[t + 1] - offsets[t];
         if (d < 1) return 0;
-        slots += (uint64_t)((d + kTile - 1) / kTile) * kTile;
+        slots += max_tiles(d) * kTile;
     }
     return head_bytes() + 2 * slots * sizeof(int2);
 }
@@ -1125,11 +1138,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     p.acc = q.acc;
     p.d = d;
     p.k = k;
-    p.ntiles = q.ntiles;
-    p.nfull = q.nfull;
-    p.nwaves = q.nwaves;
-    p.nblocks = q.nblocks;
-    p.vec_ok = q.vec_ok;
+    fill_plain(p, grad, residual, d, gt);
     p.hist = h->topk_hist;
     p.st = &h->topk;
     p.cnt = h->cnt[0];
@@ -1232,9 +1241,7 @@ int sidco_dgc_typed(void* stream, const void* grad, int grad_dtype, float* resid
     hipStream_t s = (hipStream_t)stream;
     WorkspaceHead* h = (WorkspaceHead*)c.ws;
 
-    Params q;
-    fill_common(q, h, grad, residual, d, SIDCO_DIST_EXP, gt);  // no stored acc without a residual: the one dense
-                                                              // pass keeps what it selects in the lists
+    // no stored acc without a residual: the one dense pass keeps what it selects in the lists
     DgcParams p;
     memset(&p, 0, sizeof(p));
     p.grad = grad;
@@ -1242,11 +1249,7 @@ int sidco_dgc_typed(void* stream, const void* grad, int grad_dtype, float* resid
     p.residual = residual;
     p.d = d;
     p.k = k;
-    p.ntiles = q.ntiles;
-    p.nfull = q.nfull;
-    p.nwaves = q.nwaves;
-    p.nblocks = q.nblocks;
-    p.vec_ok = q.vec_ok;
+    fill_plain(p, grad, residual, d, gt);
     p.seed = seed;
     p.n_s = (uint32_t)n_s;
     p.k_s = (uint32_t)k_s;
@@ -1269,11 +1272,7 @@ int sidco_dgc_typed(void* stream, const void* grad, int grad_dtype, float* resid
     t.d = d;
     t.k = k;
     t.k_from_state = 1;
-    t.ntiles = q.ntiles;
-    t.nfull = q.nfull;
-    t.nwaves = q.nwaves;
-    t.nblocks = q.nblocks;
-    t.vec_ok = q.vec_ok;
+    fill_plain(t, grad, residual, d, gt);
     t.hist = h->dgc_hist[1];
     t.st = &h->dgc.lists;
     t.cnt = p.cnt;

@@ -26,23 +26,27 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
-// Four consecutive gradient elements as fp32, starting at element 4 * v: one 16-byte load of an fp32
-// buffer, one 8-byte load of an fp16 / bf16 buffer (widening either type is exact).  STREAM: the
+// Four consecutive gradient elements as fp32, from element e on: one 16-byte load of an fp32 buffer, one 8-byte
+// load of an fp16 / bf16 buffer (widening either type is exact).  The address need only be aligned for one
+// element: tiles follow the alignment of the accumulated vector, the gradient's may be another one (the load
+// instruction is the same; a misaligned stream measured within 2 % of an aligned one).  STREAM: the
 // buffer is read once per call, keep it out of the caches' way (a template parameter: as a run-time
 // flag the two loads are merged and the non-temporal hint is lost).
 template <int GT, bool STREAM>
-__device__ __forceinline__ f4 load_grad4(const void* __restrict__ g, size_t v)
+__device__ __forceinline__ f4 load_grad4(const void* __restrict__ g, size_t e)
 {
     if constexpr (GT == kGradF32) {
-        const f4* g4 = reinterpret_cast<const f4*>(g);
-        if constexpr (STREAM) return __builtin_nontemporal_load(g4 + v);
-        else return g4[v];
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        const f4u* q = reinterpret_cast<const f4u*>(reinterpret_cast<const float*>(g) + e);
+        if constexpr (STREAM) return __builtin_nontemporal_load(q);
+        else return *q;
     } else {
-        const uint64_t* g8 = reinterpret_cast<const uint64_t*>(g);
-        uint64_t w;
-        if constexpr (STREAM) w = __builtin_nontemporal_load(g8 + v);
-        else w = g8[v];
-        const uint32_t w0 = (uint32_t)w, w1 = (uint32_t)(w >> 32);  // elements 0,1 and 2,3
+        typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(2)));
+        const u2* q = reinterpret_cast<const u2*>(reinterpret_cast<const uint16_t*>(g) + e);
+        u2 w;
+        if constexpr (STREAM) w = __builtin_nontemporal_load(q);
+        else w = *q;
+        const uint32_t w0 = w.x, w1 = w.y;  // elements 0,1 and 2,3
         f4 c;
         if constexpr (GT == kGradBf16) {
             c.x = __uint_as_float(w0 << 16);
@@ -83,10 +87,14 @@ __device__ __forceinline__ uint32_t lane_prefix(unsigned long long mask)
 // contiguous ranges against this: 16.2 and 13.0 us at 25.6 M elements, 38 and 29 us at 66 M, 106 and 88 us at
 // 138 M), and values of a different scale in one part of the vector spread over all lists.  The counts come
 // ready from the host (q = T / W, r = T % W): a 64-bit division in every kernel cost 0.5 us each.
+// Tiles sit on the 16-byte grid of the accumulated vector, wherever it starts: tile t holds the elements
+// 256 t - shift .. 256 t + 255 - shift, `shift` being the number of elements between the boundary before acc[0]
+// and acc[0].  So tile 0 is incomplete if shift > 0 and the last tile may be; those two take guarded scalar
+// accesses, every other one whole 16-byte accesses.
 struct WaveTiles {
     uint32_t w, W;
-    uint32_t n;     // tiles of the wave
-    uint32_t full;  // the first `full` of them are complete (the vector's last tile may not be)
+    uint32_t n;       // tiles of the wave
+    uint32_t k0, nb;  // its tiles number k0 .. k0 + nb - 1 are complete
 };
 __device__ __forceinline__ WaveTiles wave_tiles(const Params& p, uint32_t w)
 {
@@ -94,8 +102,17 @@ __device__ __forceinline__ WaveTiles wave_tiles(const Params& p, uint32_t w)
     t.w = w;
     t.W = p.nwaves;
     t.n = p.tq + (w < p.tr ? 1u : 0u);
-    t.full = t.n - ((t.n > 0 && w + (t.n - 1) * t.W >= p.nfull) ? 1u : 0u);
+    t.k0 = (w == 0 && p.shift > 0) ? 1u : 0u;
+    uint32_t k1 = t.n;
+    if (k1 > 0 && w + (k1 - 1) * t.W >= p.nfull) --k1;
+    t.nb = k1 > t.k0 ? k1 - t.k0 : 0u;
     return t;
+}
+
+// number of the wave's g-th incomplete tile, g < n - nb
+__device__ __forceinline__ uint32_t guarded_tile(const WaveTiles& t, uint32_t g)
+{
+    return (t.nb == 0 || g < t.k0) ? g : g + t.nb;
 }
 
 // Survivor list of wave w: its first slot and the slots it has (one per element of the wave's tiles).

@@ -173,7 +173,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_dgc_dense(DgcParams p)
 #pragma unroll
                 for (uint32_t u = 0; u < U; ++u) {
                     const size_t i = (size_t)(t + u) * 64 + lane;
-                    a[u] = load_grad4<GT, EC>(p.grad, i);
+                    a[u] = load_grad4<GT, EC>(p.grad, 4 * i);
                     if (EC) b[u] = r4[i];
                 }
 #pragma unroll
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_dgc_dense(DgcParams p)
             }
             for (; t < tf; ++t) {
                 const size_t i = (size_t)t * 64 + lane;
-                f4 c = load_grad4<GT, false>(p.grad, i);
+                f4 c = load_grad4<GT, false>(p.grad, 4 * i);
                 if (EC) {
                     c = c + r4[i];
                     r4[i] = c;

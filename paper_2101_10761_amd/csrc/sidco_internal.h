@@ -91,12 +91,12 @@ struct Params {
                             // workspace buffer; NULL when acc is the fp32 gradient itself
     const float* acc;       // dense working vector read by stage 1's compaction: acc_w, else grad
     int64_t d;
-    uint32_t ntiles;        // ceil(d / kTile)
-    uint32_t nfull;         // d / kTile: tiles below this index are complete
+    uint32_t shift;         // elements between the 16-byte boundary before acc[0] and acc[0] (see WaveTiles)
+    uint32_t ntiles;        // tiles of the vector: ceil((d + shift) / kTile)
+    uint32_t nfull;         // (d + shift) / kTile: tiles below this index are complete (tile 0 only if shift = 0)
     uint32_t nwaves;        // waves that own tiles
     uint32_t tq, tr;        // ntiles / nwaves and ntiles % nwaves (see WaveTiles)
     uint32_t nblocks;       // grid size of the kernels that read the dense vector or write partial sums
-    int vec_ok;             // all dense buffers aligned for 4-element accesses (16 bytes; 8 for a 16-bit gradient)
     int reverse;            // a dense stage kernel walks the tiles from the last to the first
     int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
     unsigned long long owner;  // id of the stage controller that makes the call, 0 otherwise
@@ -220,8 +220,10 @@ struct TensorDesc {
     uint32_t first_final;   // ... and in the last stage's grid
     uint32_t nfinal;
     uint32_t index;         // position in out_counts / out_etas
-    uint32_t nwaves;        // waves that own tiles of the vector, and tiles / nwaves, tiles % nwaves
+    uint32_t ntiles;        // tiles, whatever the alignment of the call's buffers (see max_tiles)
+    uint32_t nwaves;        // waves that own tiles of the vector, and ntiles / nwaves, ntiles % nwaves
     uint32_t tq, tr;
+    uint32_t reserved;
 };
 
 struct BatchTable {
@@ -266,8 +268,11 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
 // length at which the faster sweep pays for the extra kernel that folds its partial sums
 constexpr int kFlatBlock = 256;
 constexpr int64_t kFlatMinD = 12000000;
-inline bool fit_uses_flat(int64_t d, bool vec_ok) { return vec_ok && d >= kFlatMinD; }
-inline uint32_t fit_flat_blocks(int64_t d) { return (uint32_t)((d / 4 + kFlatBlock - 1) / kFlatBlock); }
+inline bool fit_uses_flat(int64_t d) { return d >= kFlatMinD; }
+inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
+{
+    return (uint32_t)(((d + shift + 3) / 4 + kFlatBlock - 1) / kFlatBlock);
+}
 void launch_fit(const Params& p, double* scratch, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);

@@ -386,33 +386,10 @@ __device__ __forceinline__ void fit_accum(float x, double& s1, double& s2, doubl
     }
 }
 
-// U complete tiles starting at tile t, 4-element accesses.  EC: acc = g + residual, stored back.  A
-// 16-bit gradient is widened to fp32 first and acc is always stored (into the residual, or, without
-// one, into the workspace's own buffer), because every later kernel reads an fp32 vector.
-template <int DIST, bool EC, int GT, int U>
-__device__ __forceinline__ void fit_tiles(const void* __restrict__ g, f4* __restrict__ a4, uint32_t t, int lane,
-                                          double& s1, double& s2, double& sl, int& se)
-{
-    constexpr bool WRITE = EC || GT != kGradF32;
-    f4 a[U], b[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const size_t i = (size_t)(t + u) * 64 + lane;
-        // the gradient is read once per call when acc is re-materialised elsewhere
-        a[u] = load_grad4<GT, WRITE>(g, i);
-        if (EC) b[u] = a4[i];
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        f4 c = a[u];
-        if (EC) c = a[u] + b[u];
-        if (WRITE) a4[(size_t)(t + u) * 64 + lane] = c;
-        fit_accum<DIST>(c.x, s1, s2, sl, se);
-        fit_accum<DIST>(c.y, s1, s2, sl, se);
-        fit_accum<DIST>(c.z, s1, s2, sl, se);
-        fit_accum<DIST>(c.w, s1, s2, sl, se);
-    }
-}
+// EC: acc = g + residual, stored back.  A 16-bit gradient is widened to fp32 first and acc is always stored (into
+// the residual, or, without one, into the workspace's own buffer), because every later kernel reads fp32.
+template <bool EC, int GT>
+constexpr bool fit_writes() { return EC || GT != kGradF32; }
 
 // start of a call: per-call device state, by one thread
 __device__ __forceinline__ void fit_reset_state(const Params& p)
@@ -441,9 +418,21 @@ __device__ __forceinline__ float fit_one(const Params& p, int64_t i, double& s1,
 {
     float c = load_grad1<GT>(p.grad, i);
     if (EC) c = c + p.acc_w[i];
-    if (EC || GT != kGradF32) p.acc_w[i] = c;
+    if (fit_writes<EC, GT>()) p.acc_w[i] = c;
     fit_accum<DIST>(c, s1, s2, sl, se);
     return c;
+}
+
+// this lane's share of a tile that is not complete
+template <int DIST, bool EC, int GT>
+__device__ __forceinline__ void fit_guarded(const Params& p, uint32_t t, int lane, double& s1, double& s2, double& sl,
+                                            int& se)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+        if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+    }
 }
 
 // One wave's tiles.  The wave requests its next tile before it adds up the one it has: one tile (1 KB of each
@@ -453,15 +442,14 @@ template <int DIST, bool EC, int GT>
 __device__ __forceinline__ void fit_wave(const Params& p, uint32_t w, int lane, double& s1, double& s2, double& sl,
                                          int& se)
 {
-    constexpr bool WRITE = EC || GT != kGradF32;
+    constexpr bool WRITE = fit_writes<EC, GT>();
     const WaveTiles wt = wave_tiles(p, w);
-    uint32_t k = 0;
-    if (p.vec_ok && wt.full > 0) {
-        f4* a4 = reinterpret_cast<f4*>(p.acc_w);
-        size_t i = (size_t)w * 64 + lane;
-        const size_t step = (size_t)wt.W * 64;
+    if (wt.nb > 0) {
+        float* acc = p.acc_w;
+        size_t i = (size_t)(w + wt.k0 * wt.W) * kTile + lane * 4 - p.shift;
+        const size_t step = (size_t)wt.W * kTile;
         f4 g = load_grad4<GT, WRITE>(p.grad, i), r = {};
-        if (EC) r = a4[i];
+        if (EC) r = *reinterpret_cast<const f4*>(acc + i);
         auto add_up = [&](f4 c) {
             fit_accum<DIST>(c.x, s1, s2, sl, se);
             fit_accum<DIST>(c.y, s1, s2, sl, se);
@@ -469,27 +457,21 @@ __device__ __forceinline__ void fit_wave(const Params& p, uint32_t w, int lane, 
             fit_accum<DIST>(c.w, s1, s2, sl, se);
         };
 #pragma unroll 1
-        for (k = 1; k < wt.full; ++k) {
+        for (uint32_t k = 1; k < wt.nb; ++k) {
             f4 c = g;
             if (EC) c = g + r;
             g = load_grad4<GT, WRITE>(p.grad, i + step);
-            if (EC) r = a4[i + step];
-            if (WRITE) a4[i] = c;
+            if (EC) r = *reinterpret_cast<const f4*>(acc + i + step);
+            if (WRITE) *reinterpret_cast<f4*>(acc + i) = c;
             add_up(c);
             i += step;
         }
         if (EC) g = g + r;
-        if (WRITE) a4[i] = g;
+        if (WRITE) *reinterpret_cast<f4*>(acc + i) = g;
         add_up(g);
     }
-    // unaligned buffers and the ragged last tile: guarded scalar accesses
-    for (; k < wt.n; ++k) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t i = (int64_t)(w + k * wt.W) * kTile + lane * 4 + j;
-            if (i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
-        }
-    }
+    for (uint32_t g = 0; g < wt.n - wt.nb; ++g)
+        fit_guarded<DIST, EC, GT>(p, w + guarded_tile(wt, g) * wt.W, lane, s1, s2, sl, se);
 }
 
 template <int DIST, bool EC, int GT>
@@ -536,23 +518,23 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat(Params p, double* __res
 {
     __shared__ double sh[kFlatBlock / 64][4];
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const size_t nvec = (size_t)(p.d / 4);
-    const size_t i = (size_t)blockIdx.x * kFlatBlock + threadIdx.x;
+    const int64_t i = ((int64_t)blockIdx.x * kFlatBlock + threadIdx.x) * 4 - p.shift;  // first of the thread's 4 elements
     double s1 = 0.0, s2 = 0.0, sl = 0.0;
     int se = 0;
-    if (i < nvec) {
-        constexpr bool WRITE = EC || GT != kGradF32;
-        f4* a4 = reinterpret_cast<f4*>(p.acc_w);
-        f4 c = load_grad4<GT, WRITE>(p.grad, i);
-        if (EC) c = c + a4[i];
-        if (WRITE) a4[i] = c;
+    if (i >= 0 && i + 4 <= p.d) {
+        constexpr bool WRITE = fit_writes<EC, GT>();
+        f4 c = load_grad4<GT, WRITE>(p.grad, (size_t)i);
+        f4* a4 = reinterpret_cast<f4*>(p.acc_w + i);
+        if (EC) c = c + *a4;
+        if (WRITE) *a4 = c;
         fit_accum<DIST>(c.x, s1, s2, sl, se);
         fit_accum<DIST>(c.y, s1, s2, sl, se);
         fit_accum<DIST>(c.z, s1, s2, sl, se);
         fit_accum<DIST>(c.w, s1, s2, sl, se);
-    }
-    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {  // the last d % 4 elements
-        for (int64_t j = (int64_t)nvec * 4; j < p.d; ++j) fit_one<DIST, EC, GT>(p, j, s1, s2, sl, se);
+    } else {  // the vector's ends
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (i + j >= 0 && i + j < p.d) fit_one<DIST, EC, GT>(p, i + j, s1, s2, sl, se);
     }
     double v[3] = {s1, s2, sl + (double)se};
     v[0] = wave_sum(v[0]);
@@ -622,10 +604,10 @@ __device__ __forceinline__ void emit(bool valid, float x, int32_t idx, float eta
 
 // one complete tile of the dense vector, already loaded
 template <bool STATS, bool WRITE>
-__device__ __forceinline__ void compact_tile(f4 a, uint32_t t, int lane, float eta_s, float eta_w, ListWriter& lw,
-                                             uint32_t& ns, double& sy, double& syy)
+__device__ __forceinline__ void compact_tile(f4 a, uint32_t t, uint32_t shift, int lane, float eta_s, float eta_w,
+                                             ListWriter& lw, uint32_t& ns, double& sy, double& syy)
 {
-    const int32_t i0 = (int32_t)(t * kTile + lane * 4);
+    const int32_t i0 = (int32_t)(t * kTile + lane * 4 - shift);
     emit<STATS, WRITE>(true, a.x, i0 + 0, eta_s, eta_w, lw, lane, ns, sy, syy);
     emit<STATS, WRITE>(true, a.y, i0 + 1, eta_s, eta_w, lw, lane, ns, sy, syy);
     emit<STATS, WRITE>(true, a.z, i0 + 2, eta_s, eta_w, lw, lane, ns, sy, syy);
@@ -641,28 +623,31 @@ __device__ __forceinline__ void compact_tile(f4 a, uint32_t t, int lane, float e
 // (k_fit_flat and a statistics-only sweep together, plain against non-temporal loads: 65.7 and 63.9 us at 25.6 M
 // elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).
 struct DenseSweep {
-    const f4* x4;     // the dense vector, or a readable stand-in if the wave has no complete tile
+    const float* x;   // the first lane's element of tile 0, or a readable stand-in if the wave has no complete tile
     uint32_t nb;      // complete tiles of the wave
-    uint32_t first;   // the first tile in walking order
+    uint32_t first;   // the first one in walking order
     int32_t step;     // from one tile to the next in walking order
+    uint32_t any;     // a complete tile, the same one for every wave
 };
 
 __device__ __forceinline__ DenseSweep dense_sweep(const Params& p, const WaveTiles& wt)
 {
     DenseSweep d;
-    d.nb = p.vec_ok ? wt.full : 0;
-    d.x4 = d.nb > 0 ? reinterpret_cast<const f4*>(p.acc) : reinterpret_cast<const f4*>(p.seg_out);
-    d.first = d.nb > 0 ? (p.reverse ? wt.w + (d.nb - 1) * wt.W : wt.w) : 0u;
+    d.nb = wt.nb;
+    d.x = d.nb > 0 ? p.acc - p.shift : reinterpret_cast<const float*>(p.seg_out);
+    const uint32_t k = wt.k0 + (p.reverse ? d.nb - 1 : 0u);
+    d.first = d.nb > 0 ? wt.w + k * wt.W : 0u;
     d.step = p.reverse ? -(int32_t)wt.W : (int32_t)wt.W;
+    d.any = (d.nb > 0 && p.shift > 0) ? 1u : 0u;
     return d;
 }
 
-// Tile number j in walking order.  Past the wave's last tile the same tile 0 for every wave: the load is
+// Tile number j in walking order.  Past the wave's last tile the same tile for every wave: the load is
 // unconditional (loads under a run-time condition come with waits on the spot), but costs no HBM traffic.
 __device__ __forceinline__ f4 dense_load(const DenseSweep& d, uint32_t j, int lane)
 {
-    const uint32_t t = j < d.nb ? d.first + (uint32_t)((int32_t)j * d.step) : 0u;
-    return __builtin_nontemporal_load(d.x4 + (size_t)t * 64 + lane);
+    const uint32_t t = j < d.nb ? d.first + (uint32_t)((int32_t)j * d.step) : d.any;
+    return __builtin_nontemporal_load(reinterpret_cast<const f4*>(d.x + (size_t)t * kTile) + lane);
 }
 
 // `a` holds the wave's first kAhead tiles, requested before the threshold was known: a stage kernel's prologue is
@@ -683,17 +668,17 @@ __device__ __forceinline__ void compact_dense(const Params& p, const WaveTiles& 
             if (j + u < d.nb) {  // wave-uniform
                 const f4 c = a[u];
                 a[u] = dense_load(d, j + u + kAhead, lane);
-                compact_tile<STATS, WRITE>(c, d.first + (uint32_t)((int32_t)(j + u) * d.step), lane, eta_s, eta_w, lw, ns, sy,
-                                           syy);
+                compact_tile<STATS, WRITE>(c, d.first + (uint32_t)((int32_t)(j + u) * d.step), p.shift, lane, eta_s, eta_w, lw,
+                                           ns, sy, syy);
             }
         }
     }
-    // unaligned buffers and the ragged last tile: guarded scalar accesses
-    for (uint32_t k = d.nb; k < wt.n; ++k) {
+    for (uint32_t g = 0; g < wt.n - wt.nb; ++g) {
+        const uint32_t t = wt.w + guarded_tile(wt, g) * wt.W;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + lane * 4 + j;
-            const bool valid = i < p.d;
+            const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+            const bool valid = i >= 0 && i < p.d;
             const float v = valid ? p.acc[i] : 0.0f;
             emit<STATS, WRITE>(valid, v, (int32_t)i, eta_s, eta_w, lw, lane, ns, sy, syy);
         }
@@ -927,8 +912,9 @@ __device__ __forceinline__ uint32_t final_count_dense(const Params& p, uint32_t 
     uint32_t c = 0;
     for (uint32_t k = 0; k < wt.n; ++k) {
         for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
-            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane;
-            const bool sel = i < p.d && __builtin_fabsf(p.acc[i < p.d ? i : 0]) > eta;
+            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane - p.shift;
+            const bool in = i >= 0 && i < p.d;
+            const bool sel = in && __builtin_fabsf(p.acc[in ? i : 0]) > eta;
             c += (uint32_t)__popcll(__ballot(sel));
         }
     }
@@ -941,9 +927,10 @@ __device__ __forceinline__ void final_emit_dense(const Params& p, uint32_t sw, i
     const WaveTiles wt = wave_tiles(p, sw);
     for (uint32_t k = 0; k < wt.n; ++k) {
         for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
-            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane;
-            const float x = i < p.d ? p.acc[i] : 0.0f;
-            const bool sel = i < p.d && __builtin_fabsf(x) > eta;
+            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane - p.shift;
+            const bool in = i >= 0 && i < p.d;
+            const float x = in ? p.acc[i] : 0.0f;
+            const bool sel = in && __builtin_fabsf(x) > eta;
             const unsigned long long mask = __ballot(sel);
             const unsigned long long at = pos + lane_prefix(mask);
             if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
@@ -1164,13 +1151,13 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.acc_w = p.residual ? p.residual : (a.acc_own ? a.acc_own + ds.offset : nullptr);
     p.acc = p.acc_w ? p.acc_w : reinterpret_cast<const float*>(p.grad);
     p.d = ds.d;
-    p.ntiles = (uint32_t)((ds.d + kTile - 1) / kTile);
-    p.nfull = (uint32_t)(ds.d / kTile);
+    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & 3u;
+    p.ntiles = ds.ntiles;
+    p.nfull = (uint32_t)((ds.d + p.shift) / kTile);
     p.nwaves = ds.nwaves;
     p.tq = ds.tq;
     p.tr = ds.tr;
     p.nblocks = ds.nblocks;
-    p.vec_ok = ((uintptr_t)p.grad & (a.gt == kGradF32 ? 15u : 7u)) == 0 && ((uintptr_t)p.acc_w & 15u) == 0;
     p.reverse = a.reverse;
     p.acc_reset = 1;
     p.dist = a.dist;
@@ -1229,8 +1216,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // - it names the vector and, within it, the tiles that block's waves own - and blockIdx.x a chunk of
 // kFlatBlock / 64 = 4 of those tiles, one tile per wave.  Blocks run in the order x first, then y: address
 // order.  Chunks past the end of a y's tiles exit at once (the host launches the flat shape only when few
-// are).  A vector that does not start on a 16-byte boundary (8 for a 16-bit gradient) takes guarded scalar
-// accesses, like the incomplete last tile.
+// are).
 template <int DIST, bool EC, int GT>
 __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, double* __restrict__ flat_part,
                                                                   uint32_t stride)
@@ -1247,14 +1233,19 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, do
     double s1 = 0.0, s2 = 0.0, sl = 0.0;
     int se = 0;
     if (t < T1) {
-        if (p.vec_ok && t < p.nfull) {
-            fit_tiles<DIST, EC, GT, 1>(p.grad, reinterpret_cast<f4*>(p.acc_w), t, lane, s1, s2, sl, se);
+        if (t < p.nfull && (t > 0 || p.shift == 0)) {
+            constexpr bool WRITE = fit_writes<EC, GT>();
+            const size_t i = (size_t)t * kTile + lane * 4 - p.shift;
+            f4 c = load_grad4<GT, WRITE>(p.grad, i);
+            f4* a4 = reinterpret_cast<f4*>(p.acc_w + i);
+            if (EC) c = c + *a4;
+            if (WRITE) *a4 = c;
+            fit_accum<DIST>(c.x, s1, s2, sl, se);
+            fit_accum<DIST>(c.y, s1, s2, sl, se);
+            fit_accum<DIST>(c.z, s1, s2, sl, se);
+            fit_accum<DIST>(c.w, s1, s2, sl, se);
         } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t i = (int64_t)t * kTile + lane * 4 + j;
-                if (i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
-            }
+            fit_guarded<DIST, EC, GT>(p, t, lane, s1, s2, sl, se);
         }
     }
     double v[3] = {s1, s2, sl + (double)se};
@@ -1364,8 +1355,8 @@ static void launch_fit_flat_as(const Params& p, double* flat_part, uint32_t nfla
 template <bool EC, int GT>
 static void launch_fit_shape(const Params& p, double* scratch, hipStream_t s)
 {
-    if (fit_uses_flat(p.d, p.vec_ok != 0)) {
-        const uint32_t nflat = fit_flat_blocks(p.d);
+    if (fit_uses_flat(p.d)) {
+        const uint32_t nflat = fit_flat_blocks(p.d, p.shift);
         launch_fit_flat_as<EC, GT>(p, scratch, nflat, s);
         const uint32_t per = (nflat + kMaxBlocks - 1) / kMaxBlocks;
         hipLaunchKernelGGL(k_fit_reduce, dim3(kMaxBlocks / kWavesPerBlock), dim3(kBlock), 0, s, p, scratch, nflat, per);
@@ -1381,7 +1372,7 @@ static void launch_fit_type(const Params& p, double* scratch, hipStream_t s)
     else launch_fit_shape<false, GT>(p, scratch, s);
 }
 
-// `scratch`: device memory for 3 * fit_flat_blocks(d) doubles when the flat shape is used (else unused)
+// `scratch`: device memory for 3 * fit_flat_blocks(d, shift) doubles when the flat shape is used (else unused)
 void launch_fit(const Params& p, double* scratch, hipStream_t s)
 {
     switch (p.gt) {

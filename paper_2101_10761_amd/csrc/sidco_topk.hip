@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
                 for (int u = 0; u < U; ++u) {
                     const size_t i = (size_t)(t + u) * 64 + lane;
                     // read once per call when acc is stored elsewhere: keep it out of the caches' way
-                    a[u] = load_grad4<GT, WRITE>(p.grad, i);
+                    a[u] = load_grad4<GT, WRITE>(p.grad, 4 * i);
                     if (EC) b[u] = r4[i];
                 }
 #pragma unroll
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
             }
             for (; t < tf; ++t) {
                 const size_t i = (size_t)t * 64 + lane;
-                f4 c = load_grad4<GT, false>(p.grad, i);
+                f4 c = load_grad4<GT, false>(p.grad, 4 * i);
                 if (EC) c = c + r4[i];
                 if (WRITE) r4[i] = c;
                 atomicAdd(&sh_hist[mag_key(c.x) >> 20], 1u);

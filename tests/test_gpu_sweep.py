@@ -53,3 +53,33 @@ def test_batch_of_more_blocks_than_one_vector_uses(oracle, n_short, n_long):
     for dist, delta, stages in ((2, 0.01, 3), (0, 0.02, 1)):
         out = run_batched(g, r, offs, delta, dist, stages, repeat=2)
         check_batched(oracle, g, r, offs, delta, dist, stages, out, f"{n_short} short, {n_long} long, M={stages}")
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 5, 254, 255, 256, 257, 511, ROUND - 2, ROUND + 255, 12_000_001])
+@pytest.mark.parametrize("grad_offset,res_offset", [(1, 1), (3, 3), (2, 0), (0, 3), (1, 2)])
+def test_buffers_off_the_16_byte_grid(oracle, d, grad_offset, res_offset):
+    """Tiles follow the alignment of the accumulated vector; the gradient may have another one."""
+    rng = np.random.default_rng(d + 10 * grad_offset + res_offset)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual, dist, stages in ((r, 2, 3), (None, 0, 1)):
+        if d > ROUND + 255 and residual is None:
+            continue
+        ratios = oracle.schedule(0.01, stages, 0.25)
+        out = run_gpu(g, residual, dist, ratios, grad_offset=grad_offset, res_offset=res_offset)
+        check_parity(oracle, g, residual, dist, ratios, out, label=f"d={d} offsets {grad_offset},{res_offset} M={stages}")
+
+
+@pytest.mark.parametrize("dtype", ["bfloat16", "float16"])
+@pytest.mark.parametrize("base", [1, 2, 3, 6])
+@pytest.mark.parametrize("ec", [True, False])
+def test_16_bit_batches_off_the_grid(oracle, dtype, base, ec):
+    import torch
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(base)
+    offs = [0] + [int(v) for v in np.cumsum(rng.integers(1, 3000, 40))] + [150_001]
+    g16 = torch.from_numpy((rng.standard_t(3.0, size=offs[-1]) * 1e-2).astype(np.float32)).to(getattr(torch, dtype))
+    g = g16.to(torch.float32).numpy()
+    r = rng.laplace(0, 3e-3, size=offs[-1]).astype(np.float32) if ec else None
+    out = run_batched(g16, r, offs, 0.02, 2, 2, base_offset=base, repeat=2)
+    check_batched(oracle, g, r, offs, 0.02, 2, 2, out, f"{dtype} base {base} ec={ec}")
