@@ -1007,7 +1007,8 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     a.grad = grad;
     a.gt = gt;
     a.residual = residual;
-    a.acc_own = own_acc ? (float*)((char*)c.ws + head_bytes() + 2 * pl.slots * sizeof(int2)) : nullptr;
+    // the kernels add a tensor's offset to every base pointer: the copy starts at the first tensor's
+    a.acc_own = own_acc ? (float*)((char*)c.ws + head_bytes() + 2 * pl.slots * sizeof(int2)) - offsets[0] : nullptr;
     a.out_idx = out_idx;
     a.out_val = out_val;
     a.out_counts = out_counts;

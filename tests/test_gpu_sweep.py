@@ -83,3 +83,24 @@ def test_16_bit_batches_off_the_grid(oracle, dtype, base, ec):
     r = rng.laplace(0, 3e-3, size=offs[-1]).astype(np.float32) if ec else None
     out = run_batched(g16, r, offs, 0.02, 2, 2, base_offset=base, repeat=2)
     check_batched(oracle, g, r, offs, 0.02, 2, 2, out, f"{dtype} base {base} ec={ec}")
+
+
+def test_16_bit_batch_without_residual_may_start_inside_its_buffer(oracle):
+    """offsets[0] > 0: the widened copy of the tensors starts at the first tensor, not at the buffer's element 0."""
+    import torch
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(5)
+    start, sizes = 3_000_000, [70_001, 5, 20_000]
+    offs = [start] + [start + int(v) for v in np.cumsum(sizes)]
+    full = (rng.standard_t(3.0, size=offs[-1]) * 1e-2).astype(np.float32)
+    g16 = torch.from_numpy(full).to(torch.bfloat16)
+    import paper_2101_10761_amd as sidco
+    need = sidco.sidco_workspace_bytes_batched_typed(offs, sidco.GRAD_BF16, False)
+    ws = torch.full((need + 16_000_000,), 0x5a, dtype=torch.uint8, device="cuda:0")   # slack that nothing may touch
+    sidco.sidco_set_workspace(ws[:need])
+    try:
+        out = run_batched(g16, None, offs, 0.02, 2, 2)
+    finally:
+        sidco.sidco_set_workspace(None)
+    assert torch.all(ws[need:] == 0x5a)
+    check_batched(oracle, g16.to(torch.float32).numpy(), None, offs, 0.02, 2, 2, out, "start inside the buffer")
