@@ -35,9 +35,9 @@ struct WorkspaceHead {
 
 constexpr size_t head_bytes() { return (sizeof(WorkspaceHead) + kAlign - 1) / kAlign * kAlign; }
 
-// Tiles of a vector of d elements if it starts right before a 16-byte boundary, the most it can have (see
+// Tiles of a vector of d elements if it starts right before a line's boundary, the most it can have (see
 // WaveTiles): workspaces must not depend on where the caller's buffers start.
-constexpr uint64_t max_tiles(int64_t d) { return ((uint64_t)d + 3 + kTile - 1) / kTile; }
+constexpr uint64_t max_tiles(int64_t d) { return ((uint64_t)d + (kGrid - 1) + kTile - 1) / kTile; }
 
 constexpr size_t seg_bytes(int64_t d) { return max_tiles(d) * kTile * sizeof(int2); }  // one slot per element: no list can overflow
 
@@ -189,7 +189,7 @@ void fill_common(Params& p, WorkspaceHead* h, const void* grad, float* residual,
     p.acc_w = residual ? residual : (gt != kGradF32 ? acc_scratch : nullptr);
     p.acc = p.acc_w ? p.acc_w : (const float*)grad;
     p.d = d;
-    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & 3u;
+    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & (uint32_t)(kGrid - 1);
     p.ntiles = (uint32_t)((d + p.shift + kTile - 1) / kTile);
     p.nfull = (uint32_t)((d + p.shift) / kTile);
     p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;

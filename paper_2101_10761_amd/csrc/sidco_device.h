@@ -87,9 +87,11 @@ __device__ __forceinline__ uint32_t lane_prefix(unsigned long long mask)
 // contiguous ranges against this: 16.2 and 13.0 us at 25.6 M elements, 38 and 29 us at 66 M, 106 and 88 us at
 // 138 M), and values of a different scale in one part of the vector spread over all lists.  The counts come
 // ready from the host (q = T / W, r = T % W): a 64-bit division in every kernel cost 0.5 us each.
-// Tiles sit on the 16-byte grid of the accumulated vector, wherever it starts: tile t holds the elements
+// Tiles sit on the grid of 128-byte lines of the accumulated vector, wherever it starts: tile t holds the elements
 // 256 t - shift .. 256 t + 255 - shift, `shift` being the number of elements between the boundary before acc[0]
-// and acc[0].  So tile 0 is incomplete if shift > 0 and the last tile may be; those two take guarded scalar
+// and acc[0].  On the 16-byte grid alone a tile began and ended inside a line, and that line was fetched, and
+// written back in part, by the L2s of two XCDs: 50 tensors of odd lengths, 66 M elements in all, 129 us for the
+// first pass and 65 for the dense stage against 124 and 51 now (kGrid of 64 and 256 measured the same as 32).  So tile 0 is incomplete if shift > 0 and the last tile may be; those two take guarded scalar
 // accesses, every other one whole 16-byte accesses.
 struct WaveTiles {
     uint32_t w, W;

@@ -12,6 +12,7 @@ namespace sidco {
 constexpr int kBlock = 512;                       // threads per block: 8 wave64
 constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kTile = 256;                        // elements per wave step: 64 lanes x float4
+constexpr int kGrid = 32;                         // tiles sit on the grid of 128-byte lines of the vector (see WaveTiles)
 constexpr int kMaxBlocks = 512;                   // 2 blocks per CU on 256 CUs
 constexpr int kMaxWaves = kMaxBlocks * kWavesPerBlock;
 // A batch's launch: its vectors share kMaxBlocks blocks' worth of tiles evenly, and each may leave one block
@@ -91,7 +92,7 @@ struct Params {
                             // workspace buffer; NULL when acc is the fp32 gradient itself
     const float* acc;       // dense working vector read by stage 1's compaction: acc_w, else grad
     int64_t d;
-    uint32_t shift;         // elements between the 16-byte boundary before acc[0] and acc[0] (see WaveTiles)
+    uint32_t shift;         // elements between the 128-byte boundary before acc[0] and acc[0] (see WaveTiles)
     uint32_t ntiles;        // tiles of the vector: ceil((d + shift) / kTile)
     uint32_t nfull;         // (d + shift) / kTile: tiles below this index are complete (tile 0 only if shift = 0)
     uint32_t nwaves;        // waves that own tiles

@@ -1151,7 +1151,7 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.acc_w = p.residual ? p.residual : (a.acc_own ? a.acc_own + ds.offset : nullptr);
     p.acc = p.acc_w ? p.acc_w : reinterpret_cast<const float*>(p.grad);
     p.d = ds.d;
-    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & 3u;
+    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & (uint32_t)(kGrid - 1);
     p.ntiles = ds.ntiles;
     p.nfull = (uint32_t)((ds.d + p.shift) / kTile);
     p.nwaves = ds.nwaves;

@@ -104,3 +104,29 @@ def test_16_bit_batch_without_residual_may_start_inside_its_buffer(oracle):
         sidco.sidco_set_workspace(None)
     assert torch.all(ws[need:] == 0x5a)
     check_batched(oracle, g16.to(torch.float32).numpy(), None, offs, 0.02, 2, 2, out, "start inside the buffer")
+
+
+@pytest.mark.parametrize("d", [1, 31, 225, 226, 256, 287, 481, ROUND - 16])
+@pytest.mark.parametrize("grad_offset,res_offset", [(5, 5), (16, 16), (31, 31), (0, 30), (29, 4)])
+def test_buffers_off_the_line_grid(oracle, d, grad_offset, res_offset):
+    """Tiles sit on the 128-byte lines of the accumulated vector: lengths that end just before, on and after a tile."""
+    rng = np.random.default_rng(d + 100 * grad_offset + res_offset)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual, dist, stages in ((r, 2, 3), (None, 0, 1)):
+        ratios = oracle.schedule(0.01, stages, 0.25)
+        out = run_gpu(g, residual, dist, ratios, grad_offset=grad_offset, res_offset=res_offset)
+        check_parity(oracle, g, residual, dist, ratios, out, label=f"d={d} offsets {grad_offset},{res_offset} M={stages}")
+
+
+def test_batch_of_tensors_that_end_inside_lines(oracle):
+    """Tensors at every place inside a 128-byte line, of one tile and of two tiles that are both incomplete."""
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(3)
+    sizes = [n for k in range(34) for n in (225 + k, 1 + k, 481 + k)]
+    offs = [0] + [int(v) for v in np.cumsum(sizes)]
+    g = (rng.standard_t(3.0, size=offs[-1]) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
+    for residual, dist, delta, stages in ((r, 2, 0.01, 3), (None, 0, 0.02, 1)):
+        out = run_batched(g, residual, offs, delta, dist, stages, repeat=2)
+        check_batched(oracle, g, residual, offs, delta, dist, stages, out, f"ends inside lines M={stages}")
