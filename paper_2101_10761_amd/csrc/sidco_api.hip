@@ -385,6 +385,16 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     };
     mark(nullptr);
 
+    if (d <= kSmallMaxD) {
+        launch_small(p, s);
+        ++k;
+        mark("k_small");
+        c.prof_n = prof ? k : 0;
+        e = hipGetLastError();
+        if (e != hipSuccess) return hip_fail(e, "kernel launch");
+        return SIDCO_OK;
+    }
+
     // stage-1 sums (and acc) -> part[0]
     p.part_out = h->part[0];
     launch_fit(p, (double*)segbuf[1], s);  // the second list buffer is free until the first stage kernel writes it

@@ -274,6 +274,12 @@ inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 {
     return (uint32_t)(((d + shift + 3) / 4 + kFlatBlock - 1) / kFlatBlock);
 }
+// k_small's block, and the longest vector that goes through it: 144 KB of the 160 KB of LDS.  A training step's call
+// and its scatter, one kernel against three to five: 64 elements 29.4 -> 19.3 us, 20000 28.4 -> 19.5, 36000
+// 30.2 -> 21.6 (three stages), 30011 27.1 -> 20.3 (one stage).
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
+void launch_small(const Params& p, hipStream_t s);
 void launch_fit(const Params& p, double* scratch, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);

@@ -24,6 +24,7 @@
 //                k_final_lists: the last stage for M >= 2; it selects, writes the contiguous
 //                (index, value) output and zeroes the residual at those indices in one kernel, each
 //                block reserving its output range with one atomic.
+//   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements.
 //   k_gather     M = 1 only (last stage read the dense vector): exclusive prefix over the per-block
 //                survivor counts, copy of the lists into the output, residual zeroing.
 //
@@ -227,9 +228,9 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
     return g;
 }
 
-// Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
-// in every thread of every block.  Block 0 records the stage in the diagnostics.
-__device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, PrologueLoads& g, double (*sh)[4])
+// Evaluates eta for stage p.stage from the reduced sums in g.v; called by the first wave of a block, and block 0's
+// thread 0 records the stage in the diagnostics.  g.status and g.frozen leave with what this stage adds to them.
+__device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto_src, PrologueLoads& g)
 {
     const int m = p.stage;  // 1-based
     const uint32_t t = threadIdx.x;
@@ -249,99 +250,111 @@ __device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, Prolo
     StageEta r;
     bool frozen = g.frozen;
     unsigned long long n;
-    block_sum<3>(g.v, sh);
     r.eta = r.eta_w = 0.0f;
     r.lists_ok = false;
-    // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
-    // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
-    // arithmetic and the prologue lasts that much longer (measured).
-    if (t < 64) {
-        if (m == 1) {
-            n = (unsigned long long)p.d;
-            const double d = (double)p.d;
-            const double mu = g.v[0] / d;
-            double var = 0.0, mulog = 0.0;
-            bool finite = isfinite(mu);
-            if (p.dist == kDistGpd) {
-                var = g.v[1] / d - mu * mu;
-                finite = finite && isfinite(var);
-            } else if (p.dist == kDistGamma) {
-                mulog = (g.v[2] / d) * 0.6931471805599453094;  // log2 -> natural log
-                finite = finite && isfinite(mulog);
+    if (m == 1) {
+        n = (unsigned long long)p.d;
+        const double d = (double)p.d;
+        const double mu = g.v[0] / d;
+        double var = 0.0, mulog = 0.0;
+        bool finite = isfinite(mu);
+        if (p.dist == kDistGpd) {
+            var = g.v[1] / d - mu * mu;
+            finite = finite && isfinite(var);
+        } else if (p.dist == kDistGamma) {
+            mulog = (g.v[2] / d) * 0.6931471805599453094;  // log2 -> natural log
+            finite = finite && isfinite(mulog);
+        }
+        stats[0] = mu;
+        stats[1] = var;
+        stats[2] = mulog;
+        if (!finite) {
+            status |= kStNonfinite;
+            r.eta = r.eta_w = __builtin_nanf("");
+        } else {
+            fit = stage1_fit(p.dist, mu, var, mulog, status);
+            double tq = fit_quantile(fit, L);
+            if (tq < 0.0) {  // only the gamma form can be negative: delta_1 * Gamma(alpha) > 1
+                status |= kStGammaClamp;
+                tq = 0.0;
             }
-            stats[0] = mu;
-            stats[1] = var;
-            stats[2] = mulog;
-            if (!finite) {
-                status |= kStNonfinite;
-                r.eta = r.eta_w = __builtin_nanf("");
+            r.eta = r.eta_w = (float)tq;
+            if (Lw > L) {
+                const float c = fit_quantile_fast(fit, Lw);
+                if (c > r.eta) r.eta_w = c;
+            }
+        }
+    } else {
+        const float eta_prev = g.eta_prev;
+        n = (unsigned long long)g.v[2];
+        r.eta = r.eta_w = eta_prev;
+        if (!frozen) {
+            if (n == 0) {  // nothing exceeds eta_prev: keep it for all later stages
+                frozen = true;
+                status |= kStStopped;
             } else {
-                fit = stage1_fit(p.dist, mu, var, mulog, status);
-                double tq = fit_quantile(fit, L);
-                if (tq < 0.0) {  // only the gamma form can be negative: delta_1 * Gamma(alpha) > 1
-                    status |= kStGammaClamp;
-                    tq = 0.0;
-                }
-                r.eta = r.eta_w = (float)tq;
+                const double ybar = g.v[0] / (double)n;
+                const double yvar = p.dist == kDistExp ? 0.0 : g.v[1] / (double)n - ybar * ybar;
+                stats[0] = ybar;
+                stats[1] = yvar;
+                fit = pot_fit(p.dist, ybar, yvar, status);
+                loc = eta_prev;
+                r.eta = r.eta_w = (float)((double)eta_prev + fit_quantile(fit, L));
                 if (Lw > L) {
-                    const float c = fit_quantile_fast(fit, Lw);
+                    const float c = eta_prev + fit_quantile_fast(fit, Lw);
                     if (c > r.eta) r.eta_w = c;
                 }
             }
-        } else {
-            const float eta_prev = g.eta_prev;
-            n = (unsigned long long)g.v[2];
-            r.eta = r.eta_w = eta_prev;
-            if (!frozen) {
-                if (n == 0) {  // nothing exceeds eta_prev: keep it for all later stages
-                    frozen = true;
-                    status |= kStStopped;
-                } else {
-                    const double ybar = g.v[0] / (double)n;
-                    const double yvar = p.dist == kDistExp ? 0.0 : g.v[1] / (double)n - ybar * ybar;
-                    stats[0] = ybar;
-                    stats[1] = yvar;
-                    fit = pot_fit(p.dist, ybar, yvar, status);
-                    loc = eta_prev;
-                    r.eta = r.eta_w = (float)((double)eta_prev + fit_quantile(fit, L));
-                    if (Lw > L) {
-                        const float c = eta_prev + fit_quantile_fast(fit, Lw);
-                        if (c > r.eta) r.eta_w = c;
-                    }
-                }
-            }
-        }
-        r.lists_ok = auto_src && (r.eta >= g.list_eta);  // false for a NaN threshold, which selects nothing anyway
-        if (auto_src && !r.lists_ok) status |= kStFallback;
-        if (b.id == 0 && t == 0) {
-            p.st->diag.eta[m - 1] = r.eta;
-            p.st->diag.n[m - 1] = (int64_t)n;
-            p.st->diag.stats[m - 1][0] = stats[0];
-            p.st->diag.stats[m - 1][1] = stats[1];
-            p.st->diag.stats[m - 1][2] = stats[2];
-            p.st->status_after[m] = status;
-            p.st->frozen_after[m] = frozen ? 1u : 0u;
-            p.st->list_eta[m] = r.eta_w;
-            if (p.theta > 0.0f) {
-                FitRecord rec;
-                rec.gpd = fit.gpd ? 1 : 0;
-                rec.loc = loc;
-                rec.s = fit.s;
-                rec.c = fit.c;
-                rec.a = fit.a;
-                rec.b = fit.b;
-                p.st->cand_fit[m] = rec;
-            }
-            if (auto_src && p.prev_cand) {
-                // invert the producer's quantile function at this stage's threshold:
-                // eta = loc + Q(L_{m-1} + theta * L_m)  ->  theta
-                const double tq = (double)r.eta - (double)prev_fit.loc;
-                const double Lq = prev_fit.gpd ? log1p(tq * prev_fit.a / prev_fit.b) / prev_fit.a : (tq - prev_fit.c) / prev_fit.s;
-                const float seen = (float)((Lq - stage_L(p, m - 2)) / L);
-                p.st->theta_seen[m - 1] = (frozen || !(fabsf(seen) < 1.0e6f)) ? __builtin_nanf("") : seen;
-            }
         }
     }
+    r.lists_ok = auto_src && (r.eta >= g.list_eta);  // false for a NaN threshold, which selects nothing anyway
+    if (auto_src && !r.lists_ok) status |= kStFallback;
+    if (b.id == 0 && t == 0) {
+        p.st->diag.eta[m - 1] = r.eta;
+        p.st->diag.n[m - 1] = (int64_t)n;
+        p.st->diag.stats[m - 1][0] = stats[0];
+        p.st->diag.stats[m - 1][1] = stats[1];
+        p.st->diag.stats[m - 1][2] = stats[2];
+        p.st->status_after[m] = status;
+        p.st->frozen_after[m] = frozen ? 1u : 0u;
+        p.st->list_eta[m] = r.eta_w;
+        if (p.theta > 0.0f) {
+            FitRecord rec;
+            rec.gpd = fit.gpd ? 1 : 0;
+            rec.loc = loc;
+            rec.s = fit.s;
+            rec.c = fit.c;
+            rec.a = fit.a;
+            rec.b = fit.b;
+            p.st->cand_fit[m] = rec;
+        }
+        if (auto_src && p.prev_cand) {
+            // invert the producer's quantile function at this stage's threshold:
+            // eta = loc + Q(L_{m-1} + theta * L_m)  ->  theta
+            const double tq = (double)r.eta - (double)prev_fit.loc;
+            const double Lq = prev_fit.gpd ? log1p(tq * prev_fit.a / prev_fit.b) / prev_fit.a : (tq - prev_fit.c) / prev_fit.s;
+            const float seen = (float)((Lq - stage_L(p, m - 2)) / L);
+            p.st->theta_seen[m - 1] = (frozen || !(fabsf(seen) < 1.0e6f)) ? __builtin_nanf("") : seen;
+        }
+    }
+    g.status = status;
+    g.frozen = frozen;
+    return r;
+}
+
+// Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
+// in every thread of every block.  Block 0 records the stage in the diagnostics.
+__device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, PrologueLoads& g, double (*sh)[4])
+{
+    const uint32_t t = threadIdx.x;
+    StageEta r;
+    r.eta = r.eta_w = 0.0f;
+    r.lists_ok = false;
+    block_sum<3>(g.v, sh);
+    // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
+    // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
+    // arithmetic and the prologue lasts that much longer (measured).
+    if (t < 64) r = stage_eval(p, b, auto_src, g);
     __syncthreads();  // every thread has left block_sum: sh is free
     if (t == 0) {
         float* out = reinterpret_cast<float*>(&sh[0][0]);
@@ -1093,6 +1106,211 @@ __device__ __forceinline__ void gather_body(const Params& p, Blk b)
 }
 
 // ---------------------------------------------------------------------------------------------
+// k_small: a whole call in one block of 1024 threads, for a vector short enough to stay in the LDS of one CU.  A call
+// of several kernels on such a vector is all launches, prologues and drains; here a stage is a sweep over LDS, a
+// block sum and the closed form.  All loads of a thread are in flight at once: one round trip to HBM.  What bounds it
+// is a serial chain on one CU: at 64 elements and three stages 9.8 us, all latency; at 30011 elements 17.8 us against
+// 20.6 for the four kernels and the three launches between them, at 36000 19.5.  It pays as far as the LDS reaches.
+// The sums, the thresholds and the order of the output are fixed.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSmallWaves = kSmallBlock / 64;
+
+template <int Q>
+__device__ __forceinline__ void small_sum(double (&v)[Q], double (*sh)[4], int lane, int wib)
+{
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = wave_sum(v[q]);
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q) sh[wib][q] = v[q];
+    }
+    __syncthreads();
+    if (wib == 0) {  // the wave that evaluates the closed form
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            double t = 0.0;
+#pragma unroll
+            for (int i = 0; i < kSmallWaves; ++i) t += sh[i][q];
+            v[q] = t;
+        }
+    }
+}
+
+template <int DIST>
+__device__ __forceinline__ void small_fit(const float* x, int32_t t, int32_t d, double (&v)[3])
+{
+    double s1 = 0.0, s2 = 0.0, sl = 0.0;
+    int se = 0;
+#pragma unroll 1
+    for (int32_t i = 4 * t; i < d; i += 4 * kSmallBlock) {
+        const f4 c = *reinterpret_cast<const f4*>(x + i);  // past the end zeros, which leave s1 and s2 alone
+        fit_accum<DIST>(c.x, s1, s2, sl, se);
+        if (DIST != kDistGamma || i + 1 < d) fit_accum<DIST>(c.y, s1, s2, sl, se);
+        if (DIST != kDistGamma || i + 2 < d) fit_accum<DIST>(c.z, s1, s2, sl, se);
+        if (DIST != kDistGamma || i + 3 < d) fit_accum<DIST>(c.w, s1, s2, sl, se);
+    }
+    v[0] = s1;
+    v[1] = s2;
+    v[2] = sl + (double)se;
+}
+
+// N: float4s per thread, 4 * 1024 * N >= d
+template <bool EC, int GT, int N>
+__global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
+{
+    __shared__ __align__(16) float x[4 * kSmallBlock * N];
+    __shared__ double sh[kSmallWaves][4];
+    __shared__ uint32_t sh_cnt[kSmallWaves];
+    __shared__ float sh_eta;
+    __shared__ uint32_t sh_status, sh_frozen;
+    const int32_t t = (int32_t)threadIdx.x, d = (int32_t)p.d;
+    const int lane = t & 63, wib = t >> 6;
+    p.theta = 0.0f;  // no candidate lists
+
+    if (d >= 4) {
+        // whole float4s, wherever the buffers start; past the end the last one again: the loads stay unconditional
+        f4 c[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int32_t i = 4 * (u * kSmallBlock + t);
+            c[u] = load_grad4<GT, true>(p.grad, (size_t)(i + 4 <= d ? i : d - 4));
+        }
+        if constexpr (EC) {
+            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+            f4 r[N];
+#pragma unroll
+            for (int u = 0; u < N; ++u) {
+                const int32_t i = 4 * (u * kSmallBlock + t);
+                r[u] = *reinterpret_cast<const f4u*>(p.residual + (i + 4 <= d ? i : d - 4));
+            }
+#pragma unroll
+            for (int u = 0; u < N; ++u) c[u] = c[u] + r[u];
+        }
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int32_t i = 4 * (u * kSmallBlock + t);
+            if (i + 4 <= d) *reinterpret_cast<f4*>(x + i) = c[u];
+        }
+    }
+    if (t < 4 && (d & ~3) + t < 4 * kSmallBlock * N) {  // the last incomplete float4, zeros behind it
+        const int32_t i = (d & ~3) + t;
+        float c = 0.0f;
+        if (i < d) {
+            c = load_grad1<GT>(p.grad, i);
+            if (EC) c = c + p.residual[i];
+        }
+        x[i] = c;
+    }
+    if (t == 64) fit_reset_state(p);  // not in the wave that evaluates the closed form
+    __syncthreads();
+
+    PrologueLoads g = {};
+    g.seen = __builtin_nanf("");
+    switch (p.dist) {
+        case kDistExp: small_fit<kDistExp>(x, t, d, g.v); break;
+        case kDistGamma: small_fit<kDistGamma>(x, t, d, g.v); break;
+        default: small_fit<kDistGpd>(x, t, d, g.v); break;
+    }
+    auto evaluate = [&](int m) {  // the sums of all threads -> eta_m, the same in every thread
+        small_sum<3>(g.v, sh, lane, wib);
+        if (wib == 0) {
+            p.stage = m;
+            const StageEta r = stage_eval(p, Blk{0, 1}, false, g);
+            if (lane == 0) {
+                sh_eta = r.eta;
+                sh_status = g.status;
+                sh_frozen = g.frozen ? 1u : 0u;
+            }
+        }
+        __syncthreads();
+        g.eta_prev = sh_eta;
+        g.status = sh_status;
+        g.frozen = sh_frozen != 0;
+    };
+    evaluate(1);
+#pragma unroll 1
+    for (int m = 2; m <= p.M; ++m) {
+        __builtin_assume(m >= 2);
+        // exceedances of eta_{m-1}: their number and the sums of y = |x| - eta_{m-1} (see emit)
+        const float eta = g.eta_prev;
+        uint32_t ns = 0;
+        double sy = 0.0, syy = 0.0;
+#pragma unroll 1
+        for (int32_t i = 4 * t; i < d; i += 4 * kSmallBlock) {
+            const f4 c = *reinterpret_cast<const f4*>(x + i);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float a = __builtin_fabsf(c[j]);  // past the end zero, never above eta
+                const bool sel = a > eta;
+                ns += sel ? 1u : 0u;
+                const double y = (double)(sel ? a : eta) - (double)eta;
+                sy += y;
+                syy = __builtin_fma(y, y, syy);
+            }
+        }
+        g.v[0] = sy;
+        g.v[1] = syy;
+        g.v[2] = (double)ns;
+        evaluate(m);
+    }
+
+    // selection: wave w takes the elements of its threads' float4s, in address order
+    const float eta = g.eta_prev;
+    const int32_t last = 4 * (t - lane);  // lanes of a wave stay together
+    uint32_t mine = 0;
+#pragma unroll 1
+    for (int32_t b = last; b < d; b += 4 * kSmallBlock) {
+        const int32_t i = b + 4 * lane;
+        const f4 c = i < d ? *reinterpret_cast<const f4*>(x + i) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mine += (uint32_t)__popcll(__ballot(__builtin_fabsf(c[j]) > eta));
+    }
+    if (lane == 0) sh_cnt[wib] = mine;
+    __syncthreads();
+    uint32_t pos = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallWaves; ++i) {
+        if (i < wib) pos += sh_cnt[i];
+        total += sh_cnt[i];
+    }
+    const uint32_t cap = (uint32_t)p.out_cap;
+    if (t == 64) {
+        *p.out_count = (int32_t)(total > cap ? cap : total);
+        *p.out_eta = eta;
+        p.st->selected_ctr = total;
+        p.st->overflow = total > cap ? 1u : 0u;
+        p.st->diag.status = g.status;
+        if (p.status_out) *p.status_out = g.status | (total > cap ? kStOverflow : 0u);
+    }
+#pragma unroll 1
+    for (int32_t b = last; b < d; b += 4 * kSmallBlock) {
+        const int32_t i = b + 4 * lane;
+        f4 c = i < d ? *reinterpret_cast<const f4*>(x + i) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool sel = __builtin_fabsf(c[j]) > eta;
+            const unsigned long long mask = __ballot(sel);
+            const uint32_t at = pos + lane_prefix(mask);
+            if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
+                p.out_idx[at] = i + j;
+                p.out_val[at] = c[j];
+                c[j] = 0.0f;
+            }
+            pos += (uint32_t)__popcll(mask);
+        }
+        if constexpr (EC) {
+            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+            if (i + 4 <= d) *reinterpret_cast<f4u*>(p.residual + i) = c;
+            else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i + j < d) p.residual[i + j] = c[j];
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // k_scatter_add: the step after the sparsifier in Algorithm 2 - a worker's (index, value) pairs are
 // added into the dense aggregate, dense[idx[i]] += scale * val[i].  The indices of one list are
 // distinct, so plain read-modify-write needs no atomics and the result is deterministic; lists of
@@ -1370,6 +1588,31 @@ static void launch_fit_type(const Params& p, double* scratch, hipStream_t s)
 {
     if (p.residual) launch_fit_shape<true, GT>(p, scratch, s);
     else launch_fit_shape<false, GT>(p, scratch, s);
+}
+
+template <bool EC, int GT>
+static void launch_small_as(const Params& p, hipStream_t s)
+{
+    const dim3 grid(1), block(kSmallBlock);
+    if (p.d <= 3 * 4 * kSmallBlock) hipLaunchKernelGGL((k_small<EC, GT, 3>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_small<EC, GT, kSmallMaxD / (4 * kSmallBlock)>), grid, block, 0, s, p);
+}
+
+template <int GT>
+static void launch_small_type(const Params& p, hipStream_t s)
+{
+    if (p.residual) launch_small_as<true, GT>(p, s);
+    else launch_small_as<false, GT>(p, s);
+}
+
+// needs p.d <= kSmallMaxD
+void launch_small(const Params& p, hipStream_t s)
+{
+    switch (p.gt) {
+        case kGradF16: launch_small_type<kGradF16>(p, s); break;
+        case kGradBf16: launch_small_type<kGradBf16>(p, s); break;
+        default: launch_small_type<kGradF32>(p, s); break;
+    }
 }
 
 // `scratch`: device memory for 3 * fit_flat_blocks(d, shift) doubles when the flat shape is used (else unused)

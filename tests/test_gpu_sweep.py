@@ -130,3 +130,70 @@ def test_batch_of_tensors_that_end_inside_lines(oracle):
     for residual, dist, delta, stages in ((r, 2, 0.01, 3), (None, 0, 0.02, 1)):
         out = run_batched(g, residual, offs, delta, dist, stages, repeat=2)
         check_batched(oracle, g, residual, offs, delta, dist, stages, out, f"ends inside lines M={stages}")
+
+
+ONE_BLOCK = 36_864  # the longest vector that one block takes as a whole
+
+
+@pytest.mark.parametrize("d", [1, 2, 3, 4, 5, 63, 4095, 4097, 12_287, 12_288, 12_289, ONE_BLOCK - 1, ONE_BLOCK, ONE_BLOCK + 1])
+@pytest.mark.parametrize("dist,delta,stages", [(0, 0.02, 1), (2, 0.01, 3), (1, 0.002, 2), (0, 0.001, 8)])
+def test_one_block_calls(oracle, d, dist, delta, stages):
+    rng = np.random.default_rng(d + dist + stages)
+    ratios = oracle.schedule(delta, stages, 0.25)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual, cap, offs in ((r, None, (0, 0)), (None, None, (1, 0)), (r, max(1, d // 200), (3, 1))):
+        out = run_gpu(g, residual, dist, ratios, cap=cap, grad_offset=offs[0], res_offset=offs[1])
+        check_parity(oracle, g, residual, dist, ratios, out, capacity=cap, label=f"d={d} dist={dist} M={stages} cap={cap} {offs}")
+        if stages == 1 and d <= ONE_BLOCK:
+            again = run_gpu(g, residual, dist, ratios, cap=cap, grad_offset=offs[0], res_offset=offs[1])
+            np.testing.assert_array_equal(again.idx, out.idx)  # a single stage's order is fixed
+
+
+@pytest.mark.parametrize("kind", ["f16", "bf16"])
+@pytest.mark.parametrize("d", [1, 3, 12_289, ONE_BLOCK - 2, ONE_BLOCK + 1])
+def test_one_block_calls_on_16_bit_gradients(oracle, kind, d):
+    from test_gpu_typed import narrow, run_typed
+    rng = np.random.default_rng(d)
+    g16, g = narrow((rng.standard_t(3.0, size=d) * 1e-2).astype(np.float32), kind)
+    r = rng.laplace(0, 3e-3, size=d).astype(np.float32)
+    for residual in (r, None):
+        out = run_typed(g16, residual, 2, 0.01, 2, grad_offset=1, res_offset=1)
+        check_parity(oracle, g, residual, 2, oracle.schedule(0.01, 2, 0.25), out, label=f"{kind} d={d} ec={residual is not None}")
+
+
+@pytest.mark.parametrize("d", [ONE_BLOCK, ONE_BLOCK + 1])
+@pytest.mark.parametrize("dist", [0, 1, 2])
+@pytest.mark.parametrize("kind", ["nan", "inf", "zero", "constant", "denormal", "one"])
+def test_special_inputs_on_both_sides_of_the_one_block_limit(oracle, d, dist, kind):
+    rng = np.random.default_rng(7)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    if kind == "nan":
+        g[d // 2] = np.nan
+    elif kind == "inf":
+        g[d - 1] = np.inf
+    elif kind == "zero":
+        g[:] = 0.0
+    elif kind == "constant":
+        g = np.where(rng.uniform(size=d) < 0.5, -1e-3, 1e-3).astype(np.float32)
+    elif kind == "denormal":
+        g = (g * 1e-37).astype(np.float32)
+    else:
+        g[:] = 0.0
+        g[d // 3] = 1.0
+    for ratios in ([0.01], oracle.schedule(0.01, 3, 0.25)):
+        out = run_gpu(g, np.zeros(d, np.float32), dist, ratios)
+        check_parity(oracle, g, np.zeros(d, np.float32), dist, ratios, out, label=f"{kind} d={d} dist={dist} M={len(ratios)}")
+
+
+def test_which_calls_one_block_takes():
+    import paper_2101_10761_amd as sidco
+    g = np.random.default_rng(1).standard_normal(ONE_BLOCK + 1).astype(np.float32)
+    sidco.sidco_set_profiling(True)
+    try:
+        run_gpu(g[:ONE_BLOCK], None, 0, [0.25, 0.04])
+        assert [n for n, _ in sidco.sidco_get_profile()] == ["k_small"]
+        run_gpu(g, None, 0, [0.25, 0.04])
+        assert [n for n, _ in sidco.sidco_get_profile()] == ["k_fit", "k_compact_dense", "k_final_lists"]
+    finally:
+        sidco.sidco_set_profiling(False)
