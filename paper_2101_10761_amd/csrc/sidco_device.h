@@ -12,19 +12,40 @@ namespace sidco {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-__device__ __forceinline__ double wave_sum(double v)
+// The value `v` as a lane finds it through one DPP move, zero where the move has no source: within rows of 16 lanes
+// from the lane CTRL below (row_shr:1 .. 15 = 0x111 .. 0x11f), or from the last lane of the row(s) before
+// (row_bcast:15 = 0x142 into the rows of ROWS = 0xa, row_bcast:31 = 0x143 into those of 0xc).
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_or_zero(T v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;  // lane 0 holds the sum
+    static_assert(sizeof(T) == 8, "two registers");
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, ROWS, 0xf, true);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, ROWS, 0xf, true);
+    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
 }
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
+// Sum over the wave in a fixed order, the same in every lane.  Six DPP moves and adds: a shuffle through LDS costs
+// several times the latency, and these sums stand in the serial chain of every kernel's prologue and epilogue
+// (25.6 M elements, three stages: dense stage 21.6 -> 20.8 us, the two list stages 8.6 -> 6.8 and 7.7 -> 7.0;
+// 14.7 M, two stages: dense stage 16.1 -> 14.7, last stage 10.1 -> 9.4).
+template <typename T>
+__device__ __forceinline__ T wave_total(T v)
 {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    return v;
+    v += dpp_or_zero<0x111, 0xf>(v);
+    v += dpp_or_zero<0x112, 0xf>(v);
+    v += dpp_or_zero<0x114, 0xf>(v);
+    v += dpp_or_zero<0x118, 0xf>(v);  // lane 15 of each row: the row's sum
+    v += dpp_or_zero<0x142, 0xa>(v);
+    v += dpp_or_zero<0x143, 0xc>(v);  // lane 63: the wave's sum
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
+    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
 }
+
+__device__ __forceinline__ double wave_sum(double v) { return wave_total(v); }
+__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) { return wave_total(v); }
 
 // Four consecutive gradient elements as fp32, from element e on: one 16-byte load of an fp32 buffer, one 8-byte
 // load of an fp16 / bf16 buffer (widening either type is exact).  The address need only be aligned for one

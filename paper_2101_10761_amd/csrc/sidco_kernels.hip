@@ -6,8 +6,7 @@
 //                |acc|, acc^2, log2|acc| (whichever the chosen law needs)       [reads 8 B, writes 4 B / element]
 //                Two launch shapes: every wave walks its own tiles (short vectors), or
 //                k_fit_flat, one float4 per thread in address order, followed by k_fit_reduce, which
-//                folds the per-block sums into the 512 slots the next kernel expects (long vectors,
-//                whose operands come from HBM: that shape streams 15 % faster there).
+//                folds the per-block sums into the 512 slots the next kernel expects (long vectors).
 //                The gradient may be fp16 / bf16; it is widened as it is read.
 //   stage m      m = 1..M, one kernel each.  Prologue: every block reduces the previous kernel's partial
 //                sums in a fixed order and its first wave evaluates the closed-form threshold eta_m in
@@ -518,11 +517,7 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b)
 // ---------------------------------------------------------------------------------------------
 // k_fit_flat + k_fit_reduce: the same pass for large vectors.  One float4 per thread and a grid that
 // covers the vector in address order: the blocks in flight at any time touch one narrow window of each
-// buffer, which DRAM serves better than the 3 x 4096 separate streams of contiguous per-wave ranges when
-// the operands come from HBM (measured with a gradient and a residual that no cache holds: 52.9 us
-// against 62.5 us at d = 25.6 M, 129 us against 156 us at 66 M, i.e. what a plain in-place add reaches;
-// with a residual that is still in the memory-side cache from the previous call the per-wave shape is
-// the faster one up to 66 M, but no training loop leaves it there).
+// buffer, however long the vector is (see kFlatMinD for both shapes' times).
 // The price is one partial sum per 256-thread block - far too many for every block of the next
 // kernel to add up - so a second, small kernel folds them into the usual 512 slots, in a fixed order.
 // ---------------------------------------------------------------------------------------------
@@ -1109,8 +1104,8 @@ __device__ __forceinline__ void gather_body(const Params& p, Blk b)
 // k_small: a whole call in one block of 1024 threads, for a vector short enough to stay in the LDS of one CU.  A call
 // of several kernels on such a vector is all launches, prologues and drains; here a stage is a sweep over LDS, a
 // block sum and the closed form.  All loads of a thread are in flight at once: one round trip to HBM.  What bounds it
-// is a serial chain on one CU: at 64 elements and three stages 9.8 us, all latency; at 30011 elements 17.8 us against
-// 20.6 for the four kernels and the three launches between them, at 36000 19.5.  It pays as far as the LDS reaches.
+// is a serial chain on one CU: at 64 elements and three stages 9 us, all latency; at 30011 elements 16.5 us against
+// 20.6 for the four kernels and the three launches between them.  It pays as far as the LDS reaches.
 // The sums, the thresholds and the order of the output are fixed.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallWaves = kSmallBlock / 64;
