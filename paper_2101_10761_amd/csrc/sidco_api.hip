@@ -865,8 +865,8 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     pl.final_blocks = ff;
     pl.slots = slot;
     // The flat first pass (k_fit_flat_batched) launches, for every block of the dense grid, as many chunks of
-    // 4 tiles as the block with the most tiles needs.  It pays from the same total length as for a single vector,
-    // and only while most of the launched chunks exist: with a few long vectors among many short ones (whose one
+    // 4 tiles as the block with the most tiles needs.  It pays from kFlatMinBatch elements in all, and
+    // only while most of the launched chunks exist: with a few long vectors among many short ones (whose one
     // block has few tiles) the grid would be mostly empty.
     uint64_t total = 0, chunks = 0, most = 0;
     for (int t = 0; t < n; ++t) {
@@ -883,7 +883,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         }
     }
     pl.flat_gx = 0;
-    if ((int64_t)total >= kFlatMinD && most * fb <= 2 * chunks && most <= 0x7fffffffull / fb &&
+    if ((int64_t)total >= kFlatMinBatch && most * fb <= 2 * chunks && most <= 0x7fffffffull / fb &&
         3 * most * fb <= slot)  // the partial sums borrow the second list buffer
         pl.flat_gx = (uint32_t)most;
     return SIDCO_OK;

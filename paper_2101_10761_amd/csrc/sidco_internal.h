@@ -265,10 +265,17 @@ void launch_gather_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
 void launch_clear_u32(uint32_t* p, hipStream_t s);
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s);
-// k_fit's shape for large vectors (see k_fit_flat): one float4 per thread, 256-thread blocks; from the
-// length at which the faster sweep pays for the extra kernel that folds its partial sums
+// k_fit's shape for large vectors (see k_fit_flat): one float4 per thread, 256-thread blocks.  Waves that walk
+// interleaved tiles drift apart, the more the longer they run, and the window of addresses widens with them; the
+// flat shape's blocks start in address order, but it needs a kernel that folds its partial sums.  A two-stage call
+// in the per-wave shape and in the flat one, us: 25.6 M elements 84.3 and 87.5, 41 M 111.2 and 113.7, 50 M 133.2
+// and 135.0, 58 M 154.2 and 155.1, 62 M 164.5 and 161.2, 80 M 217.0 and 205.7; with a bf16 gradient 50 M 120.1 and
+// 126.8, 62 M 148.7 and 150.8, 80 M 193.3 and 191.2.
 constexpr int kFlatBlock = 256;
-constexpr int64_t kFlatMinD = 12000000;
+constexpr int64_t kFlatMinD = 58000000;
+// A batch's waves walk the tiles of their own vector, so that its window is as many as it has vectors, and the flat
+// shape pays earlier: 25.6 M elements in 161 tensors 96.6 us per wave and 90.6 flat, 66 M in 50 tensors 236.6 and 204.
+constexpr int64_t kFlatMinBatch = 12000000;
 inline bool fit_uses_flat(int64_t d) { return d >= kFlatMinD; }
 inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 {

@@ -271,3 +271,15 @@ def test_comparators_at_headline_size(oracle, kind):
     check_topk(oracle, gw, w.residual, k, run_topk(g16, w.residual, k), label=f"{kind} cfg3 top-k")
     out = run_dgc(g16, w.residual, w.delta, 0.01, 3)
     check_dgc(oracle, gw, w.residual, w.delta, 0.01, 3, out, f"{kind} cfg3 dgc")
+
+
+@pytest.mark.parametrize("kind,ec", [("bf16", True), ("f16", False)])
+def test_first_pass_in_address_order_on_the_longest_vectors(oracle, kind, ec):
+    """Single vectors take the flat first pass from 58 M elements on."""
+    d = 58_000_003
+    g32, rng = _grad(77, d, 1e-2)
+    g16, g = narrow(g32, kind)
+    del g32
+    r = rng.laplace(0, 1e-3, d).astype(np.float32) if ec else None
+    out = run_typed(g16, r, 2, 0.001, 2, grad_offset=3, res_offset=2)
+    check_parity(oracle, g, r, 2, oracle.schedule(0.001, 2, 0.25), out, label=f"flat {kind} ec={ec}")
