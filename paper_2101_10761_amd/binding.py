@@ -193,19 +193,34 @@ def _check(rc: int, where: str) -> None:
         raise SidcoError(rc, where)
 
 
+_torch = None
+
+
+def _import_torch():
+    """torch, imported with the first call that needs it and kept: an import statement in every function and check of a
+    call costs as much as the check."""
+    global _torch
+    import torch
+    _torch = torch
+    return torch
+
+
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream_handle(stream):
-    import torch
+    torch = _torch or _import_torch()
     if stream is None:
+        # the current device's current stream; building torch's Stream object around it takes 2.9 us against 0.3
+        if torch.cuda.is_initialized():
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
         stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream)
+    return stream.cuda_stream
 
 
 def _check_tensor(t, dtype, name, n=None):
-    import torch
+    torch = _torch or _import_torch()
     if not isinstance(t, torch.Tensor) or not t.is_cuda or t.dtype != dtype or not t.is_contiguous():
         raise TypeError(f"{name} must be a contiguous CUDA tensor of dtype {dtype}")
     if n is not None and t.numel() < n:
@@ -266,7 +281,7 @@ def sidco_set_delta1(delta1: float) -> None:
 def sidco_compress(grad, residual, delta: float, dist: int, stages: int, out_idx, out_val, out_count, out_eta,
                    stream=None) -> None:
     """Enqueues one sparsifier call; see include/sidco.h.  `residual` may be None."""
-    import torch
+    torch = _torch or _import_torch()
     d = grad.numel()
     _check_tensor(grad, torch.float32, "grad")
     if residual is not None:
@@ -283,7 +298,7 @@ def sidco_compress(grad, residual, delta: float, dist: int, stages: int, out_idx
 def sidco_compress_static(grad, residual, delta: float, dist: int, stages: int, out_idx, out_val, out_count, out_eta,
                           stream=None) -> None:
     """sidco_compress in the library's static scratch: no device allocation; d <= sidco_static_max_elements()."""
-    import torch
+    torch = _torch or _import_torch()
     d = grad.numel()
     _check_tensor(grad, torch.float32, "grad")
     if residual is not None:
@@ -312,7 +327,7 @@ GRAD_F32, GRAD_F16, GRAD_BF16 = 0, 1, 2
 def sidco_compress_typed(grad, residual, delta: float, dist: int, stages: int, out_idx, out_val, out_count, out_eta,
                          stream=None) -> None:
     """sidco_compress on a gradient tensor of dtype float32, float16 or bfloat16 (the residual stays float32)."""
-    import torch
+    torch = _torch or _import_torch()
     codes = {torch.float32: GRAD_F32, torch.float16: GRAD_F16, torch.bfloat16: GRAD_BF16}
     if not isinstance(grad, torch.Tensor) or grad.dtype not in codes:
         raise TypeError("grad must be a CUDA tensor of dtype float32, float16 or bfloat16")
@@ -332,7 +347,7 @@ def sidco_compress_typed(grad, residual, delta: float, dist: int, stages: int, o
 
 def sidco_compress_ex(grad, residual, dist: int, ratios, out_idx, out_val, out_count, out_eta, stream=None) -> None:
     """Explicit stage ratios; the output capacity is min(len(out_idx), len(out_val))."""
-    import torch
+    torch = _torch or _import_torch()
     d = grad.numel()
     _check_tensor(grad, torch.float32, "grad")
     if residual is not None:
@@ -349,7 +364,10 @@ def sidco_compress_ex(grad, residual, dist: int, ratios, out_idx, out_val, out_c
 
 
 def _i64_array(values):
-    return (C.c_int64 * len(values))(*[int(v) for v in values])
+    try:
+        return (C.c_int64 * len(values))(*values)
+    except TypeError:  # integers of other types than int
+        return (C.c_int64 * len(values))(*[int(v) for v in values])
 
 
 def sidco_batched_out_offsets(offsets, delta: float) -> list[int]:
@@ -367,7 +385,7 @@ def sidco_workspace_bytes_batched(offsets) -> int:
 def sidco_compress_batched(grad, residual, offsets, delta: float, dist: int, stages: int, out_idx, out_val, out_offsets,
                            out_counts, out_etas, stream=None) -> None:
     """Enqueues one sparsifier call per tensor of the flat buffer, all in one launch sequence; see include/sidco.h."""
-    import torch
+    torch = _torch or _import_torch()
     n = len(offsets) - 1
     _check_tensor(grad, torch.float32, "grad", offsets[-1])
     if residual is not None:
@@ -389,7 +407,7 @@ def sidco_read_diag_batched(t: int, stream=None) -> Diag:
 
 def sidco_topk(grad, residual, k: int, out_idx, out_val, out_count, out_kth, stream=None) -> None:
     """Enqueues the exact Top-k comparator; see include/sidco.h.  `residual` may be None."""
-    import torch
+    torch = _torch or _import_torch()
     d = grad.numel()
     _check_tensor(grad, torch.float32, "grad")
     if residual is not None:
@@ -412,7 +430,7 @@ def sidco_dgc_sizes(d: int, delta: float, sample_ratio: float = 0.01):
 def sidco_dgc(grad, residual, delta: float, sample_ratio: float, seed: int, out_idx, out_val, out_count, out_eta,
               stream=None) -> None:
     """Enqueues the DGC comparator; see include/sidco.h.  `residual` may be None."""
-    import torch
+    torch = _torch or _import_torch()
     d = grad.numel()
     _check_tensor(grad, torch.float32, "grad")
     if residual is not None:
@@ -428,7 +446,7 @@ def sidco_dgc(grad, residual, delta: float, sample_ratio: float, seed: int, out_
 
 def _grad_code(grad):
     """SIDCO_GRAD_* of a gradient tensor (float32, float16 or bfloat16)."""
-    import torch
+    torch = _torch or _import_torch()
     codes = {torch.float32: GRAD_F32, torch.float16: GRAD_F16, torch.bfloat16: GRAD_BF16}
     if not isinstance(grad, torch.Tensor) or grad.dtype not in codes:
         raise TypeError("grad must be a CUDA tensor of dtype float32, float16 or bfloat16")
@@ -438,7 +456,7 @@ def _grad_code(grad):
 
 def sidco_topk_typed(grad, residual, k: int, out_idx, out_val, out_count, out_kth, stream=None) -> None:
     """sidco_topk on a gradient tensor of dtype float32, float16 or bfloat16 (the residual stays float32)."""
-    import torch
+    torch = _torch or _import_torch()
     code = _grad_code(grad)
     d = grad.numel()
     if residual is not None:
@@ -454,7 +472,7 @@ def sidco_topk_typed(grad, residual, k: int, out_idx, out_val, out_count, out_kt
 def sidco_dgc_typed(grad, residual, delta: float, sample_ratio: float, seed: int, out_idx, out_val, out_count, out_eta,
                     stream=None) -> None:
     """sidco_dgc on a gradient tensor of dtype float32, float16 or bfloat16 (the residual stays float32)."""
-    import torch
+    torch = _torch or _import_torch()
     code = _grad_code(grad)
     d = grad.numel()
     if residual is not None:
@@ -471,7 +489,7 @@ def sidco_dgc_typed(grad, residual, delta: float, sample_ratio: float, seed: int
 def sidco_compress_batched_typed(grad, residual, offsets, delta: float, dist: int, stages: int, out_idx, out_val,
                                  out_offsets, out_counts, out_etas, stream=None) -> None:
     """sidco_compress_batched on a gradient buffer of dtype float32, float16 or bfloat16."""
-    import torch
+    torch = _torch or _import_torch()
     code = _grad_code(grad)
     n = len(offsets) - 1
     if grad.numel() < offsets[-1]:
@@ -545,7 +563,7 @@ class Controller:
     def compress(self, grad, residual, out_idx, out_val, out_count, out_eta, stream=None) -> None:
         """One iteration; `grad` may be float32 (sidco_controller_compress) or float16 / bfloat16
         (sidco_controller_compress_typed)."""
-        import torch
+        torch = _torch or _import_torch()
         d = grad.numel()
         code = _grad_code(grad)
         if residual is not None:
@@ -568,7 +586,7 @@ class Controller:
 
 def sidco_scatter_add(dense, idx, val, count, scale: float = 1.0, stream=None) -> None:
     """dense[idx[i]] += scale * val[i] for i < count (a device scalar); see include/sidco.h."""
-    import torch
+    torch = _torch or _import_torch()
     _check_tensor(dense, torch.float32, "dense")
     _check_tensor(idx, torch.int32, "idx", 1)
     _check_tensor(val, torch.float32, "val", 1)
@@ -588,7 +606,7 @@ def sidco_scatter_check(stream=None) -> bool:
 def sidco_fit(grad, residual, dist: int, stream=None) -> None:
     """Enqueues steps 1-2 alone (error-compensation add fused with the stage-1 sums); the gradient may be
     float32, float16 or bfloat16."""
-    import torch
+    torch = _torch or _import_torch()
     codes = {torch.float32: GRAD_F32, torch.float16: GRAD_F16, torch.bfloat16: GRAD_BF16}
     if not isinstance(grad, torch.Tensor) or grad.dtype not in codes:
         raise TypeError("grad must be a CUDA tensor of dtype float32, float16 or bfloat16")
