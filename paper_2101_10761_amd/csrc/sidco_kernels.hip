@@ -1153,7 +1153,7 @@ __device__ __forceinline__ void small_fit(const float* x, int32_t t, int32_t d, 
 template <bool EC, int GT, int N>
 __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 {
-    __shared__ __align__(16) float x[4 * kSmallBlock * N];
+    extern __shared__ __align__(16) float x[];  // 4 * kSmallBlock * N
     __shared__ double sh[kSmallWaves][4];
     __shared__ uint32_t sh_cnt[kSmallWaves];
     __shared__ float sh_eta;
@@ -1585,19 +1585,24 @@ static void launch_fit_type(const Params& p, double* scratch, hipStream_t s)
     else launch_fit_shape<false, GT>(p, scratch, s);
 }
 
-template <bool EC, int GT>
+template <bool EC, int GT, int N>
 static void launch_small_as(const Params& p, hipStream_t s)
 {
-    const dim3 grid(1), block(kSmallBlock);
-    if (p.d <= 3 * 4 * kSmallBlock) hipLaunchKernelGGL((k_small<EC, GT, 3>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_small<EC, GT, kSmallMaxD / (4 * kSmallBlock)>), grid, block, 0, s, p);
+    hipLaunchKernelGGL((k_small<EC, GT, N>), dim3(1), dim3(kSmallBlock), 4 * kSmallBlock * N * sizeof(float), s, p);
+}
+
+template <bool EC, int GT>
+static void launch_small_size(const Params& p, hipStream_t s)
+{
+    if (p.d <= 3 * 4 * kSmallBlock) launch_small_as<EC, GT, 3>(p, s);
+    else launch_small_as<EC, GT, kSmallMaxD / (4 * kSmallBlock)>(p, s);
 }
 
 template <int GT>
 static void launch_small_type(const Params& p, hipStream_t s)
 {
-    if (p.residual) launch_small_as<true, GT>(p, s);
-    else launch_small_as<false, GT>(p, s);
+    if (p.residual) launch_small_size<true, GT>(p, s);
+    else launch_small_size<false, GT>(p, s);
 }
 
 // needs p.d <= kSmallMaxD
