@@ -26,7 +26,7 @@ struct WorkspaceHead {
     alignas(256) double part[2][4 * kBatchBlocks];
     alignas(256) uint32_t cnt[2][kBatchBlocks * kWavesPerBlock];
     alignas(256) uint32_t blk[2][kBatchBlocks];
-    alignas(256) uint32_t topk_hist[3 * kTopkBins];
+    alignas(256) uint32_t topk_hist[kTopkHist];
     alignas(256) TopkState topk;
     alignas(256) uint32_t dgc_hist[2][3 * kTopkBins];
     alignas(256) DgcState dgc;
@@ -128,7 +128,6 @@ int grad_type(int grad_dtype)
 }
 
 bool aligned4(const void* p) { return ((uintptr_t)p & 3u) == 0; }
-bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 // `grad_align`: alignment the gradient's element type needs (4 for fp32, 2 for the 16-bit types)
 int check_common(const void* grad, const float* residual, int64_t d, int dist, const int32_t* out_idx,
@@ -165,16 +164,18 @@ int ensure_workspace(WsCtx& c, size_t need)
     return SIDCO_OK;
 }
 
-// Launch geometry of the comparators' kernels, which start their tiles at the vector's first element and use
-// 16-byte accesses only where all buffers allow them.
+// Launch geometry of a sweep (see WaveTiles): `base` is the vector whose lines the tiles sit on, NULL if its alignment
+// does not matter.
 template <typename P>
-void fill_plain(P& p, const void* grad, const float* residual, int64_t d, int gt)
+void fill_sweep(P& p, const float* base, int64_t d)
 {
-    p.ntiles = (uint32_t)((d + kTile - 1) / kTile);
-    p.nfull = (uint32_t)(d / kTile);
-    p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;
+    p.shift = (uint32_t)((uintptr_t)base >> 2) & (uint32_t)(kGrid - 1);
+    const uint32_t ntiles = (uint32_t)((d + p.shift + kTile - 1) / kTile);
+    p.nfull = (uint32_t)((d + p.shift) / kTile);
+    p.nwaves = ntiles < (uint32_t)kMaxWaves ? ntiles : (uint32_t)kMaxWaves;
+    p.tq = ntiles / p.nwaves;
+    p.tr = ntiles % p.nwaves;
     p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
-    p.vec_ok = (gt == kGradF32 ? aligned16(grad) : ((uintptr_t)grad & 7u) == 0) && aligned16(residual);
 }
 
 // Fills the launch geometry and buffer pointers that every kernel of a call shares.
@@ -189,13 +190,7 @@ void fill_common(Params& p, WorkspaceHead* h, const void* grad, float* residual,
     p.acc_w = residual ? residual : (gt != kGradF32 ? acc_scratch : nullptr);
     p.acc = p.acc_w ? p.acc_w : (const float*)grad;
     p.d = d;
-    p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & (uint32_t)(kGrid - 1);
-    p.ntiles = (uint32_t)((d + p.shift + kTile - 1) / kTile);
-    p.nfull = (uint32_t)((d + p.shift) / kTile);
-    p.nwaves = p.ntiles < (uint32_t)kMaxWaves ? p.ntiles : (uint32_t)kMaxWaves;
-    p.tq = p.ntiles / p.nwaves;
-    p.tr = p.ntiles % p.nwaves;
-    p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
+    fill_sweep(p, p.acc, d);
     p.dist = dist;
     p.st = &h->st;
 }
@@ -850,11 +845,9 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
         ds.out_offset = out_offsets[t];
         ds.out_cap = out_offsets[t + 1] - out_offsets[t];
         ds.index = (uint32_t)t;
-        ds.ntiles = (uint32_t)ntiles;
         ds.nwaves = (uint32_t)nwaves;
         ds.tq = (uint32_t)(ntiles / nwaves);
         ds.tr = (uint32_t)(ntiles % nwaves);
-        ds.reserved = 0;
         for (uint32_t i = 0; i < ds.nblocks; ++i) pl.map[fb + i] = (uint16_t)t;
         for (uint32_t i = 0; i < ds.nfinal; ++i) pl.fmap[ff + i] = (uint16_t)t;
         fb += ds.nblocks;
@@ -871,12 +864,12 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     uint64_t total = 0, chunks = 0, most = 0;
     for (int t = 0; t < n; ++t) {
         const TensorDesc& ds = pl.desc[t];
-        const uint64_t ntiles = ds.ntiles, nwaves = ds.nwaves;
+        const uint64_t nwaves = ds.nwaves;
         total += (uint64_t)ds.d;
         for (uint32_t b = 0; b < ds.nblocks; ++b) {
             const uint64_t w0 = (uint64_t)b * kWavesPerBlock;
             const uint64_t w1 = w0 + kWavesPerBlock < nwaves ? w0 + kWavesPerBlock : nwaves;
-            const uint64_t tiles = (w1 * ntiles) / nwaves - (w0 * ntiles) / nwaves;
+            const uint64_t tiles = (w1 - w0) * ds.tq + (w1 < ds.tr ? w1 : ds.tr) - (w0 < ds.tr ? w0 : ds.tr);
             const uint64_t c = (tiles + kFlatBlock / 64 - 1) / (kFlatBlock / 64);
             chunks += c;
             if (c > most) most = c;
@@ -1149,8 +1142,10 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     p.acc = q.acc;
     p.d = d;
     p.k = k;
-    fill_plain(p, grad, residual, d, gt);
-    p.hist = h->topk_hist;
+    fill_sweep(p, p.acc, d);
+    p.hist0 = h->topk_hist;
+    p.hist1 = p.hist0 + kTopkCopies * kTopkBins;
+    p.hist2 = p.hist1 + kTopkBins;
     p.st = &h->topk;
     p.cnt = h->cnt[0];
     p.seg = (int2*)((char*)c.ws + head_bytes());
@@ -1258,9 +1253,11 @@ int sidco_dgc_typed(void* stream, const void* grad, int grad_dtype, float* resid
     p.grad = grad;
     p.gt = gt;
     p.residual = residual;
+    p.acc_w = residual;
     p.d = d;
     p.k = k;
-    fill_plain(p, grad, residual, d, gt);
+    // a memoryless call only reads the gradient, and at any alignment
+    fill_sweep(p, residual ? residual : (gt == kGradF32 ? (const float*)grad : nullptr), d);
     p.seed = seed;
     p.n_s = (uint32_t)n_s;
     p.k_s = (uint32_t)k_s;
@@ -1283,8 +1280,15 @@ int sidco_dgc_typed(void* stream, const void* grad, int grad_dtype, float* resid
     t.d = d;
     t.k = k;
     t.k_from_state = 1;
-    fill_plain(t, grad, residual, d, gt);
-    t.hist = h->dgc_hist[1];
+    t.shift = p.shift;  // the lists' layout
+    t.nfull = p.nfull;
+    t.nwaves = p.nwaves;
+    t.tq = p.tq;
+    t.tr = p.tr;
+    t.nblocks = p.nblocks;
+    t.hist0 = h->dgc_hist[1];
+    t.hist1 = t.hist0 + kTopkBins;
+    t.hist2 = t.hist1 + kTopkBins;
     t.st = &h->dgc.lists;
     t.cnt = p.cnt;
     t.seg = p.seg;

@@ -119,7 +119,8 @@ struct WaveTiles {
     uint32_t n;       // tiles of the wave
     uint32_t k0, nb;  // its tiles number k0 .. k0 + nb - 1 are complete
 };
-__device__ __forceinline__ WaveTiles wave_tiles(const Params& p, uint32_t w)
+template <typename P>  // Params, TopkParams or DgcParams
+__device__ __forceinline__ WaveTiles wave_tiles(const P& p, uint32_t w)
 {
     WaveTiles t;
     t.w = w;
@@ -138,17 +139,109 @@ __device__ __forceinline__ uint32_t guarded_tile(const WaveTiles& t, uint32_t g)
     return (t.nb == 0 || g < t.k0) ? g : g + t.nb;
 }
 
-// Survivor list of wave w: its first slot and the slots it has (one per element of the wave's tiles).
-__device__ __forceinline__ size_t seg_begin(const Params& p, uint32_t w)
+// First tile of wave w if the waves took contiguous ranges of the same lengths.
+template <typename P>
+__device__ __forceinline__ uint32_t tile_begin(const P& p, uint32_t w)
 {
-    return (size_t)(w * p.tq + (w < p.tr ? w : p.tr)) * kTile;
+    return w * p.tq + (w < p.tr ? w : p.tr);
 }
-__device__ __forceinline__ uint32_t seg_slots(const Params& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
 
-// first tile of wave w where the waves take contiguous ranges: tiles are split as evenly as possible
-__device__ __forceinline__ uint32_t tile_begin(uint32_t w, uint32_t ntiles, uint32_t nwaves)
+// Survivor list of wave w: its first slot and the slots it has (one per element of the wave's tiles).
+template <typename P>
+__device__ __forceinline__ size_t seg_begin(const P& p, uint32_t w) { return (size_t)tile_begin(p, w) * kTile; }
+template <typename P>
+__device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
+
+// One wave's share of the sweep that forms acc = g + residual (EC; else acc = g) and stores it (WRITE) to p.acc_w.
+// The wave requests its next tile before it works on the one it has: one tile (1 KB of each operand) per wave in
+// flight is what 16 waves per CU need to keep HBM busy, and more only widens the window of addresses that the chip
+// works in (2 and 4 tiles ahead, and 32 waves per CU, were 1 to 5 % slower at 25.6 M to 138 M elements).
+// `v` sees every complete tile (v.tile(values, tile number)), every lane of the others (v.one(valid, value, index),
+// the wave together) and the end of each of those (v.end()).
+template <bool EC, bool WRITE, int GT, typename P, typename V>
+__device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v)
 {
-    return (uint32_t)(((unsigned long long)w * ntiles) / nwaves);
+    const WaveTiles wt = wave_tiles(p, w);
+    if (wt.nb > 0) {
+        float* acc = p.acc_w;
+        uint32_t t = w + wt.k0 * wt.W;
+        size_t i = (size_t)t * kTile + lane * 4 - p.shift;
+        const size_t step = (size_t)wt.W * kTile;
+        f4 g = load_grad4<GT, WRITE>(p.grad, i), r = {};
+        if (EC) r = *reinterpret_cast<const f4*>(acc + i);
+#pragma unroll 1
+        for (uint32_t k = 1; k < wt.nb; ++k) {
+            f4 c = g;
+            if (EC) c = g + r;
+            g = load_grad4<GT, WRITE>(p.grad, i + step);
+            if (EC) r = *reinterpret_cast<const f4*>(acc + i + step);
+            if (WRITE) *reinterpret_cast<f4*>(acc + i) = c;
+            v.tile(c, t);
+            t += wt.W;
+            i += step;
+        }
+        if (EC) g = g + r;
+        if (WRITE) *reinterpret_cast<f4*>(acc + i) = g;
+        v.tile(g, t);
+    }
+    for (uint32_t k = 0; k < wt.n - wt.nb; ++k) {
+        const uint32_t t = w + guarded_tile(wt, k) * wt.W;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+            const bool valid = i >= 0 && i < p.d;
+            float c = 0.0f;
+            if (valid) {
+                c = load_grad1<GT>(p.grad, i);
+                if (EC) c = c + p.acc_w[i];
+                if (WRITE) p.acc_w[i] = c;
+            }
+            v.one(valid, c, i);
+        }
+        v.end();
+    }
+}
+
+// The sweep of one wave over its tiles of the dense vector.  `reverse` walks them from the last to the first: the
+// kernel before this one left the end of what it touched last in the caches, and the host alternates the
+// direction from pass to pass so that each pass starts where the one before it stopped.
+// The loads are non-temporal: the vector has just been written by the first pass and much of it is still dirty in the
+// memory-side cache; reads that do not allocate behind it neither push those lines out early nor wait for them
+// (first pass and a statistics-only sweep together, plain against non-temporal loads: 65.7 and 63.9 us at 25.6 M
+// elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).
+struct DenseSweep {
+    const float* x;   // element 0 of tile 0, or a readable stand-in if the wave has no complete tile
+    uint32_t nb;      // complete tiles of the wave
+    uint32_t first;   // the first one in walking order
+    int32_t step;     // from one tile to the next in walking order
+    uint32_t any;     // a complete tile, the same one for every wave
+};
+
+template <typename P>
+__device__ __forceinline__ DenseSweep dense_sweep(const P& p, const WaveTiles& wt, bool reverse, const int2* stand_in)
+{
+    DenseSweep d;
+    d.nb = wt.nb;
+    d.x = d.nb > 0 ? p.acc - p.shift : reinterpret_cast<const float*>(stand_in);
+    const uint32_t k = wt.k0 + (reverse ? d.nb - 1 : 0u);
+    d.first = d.nb > 0 ? wt.w + k * wt.W : 0u;
+    d.step = reverse ? -(int32_t)wt.W : (int32_t)wt.W;
+    d.any = (d.nb > 0 && p.shift > 0) ? 1u : 0u;
+    return d;
+}
+
+// Tile number of the wave's j-th complete tile in walking order.
+__device__ __forceinline__ uint32_t dense_tile(const DenseSweep& d, uint32_t j)
+{
+    return d.first + (uint32_t)((int32_t)j * d.step);
+}
+
+// That tile's values.  Past the wave's last tile the same tile for every wave: the load is unconditional (loads under
+// a run-time condition come with waits on the spot), but costs no HBM traffic.
+__device__ __forceinline__ f4 dense_load(const DenseSweep& d, uint32_t j, int lane)
+{
+    const uint32_t t = j < d.nb ? dense_tile(d, j) : d.any;
+    return __builtin_nontemporal_load(reinterpret_cast<const f4*>(d.x + (size_t)t * kTile) + lane);
 }
 
 // A wave's survivor list under construction.  Entries are collected in LDS and written out in long

@@ -95,16 +95,16 @@ template <int DIGIT>
 __global__ __launch_bounds__(kBlock) void k_dgc_digit(DgcParams p)
 {
     __shared__ uint32_t sh_hist[1024];
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     uint32_t want, rest;
     if (DIGIT == 1) {
-        pick_bin<kTopkBins / kBlock>(p.hist_s, (unsigned long long)p.k_s, sh_scan, sh_out, want, rest);
+        pick_bin<kTopkBins / kBlock>(p.hist_s, (unsigned long long)p.k_s, sh_wave, sh_out, want, rest);
     } else {
         const uint32_t b0 = p.st->sample.prefix[0];
         uint32_t b1;
-        pick_bin<1024 / kBlock>(p.hist_s + kTopkBins, (unsigned long long)p.st->sample.k_rem[0], sh_scan, sh_out, b1,
+        pick_bin<1024 / kBlock>(p.hist_s + kTopkBins, (unsigned long long)p.st->sample.k_rem[0], sh_wave, sh_out, b1,
                                 rest);
         want = (b0 << 10) | b1;
         if (blockIdx.x == 0 && threadIdx.x == 0) p.st->sample.prefix[1] = b1;
@@ -134,16 +134,38 @@ __device__ __forceinline__ void dgc_emit(bool valid, float x, int32_t idx, float
     if (keep) atomicAdd(&sh_hist[mag_key(x) >> 20], 1u);
 }
 
+struct DgcTiles {
+    ListWriter lw;
+    uint32_t* sh_hist;
+    float eta;
+    int lane;
+    uint32_t shift;
+    __device__ __forceinline__ void tile(f4 c, uint32_t t)
+    {
+        const int32_t i0 = (int32_t)(t * kTile + lane * 4 - shift);
+        dgc_emit(true, c.x, i0 + 0, eta, lw, lane, sh_hist);
+        dgc_emit(true, c.y, i0 + 1, eta, lw, lane, sh_hist);
+        dgc_emit(true, c.z, i0 + 2, eta, lw, lane, sh_hist);
+        dgc_emit(true, c.w, i0 + 3, eta, lw, lane, sh_hist);
+        list_flush(lw, lane);
+    }
+    __device__ __forceinline__ void one(bool valid, float c, int64_t i)
+    {
+        dgc_emit(valid, c, (int32_t)i, eta, lw, lane, sh_hist);
+    }
+    __device__ __forceinline__ void end() { list_flush(lw, lane); }
+};
+
 template <bool EC, int GT>
 __global__ __launch_bounds__(kBlock, 4) void k_dgc_dense(DgcParams p)
 {
     __shared__ uint32_t sh_hist[kTopkBins];
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     __shared__ int2 ring[kWavesPerBlock][kRingSize];
     for (int i = threadIdx.x; i < kTopkBins; i += kBlock) sh_hist[i] = 0;
     uint32_t b2, ties;
-    pick_bin<1024 / kBlock>(p.hist_s + 2 * kTopkBins, (unsigned long long)p.st->sample.k_rem[1], sh_scan, sh_out, b2,
+    pick_bin<1024 / kBlock>(p.hist_s + 2 * kTopkBins, (unsigned long long)p.st->sample.k_rem[1], sh_wave, sh_out, b2,
                             ties);
     const uint32_t kappa = (p.st->sample.prefix[0] << 20) | (p.st->sample.prefix[1] << 10) | b2;
     const float eta = __int_as_float((int)kappa);
@@ -157,74 +179,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_dgc_dense(DgcParams p)
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     const uint32_t w = blockIdx.x * kWavesPerBlock + wib;
     if (w < p.nwaves) {
-        const uint32_t t0 = tile_begin(w, p.ntiles, p.nwaves), t1 = tile_begin(w + 1, p.ntiles, p.nwaves);
-        const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;  // tiles [t0,tf) are complete
-        ListWriter lw;
-        lw.list = p.seg + (size_t)t0 * kTile;
-        lw.ring = ring[wib];
-        lw.run = lw.fill = 0;
-        uint32_t t = t0;
-        if (p.vec_ok) {
-            f4* __restrict__ r4 = reinterpret_cast<f4*>(p.residual);
-            constexpr uint32_t U = 4;
-#pragma unroll 1
-            for (; t + U <= tf; t += U) {
-                f4 a[U], b[U];
-#pragma unroll
-                for (uint32_t u = 0; u < U; ++u) {
-                    const size_t i = (size_t)(t + u) * 64 + lane;
-                    a[u] = load_grad4<GT, EC>(p.grad, 4 * i);
-                    if (EC) b[u] = r4[i];
-                }
-#pragma unroll
-                for (uint32_t u = 0; u < U; ++u) {
-                    f4 c = a[u];
-                    if (EC) {
-                        c = a[u] + b[u];
-                        r4[(size_t)(t + u) * 64 + lane] = c;
-                    }
-                    const int32_t i0 = (int32_t)((t + u) * kTile + lane * 4);
-                    dgc_emit(true, c.x, i0 + 0, eta, lw, lane, sh_hist);
-                    dgc_emit(true, c.y, i0 + 1, eta, lw, lane, sh_hist);
-                    dgc_emit(true, c.z, i0 + 2, eta, lw, lane, sh_hist);
-                    dgc_emit(true, c.w, i0 + 3, eta, lw, lane, sh_hist);
-                    list_flush(lw, lane);
-                }
-            }
-            for (; t < tf; ++t) {
-                const size_t i = (size_t)t * 64 + lane;
-                f4 c = load_grad4<GT, false>(p.grad, 4 * i);
-                if (EC) {
-                    c = c + r4[i];
-                    r4[i] = c;
-                }
-                const int32_t i0 = (int32_t)(t * kTile + lane * 4);
-                dgc_emit(true, c.x, i0 + 0, eta, lw, lane, sh_hist);
-                dgc_emit(true, c.y, i0 + 1, eta, lw, lane, sh_hist);
-                dgc_emit(true, c.z, i0 + 2, eta, lw, lane, sh_hist);
-                dgc_emit(true, c.w, i0 + 3, eta, lw, lane, sh_hist);
-                list_flush(lw, lane);
-            }
-        }
-        // unaligned buffers and the ragged last tile: guarded scalar accesses
-        for (; t < t1; ++t) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t i = (int64_t)t * kTile + lane * 4 + j;
-                const bool valid = i < p.d;
-                float c = 0.0f;
-                if (valid) {
-                    c = load_grad1<GT>(p.grad, i);
-                    if (EC) {
-                        c = c + p.residual[i];
-                        p.residual[i] = c;
-                    }
-                }
-                dgc_emit(valid, c, (int32_t)i, eta, lw, lane, sh_hist);
-            }
-            list_flush(lw, lane);
-        }
-        const uint32_t n = list_finish(lw, lane);
+        DgcTiles v;
+        v.lw.list = p.seg + seg_begin(p, w);
+        v.lw.ring = ring[wib];
+        v.lw.run = v.lw.fill = 0;
+        v.sh_hist = sh_hist;
+        v.eta = eta;
+        v.lane = lane;
+        v.shift = p.shift;
+        acc_sweep<EC, EC, GT>(p, w, lane, v);
+        const uint32_t n = list_finish(v.lw, lane);
         if (lane == 0) p.cnt[w] = n;
     }
     __syncthreads();
@@ -238,7 +202,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_dgc_dense(DgcParams p)
 __global__ __launch_bounds__(kBlock) void k_dgc_lists(DgcParams p)
 {
     __shared__ uint32_t sh_hist[1024];
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     __shared__ unsigned long long sh_tot[kWavesPerBlock];
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
@@ -259,14 +223,14 @@ __global__ __launch_bounds__(kBlock) void k_dgc_lists(DgcParams p)
     }
     if (K == 0) return;  // block-uniform: nothing listed; the kernels after this one find k_eff = 0
     uint32_t b0, k1;
-    pick_bin<kTopkBins / kBlock>(p.hist_l, K, sh_scan, sh_out, b0, k1);
+    pick_bin<kTopkBins / kBlock>(p.hist_l, K, sh_wave, sh_out, b0, k1);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         p.st->lists.prefix[0] = b0;
         p.st->lists.k_rem[0] = k1;
     }
     const ListRange r = my_lists(p.nwaves);
     for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + (size_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
+        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
         const uint32_t n = p.cnt[sw];
         for (uint32_t c = lane; c < n; c += 64) {
             const uint32_t key = mag_key(__int_as_float(list[c].y));

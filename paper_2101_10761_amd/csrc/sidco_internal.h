@@ -93,10 +93,9 @@ struct Params {
     const float* acc;       // dense working vector read by stage 1's compaction: acc_w, else grad
     int64_t d;
     uint32_t shift;         // elements between the 128-byte boundary before acc[0] and acc[0] (see WaveTiles)
-    uint32_t ntiles;        // tiles of the vector: ceil((d + shift) / kTile)
     uint32_t nfull;         // (d + shift) / kTile: tiles below this index are complete (tile 0 only if shift = 0)
     uint32_t nwaves;        // waves that own tiles
-    uint32_t tq, tr;        // ntiles / nwaves and ntiles % nwaves (see WaveTiles)
+    uint32_t tq, tr;        // T / nwaves and T % nwaves, T = ceil((d + shift) / kTile) tiles (see WaveTiles)
     uint32_t nblocks;       // grid size of the kernels that read the dense vector or write partial sums
     int reverse;            // a dense stage kernel walks the tiles from the last to the first
     int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
@@ -128,6 +127,13 @@ struct Params {
 
 // ---- exact Top-k comparator (sidco_topk.hip) ----
 constexpr int kTopkBins = 2048;  // digit 0 = magnitude bits 30..20; digits 1 and 2 have 1024 bins
+// The blocks of k_topk_hist add their histograms of digit 0 to one of this many global copies: few of the 2048 bins
+// hold nearly all of a gradient, and same-address atomics of 512 blocks serialise at 11 ns each.  With the sweeps in
+// address order (see WaveTiles) and a search in the histogram that takes 3 barriers instead of 20, a call and its
+// scatter, us: 1 M elements 35.6 -> 26.7, 4 M 46.1 -> 36.9, 25.6 M 100.7 -> 90.2, 60 M 226.7 -> 182.8; bf16 off the
+// line grid 12 M 106.7 -> 64.0, 60 M 380.1 -> 222.3.
+constexpr int kTopkCopies = 8;
+constexpr int kTopkHist = (kTopkCopies + 2) * kTopkBins;  // words of all digits
 
 struct TopkState {
     uint32_t prefix[3];            // bin of the k-th largest key in digit 0, 1, 2
@@ -148,9 +154,10 @@ struct TopkParams {
     int64_t d;
     int64_t k;
     int k_from_state;       // the last kernel takes k from st->k_eff (may be 0) instead of `k`
-    uint32_t ntiles, nfull, nwaves, nblocks;
-    int vec_ok;
-    uint32_t* hist;         // [3][kTopkBins]
+    uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
+    uint32_t* hist0;        // [kTopkCopies][kTopkBins]
+    uint32_t* hist1;        // [1024]
+    uint32_t* hist2;        // [1024]
     TopkState* st;
     uint32_t* cnt;          // [kMaxWaves] list lengths
     int2* seg;              // per-wave lists
@@ -180,10 +187,10 @@ struct DgcParams {
     const void* grad; // d elements of type `gt`
     int gt;           // kGrad*
     float* residual;  // NULL: memoryless
+    float* acc_w;     // where the dense pass stores acc: residual, or nowhere
     int64_t d;
     int64_t k;        // target number of entries
-    uint32_t ntiles, nfull, nwaves, nblocks;
-    int vec_ok;
+    uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
     uint64_t seed;
     uint32_t n_s, k_s;  // subset size, rank of the threshold in it
     uint32_t* keys;     // [n_s] magnitude keys of the subset
@@ -221,10 +228,8 @@ struct TensorDesc {
     uint32_t first_final;   // ... and in the last stage's grid
     uint32_t nfinal;
     uint32_t index;         // position in out_counts / out_etas
-    uint32_t ntiles;        // tiles, whatever the alignment of the call's buffers (see max_tiles)
-    uint32_t nwaves;        // waves that own tiles of the vector, and ntiles / nwaves, ntiles % nwaves
-    uint32_t tq, tr;
-    uint32_t reserved;
+    uint32_t nwaves;        // waves that own tiles of the vector
+    uint32_t tq, tr;        // T / nwaves and T % nwaves, T the tiles at any alignment of the buffers (see max_tiles)
 };
 
 struct BatchTable {

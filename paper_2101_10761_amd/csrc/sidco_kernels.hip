@@ -426,65 +426,32 @@ __device__ __forceinline__ void fit_reset_state(const Params& p)
 
 // one element through the guarded scalar path
 template <int DIST, bool EC, int GT>
-__device__ __forceinline__ float fit_one(const Params& p, int64_t i, double& s1, double& s2, double& sl, int& se)
+__device__ __forceinline__ void fit_one(const Params& p, int64_t i, double& s1, double& s2, double& sl, int& se)
 {
     float c = load_grad1<GT>(p.grad, i);
     if (EC) c = c + p.acc_w[i];
     if (fit_writes<EC, GT>()) p.acc_w[i] = c;
     fit_accum<DIST>(c, s1, s2, sl, se);
-    return c;
 }
 
-// this lane's share of a tile that is not complete
-template <int DIST, bool EC, int GT>
-__device__ __forceinline__ void fit_guarded(const Params& p, uint32_t t, int lane, double& s1, double& s2, double& sl,
-                                            int& se)
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
-        if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+// the sums of one lane
+template <int DIST>
+struct FitSums {
+    double s1 = 0.0, s2 = 0.0, sl = 0.0;
+    int se = 0;
+    __device__ __forceinline__ void tile(f4 c, uint32_t)
+    {
+        fit_accum<DIST>(c.x, s1, s2, sl, se);
+        fit_accum<DIST>(c.y, s1, s2, sl, se);
+        fit_accum<DIST>(c.z, s1, s2, sl, se);
+        fit_accum<DIST>(c.w, s1, s2, sl, se);
     }
-}
-
-// One wave's tiles.  The wave requests its next tile before it adds up the one it has: one tile (1 KB of each
-// operand) per wave in flight is what 16 waves per CU need to keep HBM busy, and more only widens the window of
-// addresses that the chip works in (see WaveTiles).
-template <int DIST, bool EC, int GT>
-__device__ __forceinline__ void fit_wave(const Params& p, uint32_t w, int lane, double& s1, double& s2, double& sl,
-                                         int& se)
-{
-    constexpr bool WRITE = fit_writes<EC, GT>();
-    const WaveTiles wt = wave_tiles(p, w);
-    if (wt.nb > 0) {
-        float* acc = p.acc_w;
-        size_t i = (size_t)(w + wt.k0 * wt.W) * kTile + lane * 4 - p.shift;
-        const size_t step = (size_t)wt.W * kTile;
-        f4 g = load_grad4<GT, WRITE>(p.grad, i), r = {};
-        if (EC) r = *reinterpret_cast<const f4*>(acc + i);
-        auto add_up = [&](f4 c) {
-            fit_accum<DIST>(c.x, s1, s2, sl, se);
-            fit_accum<DIST>(c.y, s1, s2, sl, se);
-            fit_accum<DIST>(c.z, s1, s2, sl, se);
-            fit_accum<DIST>(c.w, s1, s2, sl, se);
-        };
-#pragma unroll 1
-        for (uint32_t k = 1; k < wt.nb; ++k) {
-            f4 c = g;
-            if (EC) c = g + r;
-            g = load_grad4<GT, WRITE>(p.grad, i + step);
-            if (EC) r = *reinterpret_cast<const f4*>(acc + i + step);
-            if (WRITE) *reinterpret_cast<f4*>(acc + i) = c;
-            add_up(c);
-            i += step;
-        }
-        if (EC) g = g + r;
-        if (WRITE) *reinterpret_cast<f4*>(acc + i) = g;
-        add_up(g);
+    __device__ __forceinline__ void one(bool valid, float c, int64_t)
+    {
+        if (valid) fit_accum<DIST>(c, s1, s2, sl, se);
     }
-    for (uint32_t g = 0; g < wt.n - wt.nb; ++g)
-        fit_guarded<DIST, EC, GT>(p, w + guarded_tile(wt, g) * wt.W, lane, s1, s2, sl, se);
-}
+    __device__ __forceinline__ void end() {}
+};
 
 template <int DIST, bool EC, int GT>
 __device__ __forceinline__ void fit_body(const Params& p, Blk b)
@@ -492,10 +459,9 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b)
     __shared__ double sh[kWavesPerBlock][4];
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     const uint32_t w = b.id * kWavesPerBlock + wib;
-    double s1 = 0.0, s2 = 0.0, sl = 0.0;
-    int se = 0;
-    if (w < p.nwaves) fit_wave<DIST, EC, GT>(p, w, lane, s1, s2, sl, se);
-    double v[3] = {s1, s2, sl + (double)se};
+    FitSums<DIST> f;
+    if (w < p.nwaves) acc_sweep<EC, fit_writes<EC, GT>(), GT>(p, w, lane, f);
+    double v[3] = {f.s1, f.s2, f.sl + (double)f.se};
     v[0] = wave_sum(v[0]);
     v[1] = wave_sum(v[1]);
     v[2] = wave_sum(v[2]);
@@ -623,41 +589,6 @@ __device__ __forceinline__ void compact_tile(f4 a, uint32_t t, uint32_t shift, i
     if (WRITE) list_flush(lw, lane);
 }
 
-// The sweep of one wave over its tiles of the dense vector.  p.reverse walks them from the last to the first: the
-// kernel before this one left the end of what it touched last in the caches, and the host alternates the
-// direction from pass to pass so that each pass starts where the one before it stopped.
-// The loads are non-temporal: the vector has just been written by k_fit and much of it is still dirty in the
-// memory-side cache; reads that do not allocate behind it neither push those lines out early nor wait for them
-// (k_fit_flat and a statistics-only sweep together, plain against non-temporal loads: 65.7 and 63.9 us at 25.6 M
-// elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).
-struct DenseSweep {
-    const float* x;   // the first lane's element of tile 0, or a readable stand-in if the wave has no complete tile
-    uint32_t nb;      // complete tiles of the wave
-    uint32_t first;   // the first one in walking order
-    int32_t step;     // from one tile to the next in walking order
-    uint32_t any;     // a complete tile, the same one for every wave
-};
-
-__device__ __forceinline__ DenseSweep dense_sweep(const Params& p, const WaveTiles& wt)
-{
-    DenseSweep d;
-    d.nb = wt.nb;
-    d.x = d.nb > 0 ? p.acc - p.shift : reinterpret_cast<const float*>(p.seg_out);
-    const uint32_t k = wt.k0 + (p.reverse ? d.nb - 1 : 0u);
-    d.first = d.nb > 0 ? wt.w + k * wt.W : 0u;
-    d.step = p.reverse ? -(int32_t)wt.W : (int32_t)wt.W;
-    d.any = (d.nb > 0 && p.shift > 0) ? 1u : 0u;
-    return d;
-}
-
-// Tile number j in walking order.  Past the wave's last tile the same tile for every wave: the load is
-// unconditional (loads under a run-time condition come with waits on the spot), but costs no HBM traffic.
-__device__ __forceinline__ f4 dense_load(const DenseSweep& d, uint32_t j, int lane)
-{
-    const uint32_t t = j < d.nb ? d.first + (uint32_t)((int32_t)j * d.step) : d.any;
-    return __builtin_nontemporal_load(reinterpret_cast<const f4*>(d.x + (size_t)t * kTile) + lane);
-}
-
 // `a` holds the wave's first kAhead tiles, requested before the threshold was known: a stage kernel's prologue is
 // a cold round trip for the partial sums plus a few hundred dependent fp64 instructions in which the memory pipes
 // would otherwise run dry.  From then on tile j + kAhead is requested before tile j is processed.
@@ -676,7 +607,7 @@ __device__ __forceinline__ void compact_dense(const Params& p, const WaveTiles& 
             if (j + u < d.nb) {  // wave-uniform
                 const f4 c = a[u];
                 a[u] = dense_load(d, j + u + kAhead, lane);
-                compact_tile<STATS, WRITE>(c, d.first + (uint32_t)((int32_t)(j + u) * d.step), p.shift, lane, eta_s, eta_w, lw,
+                compact_tile<STATS, WRITE>(c, dense_tile(d, j + u), p.shift, lane, eta_s, eta_w, lw,
                                            ns, sy, syy);
             }
         }
@@ -773,7 +704,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b)
     // them), then the first tiles, so that the stream runs while the partial sums are reduced and the
     // closed form is evaluated.
     PrologueLoads g = prologue_load(p, b, false);
-    const DenseSweep d = dense_sweep(p, wt);
+    const DenseSweep d = dense_sweep(p, wt, p.reverse != 0, p.seg_out);
     f4 a[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
@@ -829,7 +760,7 @@ __device__ __forceinline__ void lists_body(const Params& p, Blk b)
         if (!se.lists_ok) {
             // this stage's exceedances straight from the dense vector
             const WaveTiles wt = wave_tiles(p, w);
-            const DenseSweep d = dense_sweep(p, wt);
+            const DenseSweep d = dense_sweep(p, wt, p.reverse != 0, p.seg_out);
             f4 a[kAhead];
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
@@ -1365,7 +1296,6 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.acc = p.acc_w ? p.acc_w : reinterpret_cast<const float*>(p.grad);
     p.d = ds.d;
     p.shift = (uint32_t)((uintptr_t)p.acc >> 2) & (uint32_t)(kGrid - 1);
-    p.ntiles = ds.ntiles;
     p.nfull = (uint32_t)((ds.d + p.shift) / kTile);
     p.nwaves = ds.nwaves;
     p.tq = ds.tq;
@@ -1406,8 +1336,8 @@ __device__ __forceinline__ void block_tiles(const Params& p, Blk b, uint32_t& T0
 {
     const uint32_t w0 = b.id * kWavesPerBlock;
     const uint32_t w1 = w0 + kWavesPerBlock < p.nwaves ? w0 + kWavesPerBlock : p.nwaves;
-    T0 = w0 < p.nwaves ? tile_begin(w0, p.ntiles, p.nwaves) : 0;
-    T1 = w0 < p.nwaves ? tile_begin(w1, p.ntiles, p.nwaves) : 0;
+    T0 = w0 < p.nwaves ? tile_begin(p, w0) : 0;
+    T1 = w0 < p.nwaves ? tile_begin(p, w1) : 0;
 }
 
 template <int DIST, bool EC, int GT>
@@ -1458,7 +1388,11 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, do
             fit_accum<DIST>(c.z, s1, s2, sl, se);
             fit_accum<DIST>(c.w, s1, s2, sl, se);
         } else {
-            fit_guarded<DIST, EC, GT>(p, t, lane, s1, s2, sl, se);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+                if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+            }
         }
     }
     double v[3] = {s1, s2, sl + (double)se};

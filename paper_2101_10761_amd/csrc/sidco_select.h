@@ -14,34 +14,48 @@ namespace sidco {
 
 __device__ __forceinline__ uint32_t mag_key(float x) { return (uint32_t)__float_as_int(x) & 0x7fffffffu; }
 
-// Bin of `hist` (nb bins, nb = kBlock * PER) that holds the k-th largest entry, counted from the top
-// bin downwards, and the rank the entry has inside that bin.  Every thread of the block returns the
-// same pair.  Needs sum(hist) >= k >= 1.
-template <int PER>
-__device__ __forceinline__ void pick_bin(const uint32_t* __restrict__ hist, unsigned long long k, uint32_t* sh_scan,
-                                         uint32_t* sh_out, uint32_t& bin, uint32_t& k_in_bin)
+// A thread's PER bins of a digit histogram of kBlock * PER bins, summed over its COPIES copies.
+template <int PER, int COPIES = 1>
+__device__ __forceinline__ void load_bins(const uint32_t* __restrict__ hist, uint32_t (&local)[PER])
 {
-    const uint32_t t = threadIdx.x;
-    uint32_t local[PER];
-    uint32_t tsum = 0;
+    typedef uint32_t bins __attribute__((ext_vector_type(PER)));
+    bins c[COPIES];
+#pragma unroll
+    for (int k = 0; k < COPIES; ++k)
+        c[k] = *reinterpret_cast<const bins*>(hist + k * (kBlock * PER) + threadIdx.x * PER);
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        local[j] = hist[t * PER + j];
-        tsum += local[j];
+        local[j] = 0;
+#pragma unroll
+        for (int k = 0; k < COPIES; ++k) local[j] += c[k][j];
     }
-    // inclusive suffix sums over the threads (counts are at most d < 2^31: no overflow)
-    __syncthreads();  // protects sh_scan / sh_out against a previous use
-    sh_scan[t] = tsum;
+}
+
+// Bin of a digit histogram that holds the k-th largest entry, counted from the top bin downwards, and the rank the
+// entry has inside that bin; `local` are the thread's bins (load_bins).  Every thread of the block returns the
+// same pair.  Needs sum(hist) >= k >= 1.
+template <int PER>
+__device__ __forceinline__ void pick_bin(const uint32_t (&local)[PER], unsigned long long k, uint32_t* sh_wave,
+                                         uint32_t* sh_out, uint32_t& bin, uint32_t& k_in_bin)
+{
+    const uint32_t t = threadIdx.x, lane = t & 63, wib = t >> 6;
+    uint32_t tsum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) tsum += local[j];
+    // inclusive suffix sums over the threads (counts are at most d < 2^31: no overflow): within the wave, then
+    // the totals of the waves behind it
+    uint32_t s = tsum;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t other = __shfl_down(s, o, 64);
+        s += lane + o < 64 ? other : 0u;
+    }
+    __syncthreads();  // protects sh_wave / sh_out against a previous use
+    if (lane == 0) sh_wave[wib] = s;
     if (t == 0) sh_out[0] = sh_out[1] = 0;  // only reached if the histogram holds fewer than k entries
     __syncthreads();
-    uint32_t s = tsum;
-    for (uint32_t o = 1; o < (uint32_t)kBlock; o <<= 1) {
-        const uint32_t other = t + o < (uint32_t)kBlock ? sh_scan[t + o] : 0u;
-        __syncthreads();
-        s += other;
-        sh_scan[t] = s;
-        __syncthreads();
-    }
+#pragma unroll
+    for (uint32_t i = 1; i < (uint32_t)kWavesPerBlock; ++i) s += i > wib ? sh_wave[i] : 0u;
     const unsigned long long above = (unsigned long long)s - tsum;  // entries in the bins of later threads
     if (above < k && k <= (unsigned long long)s) {                  // exactly one thread
         unsigned long long acc = above;
@@ -57,6 +71,16 @@ __device__ __forceinline__ void pick_bin(const uint32_t* __restrict__ hist, unsi
     __syncthreads();
     bin = sh_out[0];
     k_in_bin = sh_out[1];
+}
+
+// the same from the histogram in memory
+template <int PER>
+__device__ __forceinline__ void pick_bin(const uint32_t* __restrict__ hist, unsigned long long k, uint32_t* sh_wave,
+                                         uint32_t* sh_out, uint32_t& bin, uint32_t& k_in_bin)
+{
+    uint32_t local[PER];
+    load_bins<PER>(hist, local);
+    pick_bin<PER>(local, k, sh_wave, sh_out, bin, k_in_bin);
 }
 
 // adds a block's LDS histogram to the global one

@@ -35,7 +35,7 @@ namespace sidco {
 __global__ __launch_bounds__(kBlock) void k_topk_zero(TopkParams p)
 {
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < 3u * kTopkBins) p.hist[i] = 0;
+    if (i < (uint32_t)kTopkHist) p.hist0[i] = 0;  // all digits, one piece
     if (i == 0) {
         p.st->gt_ctr = 0;
         p.st->eq_ctr = 0;
@@ -49,6 +49,22 @@ __global__ __launch_bounds__(kBlock) void k_topk_zero(TopkParams p)
 // ---------------------------------------------------------------------------------------------
 // k_topk_hist: error-compensation add + digit-0 histogram
 // ---------------------------------------------------------------------------------------------
+struct DigitHist {
+    uint32_t* sh_hist;
+    __device__ __forceinline__ void tile(f4 c, uint32_t)
+    {
+        atomicAdd(&sh_hist[mag_key(c.x) >> 20], 1u);
+        atomicAdd(&sh_hist[mag_key(c.y) >> 20], 1u);
+        atomicAdd(&sh_hist[mag_key(c.z) >> 20], 1u);
+        atomicAdd(&sh_hist[mag_key(c.w) >> 20], 1u);
+    }
+    __device__ __forceinline__ void one(bool valid, float c, int64_t)
+    {
+        if (valid) atomicAdd(&sh_hist[mag_key(c) >> 20], 1u);
+    }
+    __device__ __forceinline__ void end() {}
+};
+
 template <bool EC, int GT>
 __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
 {
@@ -57,61 +73,11 @@ __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
     __shared__ uint32_t sh_hist[kTopkBins];
     for (int i = threadIdx.x; i < kTopkBins; i += kBlock) sh_hist[i] = 0;
     __syncthreads();
-    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const uint32_t w = blockIdx.x * kWavesPerBlock + wib;
-    if (w < p.nwaves) {
-        const uint32_t t0 = tile_begin(w, p.ntiles, p.nwaves), t1 = tile_begin(w + 1, p.ntiles, p.nwaves);
-        const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;
-        uint32_t t = t0;
-        if (p.vec_ok) {
-            f4* __restrict__ r4 = reinterpret_cast<f4*>(p.acc_w);
-            constexpr int U = 4;
-            for (; t + U <= tf; t += U) {
-                f4 a[U], b[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const size_t i = (size_t)(t + u) * 64 + lane;
-                    // read once per call when acc is stored elsewhere: keep it out of the caches' way
-                    a[u] = load_grad4<GT, WRITE>(p.grad, 4 * i);
-                    if (EC) b[u] = r4[i];
-                }
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    f4 c = a[u];
-                    if (EC) c = a[u] + b[u];
-                    if (WRITE) r4[(size_t)(t + u) * 64 + lane] = c;
-                    atomicAdd(&sh_hist[mag_key(c.x) >> 20], 1u);
-                    atomicAdd(&sh_hist[mag_key(c.y) >> 20], 1u);
-                    atomicAdd(&sh_hist[mag_key(c.z) >> 20], 1u);
-                    atomicAdd(&sh_hist[mag_key(c.w) >> 20], 1u);
-                }
-            }
-            for (; t < tf; ++t) {
-                const size_t i = (size_t)t * 64 + lane;
-                f4 c = load_grad4<GT, false>(p.grad, 4 * i);
-                if (EC) c = c + r4[i];
-                if (WRITE) r4[i] = c;
-                atomicAdd(&sh_hist[mag_key(c.x) >> 20], 1u);
-                atomicAdd(&sh_hist[mag_key(c.y) >> 20], 1u);
-                atomicAdd(&sh_hist[mag_key(c.z) >> 20], 1u);
-                atomicAdd(&sh_hist[mag_key(c.w) >> 20], 1u);
-            }
-        }
-        for (; t < t1; ++t) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t i = (int64_t)t * kTile + lane * 4 + j;
-                if (i < p.d) {
-                    float c = load_grad1<GT>(p.grad, i);
-                    if (EC) c = c + p.acc_w[i];
-                    if (WRITE) p.acc_w[i] = c;
-                    atomicAdd(&sh_hist[mag_key(c) >> 20], 1u);
-                }
-            }
-        }
-    }
+    const uint32_t w = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    DigitHist h{sh_hist};
+    if (w < p.nwaves) acc_sweep<EC, WRITE, GT>(p, w, threadIdx.x & 63, h);
     __syncthreads();
-    merge_hist(sh_hist, p.hist, kTopkBins);
+    merge_hist(sh_hist, p.hist0 + (blockIdx.x % kTopkCopies) * kTopkBins, kTopkBins);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -130,63 +96,47 @@ __device__ __forceinline__ void topk_emit(bool valid, float x, int32_t idx, uint
 __global__ __launch_bounds__(kBlock, 4) void k_topk_compact(TopkParams p)
 {
     __shared__ uint32_t sh_hist[1024];
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     __shared__ int2 ring[kWavesPerBlock][kRingSize];
+    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+    const uint32_t w = blockIdx.x * kWavesPerBlock + wib;
+    const bool active = w < p.nwaves;
+    uint32_t bins[kTopkBins / kBlock];
+    load_bins<kTopkBins / kBlock, kTopkCopies>(p.hist0, bins);
+    // from the last tile to the first: k_topk_hist left the end of the vector in the caches
+    const WaveTiles wt = wave_tiles(p, active ? w : 0);
+    const DenseSweep ds = dense_sweep(p, wt, true, p.seg);
+    f4 a = dense_load(ds, 0, lane);  // behind the histogram's loads, ahead of the search in it
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     uint32_t b0, k1;
-    pick_bin<kTopkBins / kBlock>(p.hist, (unsigned long long)p.k, sh_scan, sh_out, b0, k1);
+    pick_bin<kTopkBins / kBlock>(bins, (unsigned long long)p.k, sh_wave, sh_out, b0, k1);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         p.st->prefix[0] = b0;
         p.st->k_rem[0] = k1;
     }
-    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const uint32_t w = blockIdx.x * kWavesPerBlock + wib;
-    if (w < p.nwaves) {
-        const uint32_t t0 = tile_begin(w, p.ntiles, p.nwaves), t1 = tile_begin(w + 1, p.ntiles, p.nwaves);
-        const uint32_t tf = t1 < p.nfull ? t1 : p.nfull;
+    if (active) {
         ListWriter lw;
-        lw.list = p.seg + (size_t)t0 * kTile;
+        lw.list = p.seg + seg_begin(p, w);
         lw.ring = ring[wib];
         lw.run = lw.fill = 0;
-        uint32_t ts = t0;
-        if (p.vec_ok) {
-            const f4* __restrict__ x4 = reinterpret_cast<const f4*>(p.acc);
-            constexpr uint32_t U = 4;
-            const uint32_t nb = (tf - t0) / U, rem = (tf - t0) - nb * U;
-            // from the last tile to the first: k_topk_hist left the end of the wave's range in L2
 #pragma unroll 1
-            for (uint32_t kb = 0; kb < nb; ++kb) {
-                const uint32_t t = tf - (kb + 1) * U;
-                f4 a[U];
-#pragma unroll
-                for (uint32_t u = 0; u < U; ++u) a[u] = x4[(size_t)(t + u) * 64 + lane];
-#pragma unroll
-                for (uint32_t u = 0; u < U; ++u) {
-                    const int32_t i0 = (int32_t)((t + u) * kTile + lane * 4);
-                    topk_emit(true, a[u].x, i0 + 0, b0, lw, lane, sh_hist);
-                    topk_emit(true, a[u].y, i0 + 1, b0, lw, lane, sh_hist);
-                    topk_emit(true, a[u].z, i0 + 2, b0, lw, lane, sh_hist);
-                    topk_emit(true, a[u].w, i0 + 3, b0, lw, lane, sh_hist);
-                    list_flush(lw, lane);
-                }
-            }
-            for (uint32_t t = t0; t < t0 + rem; ++t) {
-                const f4 a = x4[(size_t)t * 64 + lane];
-                const int32_t i0 = (int32_t)(t * kTile + lane * 4);
-                topk_emit(true, a.x, i0 + 0, b0, lw, lane, sh_hist);
-                topk_emit(true, a.y, i0 + 1, b0, lw, lane, sh_hist);
-                topk_emit(true, a.z, i0 + 2, b0, lw, lane, sh_hist);
-                topk_emit(true, a.w, i0 + 3, b0, lw, lane, sh_hist);
-                list_flush(lw, lane);
-            }
-            ts = tf;
+        for (uint32_t j = 0; j < ds.nb; ++j) {
+            const f4 c = a;
+            a = dense_load(ds, j + 1, lane);
+            const int32_t i0 = (int32_t)(dense_tile(ds, j) * kTile + lane * 4 - p.shift);
+            topk_emit(true, c.x, i0 + 0, b0, lw, lane, sh_hist);
+            topk_emit(true, c.y, i0 + 1, b0, lw, lane, sh_hist);
+            topk_emit(true, c.z, i0 + 2, b0, lw, lane, sh_hist);
+            topk_emit(true, c.w, i0 + 3, b0, lw, lane, sh_hist);
+            list_flush(lw, lane);
         }
-        for (uint32_t t = ts; t < t1; ++t) {
+        for (uint32_t g = 0; g < wt.n - wt.nb; ++g) {
+            const uint32_t t = w + guarded_tile(wt, g) * wt.W;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const int64_t i = (int64_t)t * kTile + lane * 4 + j;
-                const bool valid = i < p.d;
+                const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+                const bool valid = i >= 0 && i < p.d;
                 topk_emit(valid, valid ? p.acc[i] : 0.0f, (int32_t)i, b0, lw, lane, sh_hist);
             }
             list_flush(lw, lane);
@@ -195,20 +145,20 @@ __global__ __launch_bounds__(kBlock, 4) void k_topk_compact(TopkParams p)
         if (lane == 0) p.cnt[w] = n;
     }
     __syncthreads();
-    merge_hist(sh_hist, p.hist + kTopkBins, 1024);
+    merge_hist(sh_hist, p.hist1, 1024);
 }
 
 // k_topk_refine: digit-2 histogram of the list entries whose digits 0 and 1 are b0 and b1
 __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
 {
     __shared__ uint32_t sh_hist[1024];
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     const uint32_t b0 = p.st->prefix[0];
     const uint32_t k1 = p.st->k_rem[0];
     uint32_t b1, k2;
-    pick_bin<1024 / kBlock>(p.hist + kTopkBins, (unsigned long long)k1, sh_scan, sh_out, b1, k2);
+    pick_bin<1024 / kBlock>(p.hist1, (unsigned long long)k1, sh_wave, sh_out, b1, k2);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         p.st->prefix[1] = b1;
         p.st->k_rem[1] = k2;
@@ -217,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
     const uint32_t want = (b0 << 10) | b1;  // key >> 10
     const ListRange r = my_lists(p.nwaves);
     for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + (size_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
+        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
         const uint32_t n = p.cnt[sw];
         for (uint32_t c = lane; c < n; c += 64) {
             const uint32_t key = mag_key(__int_as_float(list[c].y));
@@ -225,20 +175,20 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
         }
     }
     __syncthreads();
-    merge_hist(sh_hist, p.hist + 2 * kTopkBins, 1024);
+    merge_hist(sh_hist, p.hist2, 1024);
 }
 
 // k_topk_final: the k-th largest key, the output and the residual update
 __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
 {
-    __shared__ uint32_t sh_scan[kBlock];
+    __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     __shared__ uint32_t sh_gt[kWavesPerBlock], sh_eq[kWavesPerBlock];
     __shared__ unsigned long long sh_base[2];
     const uint32_t b0 = p.st->prefix[0], b1 = p.st->prefix[1];
     const uint32_t k2 = p.st->k_rem[1];
     uint32_t b2, need;
-    pick_bin<1024 / kBlock>(p.hist + 2 * kTopkBins, (unsigned long long)k2, sh_scan, sh_out, b2, need);
+    pick_bin<1024 / kBlock>(p.hist2, (unsigned long long)k2, sh_wave, sh_out, b2, need);
     const uint32_t kappa = (b0 << 20) | (b1 << 10) | b2;
     const unsigned long long K = p.k_from_state ? (unsigned long long)p.st->k_eff : (unsigned long long)p.k;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
@@ -247,7 +197,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
     // pass A: entries above kappa and entries equal to it, per wave
     uint32_t n_gt = 0, n_eq = 0;
     for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + (size_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
+        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
         const uint32_t n = p.cnt[sw];
         for (uint32_t c = 0; c < n; c += 64) {
             const bool in = c + lane < n;
@@ -291,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
 
     // pass B: same traversal, writing
     for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + (size_t)tile_begin(sw, p.ntiles, p.nwaves) * kTile;
+        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
         const uint32_t n = p.cnt[sw];
         for (uint32_t c = 0; c < n; c += 64) {
             const bool in = c + lane < n;
@@ -325,7 +275,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
 // ---------------------------------------------------------------------------------------------
 void launch_topk_zero(const TopkParams& p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_topk_zero, dim3((3 * kTopkBins + kBlock - 1) / kBlock), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_topk_zero, dim3((kTopkHist + kBlock - 1) / kBlock), dim3(kBlock), 0, s, p);
 }
 
 template <int GT>

@@ -145,3 +145,19 @@ def test_profile_hooks_topk():
     finally:
         sidco.sidco_set_profiling(False)
     assert [n for n, _ in prof] == ["k_topk_zero", "k_topk_hist", "k_topk_compact", "k_topk_refine", "k_topk_final"]
+
+
+@pytest.mark.parametrize("d", [1, 225, 256, 257, 287, 481, 4096 * 256 - 16, 4096 * 256 + 1, 2 * 4096 * 256 - 255])
+@pytest.mark.parametrize("goff,roff", [(0, 0), (1, 1), (31, 31), (5, 30)])
+def test_edges_of_the_tile_split_off_the_line_grid(oracle, d, goff, roff):
+    """Tiles sit on the 128-byte lines of the accumulated vector; the gradient may have another alignment."""
+    import torch
+    g, r = _inputs(d, 40 + d % 97)
+    k = max(1, d // 100)
+    for residual in (r, None):
+        out = run_topk(g, residual, k, grad_offset=goff, res_offset=roff)
+        check_topk(oracle, g, residual, k, out, label=f"d={d} offsets {goff},{roff} ec={residual is not None}")
+    g16 = torch.from_numpy(g).to(torch.bfloat16)
+    for residual in (r, None):
+        out = run_topk(g16, residual, k, grad_offset=goff, res_offset=roff)
+        check_topk(oracle, g16.to(torch.float32).numpy(), residual, k, out, label=f"bf16 d={d} offsets {goff},{roff} ec={residual is not None}")
