@@ -284,6 +284,27 @@ float hint_floor(double cum, double L_stage, double L_next)
     return (float)(t > 0.0 ? t : 0.0);
 }
 
+// Whether the last stage selects from the dense vector and writes the residual back whole (k_select) although a list
+// could serve it.  Reading and writing the vector again costs the same whatever is kept; the list's writes and reads
+// grow with it, and so does the clearing of the residual, whose lines are then written in part.  A training step
+// with lists and with k_select, us (exponential law): 138 M elements, ratio 0.1 1063 and 978, 0.08 901 and 860, 0.05
+// 761 and 805; 90 M, 0.1 679 and 630; 60 M, 0.08 378 and 357; 40 M, 0.1 302 and 295; 20 M, 0.1 142 and 144.
+// Without a residual there is nothing to clear.
+constexpr int64_t kSelectMinD = 50000000;
+constexpr double kSelectMinRatio = 0.08;
+
+bool select_dense(int64_t d, bool residual, const double* ratios, int M, double theta)
+{
+    if (M < 2 || d < kSelectMinD || !residual) return false;
+    double cum = 1.0;
+    for (int m = 0; m < M; ++m) {
+        // lists that an earlier stage would write serve more than the last one
+        if (m < M - 2 && cum * exp(-(log(1.0 / ratios[m]) + theta * log(1.0 / ratios[m + 1]))) <= kMaterializeBelow) return false;
+        cum *= ratios[m];
+    }
+    return cum >= kSelectMinRatio;
+}
+
 // the host's view of a call's device state
 void fill_diag(const DevState& st, int64_t cap, sidco_diag* host_out)
 {
@@ -400,6 +421,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     // Stage m: threshold from the previous kernel's sums.  Buffers alternate with the kernel number.
     // `lists` turns true once a stage has written survivor lists (candidates or exceedances).
     bool lists = false;
+    const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
     double cum = 1.0;      // delta_1 ... delta_{m-1}
     double list_frac = 1;  // expected fraction of the vector in the current lists
     int sel = 0;           // which half of the double buffers the last kernel wrote
@@ -426,7 +448,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
             // dense source: statistics at eta_m, lists of candidates for stage m+1 (see stage_prologue)
             const double Lw = p.L[m - 1] + theta * p.L[m];
             const double frac = cum * exp(-Lw);
-            const bool write = frac <= kMaterializeBelow;
+            const bool write = frac <= kMaterializeBelow && !select;
             if (write && theta > 0.0) {
                 p.theta = (float)theta;
                 p.theta_min = hint_floor(cum, p.L[m - 1], p.L[m]);
@@ -451,7 +473,12 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
         cum *= ratios[m - 1];
     }
     bind(M);
-    if (!lists) {
+    if (select) {
+        p.reverse = reverse;
+        launch_select(p, s);
+        ++k;
+        mark("k_select_dense");
+    } else if (!lists) {
         p.reverse = reverse;
         launch_compact(p, /*stats=*/false, /*write=*/true, s);
         ++k;

@@ -23,6 +23,8 @@
 //                k_final_lists: the last stage for M >= 2; it selects, writes the contiguous
 //                (index, value) output and zeroes the residual at those indices in one kernel, each
 //                block reserving its output range with one atomic.
+//                k_eta, k_select: the last stage of a call that keeps a large part of a long vector: it selects from the
+//                dense vector and writes the residual back whole.
 //   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements.
 //   k_gather     M = 1 only (last stage read the dense vector): exclusive prefix over the per-block
 //                survivor counts, copy of the lists into the output, residual zeroing.
@@ -160,6 +162,8 @@ __device__ __forceinline__ double stage_L(const Params& p, int i)
         if (j == i) v = p.L[j];
     return v;
 }
+
+__device__ __forceinline__ Blk whole_grid() { return Blk{blockIdx.x, gridDim.x}; }
 
 // What the prologue of a stage's kernel hands to its body.
 struct StageEta {
@@ -971,6 +975,111 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
 }
 
 // ---------------------------------------------------------------------------------------------
+// k_eta + k_select: last stage of a call that keeps so much of a long vector that lists would not pay (see
+// select_dense in the host code).  k_eta, one block, evaluates eta_M; the blocks of k_select start in address order,
+// each takes kSelectTiles tiles per wave into registers, reserves its output range with one atomic and writes the pairs
+// and the tiles back with the selected entries zeroed.  Whole lines, where clearing the entries one by one leaves
+// lines that are written in part, and the pairs come in nearly ascending order, which the scatter that follows
+// profits from.  The set of pairs is deterministic, the order of the blocks' ranges is not.  Bound by HBM: at 138 M
+// elements and a ratio of 0.1 204 us for 1.22 GB, the scatter 243; k_final_lists took 235, the dense stage that wrote its
+// lists 30 more than one that only sums, and the scatter 270.
+// ---------------------------------------------------------------------------------------------
+__global__ __launch_bounds__(kBlock) void k_eta(Params p)
+{
+    __shared__ double sh[kWavesPerBlock][4];
+    const StageEta se = stage_prologue(p, whole_grid(), false, sh);
+    if (threadIdx.x == 0) {
+        *p.out_eta = se.eta;
+        const uint32_t status = p.st->status_after[p.M];  // written by this thread in the prologue
+        p.st->diag.status = status;
+        if (p.status_out && status) *p.status_out = status;
+    }
+}
+
+// WHOLE: all tiles of the block are complete
+template <bool WHOLE>
+__device__ __forceinline__ void select_body(const Params& p, uint32_t first, uint32_t* sh_cnt, uint32_t* sh_base)
+{
+    constexpr int kWaves = kSelectBlock / 64;
+    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+    const uint32_t t0 = first + wib * kSelectTiles;
+    f4 a[kSelectTiles];
+#pragma unroll
+    for (int u = 0; u < kSelectTiles; ++u) {
+        const int64_t i = (int64_t)(t0 + u) * kTile + lane * 4 - p.shift;
+        if constexpr (WHOLE) {
+            a[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.acc + i));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a[u][j] = i + j >= 0 && i + j < p.d ? p.acc[i + j] : 0.0f;  // 0 is never above eta
+        }
+    }
+    const float eta = p.st->diag.eta[p.M - 1];
+    uint32_t mine = 0;
+#pragma unroll
+    for (int u = 0; u < kSelectTiles; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mine += (uint32_t)__popcll(__ballot(__builtin_fabsf(a[u][j]) > eta));
+    if (lane == 0) sh_cnt[wib] = mine;
+    __syncthreads();
+    uint32_t pos = 0, total = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+        if (i < wib) pos += sh_cnt[i];
+        total += sh_cnt[i];
+    }
+    const uint32_t cap = (uint32_t)p.out_cap;
+    if (threadIdx.x == 0) {
+        const unsigned long long base = atomicAdd(&p.st->selected_ctr, (unsigned long long)total);
+        *sh_base = (uint32_t)base;
+        const unsigned long long end = base + total;
+        atomicMax(p.out_count, (int32_t)(end < cap ? end : cap));
+        if (end > cap) {
+            p.st->overflow = 1u;  // every writer stores the same value
+            if (p.status_out) atomicOr(p.status_out, kStOverflow);
+        }
+    }
+    __syncthreads();
+    pos += *sh_base;  // at most d: 32 bits hold it
+#pragma unroll
+    for (int u = 0; u < kSelectTiles; ++u) {
+        const int64_t i = (int64_t)(t0 + u) * kTile + lane * 4 - p.shift;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float x = a[u][j];
+            const bool sel = __builtin_fabsf(x) > eta;
+            const unsigned long long mask = __ballot(sel);
+            const uint32_t at = pos + lane_prefix(mask);
+            if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
+                p.out_idx[at] = (int32_t)(i + j);
+                p.out_val[at] = x;
+                a[u][j] = 0.0f;
+            }
+            pos += (uint32_t)__popcll(mask);
+        }
+        if (p.residual) {
+            if constexpr (WHOLE) {
+                *reinterpret_cast<f4*>(p.residual + i) = a[u];
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (i + j >= 0 && i + j < p.d) p.residual[i + j] = a[u][j];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSelectBlock) void k_select(Params p)
+{
+    __shared__ uint32_t sh_cnt[kSelectBlock / 64];
+    __shared__ uint32_t sh_base;
+    constexpr uint32_t kTiles = kSelectBlock / 64 * kSelectTiles;
+    const uint32_t first = (p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * kTiles;
+    if (first + kTiles <= p.nfull && (first > 0 || p.shift == 0)) select_body<true>(p, first, sh_cnt, &sh_base);
+    else select_body<false>(p, first, sh_cnt, &sh_base);
+}
+
+// ---------------------------------------------------------------------------------------------
 // k_gather: survivor lists of the last stage -> contiguous (index, value) output; residual update.
 // Used when the last stage read the dense vector (M = 1): no atomics, output order is fixed.
 // ---------------------------------------------------------------------------------------------
@@ -1280,8 +1389,6 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
 // kernels: one call on one vector (the grid is the vector's), or a batch of vectors in one launch
 // (every block belongs to one vector and finds that vector's arguments in a table on the device)
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ Blk whole_grid() { return Blk{blockIdx.x, gridDim.x}; }
-
 // Arguments of this block's vector in a batched launch.  final_grid: the launch uses the last stage's
 // (smaller) grid.
 __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_grid, Blk& b, uint32_t gb = blockIdx.x)
@@ -1578,6 +1685,14 @@ void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
     const uint32_t least = (p.nwaves + kFinalGroup * kWavesPerBlock - 1) / (kFinalGroup * kWavesPerBlock);
     if (grid_blocks < least) grid_blocks = least;
     hipLaunchKernelGGL(k_final_lists, dim3(grid_blocks), dim3(kBlock), 0, s, p);
+}
+
+void launch_select(const Params& p, hipStream_t s)
+{
+    constexpr uint32_t kTiles = kSelectBlock / 64 * kSelectTiles;
+    const uint32_t tiles = p.nwaves * p.tq + p.tr;
+    hipLaunchKernelGGL(k_eta, dim3(1), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_select, dim3((tiles + kTiles - 1) / kTiles), dim3(kSelectBlock), 0, s, p);
 }
 
 void launch_gather(const Params& p, hipStream_t s)

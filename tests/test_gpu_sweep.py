@@ -197,3 +197,32 @@ def test_which_calls_one_block_takes():
         assert [n for n, _ in sidco.sidco_get_profile()] == ["k_fit", "k_compact_dense", "k_final_lists"]
     finally:
         sidco.sidco_set_profiling(False)
+
+
+@pytest.mark.parametrize("dist,ratios,cap,offset", [(0, [0.25, 0.4], None, 0), (0, [0.25, 0.64, 0.64], 1_000_001, 3),
+                                                    (2, [0.4, 0.25], None, 31), (1, [0.3, 0.3], None, 1)])
+def test_last_stage_on_the_dense_vector(oracle, dist, ratios, cap, offset):
+    """From 50 M elements and a ratio of 0.08 the last stage reads the dense vector and writes the residual back whole."""
+    import paper_2101_10761_amd as sidco
+    d = 50_000_003
+    rng = np.random.default_rng(dist + len(ratios))
+    g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+    r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+    sidco.sidco_set_profiling(True)
+    try:
+        out = run_gpu(g, r, dist, ratios, cap=cap, grad_offset=offset, res_offset=offset)
+        assert [n for n, _ in sidco.sidco_get_profile()][-1] == "k_select_dense"
+    finally:
+        sidco.sidco_set_profiling(False)
+    check_parity(oracle, g, r, dist, ratios, out, capacity=cap, label=f"dist={dist} {ratios} cap={cap}")
+
+
+@pytest.mark.parametrize("kind", ["nan", "zero"])
+def test_last_stage_on_a_dense_vector_of_nothing_to_select(oracle, kind):
+    d = 50_000_000
+    g = np.zeros(d, np.float32)
+    if kind == "nan":
+        g[d // 2] = np.nan
+        g[-1] = 3.0
+    out = run_gpu(g, np.zeros(d, np.float32), 0, [0.25, 0.4], cap=1000)
+    check_parity(oracle, g, np.zeros(d, np.float32), 0, [0.25, 0.4], out, capacity=1000, label=kind)
