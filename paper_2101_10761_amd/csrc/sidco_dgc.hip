@@ -205,6 +205,7 @@ __global__ __launch_bounds__(kBlock) void k_dgc_lists(DgcParams p)
     __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
     __shared__ unsigned long long sh_tot[kWavesPerBlock];
+    const ListGroup lists = load_lists(p);
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     // S = total of the digit-0 histogram
@@ -228,15 +229,10 @@ __global__ __launch_bounds__(kBlock) void k_dgc_lists(DgcParams p)
         p.st->lists.prefix[0] = b0;
         p.st->lists.k_rem[0] = k1;
     }
-    const ListRange r = my_lists(p.nwaves);
-    for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
-        const uint32_t n = p.cnt[sw];
-        for (uint32_t c = lane; c < n; c += 64) {
-            const uint32_t key = mag_key(__int_as_float(list[c].y));
-            if ((key >> 20) == b0) atomicAdd(&sh_hist[(key >> 10) & 1023u], 1u);
-        }
-    }
+    for_lists(lists, [&](bool in, int2 e) {
+        const uint32_t key = mag_key(__int_as_float(e.y));
+        if (in && (key >> 20) == b0) atomicAdd(&sh_hist[(key >> 10) & 1023u], 1u);
+    });
     __syncthreads();
     merge_hist(sh_hist, p.hist_l + kTopkBins, 1024);
 }
@@ -299,7 +295,7 @@ void launch_dgc_dense(const DgcParams& p, hipStream_t s)
 
 void launch_dgc_lists(const DgcParams& p, uint32_t grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_dgc_lists, dim3(grid), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_dgc_lists, dim3(list_grid(p.nwaves, grid)), dim3(kBlock), 0, s, p);
 }
 
 }  // namespace sidco

@@ -1377,8 +1377,10 @@ void launch_clear_u32(uint32_t* p, hipStream_t s) { hipLaunchKernelGGL(k_clear_u
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s)
 {
-    // the list length is only known on the device: a grid for the capacity, capped; idle blocks exit at once
-    int64_t blocks = (capacity + 4 * kBlock - 1) / (4 * kBlock);
+    // the list length is only known on the device: a thread for every place of the capacity, capped; idle blocks exit at
+    // once.  Top-k's capacity is its length, and with four places per thread that was 13 blocks for 25557 pairs, each
+    // a chain of four updates: 7.1 us, against 4.0 for as many pairs in four times the capacity.
+    int64_t blocks = (capacity + kBlock - 1) / kBlock;
     if (blocks < 1) blocks = 1;
     if (blocks > 2 * kMaxBlocks) blocks = 2 * kMaxBlocks;
     hipLaunchKernelGGL(k_scatter_add, dim3((uint32_t)blocks), dim3(kBlock), 0, s, dense, d, idx, val, count, capacity,

@@ -9,6 +9,7 @@
 #include <stdint.h>
 
 #include "sidco_internal.h"
+#include "sidco_device.h"
 
 namespace sidco {
 
@@ -93,19 +94,52 @@ __device__ __forceinline__ void merge_hist(const uint32_t* sh_hist, uint32_t* __
 }
 
 // ---------------------------------------------------------------------------------------------
-// the per-wave lists split over a small grid: a wave takes the lists first, first + 8, ... below last
+// The per-wave lists split over a small grid: a wave takes the lists first, first + 8, ... below last, at most
+// kListGroup of them (list_grid), and requests the length and the first 64 entries of each at once:
+// one list after the other is two dependent round trips for a handful of entries each.
 // ---------------------------------------------------------------------------------------------
-struct ListRange {
-    uint32_t first, last;
-};
-__device__ __forceinline__ ListRange my_lists(uint32_t nwaves)
+constexpr uint32_t kListGroup = 4;
+inline uint32_t list_grid(uint32_t nwaves, uint32_t wanted)
 {
-    const uint32_t per_block = (nwaves + gridDim.x - 1) / gridDim.x;
-    ListRange r;
-    r.first = blockIdx.x * per_block + (threadIdx.x >> 6);
-    const uint32_t end = (blockIdx.x + 1) * per_block;
-    r.last = end < nwaves ? end : nwaves;
-    return r;
+    const uint32_t least = (nwaves + kListGroup * kWavesPerBlock - 1) / (kListGroup * kWavesPerBlock);
+    return wanted > least ? wanted : least;
+}
+struct ListGroup {
+    const int2* list[kListGroup];
+    uint32_t n[kListGroup];   // entries
+    int2 head[kListGroup];    // the lane's entry among the first 64; stale past the end
+};
+template <typename P>
+__device__ __forceinline__ ListGroup load_lists(const P& p)
+{
+    const uint32_t per_block = (p.nwaves + gridDim.x - 1) / gridDim.x;
+    const uint32_t first = blockIdx.x * per_block + (threadIdx.x >> 6);
+    const uint32_t end = (blockIdx.x + 1) * per_block, last = end < p.nwaves ? end : p.nwaves;
+    ListGroup g;
+#pragma unroll
+    for (uint32_t k = 0; k < kListGroup; ++k) {
+        const uint32_t sw = first + k * kWavesPerBlock;
+        const uint32_t w = sw < last ? sw : 0u;
+        g.list[k] = p.seg + seg_begin(p, w);  // room for at least a tile
+        g.n[k] = sw < last ? p.cnt[w] : 0u;
+        g.head[k] = g.list[k][threadIdx.x & 63];
+    }
+    return g;
+}
+// f(in, entry) for every group of 64 entries of the wave's lists, the wave together
+template <typename F>
+__device__ __forceinline__ void for_lists(const ListGroup& g, F f)
+{
+    const uint32_t lane = threadIdx.x & 63;
+#pragma unroll
+    for (uint32_t k = 0; k < kListGroup; ++k) {
+        const uint32_t n = __builtin_amdgcn_readfirstlane(g.n[k]);
+        if (n > 0) f(lane < n, g.head[k]);
+        for (uint32_t c = 64; c < n; c += 64) {
+            const bool in = c + lane < n;
+            f(in, in ? g.list[k][c + lane] : make_int2(0, 0));
+        }
+    }
 }
 
 }  // namespace sidco

@@ -154,6 +154,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
     __shared__ uint32_t sh_hist[1024];
     __shared__ uint32_t sh_wave[kWavesPerBlock];
     __shared__ uint32_t sh_out[2];
+    const ListGroup lists = load_lists(p);
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     const uint32_t b0 = p.st->prefix[0];
     const uint32_t k1 = p.st->k_rem[0];
@@ -163,17 +164,11 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
         p.st->prefix[1] = b1;
         p.st->k_rem[1] = k2;
     }
-    const int lane = threadIdx.x & 63;
     const uint32_t want = (b0 << 10) | b1;  // key >> 10
-    const ListRange r = my_lists(p.nwaves);
-    for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
-        const uint32_t n = p.cnt[sw];
-        for (uint32_t c = lane; c < n; c += 64) {
-            const uint32_t key = mag_key(__int_as_float(list[c].y));
-            if ((key >> 10) == want) atomicAdd(&sh_hist[key & 1023u], 1u);
-        }
-    }
+    for_lists(lists, [&](bool in, int2 e) {
+        const uint32_t key = mag_key(__int_as_float(e.y));
+        if (in && (key >> 10) == want) atomicAdd(&sh_hist[key & 1023u], 1u);
+    });
     __syncthreads();
     merge_hist(sh_hist, p.hist2, 1024);
 }
@@ -185,6 +180,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
     __shared__ uint32_t sh_out[2];
     __shared__ uint32_t sh_gt[kWavesPerBlock], sh_eq[kWavesPerBlock];
     __shared__ unsigned long long sh_base[2];
+    const ListGroup lists = load_lists(p);
     const uint32_t b0 = p.st->prefix[0], b1 = p.st->prefix[1];
     const uint32_t k2 = p.st->k_rem[1];
     uint32_t b2, need;
@@ -192,20 +188,14 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
     const uint32_t kappa = (b0 << 20) | (b1 << 10) | b2;
     const unsigned long long K = p.k_from_state ? (unsigned long long)p.st->k_eff : (unsigned long long)p.k;
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const ListRange r = my_lists(p.nwaves);
 
     // pass A: entries above kappa and entries equal to it, per wave
     uint32_t n_gt = 0, n_eq = 0;
-    for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
-        const uint32_t n = p.cnt[sw];
-        for (uint32_t c = 0; c < n; c += 64) {
-            const bool in = c + lane < n;
-            const uint32_t key = in ? mag_key(__int_as_float(list[c + lane].y)) : 0u;
-            n_gt += (uint32_t)__popcll(__ballot(in && key > kappa));
-            n_eq += (uint32_t)__popcll(__ballot(in && key == kappa));
-        }
-    }
+    for_lists(lists, [&](bool in, int2 e) {
+        const uint32_t key = mag_key(__int_as_float(e.y));
+        n_gt += (uint32_t)__popcll(__ballot(in && key > kappa));
+        n_eq += (uint32_t)__popcll(__ballot(in && key == kappa));
+    });
     if (lane == 0) {
         sh_gt[wib] = n_gt;
         sh_eq[wib] = n_eq;
@@ -240,34 +230,28 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
     const unsigned long long tie_base = K - need;
 
     // pass B: same traversal, writing
-    for (uint32_t sw = r.first; sw < r.last; sw += kWavesPerBlock) {
-        const int2* __restrict__ list = p.seg + seg_begin(p, sw);
-        const uint32_t n = p.cnt[sw];
-        for (uint32_t c = 0; c < n; c += 64) {
-            const bool in = c + lane < n;
-            const int2 e = in ? list[c + lane] : make_int2(0, 0);
-            const uint32_t key = mag_key(__int_as_float(e.y));
-            const bool gt = in && key > kappa, eq = in && key == kappa;
-            const unsigned long long m_gt = __ballot(gt), m_eq = __ballot(eq);
-            unsigned long long at = 0;
-            bool take = false;
-            if (gt) {
-                at = pos_gt + lane_prefix(m_gt);
-                take = at < tie_base;  // always true; keeps a corrupted histogram from writing out of bounds
-            } else if (eq) {
-                const unsigned long long rank = pos_eq + lane_prefix(m_eq);
-                take = rank < need;
-                at = tie_base + rank;
-            }
-            if (take) {
-                p.out_idx[at] = e.x;
-                p.out_val[at] = __int_as_float(e.y);
-                if (p.residual) p.residual[e.x] = 0.0f;
-            }
-            pos_gt += (unsigned long long)__popcll(m_gt);
-            pos_eq += (unsigned long long)__popcll(m_eq);
+    for_lists(lists, [&](bool in, int2 e) {
+        const uint32_t key = mag_key(__int_as_float(e.y));
+        const bool gt = in && key > kappa, eq = in && key == kappa;
+        const unsigned long long m_gt = __ballot(gt), m_eq = __ballot(eq);
+        unsigned long long at = 0;
+        bool take = false;
+        if (gt) {
+            at = pos_gt + lane_prefix(m_gt);
+            take = at < tie_base;  // always true; keeps a corrupted histogram from writing out of bounds
+        } else if (eq) {
+            const unsigned long long rank = pos_eq + lane_prefix(m_eq);
+            take = rank < need;
+            at = tie_base + rank;
         }
-    }
+        if (take) {
+            p.out_idx[at] = e.x;
+            p.out_val[at] = __int_as_float(e.y);
+            if (p.residual) p.residual[e.x] = 0.0f;
+        }
+        pos_gt += (unsigned long long)__popcll(m_gt);
+        pos_eq += (unsigned long long)__popcll(m_eq);
+    });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -301,12 +285,12 @@ void launch_topk_compact(const TopkParams& p, hipStream_t s)
 
 void launch_topk_refine(const TopkParams& p, uint32_t grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_topk_refine, dim3(grid), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_topk_refine, dim3(list_grid(p.nwaves, grid)), dim3(kBlock), 0, s, p);
 }
 
 void launch_topk_final(const TopkParams& p, uint32_t grid, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_topk_final, dim3(grid), dim3(kBlock), 0, s, p);
+    hipLaunchKernelGGL(k_topk_final, dim3(list_grid(p.nwaves, grid)), dim3(kBlock), 0, s, p);
 }
 
 }  // namespace sidco
