@@ -885,7 +885,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     pl.final_blocks = ff;
     pl.slots = slot;
     // The flat first pass (k_fit_flat_batched) launches, for every block of the dense grid, as many chunks of
-    // 4 tiles as the block with the most tiles needs.  It pays from kFlatMinBatch elements in all, and
+    // kFlatChunk tiles as the block with the most tiles needs.  It pays from kFlatMinBatch elements in all, and
     // only while most of the launched chunks exist: with a few long vectors among many short ones (whose one
     // block has few tiles) the grid would be mostly empty.
     uint64_t total = 0, chunks = 0, most = 0;
@@ -897,7 +897,7 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
             const uint64_t w0 = (uint64_t)b * kWavesPerBlock;
             const uint64_t w1 = w0 + kWavesPerBlock < nwaves ? w0 + kWavesPerBlock : nwaves;
             const uint64_t tiles = (w1 - w0) * ds.tq + (w1 < ds.tr ? w1 : ds.tr) - (w0 < ds.tr ? w0 : ds.tr);
-            const uint64_t c = (tiles + kFlatBlock / 64 - 1) / (kFlatBlock / 64);
+            const uint64_t c = (tiles + kFlatChunk - 1) / kFlatChunk;
             chunks += c;
             if (c > most) most = c;
         }

@@ -277,6 +277,8 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
 // and 135.0, 58 M 154.2 and 155.1, 62 M 164.5 and 161.2, 80 M 217.0 and 205.7; with a bf16 gradient 50 M 120.1 and
 // 126.8, 62 M 148.7 and 150.8, 80 M 193.3 and 191.2.
 constexpr int kFlatBlock = 256;
+constexpr int kFlatTiles = 2;                                // tiles per wave of a batch's flat first pass
+constexpr uint32_t kFlatChunk = kFlatBlock / 64 * kFlatTiles;  // and per block
 constexpr int64_t kFlatMinD = 58000000;
 // A batch's waves walk the tiles of their own vector, so that its window is as many as it has vectors, and the flat
 // shape pays earlier: 25.6 M elements in 161 tensors 96.6 us per wave and 90.6 flat, 66 M in 50 tensors 236.6 and 204.

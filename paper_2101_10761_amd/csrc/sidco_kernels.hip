@@ -1466,7 +1466,8 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 }
 // The first pass of a batch in the flat shape (see k_fit_flat): blockIdx.y is a block of the batch's dense grid
 // - it names the vector and, within it, the tiles that block's waves own - and blockIdx.x a chunk of
-// kFlatBlock / 64 = 4 of those tiles, one tile per wave.  Blocks run in the order x first, then y: address
+// kFlatChunk = 8 of those tiles, two per wave (a block's look into the batch's table is a chain of two round trips
+// ahead of its data; 161 tensors, 25.6 M elements, with one, two and four tiles per wave: 86.1, 84.1 and 87.5 us).  Blocks run in the order x first, then y: address
 // order.  Chunks past the end of a y's tiles exit at once (the host launches the flat shape only when few
 // are).
 template <int DIST, bool EC, int GT>
@@ -1478,29 +1479,48 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, do
     const Params p = batch_params(a, false, b, blockIdx.y);
     uint32_t T0, T1;
     block_tiles(p, b, T0, T1);
-    const uint32_t first = T0 + blockIdx.x * (kFlatBlock / 64);
+    const uint32_t first = T0 + blockIdx.x * kFlatChunk;
     if (first >= T1) return;  // the whole block
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const uint32_t t = first + wib;
     double s1 = 0.0, s2 = 0.0, sl = 0.0;
     int se = 0;
-    if (t < T1) {
-        if (t < p.nfull && (t > 0 || p.shift == 0)) {
-            constexpr bool WRITE = fit_writes<EC, GT>();
-            const size_t i = (size_t)t * kTile + lane * 4 - p.shift;
-            f4 c = load_grad4<GT, WRITE>(p.grad, i);
-            f4* a4 = reinterpret_cast<f4*>(p.acc_w + i);
-            if (EC) c = c + *a4;
-            if (WRITE) *a4 = c;
-            fit_accum<DIST>(c.x, s1, s2, sl, se);
-            fit_accum<DIST>(c.y, s1, s2, sl, se);
-            fit_accum<DIST>(c.z, s1, s2, sl, se);
-            fit_accum<DIST>(c.w, s1, s2, sl, se);
-        } else {
+    constexpr bool WRITE = fit_writes<EC, GT>();
+    auto add_up = [&](f4 c) {
+        fit_accum<DIST>(c.x, s1, s2, sl, se);
+        fit_accum<DIST>(c.y, s1, s2, sl, se);
+        fit_accum<DIST>(c.z, s1, s2, sl, se);
+        fit_accum<DIST>(c.w, s1, s2, sl, se);
+    };
+    if (first + kFlatChunk <= T1 && first + kFlatChunk <= p.nfull && (first > 0 || p.shift == 0)) {
+        f4 c[kFlatTiles], r[kFlatTiles];
+        const size_t i = (size_t)(first + wib) * kTile + lane * 4 - p.shift;
+        constexpr size_t step = (size_t)(kFlatBlock / 64) * kTile;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
-                if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+        for (int u = 0; u < kFlatTiles; ++u) {
+            c[u] = load_grad4<GT, WRITE>(p.grad, i + u * step);
+            if (EC) r[u] = *reinterpret_cast<const f4*>(p.acc_w + i + u * step);
+        }
+#pragma unroll
+        for (int u = 0; u < kFlatTiles; ++u) {
+            if (EC) c[u] = c[u] + r[u];
+            if (WRITE) *reinterpret_cast<f4*>(p.acc_w + i + u * step) = c[u];
+            add_up(c[u]);
+        }
+    } else {
+        const uint32_t end = first + kFlatChunk < T1 ? first + kFlatChunk : T1;
+        for (uint32_t t = first + wib; t < end; t += kFlatBlock / 64) {
+            if (t < p.nfull && (t > 0 || p.shift == 0)) {
+                const size_t i = (size_t)t * kTile + lane * 4 - p.shift;
+                f4 c = load_grad4<GT, WRITE>(p.grad, i);
+                if (EC) c = c + *reinterpret_cast<const f4*>(p.acc_w + i);
+                if (WRITE) *reinterpret_cast<f4*>(p.acc_w + i) = c;
+                add_up(c);
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+                    if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+                }
             }
         }
     }
@@ -1534,7 +1554,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a, cons
     const Params p = batch_params(a, false, b, y);
     uint32_t T0, T1;
     block_tiles(p, b, T0, T1);
-    const uint32_t nchunk = (T1 - T0 + kFlatBlock / 64 - 1) / (kFlatBlock / 64);
+    const uint32_t nchunk = (T1 - T0 + kFlatChunk - 1) / kFlatChunk;
     const size_t stride = (size_t)gx * nb, base = (size_t)y * gx;
     double v[3] = {0.0, 0.0, 0.0};
     for (uint32_t c = lane; c < nchunk; c += 64) {
@@ -1703,7 +1723,7 @@ void launch_gather(const Params& p, hipStream_t s)
 }
 
 // batched: `blocks` is the sum of the vectors' grids (the last stage's own, smaller sum for launch_final).
-// `flat_gx` > 0: the first pass in the flat shape, `flat_gx` chunks of 4 tiles per block of the dense grid, with
+// `flat_gx` > 0: the first pass in the flat shape, `flat_gx` chunks of 8 tiles per block of the dense grid, with
 // `scratch` holding 3 * flat_gx * blocks doubles; a second kernel folds them.
 template <bool EC, int GT>
 static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t flat_gx, double* scratch, hipStream_t s)
