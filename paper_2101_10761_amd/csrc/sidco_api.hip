@@ -833,6 +833,7 @@ struct BatchPlan {
     uint32_t blocks = 0, final_blocks = 0;
     uint64_t slots = 0;  // survivor-list slots of all vectors
     uint32_t flat_gx = 0;  // > 0: the first pass runs in the flat shape with this many chunks per block (see below)
+    bool fold = false;     // and its partial sums are too many for the next kernel's prologue
 };
 
 // Splits a launch over the vectors so that no block has more tiles than one of 512 blocks would have if all
@@ -904,8 +905,10 @@ int plan_batch(const int64_t* offsets, int n, const int64_t* out_offsets, BatchP
     }
     pl.flat_gx = 0;
     if ((int64_t)total >= kFlatMinBatch && most * fb <= 2 * chunks && most <= 0x7fffffffull / fb &&
-        3 * most * fb <= slot)  // the partial sums borrow the second list buffer
+        3 * most * fb <= slot)  // the partial sums borrow the first list buffer
         pl.flat_gx = (uint32_t)most;
+    for (int t = 0; t < n; ++t)
+        if ((uint64_t)pl.desc[t].nblocks * pl.flat_gx > kFlatDirect) pl.fold = true;
     return SIDCO_OK;
 }
 
@@ -1058,7 +1061,12 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     // same sequence as a single call (see run), every kernel once for all vectors
     a.in = 1;
     a.out = 0;
-    launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, (double*)a.seg[1], s);  // seg[1] is free until the first stage kernel writes it
+    // the first list buffer is free until the second stage's kernel writes it, and the first stage's reads the sums
+    a.flat = (double*)a.seg[0];
+    a.flat_gx = pl.flat_gx;
+    a.flat_blocks = pl.blocks;
+    launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, pl.fold, s);
+    const bool flat = pl.flat_gx > 0 && !pl.fold;
     bool lists = false, cand = false, reverse = true;
     double cum = 1.0;
     int sel = 0;
@@ -1081,7 +1089,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
             }
             a.reverse = reverse ? 1 : 0;
             reverse = !reverse;
-            launch_compact_batched(a, /*stats=*/true, write, pl.blocks, s);
+            launch_compact_batched(a, /*stats=*/true, write, flat && m == 1, pl.blocks, s);
             if (write) {
                 lists = true;
                 cand = theta > 0.0;
@@ -1095,7 +1103,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     bind(M);
     if (!lists) {
         a.reverse = reverse ? 1 : 0;
-        launch_compact_batched(a, /*stats=*/false, /*write=*/true, pl.blocks, s);
+        launch_compact_batched(a, /*stats=*/false, /*write=*/true, flat && M == 1, pl.blocks, s);
         a.in = sel;  // the gather reads what the compaction just wrote
         launch_gather_batched(a, pl.blocks, s);
     } else {

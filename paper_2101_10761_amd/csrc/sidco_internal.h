@@ -259,10 +259,12 @@ struct BatchArgs {
     double L[SIDCO_MAX_STAGES];
     float theta, theta_min;
     int use_hint, prev_cand;
+    double* flat;           // partial sums of a flat first pass (see k_fit_flat_batched), chunks per block and blocks
+    uint32_t flat_gx, flat_blocks;
 };
 
-void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, double* scratch, hipStream_t s);
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s);
+void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s);
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, uint32_t blocks, hipStream_t s);
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
 void launch_final_lists_batched(const BatchArgs& a, uint32_t final_blocks, hipStream_t s);
 void launch_gather_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
@@ -283,6 +285,10 @@ constexpr int64_t kFlatMinD = 58000000;
 // A batch's waves walk the tiles of their own vector, so that its window is as many as it has vectors, and the flat
 // shape pays earlier: 25.6 M elements in 161 tensors 96.6 us per wave and 90.6 flat, 66 M in 50 tensors 236.6 and 204.
 constexpr int64_t kFlatMinBatch = 12000000;
+// A batch whose longest vector has at most this many flat partial sums leaves them to the prologue of the first
+// stage's kernel, 4 loads per thread and quantity; beyond it a kernel folds them first, 4.8 us against 1 to 2.5 in that
+// prologue: 161 tensors, 25.6 M elements 83.5 -> 81.6 us, 200 tensors, 14 M 49.0 -> 47.0.
+constexpr uint32_t kFlatDirect = 4 * kBlock;
 inline bool fit_uses_flat(int64_t d) { return d >= kFlatMinD; }
 inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 {

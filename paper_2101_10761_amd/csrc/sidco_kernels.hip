@@ -201,6 +201,7 @@ struct PrologueLoads {
     FitRecord prev_fit; // the producer's candidate fit (block 0, thread 0 only)
 };
 
+template <bool FLAT = false>
 __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, bool auto_src)
 {
     const int m = p.stage;  // 1-based
@@ -216,7 +217,9 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
     g.eta_prev = 0.0f;
     g.status = 0;
     g.frozen = false;
-    if (m == 1) {
+    if (FLAT) {
+        g.v[0] = g.v[1] = g.v[2] = 0.0;  // flat_sums
+    } else if (m == 1) {
         g.v[0] = have ? p.part_in[0 * kBatchBlocks + t] : 0.0;
         g.v[1] = (have && p.dist == kDistGpd) ? p.part_in[1 * kBatchBlocks + t] : 0.0;
         g.v[2] = (have && p.dist == kDistGamma) ? p.part_in[2 * kBatchBlocks + t] : 0.0;
@@ -229,6 +232,45 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
         g.frozen = p.st->frozen_after[m - 1] != 0;
     }
     return g;
+}
+
+// Behind an unfolded flat first pass (stage 1 of a batch) a thread's share of the partial sums is several values:
+// loaded together with the prologue's other loads, added up once the bulk loads are on their way.
+struct FlatPart {
+    const double* part;  // the vector's partial sums
+    uint32_t n;          // their number for each quantity, at most kFlatDirect
+    uint32_t stride;     // from one quantity's to the next one's
+};
+struct FlatLoads {
+    double a[kFlatDirect / kBlock], b[kFlatDirect / kBlock];
+};
+__device__ __forceinline__ FlatLoads flat_load(const FlatPart& fp, int dist)
+{
+    FlatLoads f;
+    // the law's second quantity, if it has one
+    const double* second = fp.part + (size_t)(dist == kDistGamma ? 2 : dist == kDistGpd ? 1 : 0) * fp.stride;
+#pragma unroll
+    for (uint32_t k = 0; k < kFlatDirect / kBlock; ++k) {
+        const uint32_t i = k * kBlock + threadIdx.x;
+        const uint32_t at = i < fp.n ? i : 0u;
+        f.a[k] = fp.part[at];
+        f.b[k] = second[at];
+    }
+    return f;
+}
+__device__ __forceinline__ void flat_sums(const FlatPart& fp, const FlatLoads& f, int dist, PrologueLoads& g)
+{
+    double a = 0.0, b = 0.0;
+#pragma unroll
+    for (uint32_t k = 0; k < kFlatDirect / kBlock; ++k) {
+        if (k * kBlock + threadIdx.x < fp.n) {
+            a += f.a[k];
+            b += f.b[k];
+        }
+    }
+    g.v[0] = a;
+    g.v[1] = dist == kDistGpd ? b : 0.0;
+    g.v[2] = dist == kDistGamma ? b : 0.0;
 }
 
 // Evaluates eta for stage p.stage from the reduced sums in g.v; called by the first wave of a block, and block 0's
@@ -692,8 +734,8 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
 // k_compact: a stage that reads the dense vector.  STATS: form the sums for the next stage's fit.
 // WRITE: append the entries above eta_w to this stage's lists (eta_w = eta_m, or a candidate threshold
 // above it); a stage whose candidates would still be a large fraction only counts and sums.
-template <bool STATS, bool WRITE>
-__device__ __forceinline__ void compact_body(const Params& p, Blk b)
+template <bool STATS, bool WRITE, bool FLAT = false>
+__device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{})
 {
     __shared__ double sh[kWavesPerBlock][4];
     __shared__ uint32_t sh_cnt[kWavesPerBlock];
@@ -707,11 +749,14 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b)
     // prologue's go first (the memory counter retires in order: behind the tiles they would wait for
     // them), then the first tiles, so that the stream runs while the partial sums are reduced and the
     // closed form is evaluated.
-    PrologueLoads g = prologue_load(p, b, false);
+    PrologueLoads g = prologue_load<FLAT>(p, b, false);
+    FlatLoads f;
+    if constexpr (FLAT) f = flat_load(fp, p.dist);
     const DenseSweep d = dense_sweep(p, wt, p.reverse != 0, p.seg_out);
     f4 a[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
+    if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
 
     const StageEta se = prologue_finish(p, b, false, g, sh);
 
@@ -1468,11 +1513,10 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // - it names the vector and, within it, the tiles that block's waves own - and blockIdx.x a chunk of
 // kFlatChunk = 8 of those tiles, two per wave (a block's look into the batch's table is a chain of two round trips
 // ahead of its data; 161 tensors, 25.6 M elements, with one, two and four tiles per wave: 86.1, 84.1 and 87.5 us).  Blocks run in the order x first, then y: address
-// order.  Chunks past the end of a y's tiles exit at once (the host launches the flat shape only when few
+// order.  Chunks past the end of a y's tiles leave zeros and exit (the host launches the flat shape only when few
 // are).
 template <int DIST, bool EC, int GT>
-__global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, double* __restrict__ flat_part,
-                                                                  uint32_t stride)
+__global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
 {
     __shared__ double sh[kFlatBlock / 64][4];
     Blk b;
@@ -1480,7 +1524,12 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, do
     uint32_t T0, T1;
     block_tiles(p, b, T0, T1);
     const uint32_t first = T0 + blockIdx.x * kFlatChunk;
-    if (first >= T1) return;  // the whole block
+    const size_t stride = (size_t)gridDim.y * gridDim.x, slot = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    if (b.id == 0 && blockIdx.x == 0 && threadIdx.x == 0) fit_reset_state(p);
+    if (first >= T1) {  // the whole block
+        if (threadIdx.x < 3) a.flat[threadIdx.x * stride + slot] = 0.0;
+        return;
+    }
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     double s1 = 0.0, s2 = 0.0, sl = 0.0;
     int se = 0;
@@ -1538,29 +1587,26 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a, do
         double tot = 0.0;
 #pragma unroll
         for (int w = 0; w < kFlatBlock / 64; ++w) tot += sh[w][threadIdx.x];
-        flat_part[(size_t)threadIdx.x * stride + (size_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
+        a.flat[threadIdx.x * stride + slot] = tot;
     }
 }
 
 // Folds the chunks' partial sums of every block y of the batch's dense grid into that block's slot, in a
-// fixed order: one wave per y.  `gx` is the x extent of k_fit_flat_batched's grid, `nb` its y extent.
-__global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a, const double* __restrict__ flat_part,
-                                                               uint32_t gx, uint32_t nb)
+// fixed order: one wave per y.
+__global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t y = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-    if (y >= nb) return;  // the whole wave; no block-wide synchronisation below
+    if (y >= a.flat_blocks) return;  // the whole wave; no block-wide synchronisation below
     Blk b;
     const Params p = batch_params(a, false, b, y);
-    uint32_t T0, T1;
-    block_tiles(p, b, T0, T1);
-    const uint32_t nchunk = (T1 - T0 + kFlatChunk - 1) / kFlatChunk;
-    const size_t stride = (size_t)gx * nb, base = (size_t)y * gx;
+    const size_t stride = (size_t)a.flat_gx * a.flat_blocks;
+    const double* part = a.flat + (size_t)y * a.flat_gx;
     double v[3] = {0.0, 0.0, 0.0};
-    for (uint32_t c = lane; c < nchunk; c += 64) {
-        v[0] += flat_part[base + c];
-        if (p.dist == kDistGpd) v[1] += flat_part[stride + base + c];
-        if (p.dist == kDistGamma) v[2] += flat_part[2 * stride + base + c];
+    for (uint32_t c = lane; c < a.flat_gx; c += 64) {
+        v[0] += part[c];
+        if (p.dist == kDistGpd) v[1] += part[stride + c];
+        if (p.dist == kDistGamma) v[2] += part[2 * stride + c];
     }
     v[0] = wave_sum(v[0]);
     v[1] = wave_sum(v[1]);
@@ -1569,16 +1615,21 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a, cons
         p.part_out[0 * kBatchBlocks + b.id] = v[0];
         p.part_out[1 * kBatchBlocks + b.id] = v[1];
         p.part_out[2 * kBatchBlocks + b.id] = v[2];
-        if (b.id == 0) fit_reset_state(p);
     }
 }
 
-template <bool STATS, bool WRITE>
+template <bool STATS, bool WRITE, bool FLAT>
 __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
 {
     Blk b;
     const Params p = batch_params(a, false, b);
-    compact_body<STATS, WRITE>(p, b);
+    FlatPart fp = {};
+    if (FLAT) {
+        fp.part = a.flat + (size_t)(blockIdx.x - b.id) * a.flat_gx;  // from the vector's first block on
+        fp.n = p.nblocks * a.flat_gx;
+        fp.stride = a.flat_blocks * a.flat_gx;
+    }
+    compact_body<STATS, WRITE, FLAT>(p, b, fp);
 }
 __global__ __launch_bounds__(kBlock, 4) void k_lists_batched(BatchArgs a)
 {
@@ -1724,26 +1775,20 @@ void launch_gather(const Params& p, hipStream_t s)
 
 // batched: `blocks` is the sum of the vectors' grids (the last stage's own, smaller sum for launch_final).
 // `flat_gx` > 0: the first pass in the flat shape, `flat_gx` chunks of 8 tiles per block of the dense grid, with
-// `scratch` holding 3 * flat_gx * blocks doubles; a second kernel folds them.
+// a.flat holding 3 * flat_gx * blocks doubles; `fold`: a second kernel folds them.
 template <bool EC, int GT>
-static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t flat_gx, double* scratch, hipStream_t s)
+static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
 {
     if (flat_gx > 0) {
         const dim3 grid(flat_gx, blocks), block(kFlatBlock);
-        const uint32_t stride = flat_gx * blocks;
         switch (a.dist) {
-            case kDistExp:
-                hipLaunchKernelGGL((k_fit_flat_batched<kDistExp, EC, GT>), grid, block, 0, s, a, scratch, stride);
-                break;
-            case kDistGamma:
-                hipLaunchKernelGGL((k_fit_flat_batched<kDistGamma, EC, GT>), grid, block, 0, s, a, scratch, stride);
-                break;
-            default:
-                hipLaunchKernelGGL((k_fit_flat_batched<kDistGpd, EC, GT>), grid, block, 0, s, a, scratch, stride);
-                break;
+            case kDistExp: hipLaunchKernelGGL((k_fit_flat_batched<kDistExp, EC, GT>), grid, block, 0, s, a); break;
+            case kDistGamma: hipLaunchKernelGGL((k_fit_flat_batched<kDistGamma, EC, GT>), grid, block, 0, s, a); break;
+            default: hipLaunchKernelGGL((k_fit_flat_batched<kDistGpd, EC, GT>), grid, block, 0, s, a); break;
         }
-        hipLaunchKernelGGL(k_fit_reduce_batched, dim3((blocks + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, s,
-                           a, scratch, flat_gx, blocks);
+        if (fold)
+            hipLaunchKernelGGL(k_fit_reduce_batched, dim3((blocks + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, s,
+                               a);
         return;
     }
     const dim3 grid(blocks), block(kBlock);
@@ -1755,28 +1800,35 @@ static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t 
 }
 
 template <int GT>
-static void launch_fit_batched_type(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, double* scratch,
-                                    hipStream_t s)
+static void launch_fit_batched_type(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
 {
-    if (ec) launch_fit_batched_as<true, GT>(a, blocks, flat_gx, scratch, s);
-    else launch_fit_batched_as<false, GT>(a, blocks, flat_gx, scratch, s);
+    if (ec) launch_fit_batched_as<true, GT>(a, blocks, flat_gx, fold, s);
+    else launch_fit_batched_as<false, GT>(a, blocks, flat_gx, fold, s);
 }
 
-void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, double* scratch, hipStream_t s)
+void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
 {
     switch (a.gt) {
-        case kGradF16: launch_fit_batched_type<kGradF16>(a, ec, blocks, flat_gx, scratch, s); break;
-        case kGradBf16: launch_fit_batched_type<kGradBf16>(a, ec, blocks, flat_gx, scratch, s); break;
-        default: launch_fit_batched_type<kGradF32>(a, ec, blocks, flat_gx, scratch, s); break;
+        case kGradF16: launch_fit_batched_type<kGradF16>(a, ec, blocks, flat_gx, fold, s); break;
+        case kGradBf16: launch_fit_batched_type<kGradBf16>(a, ec, blocks, flat_gx, fold, s); break;
+        default: launch_fit_batched_type<kGradF32>(a, ec, blocks, flat_gx, fold, s); break;
     }
 }
 
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s)
+template <bool FLAT>
+static void launch_compact_batched_as(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s)
 {
     const dim3 grid(blocks), block(kBlock);
-    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true>), grid, block, 0, s, a);
-    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_compact_batched<false, true>), grid, block, 0, s, a);
+    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true, FLAT>), grid, block, 0, s, a);
+    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, FLAT>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_compact_batched<false, true, FLAT>), grid, block, 0, s, a);
+}
+
+// `flat`: the first stage, behind a flat first pass whose partial sums have not been folded
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, uint32_t blocks, hipStream_t s)
+{
+    if (flat) launch_compact_batched_as<true>(a, stats, write, blocks, s);
+    else launch_compact_batched_as<false>(a, stats, write, blocks, s);
 }
 
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s)

@@ -226,3 +226,17 @@ def test_last_stage_on_a_dense_vector_of_nothing_to_select(oracle, kind):
         g[-1] = 3.0
     out = run_gpu(g, np.zeros(d, np.float32), 0, [0.25, 0.4], cap=1000)
     check_parity(oracle, g, np.zeros(d, np.float32), 0, [0.25, 0.4], out, capacity=1000, label=kind)
+
+
+@pytest.mark.parametrize("sizes", [[1_100_001] * 11 + [1, 300], [4_180_000] * 3, [4_180_000, 4_220_000, 4_180_000, 5]],
+                         ids=["short", "below_the_limit", "above_the_limit"])
+@pytest.mark.parametrize("dist,delta,stages", [(0, 0.02, 1), (1, 0.002, 2), (2, 0.01, 3)])
+def test_flat_batches_with_and_without_a_fold_kernel(oracle, sizes, dist, delta, stages):
+    """2048 partial sums, of 2048 elements each, are the most that the first stage's prologue adds up by itself."""
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(len(sizes) + dist)
+    offs = [0] + [int(v) for v in np.cumsum(sizes)]
+    g = (rng.standard_t(3.0, size=offs[-1]) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
+    out = run_batched(g, r, offs, delta, dist, stages, repeat=2)
+    check_batched(oracle, g, r, offs, delta, dist, stages, out, f"{len(sizes)} tensors dist={dist} M={stages}")
