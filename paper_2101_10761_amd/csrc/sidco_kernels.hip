@@ -893,42 +893,63 @@ __device__ __forceinline__ void final_emit(const Params& p, int4 q, uint32_t slo
     }
 }
 
-// Dense fallback of the two passes: the elements of source wave sw's tiles, 64 consecutive ones per step.
-__device__ __forceinline__ uint32_t final_count_dense(const Params& p, uint32_t sw, int lane, float eta)
+// Dense fallback of the two passes over the tiles of source wave sw.  f(values, index of the first) for four
+// consecutive elements per lane, the wave together; elements outside the vector come as zeros, which are never above
+// a threshold.  kFallbackAhead tiles are requested at a time: a wave has up to four source waves' tiles to itself here,
+// and one round trip per 64 elements, as it was, took 330 us for a tensor of 83 K elements in a batch.
+constexpr int kFallbackAhead = 4;
+
+template <typename F>
+__device__ __forceinline__ void fallback_sweep(const Params& p, uint32_t sw, int lane, F f)
 {
     const WaveTiles wt = wave_tiles(p, sw);
-    uint32_t c = 0;
-    for (uint32_t k = 0; k < wt.n; ++k) {
-        for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
-            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane - p.shift;
-            const bool in = i >= 0 && i < p.d;
-            const bool sel = in && __builtin_fabsf(p.acc[in ? i : 0]) > eta;
-            c += (uint32_t)__popcll(__ballot(sel));
-        }
+    const DenseSweep d = dense_sweep(p, wt, false, p.seg_out);
+#pragma unroll 1
+    for (uint32_t j = 0; j < d.nb; j += kFallbackAhead) {
+        f4 a[kFallbackAhead];
+#pragma unroll
+        for (int u = 0; u < kFallbackAhead; ++u) a[u] = dense_load(d, j + u, lane);
+#pragma unroll
+        for (int u = 0; u < kFallbackAhead; ++u)
+            if (j + u < d.nb) f(a[u], (int64_t)dense_tile(d, j + u) * kTile + lane * 4 - p.shift);  // wave-uniform
     }
+#pragma unroll 1
+    for (uint32_t g = 0; g < wt.n - wt.nb; ++g) {
+        const int64_t i = (int64_t)(wt.w + guarded_tile(wt, g) * wt.W) * kTile + lane * 4 - p.shift;
+        f4 a;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) a[j] = i + j >= 0 && i + j < p.d ? p.acc[i + j] : 0.0f;
+        f(a, i);
+    }
+}
+
+__device__ __forceinline__ uint32_t final_count_dense(const Params& p, uint32_t sw, int lane, float eta)
+{
+    uint32_t c = 0;
+    fallback_sweep(p, sw, lane, [&](f4 a, int64_t) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) c += (uint32_t)__popcll(__ballot(__builtin_fabsf(a[j]) > eta));
+    });
     return c;
 }
 
 __device__ __forceinline__ void final_emit_dense(const Params& p, uint32_t sw, int lane, float eta,
                                                  unsigned long long cap, unsigned long long& pos)
 {
-    const WaveTiles wt = wave_tiles(p, sw);
-    for (uint32_t k = 0; k < wt.n; ++k) {
-        for (uint32_t o = 0; o < (uint32_t)kTile; o += 64) {
-            const int64_t i = (int64_t)(wt.w + k * wt.W) * kTile + o + lane - p.shift;
-            const bool in = i >= 0 && i < p.d;
-            const float x = in ? p.acc[i] : 0.0f;
-            const bool sel = in && __builtin_fabsf(x) > eta;
+    fallback_sweep(p, sw, lane, [&](f4 a, int64_t i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool sel = __builtin_fabsf(a[j]) > eta;
             const unsigned long long mask = __ballot(sel);
             const unsigned long long at = pos + lane_prefix(mask);
             if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
-                p.out_idx[at] = (int32_t)i;
-                p.out_val[at] = x;
-                if (p.residual) p.residual[i] = 0.0f;
+                p.out_idx[at] = (int32_t)(i + j);
+                p.out_val[at] = a[j];
+                if (p.residual) p.residual[i + j] = 0.0f;
             }
             pos += (unsigned long long)__popcll(mask);
         }
-    }
+    });
 }
 
 __device__ __forceinline__ void final_body(const Params& p, Blk b)
