@@ -390,7 +390,7 @@ def main():
         except Exception:
             traffic, counters = None, None
     roofline = {
-        "kernel": "k_fit (first pass; from 12 M elements k_fit_flat + k_fit_reduce)", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
+        "kernel": "k_fit (first pass; from 58 M elements k_fit_flat + k_fit_reduce)", "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
         "frac": round(achieved / HBM_PEAK_GBPS, 4), "traffic": traffic,
         "traffic_source": None if traffic is None else "from profiles/hbm_traffic.json (rocprofv3 --pmc FETCH_SIZE and WRITE_SIZE of an "
                           "earlier run of this workload, scaled by a device copy of known size); not measured in this run",
