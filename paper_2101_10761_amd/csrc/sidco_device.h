@@ -1,5 +1,5 @@
 // Device-side helpers shared by the kernels of the SIDCo library: wave primitives, the split of the
-// vector into per-wave tile ranges, and the LDS-staged writer of per-wave survivor lists.
+// vector into per-wave tiles, the sweeps over them, and the LDS-staged writer of per-wave survivor lists.
 #ifndef SIDCO_DEVICE_H
 #define SIDCO_DEVICE_H
 
