@@ -284,6 +284,32 @@ float hint_floor(double cum, double L_stage, double L_next)
     return (float)(t > 0.0 ? t : 0.0);
 }
 
+double kept_ratio(const double* ratios, int M)
+{
+    double kept = 1.0;
+    for (int m = 0; m < M; ++m) kept *= ratios[m];
+    return kept;
+}
+
+// Whether the call clears so many entries of a residual that fits the memory-side cache (256 MB) that the stores decide.
+// They fill a part of a line each, and are dearer into lines that are not in that cache.  The pass before them then
+// reads with ordinary loads, which leave the vector there, not with non-temporal ones.  Training steps of the exponential
+// law, non-temporal and ordinary loads, us: 2 stages, 25 M elements, ratio 0.1 175 and 168, 0.06 150 and 146, 0.03 111
+// and 118; 40 M, 0.1 279 and 263, 0.06 237 and 231, 0.01 116 and 134; 60 M, 0.06 343 and 338, 0.03 261 and 271; 64 M, 0.05 343
+// and 348; 3 stages (whose lists come from the second pass), 40 M, 0.045 235 and 214, 0.03 218 and 227; 1 stage, 25 M,
+// 0.1 158 and 150, 0.06 124 and 126, 0.3 202 and 203, 0.4 215 and 225; 60 M, 0.1 381 and 368, 0.06 287 and 291; 56 M, 0.3
+// 458 and 478.  The pairs (8 bytes each) take room in the cache as well.
+constexpr int64_t kKeepMaxD = 62000000;
+constexpr double kKeepMaxBytes = 290e6;
+constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
+
+bool keeps_much(int64_t d, bool residual, const double* ratios, int M)
+{
+    const double kept = kept_ratio(ratios, M);
+    if (!residual || d > kKeepMaxD || (double)d * (4.0 + 8.0 * kept) > kKeepMaxBytes) return false;
+    return M > 1 ? kept >= kKeepMinRatio : kept >= kKeepMinRatioOne && kept <= kKeepMaxRatioOne;
+}
+
 // Whether the last stage selects from the dense vector and writes the residual back whole (k_select) although a list
 // could serve it.  Reading and writing the vector again costs the same whatever is kept; the list's writes and reads
 // grow with it, and so does the clearing of the residual, whose lines are then written in part.  A training step
@@ -422,6 +448,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     // `lists` turns true once a stage has written survivor lists (candidates or exceedances).
     bool lists = false;
     const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
+    const bool much = keeps_much(d, residual != nullptr, ratios, M);
     double cum = 1.0;      // delta_1 ... delta_{m-1}
     double list_frac = 1;  // expected fraction of the vector in the current lists
     int sel = 0;           // which half of the double buffers the last kernel wrote
@@ -455,7 +482,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
             }
             p.reverse = reverse;
             reverse = !reverse;
-            launch_compact(p, /*stats=*/true, write, s);
+            launch_compact(p, /*stats=*/true, write, much && write, s);
             ++k;
             mark(write ? "k_compact_dense" : "k_scan_dense");
             if (write) {
@@ -480,7 +507,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
         mark("k_select_dense");
     } else if (!lists) {
         p.reverse = reverse;
-        launch_compact(p, /*stats=*/false, /*write=*/true, s);
+        launch_compact(p, /*stats=*/false, /*write=*/true, much, s);
         ++k;
         mark("k_compact_dense");
         p.cnt_in = h->cnt[sel];

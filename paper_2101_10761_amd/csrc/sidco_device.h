@@ -237,11 +237,14 @@ __device__ __forceinline__ uint32_t dense_tile(const DenseSweep& d, uint32_t j)
 }
 
 // That tile's values.  Past the wave's last tile the same tile for every wave: the load is unconditional (loads under
-// a run-time condition come with waits on the spot), but costs no HBM traffic.
+// a run-time condition come with waits on the spot), but costs no HBM traffic.  KEEP: an ordinary load.
+template <bool KEEP = false>
 __device__ __forceinline__ f4 dense_load(const DenseSweep& d, uint32_t j, int lane)
 {
     const uint32_t t = j < d.nb ? dense_tile(d, j) : d.any;
-    return __builtin_nontemporal_load(reinterpret_cast<const f4*>(d.x + (size_t)t * kTile) + lane);
+    const f4* q = reinterpret_cast<const f4*>(d.x + (size_t)t * kTile) + lane;
+    if constexpr (KEEP) return *q;
+    else return __builtin_nontemporal_load(q);
 }
 
 // A wave's survivor list under construction.  Entries are collected in LDS and written out in long

@@ -301,7 +301,7 @@ constexpr int kSmallBlock = 1024;
 constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
 void launch_small(const Params& p, hipStream_t s);
 void launch_fit(const Params& p, double* scratch, hipStream_t s);
-void launch_compact(const Params& p, bool stats, bool write, hipStream_t s);
+void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);
 constexpr int kSelectBlock = 256, kSelectTiles = 16;  // k_select's block, and its tiles per wave

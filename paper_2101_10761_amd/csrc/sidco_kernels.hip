@@ -641,7 +641,7 @@ __device__ __forceinline__ void compact_tile(f4 a, uint32_t t, uint32_t shift, i
 // One tile (1 KB per wave, 16 KB per CU) is enough: 1, 2 and 4 measured alike at 14.7 M, 25.6 M and 138 M elements.
 constexpr int kAhead = 1;
 
-template <bool STATS, bool WRITE>
+template <bool STATS, bool WRITE, bool KEEP = false>
 __device__ __forceinline__ void compact_dense(const Params& p, const WaveTiles& wt, const DenseSweep& d, f4 (&a)[kAhead],
                                               int lane, float eta_s, float eta_w, ListWriter& lw, uint32_t& ns, double& sy,
                                               double& syy)
@@ -652,7 +652,7 @@ __device__ __forceinline__ void compact_dense(const Params& p, const WaveTiles& 
         for (int u = 0; u < kAhead; ++u) {
             if (j + u < d.nb) {  // wave-uniform
                 const f4 c = a[u];
-                a[u] = dense_load(d, j + u + kAhead, lane);
+                a[u] = dense_load<KEEP>(d, j + u + kAhead, lane);
                 compact_tile<STATS, WRITE>(c, dense_tile(d, j + u), p.shift, lane, eta_s, eta_w, lw,
                                            ns, sy, syy);
             }
@@ -733,8 +733,9 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
 
 // k_compact: a stage that reads the dense vector.  STATS: form the sums for the next stage's fit.
 // WRITE: append the entries above eta_w to this stage's lists (eta_w = eta_m, or a candidate threshold
-// above it); a stage whose candidates would still be a large fraction only counts and sums.
-template <bool STATS, bool WRITE, bool FLAT = false>
+// above it); a stage whose candidates would still be a large fraction only counts and sums.  KEEP: with ordinary loads,
+// which leave the vector in the memory-side cache (see keeps_much in the host code).
+template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false>
 __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{})
 {
     __shared__ double sh[kWavesPerBlock][4];
@@ -755,7 +756,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     const DenseSweep d = dense_sweep(p, wt, p.reverse != 0, p.seg_out);
     f4 a[kAhead];
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) a[u] = dense_load(d, u, lane);
+    for (int u = 0; u < kAhead; ++u) a[u] = dense_load<KEEP>(d, u, lane);
     if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
 
     const StageEta se = prologue_finish(p, b, false, g, sh);
@@ -767,7 +768,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         lw.list = p.seg_out + seg_begin(p, w);  // room for every element of the wave's tiles
         lw.ring = ring[WRITE ? wib : 0];
         lw.run = lw.fill = 0;
-        compact_dense<STATS, WRITE>(p, wt, d, a, lane, se.eta, se.eta_w, lw, ns, sy, syy);
+        compact_dense<STATS, WRITE, KEEP>(p, wt, d, a, lane, se.eta, se.eta_w, lw, ns, sy, syy);
         if (WRITE) run = list_finish(lw, lane);
         if (lane == 0) p.cnt_out[w] = run;
     }
@@ -1517,8 +1518,8 @@ __device__ __forceinline__ void block_tiles(const Params& p, Blk b, uint32_t& T0
 
 template <int DIST, bool EC, int GT>
 __global__ __launch_bounds__(kBlock, 4) void k_fit(Params p) { fit_body<DIST, EC, GT>(p, whole_grid()); }
-template <bool STATS, bool WRITE>
-__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p) { compact_body<STATS, WRITE>(p, whole_grid()); }
+template <bool STATS, bool WRITE, bool KEEP>
+__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p) { compact_body<STATS, WRITE, false, KEEP>(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock, 4) void k_lists(Params p) { lists_body(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock) void k_final_lists(Params p) { final_body(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock) void k_gather(Params p) { gather_body(p, whole_grid()); }
@@ -1760,12 +1761,14 @@ void launch_fit(const Params& p, double* scratch, hipStream_t s)
     }
 }
 
-void launch_compact(const Params& p, bool stats, bool write, hipStream_t s)
+void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s)
 {
     const dim3 grid(p.nblocks), block(kBlock);
-    if (stats && write) hipLaunchKernelGGL((k_compact<true, true>), grid, block, 0, s, p);
-    else if (stats) hipLaunchKernelGGL((k_compact<true, false>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_compact<false, true>), grid, block, 0, s, p);
+    if (stats && write && keep) hipLaunchKernelGGL((k_compact<true, true, true>), grid, block, 0, s, p);
+    else if (stats && write) hipLaunchKernelGGL((k_compact<true, true, false>), grid, block, 0, s, p);
+    else if (stats) hipLaunchKernelGGL((k_compact<true, false, false>), grid, block, 0, s, p);
+    else if (keep) hipLaunchKernelGGL((k_compact<false, true, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_compact<false, true, false>), grid, block, 0, s, p);
 }
 
 void launch_lists(const Params& p, hipStream_t s)

@@ -240,3 +240,14 @@ def test_flat_batches_with_and_without_a_fold_kernel(oracle, sizes, dist, delta,
     r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
     out = run_batched(g, r, offs, delta, dist, stages, repeat=2)
     check_batched(oracle, g, r, offs, delta, dist, stages, out, f"{len(sizes)} tensors dist={dist} M={stages}")
+
+
+@pytest.mark.parametrize("d,offset", [(ONE_BLOCK + 1, 31), (145 * 256 - 16, 16), (ROUND + 257, 0), (2 * ROUND - 255, 5)])
+@pytest.mark.parametrize("dist,ratios", [(0, [0.1]), (2, [0.25, 0.3]), (1, [0.25, 0.45, 0.45]), (0, [0.5, 0.9])])
+def test_calls_that_clear_much_of_the_residual(oracle, d, offset, dist, ratios):
+    """Their last pass over the vector reads with ordinary loads; lists from the first, the second and the last stage."""
+    rng = np.random.default_rng(d + len(ratios))
+    g = rng.laplace(0, 1e-3, size=d).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    out = run_gpu(g, r, dist, ratios, grad_offset=offset, res_offset=offset)
+    check_parity(oracle, g, r, dist, ratios, out, label=f"d={d} dist={dist} {ratios}")
