@@ -437,9 +437,12 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
         return SIDCO_OK;
     }
 
+    const bool much = keeps_much(d, residual != nullptr, ratios, M);
+
     // stage-1 sums (and acc) -> part[0]
     p.part_out = h->part[0];
-    launch_fit(p, (double*)segbuf[1], s);  // the second list buffer is free until the first stage kernel writes it
+    // the second list buffer is free until the first stage kernel writes it
+    launch_fit(p, fit_uses_flat(d, much), (double*)segbuf[1], s);
 
     ++k;
     mark("k_fit");
@@ -448,7 +451,6 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     // `lists` turns true once a stage has written survivor lists (candidates or exceedances).
     bool lists = false;
     const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
-    const bool much = keeps_much(d, residual != nullptr, ratios, M);
     double cum = 1.0;      // delta_1 ... delta_{m-1}
     double list_frac = 1;  // expected fraction of the vector in the current lists
     int sel = 0;           // which half of the double buffers the last kernel wrote
@@ -1452,7 +1454,7 @@ int sidco_fit_typed(void* stream, const void* grad, int grad_dtype, float* resid
     p.M = 1;
     p.acc_reset = 1;
     p.part_out = h->part[0];
-    launch_fit(p, (double*)((char*)cp->ws + head_bytes() + seg_bytes(d)), (hipStream_t)stream);
+    launch_fit(p, fit_uses_flat(d, false), (double*)((char*)cp->ws + head_bytes() + seg_bytes(d)), (hipStream_t)stream);
     cp->fit_nblocks = p.nblocks;
     cp->fit_d = d;
     cp->fit_dist = dist;

@@ -282,6 +282,10 @@ constexpr int kFlatBlock = 256;
 constexpr int kFlatTiles = 2;                                // tiles per wave of a batch's flat first pass
 constexpr uint32_t kFlatChunk = kFlatBlock / 64 * kFlatTiles;  // and per block
 constexpr int64_t kFlatMinD = 58000000;
+// That line for calls that clear much of the residual (see keeps_much), us per wave and flat: 2 stages, 50 M elements,
+// ratio 0.08 308 and 302, 0.1 321 and 315; 40 M, 0.1 263 and 260; 25 M, 0.1 169 and 167; 15 M, 0.1 100.9 and 101.2;
+// 1 stage, 15 M, 0.1 89.4 and 91.2.
+constexpr int64_t kFlatMinMuch = 20000000;
 // A batch's waves walk the tiles of their own vector, so that its window is as many as it has vectors, and the flat
 // shape pays earlier: 25.6 M elements in 161 tensors 96.6 us per wave and 90.6 flat, 66 M in 50 tensors 236.6 and 204.
 constexpr int64_t kFlatMinBatch = 12000000;
@@ -289,7 +293,7 @@ constexpr int64_t kFlatMinBatch = 12000000;
 // stage's kernel, 4 loads per thread and quantity; beyond it a kernel folds them first, 4.8 us against 1 to 2.5 in that
 // prologue: 161 tensors, 25.6 M elements 83.5 -> 81.6 us, 200 tensors, 14 M 49.0 -> 47.0.
 constexpr uint32_t kFlatDirect = 4 * kBlock;
-inline bool fit_uses_flat(int64_t d) { return d >= kFlatMinD; }
+inline bool fit_uses_flat(int64_t d, bool much) { return d >= (much ? kFlatMinMuch : kFlatMinD); }
 inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 {
     return (uint32_t)(((d + shift + 3) / 4 + kFlatBlock - 1) / kFlatBlock);
@@ -300,7 +304,7 @@ inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
 void launch_small(const Params& p, hipStream_t s);
-void launch_fit(const Params& p, double* scratch, hipStream_t s);
+void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);

@@ -1702,9 +1702,9 @@ static void launch_fit_flat_as(const Params& p, double* flat_part, uint32_t nfla
 }
 
 template <bool EC, int GT>
-static void launch_fit_shape(const Params& p, double* scratch, hipStream_t s)
+static void launch_fit_shape(const Params& p, bool flat, double* scratch, hipStream_t s)
 {
-    if (fit_uses_flat(p.d)) {
+    if (flat) {
         const uint32_t nflat = fit_flat_blocks(p.d, p.shift);
         launch_fit_flat_as<EC, GT>(p, scratch, nflat, s);
         const uint32_t per = (nflat + kMaxBlocks - 1) / kMaxBlocks;
@@ -1715,10 +1715,10 @@ static void launch_fit_shape(const Params& p, double* scratch, hipStream_t s)
 }
 
 template <int GT>
-static void launch_fit_type(const Params& p, double* scratch, hipStream_t s)
+static void launch_fit_type(const Params& p, bool flat, double* scratch, hipStream_t s)
 {
-    if (p.residual) launch_fit_shape<true, GT>(p, scratch, s);
-    else launch_fit_shape<false, GT>(p, scratch, s);
+    if (p.residual) launch_fit_shape<true, GT>(p, flat, scratch, s);
+    else launch_fit_shape<false, GT>(p, flat, scratch, s);
 }
 
 template <bool EC, int GT, int N>
@@ -1751,13 +1751,14 @@ void launch_small(const Params& p, hipStream_t s)
     }
 }
 
-// `scratch`: device memory for 3 * fit_flat_blocks(d, shift) doubles when the flat shape is used (else unused)
-void launch_fit(const Params& p, double* scratch, hipStream_t s)
+// `flat`: the launch shape (see fit_uses_flat).  `scratch`: device memory for 3 * fit_flat_blocks(d, shift) doubles in
+// the flat shape (else unused)
+void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s)
 {
     switch (p.gt) {
-        case kGradF16: launch_fit_type<kGradF16>(p, scratch, s); break;
-        case kGradBf16: launch_fit_type<kGradBf16>(p, scratch, s); break;
-        default: launch_fit_type<kGradF32>(p, scratch, s); break;
+        case kGradF16: launch_fit_type<kGradF16>(p, flat, scratch, s); break;
+        case kGradBf16: launch_fit_type<kGradBf16>(p, flat, scratch, s); break;
+        default: launch_fit_type<kGradF32>(p, flat, scratch, s); break;
     }
 }
 

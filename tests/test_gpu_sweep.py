@@ -251,3 +251,15 @@ def test_calls_that_clear_much_of_the_residual(oracle, d, offset, dist, ratios):
     r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
     out = run_gpu(g, r, dist, ratios, grad_offset=offset, res_offset=offset)
     check_parity(oracle, g, r, dist, ratios, out, label=f"d={d} dist={dist} {ratios}")
+
+
+@pytest.mark.parametrize("d", [20_000_000 - 1, 20_000_000, 20_000_003])
+@pytest.mark.parametrize("offset", [(0, 0), (3, 1)])
+def test_flat_first_pass_of_calls_that_clear_much_of_the_residual(oracle, d, offset):
+    """Such calls take the first pass in address order from 20 M elements, not from 58 M."""
+    rng = np.random.default_rng(d)
+    g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+    r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+    for dist, ratios in ((0, [0.1]), (1, [0.25, 0.3])):
+        out = run_gpu(g, r, dist, ratios, grad_offset=offset[0], res_offset=offset[1])
+        check_parity(oracle, g, r, dist, ratios, out, label=f"d={d} dist={dist} {ratios} offsets {offset}")
