@@ -298,7 +298,7 @@ double kept_ratio(const double* ratios, int M)
 // and 118; 40 M, 0.1 279 and 263, 0.06 237 and 231, 0.01 116 and 134; 60 M, 0.06 343 and 338, 0.03 261 and 271; 64 M, 0.05 343
 // and 348; 3 stages (whose lists come from the second pass), 40 M, 0.045 235 and 214, 0.03 218 and 227; 1 stage, 25 M,
 // 0.1 158 and 150, 0.06 124 and 126, 0.3 202 and 203, 0.4 215 and 225; 60 M, 0.1 381 and 368, 0.06 287 and 291; 56 M, 0.3
-// 458 and 478.  The pairs (8 bytes each) take room in the cache as well.
+// 458 and 478.  The pairs (8 bytes each) take room in the cache as well: select from 60 M at 0.2 396 and 402.
 constexpr int64_t kKeepMaxD = 62000000;
 constexpr double kKeepMaxBytes = 290e6;
 constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
@@ -313,22 +313,27 @@ bool keeps_much(int64_t d, bool residual, const double* ratios, int M)
 // Whether the last stage selects from the dense vector and writes the residual back whole (k_select) although a list
 // could serve it.  Reading and writing the vector again costs the same whatever is kept; the list's writes and reads
 // grow with it, and so does the clearing of the residual, whose lines are then written in part.  A training step
-// with lists and with k_select, us (exponential law): 138 M elements, ratio 0.1 1063 and 978, 0.08 901 and 860, 0.05
-// 761 and 805; 90 M, 0.1 679 and 630; 60 M, 0.08 378 and 357; 40 M, 0.1 302 and 295; 20 M, 0.1 142 and 144.
-// Without a residual there is nothing to clear.
-constexpr int64_t kSelectMinD = 50000000;
-constexpr double kSelectMinRatio = 0.08;
+// with lists and with k_select, us: exponential law, 2 stages, 138 M elements, ratio 0.1 1063 and 978, 0.08 901 and 860,
+// 0.05 756 and 798; 90 M, 0.1 623 and 574; 60 M, 0.08 370 and 359; 55 M, 0.09 345 and 334; 50 M, 0.1 315 and 315, 0.08 304
+// and 306; 40 M, 0.1 260 and 272; 3 stages, 50 M, 0.09 327 and 342, 0.08 316 and 330; 56 M, 0.1 381 and 374; 60 M, 0.08
+// 382 and 391, 90 M, 634 and 623; GPD law, 2 stages, 50 M, 0.1 324 and 313; gamma law (whose lists turn out too short
+// here) 627 and 354.  Without a residual there is nothing to clear.
+constexpr int64_t kSelectMinD = 50000000, kSelectLongD = 60000000;
+// least ratios (as products of rounded ones) of vectors below kSelectLongD with two and with more stages, and beyond it
+constexpr double kSelectMinRatioTwo = 0.0899, kSelectMinRatio = 0.0999, kSelectMinRatioLong = 0.0799;
 
 bool select_dense(int64_t d, bool residual, const double* ratios, int M, double theta)
 {
     if (M < 2 || d < kSelectMinD || !residual) return false;
+    const double least = d >= kSelectLongD ? kSelectMinRatioLong : M == 2 ? kSelectMinRatioTwo : kSelectMinRatio;
+    if (kept_ratio(ratios, M) < least) return false;
     double cum = 1.0;
-    for (int m = 0; m < M; ++m) {
+    for (int m = 0; m < M - 2; ++m) {
         // lists that an earlier stage would write serve more than the last one
-        if (m < M - 2 && cum * exp(-(log(1.0 / ratios[m]) + theta * log(1.0 / ratios[m + 1]))) <= kMaterializeBelow) return false;
+        if (cum * exp(-(log(1.0 / ratios[m]) + theta * log(1.0 / ratios[m + 1]))) <= kMaterializeBelow) return false;
         cum *= ratios[m];
     }
-    return cum >= kSelectMinRatio;
+    return true;
 }
 
 // the host's view of a call's device state
@@ -437,6 +442,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
         return SIDCO_OK;
     }
 
+    const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
     const bool much = keeps_much(d, residual != nullptr, ratios, M);
 
     // stage-1 sums (and acc) -> part[0]
@@ -450,7 +456,6 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     // Stage m: threshold from the previous kernel's sums.  Buffers alternate with the kernel number.
     // `lists` turns true once a stage has written survivor lists (candidates or exceedances).
     bool lists = false;
-    const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
     double cum = 1.0;      // delta_1 ... delta_{m-1}
     double list_frac = 1;  // expected fraction of the vector in the current lists
     int sel = 0;           // which half of the double buffers the last kernel wrote
@@ -484,7 +489,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
             }
             p.reverse = reverse;
             reverse = !reverse;
-            launch_compact(p, /*stats=*/true, write, much && write, s);
+            launch_compact(p, /*stats=*/true, write, much && (write || (select && m == M - 1)), s);
             ++k;
             mark(write ? "k_compact_dense" : "k_scan_dense");
             if (write) {
@@ -504,7 +509,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     bind(M);
     if (select) {
         p.reverse = reverse;
-        launch_select(p, s);
+        launch_select(p, much, s);
         ++k;
         mark("k_select_dense");
     } else if (!lists) {

@@ -309,7 +309,7 @@ void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStrea
 void launch_lists(const Params& p, hipStream_t s);
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);
 constexpr int kSelectBlock = 256, kSelectTiles = 16;  // k_select's block, and its tiles per wave
-void launch_select(const Params& p, hipStream_t s);
+void launch_select(const Params& p, bool keep, hipStream_t s);
 void launch_gather(const Params& p, hipStream_t s);
 
 }  // namespace sidco

@@ -1063,8 +1063,8 @@ __global__ __launch_bounds__(kBlock) void k_eta(Params p)
     }
 }
 
-// WHOLE: all tiles of the block are complete
-template <bool WHOLE>
+// WHOLE: all tiles of the block are complete.  KEEP: ordinary loads (see keeps_much in the host code)
+template <bool WHOLE, bool KEEP>
 __device__ __forceinline__ void select_body(const Params& p, uint32_t first, uint32_t* sh_cnt, uint32_t* sh_base)
 {
     constexpr int kWaves = kSelectBlock / 64;
@@ -1074,7 +1074,9 @@ __device__ __forceinline__ void select_body(const Params& p, uint32_t first, uin
 #pragma unroll
     for (int u = 0; u < kSelectTiles; ++u) {
         const int64_t i = (int64_t)(t0 + u) * kTile + lane * 4 - p.shift;
-        if constexpr (WHOLE) {
+        if constexpr (WHOLE && KEEP) {
+            a[u] = *reinterpret_cast<const f4*>(p.acc + i);
+        } else if constexpr (WHOLE) {
             a[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.acc + i));
         } else {
 #pragma unroll
@@ -1136,14 +1138,15 @@ __device__ __forceinline__ void select_body(const Params& p, uint32_t first, uin
     }
 }
 
+template <bool KEEP>
 __global__ __launch_bounds__(kSelectBlock) void k_select(Params p)
 {
     __shared__ uint32_t sh_cnt[kSelectBlock / 64];
     __shared__ uint32_t sh_base;
     constexpr uint32_t kTiles = kSelectBlock / 64 * kSelectTiles;
     const uint32_t first = (p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * kTiles;
-    if (first + kTiles <= p.nfull && (first > 0 || p.shift == 0)) select_body<true>(p, first, sh_cnt, &sh_base);
-    else select_body<false>(p, first, sh_cnt, &sh_base);
+    if (first + kTiles <= p.nfull && (first > 0 || p.shift == 0)) select_body<true, KEEP>(p, first, sh_cnt, &sh_base);
+    else select_body<false, KEEP>(p, first, sh_cnt, &sh_base);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1767,6 +1770,7 @@ void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStrea
     const dim3 grid(p.nblocks), block(kBlock);
     if (stats && write && keep) hipLaunchKernelGGL((k_compact<true, true, true>), grid, block, 0, s, p);
     else if (stats && write) hipLaunchKernelGGL((k_compact<true, true, false>), grid, block, 0, s, p);
+    else if (stats && keep) hipLaunchKernelGGL((k_compact<true, false, true>), grid, block, 0, s, p);
     else if (stats) hipLaunchKernelGGL((k_compact<true, false, false>), grid, block, 0, s, p);
     else if (keep) hipLaunchKernelGGL((k_compact<false, true, true>), grid, block, 0, s, p);
     else hipLaunchKernelGGL((k_compact<false, true, false>), grid, block, 0, s, p);
@@ -1785,12 +1789,14 @@ void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
     hipLaunchKernelGGL(k_final_lists, dim3(grid_blocks), dim3(kBlock), 0, s, p);
 }
 
-void launch_select(const Params& p, hipStream_t s)
+void launch_select(const Params& p, bool keep, hipStream_t s)
 {
     constexpr uint32_t kTiles = kSelectBlock / 64 * kSelectTiles;
     const uint32_t tiles = p.nwaves * p.tq + p.tr;
     hipLaunchKernelGGL(k_eta, dim3(1), dim3(kBlock), 0, s, p);
-    hipLaunchKernelGGL(k_select, dim3((tiles + kTiles - 1) / kTiles), dim3(kSelectBlock), 0, s, p);
+    const dim3 grid((tiles + kTiles - 1) / kTiles), block(kSelectBlock);
+    if (keep) hipLaunchKernelGGL(k_select<true>, grid, block, 0, s, p);
+    else hipLaunchKernelGGL(k_select<false>, grid, block, 0, s, p);
 }
 
 void launch_gather(const Params& p, hipStream_t s)

@@ -263,3 +263,21 @@ def test_flat_first_pass_of_calls_that_clear_much_of_the_residual(oracle, d, off
     for dist, ratios in ((0, [0.1]), (1, [0.25, 0.3])):
         out = run_gpu(g, r, dist, ratios, grad_offset=offset[0], res_offset=offset[1])
         check_parity(oracle, g, r, dist, ratios, out, label=f"d={d} dist={dist} {ratios} offsets {offset}")
+
+
+@pytest.mark.parametrize("d,ratios,last", [(50_000_003, [0.25, 0.32], "k_final_lists"), (50_000_003, [0.25, 0.62, 0.62], "k_final_lists"),
+                                           (59_999_999, [0.25, 0.35], "k_final_lists"), (60_000_000, [0.25, 0.33], "k_select_dense"),
+                                           (62_000_001, [0.25, 0.4], "k_select_dense")])
+def test_which_last_stages_read_the_dense_vector(oracle, d, ratios, last):
+    """Below 60 M elements lists serve up to a ratio of 0.09 with two stages and 0.1 with more, beyond it up to 0.08."""
+    import paper_2101_10761_amd as sidco
+    rng = np.random.default_rng(len(ratios))
+    g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+    r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+    sidco.sidco_set_profiling(True)
+    try:
+        out = run_gpu(g, r, 0, ratios)
+        assert [n for n, _ in sidco.sidco_get_profile()][-1] == last
+    finally:
+        sidco.sidco_set_profiling(False)
+    check_parity(oracle, g, r, 0, ratios, out, label=f"d={d} {ratios}")
