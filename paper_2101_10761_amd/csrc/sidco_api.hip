@@ -443,6 +443,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     }
 
     const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
+    if (select) c.sig_d = 0;  // no lists, no record of where the thresholds fell for a call of this shape without a residual
     const bool much = keeps_much(d, residual != nullptr, ratios, M);
 
     // stage-1 sums (and acc) -> part[0]

@@ -281,3 +281,21 @@ def test_which_last_stages_read_the_dense_vector(oracle, d, ratios, last):
     finally:
         sidco.sidco_set_profiling(False)
     check_parity(oracle, g, r, 0, ratios, out, label=f"d={d} {ratios}")
+
+
+def test_a_dense_last_stage_leaves_no_threshold_hint(oracle):
+    """The call after it has the same shape and, without a residual, writes candidate lists: with what the workspace held
+    before for a hint (10: the lists would start close to the stage's own target) a Gaussian vector falls back."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    d, ratios = 50_000_003, [0.25, 0.4]
+    g = np.random.default_rng(1).standard_normal(d, dtype=np.float32)
+    ws = torch.full((sidco.sidco_workspace_bytes(d) // 4,), 10.0, dtype=torch.float32, device="cuda:0").view(torch.uint8)
+    sidco.sidco_set_workspace(ws)
+    try:
+        run_gpu(g, np.zeros(d, np.float32), 0, ratios)
+        out = run_gpu(g, None, 0, ratios)
+    finally:
+        sidco.sidco_set_workspace(None)
+    assert not out.status & sidco.ST_FALLBACK
+    check_parity(oracle, g, None, 0, ratios, out, label="after a dense last stage")
