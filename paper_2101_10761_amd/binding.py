@@ -212,9 +212,12 @@ def _ptr(t):
 def _stream_handle(stream):
     torch = _torch or _import_torch()
     if stream is None:
-        # the current device's current stream; building torch's Stream object around it takes 2.9 us against 0.3
-        if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # the current device's current stream; building torch's Stream object around it takes 2.9 us against 0.3.
+        # Builds of torch that lack either of these two internal functions go that way.
+        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        device = getattr(torch._C, "_cuda_getDevice", None)
+        if raw and device and torch.cuda.is_initialized():
+            return raw(device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream
 

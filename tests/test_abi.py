@@ -250,3 +250,13 @@ def test_typed_variants_of_the_other_calls_reject_bad_arguments(lib):
 def test_new_setters_reject_bad_arguments(lib):
     assert lib.sidco_set_delta1(0.0) == -3 and lib.sidco_set_delta1(1.0) == -3 and lib.sidco_set_delta1(float("nan")) == -3
     assert lib.sidco_controller_disturbed(None) == -1
+
+
+@pytest.mark.parametrize("internals,want", [(("_cuda_getCurrentRawStream", "_cuda_getDevice"), 5), (("_cuda_getDevice",), 77),
+                                            (("_cuda_getCurrentRawStream",), 77), ((), 77)])
+def test_current_stream_without_torchs_internal_functions(monkeypatch, internals, want):
+    from types import SimpleNamespace as Ns
+    have = {"_cuda_getCurrentRawStream": lambda device: device + 2, "_cuda_getDevice": lambda: 3}
+    cuda = Ns(is_initialized=lambda: True, current_stream=lambda: Ns(cuda_stream=77))
+    monkeypatch.setattr(binding, "_torch", Ns(cuda=cuda, _C=Ns(**{n: have[n] for n in internals})))
+    assert binding._stream_handle(None) == want
