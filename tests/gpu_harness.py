@@ -175,3 +175,23 @@ def check_parity(oracle, g, r, dist, ratios, res: GpuResult, *, capacity=None, l
             want[gi] = 0
             np.testing.assert_array_equal(res.residual.view(np.uint32), want.view(np.uint32))
     return ref
+
+
+def batch_plan(sizes):
+    """The first pass of a batch of tensors of these sizes, as the library plans it: (chunks of eight tiles that the flat
+    shape launches per block, 0 if it keeps the per-wave shape; partial sums of the tensor with the most).  A tensor
+    has its tiles at the worst alignment, a block no more than one of 512 blocks would have of all tiles."""
+    tiles = [(d + 31 + 255) // 256 for d in sizes]
+    per_block = max(8, -(-sum(tiles) // 512))
+    most = chunks = blocks = longest = 0
+    for n in tiles:
+        waves = min(-(-n // per_block) * 8, n)
+        each, more = divmod(n, waves)
+        here = -(-waves // 8)
+        for b in range(here):
+            w0, w1 = 8 * b, min(8 * b + 8, waves)
+            c = -(-((w1 - w0) * each + min(w1, more) - min(w0, more)) // 8)
+            chunks, most = chunks + c, max(most, c)
+        blocks, longest = blocks + here, max(longest, here)
+    flat = sum(sizes) >= 12_000_000 and most * blocks <= 2 * chunks
+    return (most, longest * most) if flat else (0, 0)

@@ -2,7 +2,7 @@
 import numpy as np
 import pytest
 
-from gpu_harness import GpuResult, check_parity
+from gpu_harness import GpuResult, batch_plan, check_parity
 from paper_2101_10761_amd import workloads
 
 pytestmark = pytest.mark.gpu
@@ -95,9 +95,9 @@ def test_config4_full_size_per_tensor(oracle):
 
 @pytest.mark.parametrize("base_offset", [0, 3])
 def test_long_batches_take_the_flat_first_pass(oracle, base_offset):
-    """From 12 M elements in all the first pass runs as a grid in address order (chunks of four tiles per block of
-    the dense grid): long and tiny tensors side by side, ragged ends, and - with an odd base offset - tensors that
-    do not start on a 16-byte boundary and take the guarded element-wise accesses."""
+    """From 12 M elements in all the first pass runs as a grid in address order (chunks of eight tiles per block of
+    the dense grid): long and tiny tensors side by side, ragged ends, and tensors that do not start on a 128-byte
+    line, whose first and last tiles take the guarded element-wise accesses."""
     rng = np.random.default_rng(21 + base_offset)
     sizes = [1, 5_000_003, 17, 7_000_001, 256, 3_000_000, 63, 1025, 2_000_000]
     offs = [0] + [int(x) for x in np.cumsum(sizes)]
@@ -110,16 +110,19 @@ def test_long_batches_take_the_flat_first_pass(oracle, base_offset):
                           f"flat batched dist={dist} M={stages} ec={res_in is not None} offset={base_offset}")
 
 
-def test_one_long_tensor_among_many_short_ones_keeps_the_per_wave_first_pass(oracle):
-    """400 short tensors leave the long one a fifth of the blocks: a flat grid would be mostly empty chunks, so the
-    per-wave shape stays; the result does not depend on the choice."""
+@pytest.mark.parametrize("sizes,flat", [([300] * 200 + [13_000_001] + [500] * 200, True), ([300] * 255 + [12_346_700] + [300] * 256, False)],
+                         ids=["400_short", "511_short"])
+def test_one_long_tensor_among_many_short_ones_keeps_the_per_wave_first_pass(oracle, sizes, flat):
+    """Every short tensor is a block whose flat grid holds one chunk and otherwise empty ones: with 400 of them fewer than
+    half of all chunks are empty and the batch is flat, with 511 more are and the per-wave shape stays; the result does
+    not depend on the choice."""
+    assert (batch_plan(sizes)[0] > 0) == flat
     rng = np.random.default_rng(23)
-    sizes = [300] * 200 + [13_000_001] + [500] * 200
     offs = [0] + [int(x) for x in np.cumsum(sizes)]
     g = rng.laplace(0, 1e-3, size=offs[-1]).astype(np.float32)
     r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
     out = run_batched(g, r, offs, 0.01, 0, 2)
-    check_batched(oracle, g, r, offs, 0.01, 0, 2, out, "one long among 400 short")
+    check_batched(oracle, g, r, offs, 0.01, 0, 2, out, f"one long among {len(sizes) - 1} short")
 
 
 def test_sizes_from_one_element_to_millions(oracle):

@@ -69,6 +69,6 @@ def test_captured_call_replays_correctly(oracle, d, dist, delta, stages):
     sidco.sidco_release(stream=side)
 
 
-@pytest.mark.parametrize("d,dist,delta,stages", [(5_000, 0, 0.01, 1), (30_011, 2, 0.01, 3), (50_000_003, 0, 0.1, 2)])
+@pytest.mark.parametrize("d,dist,delta,stages", [(5_000, 0, 0.01, 1), (30_011, 2, 0.01, 3), (20_000_001, 0, 0.1, 1), (50_000_003, 0, 0.1, 2)])
 def test_captured_calls_in_one_block_and_with_a_dense_last_stage(oracle, d, dist, delta, stages):
     test_captured_call_replays_correctly(oracle, d, dist, delta, stages)

@@ -32,9 +32,9 @@ def _length(rng):
         return int(rng.integers(3000, 300_000))
     if c == 2:
         return int(rng.integers(300_000, 4_000_000))
-    if c == 3:                                               # around the lengths at which the dense stages prefetch
+    if c == 3:                                               # around whole rounds of 4096 waves
         return int(rng.integers(4, 8)) * 4096 * 256 + int(rng.integers(0, 300))
-    return int(rng.integers(12_000_000, 16_000_000))         # the first pass in address order
+    return int(rng.integers(12_000_000, 16_000_000))         # in a batch: the first pass in address order
 
 
 @pytest.mark.parametrize("seed", range(8))

@@ -1,9 +1,11 @@
-"""GPU parity where the split of the vector into waves' tiles changes shape: fewer tiles than waves, one tile, a tile
-more or less than a whole round of 4096 waves, an incomplete last tile owned by the first, a middle or the last wave."""
+"""GPU parity where the split of the vector into waves' tiles changes shape: fewer tiles than waves, a tile more or less
+than a whole round of 4096 waves, an incomplete last tile owned by a middle or the last wave, one tile (in a batch); and
+on both sides of the lengths and ratios where a call takes other kernels.  Single vectors of up to ONE_BLOCK elements
+have no tiles: one block takes them as a whole."""
 import numpy as np
 import pytest
 
-from gpu_harness import check_parity, run_gpu
+from gpu_harness import batch_plan, check_parity, run_gpu
 
 pytestmark = pytest.mark.gpu
 
@@ -109,7 +111,8 @@ def test_16_bit_batch_without_residual_may_start_inside_its_buffer(oracle):
 @pytest.mark.parametrize("d", [1, 31, 225, 226, 256, 287, 481, ROUND - 16])
 @pytest.mark.parametrize("grad_offset,res_offset", [(5, 5), (16, 16), (31, 31), (0, 30), (29, 4)])
 def test_buffers_off_the_line_grid(oracle, d, grad_offset, res_offset):
-    """Tiles sit on the 128-byte lines of the accumulated vector: lengths that end just before, on and after a tile."""
+    """Tiles sit on the 128-byte lines of the accumulated vector (a whole round less a tile's end; the short lengths, one
+    block each, go through unaligned accesses there)."""
     rng = np.random.default_rng(d + 100 * grad_offset + res_offset)
     g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
     r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
@@ -228,12 +231,14 @@ def test_last_stage_on_a_dense_vector_of_nothing_to_select(oracle, kind):
     check_parity(oracle, g, np.zeros(d, np.float32), 0, [0.25, 0.4], out, capacity=1000, label=kind)
 
 
-@pytest.mark.parametrize("sizes", [[1_100_001] * 11 + [1, 300], [4_180_000] * 3, [4_180_000, 4_220_000, 4_180_000, 5]],
-                         ids=["short", "below_the_limit", "above_the_limit"])
+@pytest.mark.parametrize("sizes,sums", [([1_100_001] * 11 + [1, 300], 564), ([4_160_000] * 3, 2040), ([4_180_000] * 3, 2052),
+                                        ([4_180_000, 4_220_000, 4_180_000, 5], 2064)],
+                         ids=["short", "below_the_limit", "just_above", "above_the_limit"])
 @pytest.mark.parametrize("dist,delta,stages", [(0, 0.02, 1), (1, 0.002, 2), (2, 0.01, 3)])
-def test_flat_batches_with_and_without_a_fold_kernel(oracle, sizes, dist, delta, stages):
-    """2048 partial sums, of 2048 elements each, are the most that the first stage's prologue adds up by itself."""
+def test_flat_batches_with_and_without_a_fold_kernel(oracle, sizes, sums, dist, delta, stages):
+    """2048 partial sums of a tensor are the most that the first stage's prologue adds up by itself."""
     from test_gpu_batched import check_batched, run_batched
+    assert batch_plan(sizes)[1] == sums
     rng = np.random.default_rng(len(sizes) + dist)
     offs = [0] + [int(v) for v in np.cumsum(sizes)]
     g = (rng.standard_t(3.0, size=offs[-1]) * 1e-3).astype(np.float32)
@@ -299,3 +304,55 @@ def test_a_dense_last_stage_leaves_no_threshold_hint(oracle):
         sidco.sidco_set_workspace(None)
     assert not out.status & sidco.ST_FALLBACK
     check_parity(oracle, g, None, 0, ratios, out, label="after a dense last stage")
+
+
+@pytest.mark.parametrize("d", [145 * 256 + k for k in (-31, -16, -1, 0, 1, 225)])
+@pytest.mark.parametrize("grad_offset,res_offset", [(5, 5), (16, 16), (31, 31), (0, 30), (29, 4)])
+def test_few_tiles_off_the_line_grid(oracle, d, grad_offset, res_offset):
+    """Vectors just too long for one block: as many waves as tiles, which end before, on and after the last element."""
+    assert d > ONE_BLOCK
+    rng = np.random.default_rng(d + 100 * grad_offset + res_offset)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual, dist, stages in ((r, 2, 3), (r, 1, 1), (None, 0, 2)):
+        ratios = oracle.schedule(0.01, stages, 0.25)
+        out = run_gpu(g, residual, dist, ratios, grad_offset=grad_offset, res_offset=res_offset)
+        check_parity(oracle, g, residual, dist, ratios, out, label=f"d={d} offsets {grad_offset},{res_offset} M={stages}")
+
+
+@pytest.mark.parametrize("d", [1, 5, 31, 225, 226, 255, 256, 257, 287, 481, 511, 8 * 256 + 1])
+@pytest.mark.parametrize("base", [0, 1, 5, 16, 31])
+def test_one_and_two_tiles_in_a_batch_of_one_tensor(oracle, d, base):
+    """A batch keeps to tiles however short its tensors are."""
+    from test_gpu_batched import check_batched, run_batched
+    rng = np.random.default_rng(d + 100 * base)
+    g = (rng.standard_t(3.0, size=d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=d).astype(np.float32)
+    for residual, dist, stages in ((r, 2, 3), (None, 0, 1)):
+        out = run_batched(g, residual, [0, d], 0.05, dist, stages, base_offset=base)
+        check_batched(oracle, g, residual, [0, d], 0.05, dist, stages, out, f"d={d} base {base} M={stages}")
+
+
+@pytest.mark.parametrize("dist,stages,offset", [(0, 2, (1, 3)), (1, 2, (0, 31)), (2, 3, (5, 16))])
+def test_flat_first_pass_of_single_vectors(oracle, dist, stages, offset):
+    """From 58 M elements the first pass runs in address order: every law, gradient and residual off the line grid."""
+    d = 58_000_003
+    rng = np.random.default_rng(dist)
+    g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+    r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+    ratios = oracle.schedule(0.001, stages, 0.25)
+    out = run_gpu(g, r, dist, ratios, grad_offset=offset[0], res_offset=offset[1])
+    check_parity(oracle, g, r, dist, ratios, out, label=f"flat dist={dist} offsets {offset}")
+
+
+@pytest.mark.parametrize("dist", [0, 1, 2])
+@pytest.mark.parametrize("value,at", [(np.nan, 0), (np.inf, -1), (-np.inf, 29_000_000)])
+def test_non_finite_values_in_a_flat_first_pass(oracle, dist, value, at):
+    """One of them makes the first stage's sums non-finite: nothing is selected, the residual takes the sum."""
+    d = 58_000_001
+    g = np.full(d, 1e-3, np.float32)
+    g[at] = value
+    r = np.zeros(d, np.float32)
+    out = run_gpu(g, r, dist, [0.25, 0.04], res_offset=1)
+    assert out.count == 0 and np.isnan(out.eta) and out.status & 1
+    check_parity(oracle, g, r, dist, [0.25, 0.04], out, label=f"{value} at {at} dist={dist}")

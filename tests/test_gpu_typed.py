@@ -91,7 +91,7 @@ def test_small_and_ragged_sizes(oracle, kind, d):
 @pytest.mark.parametrize("kind", ["f16", "bf16"])
 @pytest.mark.parametrize("go,ro", [(1, 0), (4, 0), (0, 1), (3, 2), (4, 4)])
 def test_unaligned_buffers(oracle, kind, go, ro):
-    """A gradient offset of 4 elements keeps the 8-byte alignment of the vector path; 1 and 3 do not."""
+    """The gradient is read 8 bytes at a time wherever it starts; an offset of 4 elements keeps those aligned, 1 and 3 do not."""
     import paper_2101_10761_amd as sidco
     d = 400_009
     g32, rng = _grad(5, d)
@@ -151,8 +151,7 @@ def test_f32_code_is_the_plain_call(oracle):
 
 @pytest.mark.parametrize("kind", ["f16", "bf16"])
 def test_long_vector_without_residual(oracle, kind):
-    """From 12 M elements the first pass runs as a flat grid; without a residual the widened vector lives in the
-    library's workspace."""
+    """Without a residual the widened vector lives in the library's workspace."""
     import paper_2101_10761_amd as sidco
     d = 12_500_003
     g32, _ = _grad(123, d)
@@ -167,8 +166,7 @@ def test_long_vector_without_residual(oracle, kind):
 @pytest.mark.parametrize("kind", ["f16", "bf16"])
 @pytest.mark.parametrize("with_residual", [True, False])
 def test_batched_ragged_tensors(oracle, kind, with_residual):
-    """50 ragged tensors at odd offsets: a 16-bit tensor whose first element is not 8-byte aligned takes the
-    element-wise path, the others the vector path."""
+    """50 ragged tensors at odd offsets: gradients on and off 8-byte boundaries, accumulated vectors on and off the lines."""
     from test_gpu_batched import run_batched, check_batched
     from paper_2101_10761_amd import workloads
     w = workloads.config4(d=6_600_000, ragged=True)
@@ -182,8 +180,8 @@ def test_batched_ragged_tensors(oracle, kind, with_residual):
 
 @pytest.mark.parametrize("kind", ["f16", "bf16"])
 def test_batched_flat_first_pass(oracle, kind):
-    """Long batches (12 M elements and more) take the first pass in address order; 16-bit tensors that start on an
-    8-byte boundary are read four elements at a time there, the others element by element."""
+    """Long batches (12 M elements and more) take the first pass in address order, four 16-bit elements at a time wherever
+    a tensor starts."""
     from test_gpu_batched import run_batched, check_batched
     rng = np.random.default_rng(31)
     sizes = [6_000_001, 2, 4_000_000, 1023, 3_000_004]
