@@ -25,14 +25,21 @@
  * reads one counter back on every Q-th call; that is its contract.)
  *
  * Results are deterministic for a given history of calls on a workspace: the
- * same inputs after the same previous calls give the same bits.  Across
+ * same inputs at the same places after the same previous calls give the same
+ * bits.  The place counts modulo 128 bytes: the fp64 sums of a vector of more
+ * than 36,864 elements (of any length in the batched call) are grouped by the
+ * 128-byte lines of the accumulated vector - the residual, or without one an
+ * fp32 gradient - so that equal data at another offset in its line can give a
+ * threshold that differs in its last bit.  Across
  * different histories the exceedance statistics of the stages after the first
  * are summed in a different order (the candidate lists follow the previous
  * call's thresholds, see sidco_set_speculation), so a threshold can differ in
  * its last bit, far inside the 1e-5 the fitted values are specified to; given
  * the threshold, the selected set, its values and the residual are exact.  The
  * order of the output pairs is fixed for a single-stage call and may vary
- * between runs for M >= 2.
+ * between runs for M >= 2.  It is not the order of the vector in either case, so
+ * the pairs that a call drops for want of capacity (SIDCO_ST_OVERFLOW) may come
+ * from any part of the vector.
  *
  * Return value: 0 on success, a negative SIDCO_ERR_* otherwise.  Argument
  * errors are detected on the host before any HIP call is made.  Conditions

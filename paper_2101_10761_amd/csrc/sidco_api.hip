@@ -264,9 +264,9 @@ void free_ws(WsCtx& c)
 // Grid of the last stage's kernel when it reads survivor lists.  The host only knows the expected
 // number of entries; a wrong guess costs time, never correctness.  Every block reserves its output
 // range with one same-address atomic, so few blocks for short lists (4 lists per wave, everything loaded
-// before the prologue) and one list per wave for long ones (millions of pairs out: 1057 us against 1152 us per
-// call with 512 instead of 256 blocks at d = 138 M, delta = 0.1, where the kernel is bound by the scattered
-// stores that clear the residual; no difference at delta = 0.01 and below).
+// before the prologue) and one list per wave for long ones.  A training step with few blocks and with one list per wave,
+// us (exponential law): 3 stages, 138 M elements, ratio 0.01 526 and 511; 2 stages, 56 M, 0.06 321 and 312; 40 M, 0.1 262
+// and 259; 138 M, 0.05 759 and 757; 25 M, 0.03 (2.2 M expected entries) 110.5 and 112.8; 66 M, 0.001 172.9 and 177.3.
 uint32_t final_grid(const Params& p, double expect)
 {
     uint32_t grid = (p.nwaves + kFinalLists - 1) / kFinalLists;

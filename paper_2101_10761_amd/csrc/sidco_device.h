@@ -112,8 +112,9 @@ __device__ __forceinline__ uint32_t lane_prefix(unsigned long long mask)
 // 256 t - shift .. 256 t + 255 - shift, `shift` being the number of elements between the boundary before acc[0]
 // and acc[0].  On the 16-byte grid alone a tile began and ended inside a line, and that line was fetched, and
 // written back in part, by the L2s of two XCDs: 50 tensors of odd lengths, 66 M elements in all, 129 us for the
-// first pass and 65 for the dense stage against 124 and 51 now (kGrid of 64 and 256 measured the same as 32).  So tile 0 is incomplete if shift > 0 and the last tile may be; those two take guarded scalar
-// accesses, every other one whole 16-byte accesses.
+// first pass and 65 for the dense stage against 124 and 51 now (kGrid of 64 and 256 measured the same as 32).  So tile 0
+// is incomplete if shift > 0 and the last tile may be; those two take guarded scalar accesses, every other one whole
+// 16-byte accesses.
 struct WaveTiles {
     uint32_t w, W;
     uint32_t n;       // tiles of the wave
@@ -208,7 +209,8 @@ __device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v
 // The loads are non-temporal: the vector has just been written by the first pass and much of it is still dirty in the
 // memory-side cache; reads that do not allocate behind it neither push those lines out early nor wait for them
 // (first pass and a statistics-only sweep together, plain against non-temporal loads: 65.7 and 63.9 us at 25.6 M
-// elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).
+// elements, 160 and 153 us at 66 M, 366 and 334 us at 138 M).  Calls that clear much of the residual right after such a
+// sweep take ordinary loads (see keeps_much in the host code).
 struct DenseSweep {
     const float* x;   // element 0 of tile 0, or a readable stand-in if the wave has no complete tile
     uint32_t nb;      // complete tiles of the wave

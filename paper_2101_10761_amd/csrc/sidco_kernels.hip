@@ -6,7 +6,8 @@
 //                |acc|, acc^2, log2|acc| (whichever the chosen law needs)       [reads 8 B, writes 4 B / element]
 //                Two launch shapes: every wave walks its own tiles (short vectors), or
 //                k_fit_flat, one float4 per thread in address order, followed by k_fit_reduce, which
-//                folds the per-block sums into the 512 slots the next kernel expects (long vectors).
+//                folds the per-block sums into the 512 slots the next kernel expects (long vectors, and from a
+//                lower length on calls that clear much of the residual; see fit_uses_flat).
 //                The gradient may be fp16 / bf16; it is widened as it is read.
 //   stage m      m = 1..M, one kernel each.  Prologue: every block reduces the previous kernel's partial
 //                sums in a fixed order and its first wave evaluates the closed-form threshold eta_m in
