@@ -299,14 +299,17 @@ double kept_ratio(const double* ratios, int M)
 // and 348; 3 stages (whose lists come from the second pass), 40 M, 0.045 235 and 214, 0.03 218 and 227; 1 stage, 25 M,
 // 0.1 158 and 150, 0.06 124 and 126, 0.3 202 and 203, 0.4 215 and 225; 60 M, 0.1 381 and 368, 0.06 287 and 291; 56 M, 0.3
 // 458 and 478.  The pairs (8 bytes each) take room in the cache as well: select from 60 M at 0.2 396 and 402.
+// The gamma law's lists of two stages mostly turn out too short at these ratios, and what reads the vector again then is
+// slower behind ordinary loads: 25 M, 0.1 351 and 388, 40 M, 0.1 478 and 501.
 constexpr int64_t kKeepMaxD = 62000000;
 constexpr double kKeepMaxBytes = 290e6;
 constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
 
-bool keeps_much(int64_t d, bool residual, const double* ratios, int M)
+bool keeps_much(int64_t d, bool residual, int dist, const double* ratios, int M)
 {
     const double kept = kept_ratio(ratios, M);
     if (!residual || d > kKeepMaxD || (double)d * (4.0 + 8.0 * kept) > kKeepMaxBytes) return false;
+    if (dist == kDistGamma && M == 2) return false;
     return M > 1 ? kept >= kKeepMinRatio : kept >= kKeepMinRatioOne && kept <= kKeepMaxRatioOne;
 }
 
@@ -444,7 +447,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
 
     const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
     if (select) c.sig_d = 0;  // no lists, no record of where the thresholds fell for a call of this shape without a residual
-    const bool much = keeps_much(d, residual != nullptr, ratios, M);
+    const bool much = keeps_much(d, residual != nullptr, dist, ratios, M);
 
     // stage-1 sums (and acc) -> part[0]
     p.part_out = h->part[0];
