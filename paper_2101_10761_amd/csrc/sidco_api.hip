@@ -301,7 +301,10 @@ double kept_ratio(const double* ratios, int M)
 // 458 and 478.  The pairs (8 bytes each) take room in the cache as well: select from 60 M at 0.2 396 and 402.
 // The gamma law's lists of two stages mostly turn out too short at these ratios, and what reads the vector again then is
 // slower behind ordinary loads: 25 M, 0.1 351 and 388, 40 M, 0.1 478 and 501.
-constexpr int64_t kKeepMaxD = 62000000;
+// Batches, whose length is that of all tensors together: 161 tensors (aligned, 64 elements up), 2 stages, 25 M, 0.05 104 and
+// 96; 40 M, 0.1 212 and 183; 50 M, 0.1 262 and 248; 60 M, 0.1 312 and 317; 1 stage, 50 M, 0.1 250 and 223; 50 ragged
+// tensors, 2 stages, 40 M, 0.1 210 and 181; 30 of them, 60 M 322 and 335.
+constexpr int64_t kKeepMaxD = 62000000, kKeepMaxBatch = 55000000;
 constexpr double kKeepMaxBytes = 290e6;
 constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
 
@@ -1105,6 +1108,8 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     a.flat_blocks = pl.blocks;
     launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, pl.fold, s);
     const bool flat = pl.flat_gx > 0 && !pl.fold;
+    const int64_t total = offsets[n] - offsets[0];
+    const bool much = total <= kKeepMaxBatch && keeps_much(total, residual != nullptr, dist, ratios, M);
     bool lists = false, cand = false, reverse = true;
     double cum = 1.0;
     int sel = 0;
@@ -1127,7 +1132,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
             }
             a.reverse = reverse ? 1 : 0;
             reverse = !reverse;
-            launch_compact_batched(a, /*stats=*/true, write, flat && m == 1, pl.blocks, s);
+            launch_compact_batched(a, /*stats=*/true, write, flat && m == 1, much, pl.blocks, s);
             if (write) {
                 lists = true;
                 cand = theta > 0.0;
@@ -1141,7 +1146,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     bind(M);
     if (!lists) {
         a.reverse = reverse ? 1 : 0;
-        launch_compact_batched(a, /*stats=*/false, /*write=*/true, flat && M == 1, pl.blocks, s);
+        launch_compact_batched(a, /*stats=*/false, /*write=*/true, flat && M == 1, much, pl.blocks, s);
         a.in = sel;  // the gather reads what the compaction just wrote
         launch_gather_batched(a, pl.blocks, s);
     } else {

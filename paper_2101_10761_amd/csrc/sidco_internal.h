@@ -264,7 +264,7 @@ struct BatchArgs {
 };
 
 void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s);
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, uint32_t blocks, hipStream_t s);
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, bool keep, uint32_t blocks, hipStream_t s);
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);
 void launch_final_lists_batched(const BatchArgs& a, uint32_t final_blocks, hipStream_t s);
 void launch_gather_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s);

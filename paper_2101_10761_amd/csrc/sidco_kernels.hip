@@ -1644,7 +1644,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
     }
 }
 
-template <bool STATS, bool WRITE, bool FLAT>
+template <bool STATS, bool WRITE, bool FLAT, bool KEEP>
 __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
 {
     Blk b;
@@ -1655,7 +1655,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
         fp.n = p.nblocks * a.flat_gx;
         fp.stride = a.flat_blocks * a.flat_gx;
     }
-    compact_body<STATS, WRITE, FLAT>(p, b, fp);
+    compact_body<STATS, WRITE, FLAT, KEEP>(p, b, fp);
 }
 __global__ __launch_bounds__(kBlock, 4) void k_lists_batched(BatchArgs a)
 {
@@ -1847,20 +1847,22 @@ void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t f
     }
 }
 
-template <bool FLAT>
+template <bool FLAT, bool KEEP>
 static void launch_compact_batched_as(const BatchArgs& a, bool stats, bool write, uint32_t blocks, hipStream_t s)
 {
     const dim3 grid(blocks), block(kBlock);
-    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true, FLAT>), grid, block, 0, s, a);
-    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, FLAT>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_compact_batched<false, true, FLAT>), grid, block, 0, s, a);
+    if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true, FLAT, KEEP>), grid, block, 0, s, a);
+    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, FLAT, false>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_compact_batched<false, true, FLAT, KEEP>), grid, block, 0, s, a);
 }
 
-// `flat`: the first stage, behind a flat first pass whose partial sums have not been folded
-void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, uint32_t blocks, hipStream_t s)
+// `flat`: the first stage, behind a flat first pass whose partial sums have not been folded.  `keep`: ordinary loads
+void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, bool keep, uint32_t blocks, hipStream_t s)
 {
-    if (flat) launch_compact_batched_as<true>(a, stats, write, blocks, s);
-    else launch_compact_batched_as<false>(a, stats, write, blocks, s);
+    if (flat && keep) launch_compact_batched_as<true, true>(a, stats, write, blocks, s);
+    else if (flat) launch_compact_batched_as<true, false>(a, stats, write, blocks, s);
+    else if (keep) launch_compact_batched_as<false, true>(a, stats, write, blocks, s);
+    else launch_compact_batched_as<false, false>(a, stats, write, blocks, s);
 }
 
 void launch_lists_batched(const BatchArgs& a, uint32_t blocks, hipStream_t s)

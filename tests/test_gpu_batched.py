@@ -165,3 +165,16 @@ def test_repeated_layout_and_layout_change(oracle):
     offs2 = [0, 500_000, offs[-1]]
     out = run_batched(g, r, offs2, 0.001, 2, 3)
     check_batched(oracle, g, r, offs2, 0.001, 2, 3, out, "new layout")
+
+
+@pytest.mark.parametrize("sizes", [[1, 300, 70_001, 5, 400_003, 256, 33], [1_100_001] * 11 + [1, 300], [4_180_000] * 3],
+                         ids=["per_wave", "flat", "flat_with_a_fold"])
+@pytest.mark.parametrize("dist,stages,delta", [(0, 1, 0.1), (2, 2, 0.08), (1, 3, 0.05)])
+def test_batches_that_clear_much_of_the_residual(oracle, sizes, dist, stages, delta):
+    """The pass that writes their last lists reads with ordinary loads, behind each form of the first pass."""
+    rng = np.random.default_rng(len(sizes) + stages)
+    offs = [0] + [int(x) for x in np.cumsum(sizes)]
+    g = rng.laplace(0, 1e-3, size=offs[-1]).astype(np.float32)
+    r = rng.laplace(0, 3e-4, size=offs[-1]).astype(np.float32)
+    out = run_batched(g, r, offs, delta, dist, stages, base_offset=3, repeat=2)
+    check_batched(oracle, g, r, offs, delta, dist, stages, out, f"much dist={dist} M={stages}")
