@@ -299,19 +299,24 @@ double kept_ratio(const double* ratios, int M)
 // and 348; 3 stages (whose lists come from the second pass), 40 M, 0.045 235 and 214, 0.03 218 and 227; 1 stage, 25 M,
 // 0.1 158 and 150, 0.06 124 and 126, 0.3 202 and 203, 0.4 215 and 225; 60 M, 0.1 381 and 368, 0.06 287 and 291; 56 M, 0.3
 // 458 and 478.  The pairs (8 bytes each) take room in the cache as well: select from 60 M at 0.2 396 and 402.
+// Without a residual nothing is cleared, but a call whose first stages only sum reads the vector a third time: 3 stages,
+// 60 M, 0.1 309 and 294, 50 M, 0.05 218 and 211; 40 M, 0.1 207 and 203, but with 50 scales 0.05 118 and 121; 25 M, 0.1
+// 138.6 and 138.8; 2 stages within 2 % either way.
 // The gamma law's lists of two stages mostly turn out too short at these ratios, and what reads the vector again then is
 // slower behind ordinary loads: 25 M, 0.1 351 and 388, 40 M, 0.1 478 and 501.
 // Batches, whose length is that of all tensors together: 161 tensors (aligned, 64 elements up), 2 stages, 25 M, 0.05 104 and
 // 96; 40 M, 0.1 212 and 183; 50 M, 0.1 262 and 248; 60 M, 0.1 312 and 317; 1 stage, 50 M, 0.1 250 and 223; 50 ragged
 // tensors, 2 stages, 40 M, 0.1 210 and 181; 30 of them, 60 M 322 and 335.
 constexpr int64_t kKeepMaxD = 62000000, kKeepMaxBatch = 55000000;
+constexpr int64_t kKeepMinBare = 45000000;  // without a residual
 constexpr double kKeepMaxBytes = 290e6;
 constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
 
 bool keeps_much(int64_t d, bool residual, int dist, const double* ratios, int M)
 {
     const double kept = kept_ratio(ratios, M);
-    if (!residual || d > kKeepMaxD || (double)d * (4.0 + 8.0 * kept) > kKeepMaxBytes) return false;
+    if (d > kKeepMaxD || (double)d * (4.0 + 8.0 * kept) > kKeepMaxBytes) return false;
+    if (!residual) return M > 2 && d >= kKeepMinBare && kept >= kKeepMinRatio;
     if (dist == kDistGamma && M == 2) return false;
     return M > 1 ? kept >= kKeepMinRatio : kept >= kKeepMinRatioOne && kept <= kKeepMaxRatioOne;
 }
@@ -496,7 +501,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
             }
             p.reverse = reverse;
             reverse = !reverse;
-            launch_compact(p, /*stats=*/true, write, much && (write || (select && m == M - 1)), s);
+            launch_compact(p, /*stats=*/true, write, much && (write || !residual || (select && m == M - 1)), s);
             ++k;
             mark(write ? "k_compact_dense" : "k_scan_dense");
             if (write) {
@@ -1109,7 +1114,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, pl.fold, s);
     const bool flat = pl.flat_gx > 0 && !pl.fold;
     const int64_t total = offsets[n] - offsets[0];
-    const bool much = total <= kKeepMaxBatch && keeps_much(total, residual != nullptr, dist, ratios, M);
+    const bool much = residual && total <= kKeepMaxBatch && keeps_much(total, true, dist, ratios, M);
     bool lists = false, cand = false, reverse = true;
     double cum = 1.0;
     int sel = 0;

@@ -356,3 +356,14 @@ def test_non_finite_values_in_a_flat_first_pass(oracle, dist, value, at):
     out = run_gpu(g, r, dist, [0.25, 0.04], res_offset=1)
     assert out.count == 0 and np.isnan(out.eta) and out.status & 1
     check_parity(oracle, g, r, dist, [0.25, 0.04], out, label=f"{value} at {at} dist={dist}")
+
+
+@pytest.mark.parametrize("d", [44_999_999, 45_000_001])
+@pytest.mark.parametrize("dist,offset", [(0, 0), (2, 7)])
+def test_sums_only_stages_without_a_residual(oracle, d, dist, offset):
+    """Calls of three stages whose first only sums read with ordinary loads from 45 M elements."""
+    rng = np.random.default_rng(d + dist)
+    g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+    ratios = oracle.schedule(0.06, 3, 0.25)
+    out = run_gpu(g, None, dist, ratios, grad_offset=offset)
+    check_parity(oracle, g, None, dist, ratios, out, label=f"d={d} dist={dist} offset {offset}")
