@@ -305,9 +305,12 @@ double kept_ratio(const double* ratios, int M)
 // The gamma law's lists of two stages mostly turn out too short at these ratios, and what reads the vector again then is
 // slower behind ordinary loads: 25 M, 0.1 351 and 388, 40 M, 0.1 478 and 501.
 // Batches, whose length is that of all tensors together: 161 tensors (aligned, 64 elements up), 2 stages, 25 M, 0.05 104 and
-// 96; 40 M, 0.1 212 and 183; 50 M, 0.1 262 and 248; 60 M, 0.1 312 and 317; 1 stage, 50 M, 0.1 250 and 223; 50 ragged
-// tensors, 2 stages, 40 M, 0.1 210 and 181; 30 of them, 60 M 322 and 335.
-constexpr int64_t kKeepMaxD = 62000000, kKeepMaxBatch = 55000000;
+// 96; 40 M, 0.1 212 and 183; 50 M, 0.1 262 and 248; 60 M, 0.1 312 and 317; 1 stage, 50 M, 0.1 250 and 223, 60 M, 0.1 295
+// and 288; 20 equal ones, 2 stages, 60 M, 0.05 261 and 254; 50 ragged ones, 2 stages, 40 M, 0.1 210 and 181.  Their stages
+// that only sum read with ordinary loads too: 3 stages, 161 tensors, 40 M, 0.1 222 and 201, 60 M, 0.05 290 and 279; 50
+// ragged ones, 40 M, 0.1 219 and 202 (a single vector's are slower so: 40 M, 0.08 252 and 258).
+constexpr int64_t kKeepMaxD = 62000000;
+constexpr double kKeepMaxBytesBatchTwo = 270e6;  // a batch of two stages
 constexpr int64_t kKeepMinBare = 45000000;  // without a residual
 constexpr double kKeepMaxBytes = 290e6;
 constexpr double kKeepMinRatio = 0.04, kKeepMinRatioOne = 0.08, kKeepMaxRatioOne = 0.3;  // several stages, one stage
@@ -1114,7 +1117,8 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, pl.fold, s);
     const bool flat = pl.flat_gx > 0 && !pl.fold;
     const int64_t total = offsets[n] - offsets[0];
-    const bool much = residual && total <= kKeepMaxBatch && keeps_much(total, true, dist, ratios, M);
+    const bool much = residual && keeps_much(total, true, dist, ratios, M) &&
+                      (M != 2 || (double)total * (4.0 + 8.0 * kept_ratio(ratios, M)) <= kKeepMaxBytesBatchTwo);
     bool lists = false, cand = false, reverse = true;
     double cum = 1.0;
     int sel = 0;

@@ -1852,7 +1852,7 @@ static void launch_compact_batched_as(const BatchArgs& a, bool stats, bool write
 {
     const dim3 grid(blocks), block(kBlock);
     if (stats && write) hipLaunchKernelGGL((k_compact_batched<true, true, FLAT, KEEP>), grid, block, 0, s, a);
-    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, FLAT, false>), grid, block, 0, s, a);
+    else if (stats) hipLaunchKernelGGL((k_compact_batched<true, false, FLAT, KEEP>), grid, block, 0, s, a);
     else hipLaunchKernelGGL((k_compact_batched<false, true, FLAT, KEEP>), grid, block, 0, s, a);
 }
 
