@@ -32,8 +32,8 @@
  * fp32 gradient - so that equal data at another offset in its line can give a
  * threshold that differs in its last bit.  Across
  * different histories the exceedance statistics of the stages after the first
- * are summed in a different order (the candidate lists follow the previous
- * call's thresholds, see sidco_set_speculation), so a threshold can differ in
+ * are summed in a different order (the lists follow the previous calls'
+ * thresholds, see sidco_set_speculation), so a threshold can differ in
  * its last bit, far inside the 1e-5 the fitted values are specified to; given
  * the threshold, the selected set, its values and the residual are exact.  The
  * order of the output pairs is fixed for a single-stage call and may vary
@@ -91,10 +91,10 @@ extern "C" {
 #define SIDCO_ST_STOPPED      (1u << 4) /* an exceedance set was empty: later stages keep eta         */
 #define SIDCO_ST_OVERFLOW     (1u << 5) /* more pairs selected than the output capacity; the excess
                                            stays in the residual and is not reported                  */
-#define SIDCO_ST_FALLBACK     (1u << 6) /* performance only: a stage found the candidate lists of the
-                                           stage before it too short for its threshold and read the
-                                           dense vector again (see sidco_set_speculation); the result
-                                           is the same either way                                     */
+#define SIDCO_ST_FALLBACK     (1u << 6) /* performance only: a stage found the lists of the stage before it,
+                                           or of the first pass, too short for its threshold and read
+                                           the dense vector again (see sidco_set_speculation); the
+                                           result is the same either way                              */
 
 /* Per-call diagnostics, filled on the device by the kernels of the last call. */
 typedef struct sidco_diag {
@@ -442,7 +442,10 @@ int sidco_set_status_word(void *stream, uint32_t *device_word);
  * exceedances, is at or above the candidate threshold, and reads the dense
  * vector again otherwise (SIDCO_ST_FALLBACK).  theta in [0, 1]; 0 = the list
  * holds all exceedances of eta_m and is always usable; default 0.5.  Applies
- * to the calls that follow, on every device.
+ * to the calls that follow, on every device.  With theta > 0 a call that repeats
+ * the call before it on the workspace in shape (length, law, ratios, with or
+ * without a residual) may also look for its thresholds near that call's while it
+ * forms acc, and read the vector again only where one fell elsewhere.
  */
 int sidco_set_speculation(double theta);
 

@@ -26,6 +26,8 @@ struct WorkspaceHead {
     alignas(256) double part[2][4 * kBatchBlocks];
     alignas(256) uint32_t cnt[2][kBatchBlocks * kWavesPerBlock];
     alignas(256) uint32_t blk[2][kBatchBlocks];
+    alignas(256) double band_part[3 * (kBandStages - 1) * kMaxBlocks];
+    alignas(256) uint32_t band_cnt[kMaxWaves];
     alignas(256) uint32_t topk_hist[kTopkHist];
     alignas(256) TopkState topk;
     alignas(256) uint32_t dgc_hist[2][3 * kTopkBins];
@@ -62,6 +64,8 @@ struct WsCtx {
     int sig_dist = -1, sig_M = 0;
     double sig_ratios[SIDCO_MAX_STAGES] = {};
     double sig_theta = -1.0;
+    bool sig_lists = false;    // the record of where the thresholds fell is that call's (a call without lists keeps none)
+    bool sig_residual = false;
     // batched calls: host images of the tables uploaded so far (descriptors and block maps; kept alive
     // because their upload is asynchronous), which of them the device holds, the shared arguments it was
     // used with, and the output capacities for the diagnostics
@@ -324,6 +328,19 @@ bool keeps_much(int64_t d, bool residual, int dist, const double* ratios, int M)
     return M > 1 ? kept >= kKeepMinRatio : kept >= kKeepMinRatioOne && kept <= kKeepMaxRatioOne;
 }
 
+// Expected fraction of the vector in the lists that a stage m < M (0-based here) would write from the dense vector, and
+// whether one before the last writes any.
+double list_fraction(const double* ratios, int m, double theta)
+{
+    return kept_ratio(ratios, m) * exp(-(log(1.0 / ratios[m]) + theta * log(1.0 / ratios[m + 1])));
+}
+bool writes_lists(const double* ratios, int M, double theta)
+{
+    for (int m = 0; m + 1 < M; ++m)
+        if (list_fraction(ratios, m, theta) <= kMaterializeBelow) return true;
+    return false;
+}
+
 // Whether the last stage selects from the dense vector and writes the residual back whole (k_select) although a list
 // could serve it.  Reading and writing the vector again costs the same whatever is kept; the list's writes and reads
 // grow with it, and so does the clearing of the residual, whose lines are then written in part.  A training step
@@ -348,6 +365,31 @@ bool select_dense(int64_t d, bool residual, const double* ratios, int M, double 
         cum *= ratios[m];
     }
     return true;
+}
+
+// Whether a call of this kind leaves bands for the next one of its shape (see k_fit_bands).  Shorter vectors are served by
+// the caches (a training step without and with bands, us: 4.2 M, 2 stages 24.8 and 25.5; 7 M, 3 stages 38.8 and 39.7; 10 M
+// 40.2 and 40.0; 14.7 M 55.5 and 46.3), and calls that clear much of the residual want it there (see keeps_much: 25 M, 2
+// stages, ratio 0.1 166 and 169, 0.03 111 and 99; 40 M, 0.1 260 and 268; 56 M, 0.08 339 and 353; with k_select 60 M, 0.1 375
+// and 382, 120 M 772 and 723, 138 M, 3 stages 978 and 865).  Four and more stages would need more bands.
+constexpr int64_t kBandMinD = 10000000;
+bool uses_bands(int64_t d, const double* ratios, int M, double theta, bool select)
+{
+    if (d < kBandMinD || M < 2 || M > kBandStages || !(theta > 0.0)) return false;
+    if (select) return d > kKeepMaxD;
+    return kept_ratio(ratios, M) < kKeepMinRatio && writes_lists(ratios, M, theta);  // else the order of the pairs is fixed
+}
+
+// Least half-width of stage m's band (0-based), relative to the threshold: what holds a given share of the vector's
+// entries on an exponential slope; for the last stage, whose list starts there, a share more than the call keeps.
+constexpr double kBandShare = 0.0075, kBandWidest = 0.1;
+float band_width(const double* ratios, int M, int m)
+{
+    const double cum = kept_ratio(ratios, m + 1), slope = log(1.0 / cum);
+    const bool last = m + 1 == M;
+    const double w = last ? log(1.25 + 0.0025 / cum) / slope : kBandShare / (2.0 * cum * slope);
+    const double most = last ? 3.0 * kBandWidest : kBandWidest;
+    return (float)(w < most ? w : most);
 }
 
 // the host's view of a call's device state
@@ -426,6 +468,16 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     const double theta = g_speculation;
     bool same_shape = c.sig_d == d && c.sig_dist == dist && c.sig_M == M && c.sig_theta == theta;
     for (int m = 0; m < M && same_shape; ++m) same_shape = c.sig_ratios[m] == ratios[m];
+    const bool select = d > kSmallMaxD && select_dense(d, residual != nullptr, ratios, M, theta);
+    const bool banded = uses_bands(d, ratios, M, theta, select);
+    p.bands = !banded ? kBandsNone : same_shape && c.sig_residual == (residual != nullptr) ? kBandsUse : kBandsRecord;
+    for (int m = 0; banded && m < M; ++m) p.band_w[m] = m + 1 == M && select ? 0.0f : band_width(ratios, M, m);
+    p.band_part = h->band_part;
+    p.band_cnt = h->band_cnt;
+    p.band_seg = segbuf[0];  // free until a stage that could not use them writes lists of its own
+    same_shape = same_shape && c.sig_lists;
+    c.sig_residual = residual != nullptr;
+    c.sig_lists = !select;
     c.sig_d = d;
     c.sig_dist = dist;
     c.sig_M = M;
@@ -456,15 +508,13 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
         return SIDCO_OK;
     }
 
-    const bool select = select_dense(d, residual != nullptr, ratios, M, theta);
-    if (select) c.sig_d = 0;  // no lists, no record of where the thresholds fell for a call of this shape without a residual
     const bool much = keeps_much(d, residual != nullptr, dist, ratios, M);
 
     // stage-1 sums (and acc) -> part[0]
     p.part_out = h->part[0];
     // the second list buffer is free until the first stage kernel writes it
-    launch_fit(p, fit_uses_flat(d, much), (double*)segbuf[1], s);
-
+    if (p.bands == kBandsUse) launch_fit_bands(p, s);
+    else launch_fit(p, fit_uses_flat(d, much), (double*)segbuf[1], s);
     ++k;
     mark("k_fit");
 

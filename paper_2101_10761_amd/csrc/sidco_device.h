@@ -159,8 +159,35 @@ __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (
 // works in (2 and 4 tiles ahead, and 32 waves per CU, were 1 to 5 % slower at 25.6 M to 138 M elements).
 // `v` sees every complete tile (v.tile(values, tile number)), every lane of the others (v.one(valid, value, index),
 // the wave together) and the end of each of those (v.end()).
-template <bool EC, bool WRITE, int GT, typename P, typename V>
-__device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v)
+// PAST: the residual is read and written past the caches, for a pass whose result is not read again soon.
+struct AccTile {
+    f4 g, r;
+};
+template <bool EC, bool WRITE, int GT, bool PAST, typename P>
+__device__ __forceinline__ AccTile acc_load(const P& p, size_t i)
+{
+    AccTile a = {};
+    a.g = load_grad4<GT, WRITE>(p.grad, i);
+    if constexpr (EC && PAST) a.r = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.acc_w + i));
+    else if constexpr (EC) a.r = *reinterpret_cast<const f4*>(p.acc_w + i);
+    return a;
+}
+template <bool PAST>
+__device__ __forceinline__ void acc_store(float* acc, size_t i, f4 c)
+{
+    if constexpr (PAST) __builtin_nontemporal_store(c, reinterpret_cast<f4*>(acc + i));
+    else *reinterpret_cast<f4*>(acc + i) = c;
+}
+// The first tile of a wave that has a complete one, for a kernel that has something to wait for before its sweep.
+template <bool EC, bool WRITE, int GT, bool PAST, typename P>
+__device__ __forceinline__ AccTile acc_first(const P& p, uint32_t w, int lane)
+{
+    const uint32_t t = w + ((w == 0 && p.shift > 0) ? p.nwaves : 0u);
+    return acc_load<EC, WRITE, GT, PAST>(p, (size_t)t * kTile + lane * 4 - p.shift);
+}
+// `first`: NULL, or that tile
+template <bool EC, bool WRITE, int GT, bool PAST = false, typename P, typename V>
+__device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v, const AccTile* first = nullptr)
 {
     const WaveTiles wt = wave_tiles(p, w);
     if (wt.nb > 0) {
@@ -168,22 +195,20 @@ __device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v
         uint32_t t = w + wt.k0 * wt.W;
         size_t i = (size_t)t * kTile + lane * 4 - p.shift;
         const size_t step = (size_t)wt.W * kTile;
-        f4 g = load_grad4<GT, WRITE>(p.grad, i), r = {};
-        if (EC) r = *reinterpret_cast<const f4*>(acc + i);
+        AccTile a = first ? *first : acc_load<EC, WRITE, GT, PAST>(p, i);
 #pragma unroll 1
         for (uint32_t k = 1; k < wt.nb; ++k) {
-            f4 c = g;
-            if (EC) c = g + r;
-            g = load_grad4<GT, WRITE>(p.grad, i + step);
-            if (EC) r = *reinterpret_cast<const f4*>(acc + i + step);
-            if (WRITE) *reinterpret_cast<f4*>(acc + i) = c;
+            f4 c = a.g;
+            if (EC) c = a.g + a.r;
+            a = acc_load<EC, WRITE, GT, PAST>(p, i + step);
+            if (WRITE) acc_store<PAST>(acc, i, c);
             v.tile(c, t);
             t += wt.W;
             i += step;
         }
-        if (EC) g = g + r;
-        if (WRITE) *reinterpret_cast<f4*>(acc + i) = g;
-        v.tile(g, t);
+        if (EC) a.g = a.g + a.r;
+        if (WRITE) acc_store<PAST>(acc, i, a.g);
+        v.tile(a.g, t);
     }
     for (uint32_t k = 0; k < wt.n - wt.nb; ++k) {
         const uint32_t t = w + guarded_tile(wt, k) * wt.W;

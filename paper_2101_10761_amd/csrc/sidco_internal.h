@@ -56,6 +56,14 @@ struct FitRecord {
     double s, c, a, b;
 };
 
+// Bands of a first pass (see k_fit_bands): what it looks for besides the sums of the fit.  Stage m < M: magnitudes in
+// (lo[m-1], hi[m-1]] are listed, those above hi[m-1] summed up; the last stage: everything above lo[M-1] is listed.
+constexpr int kBandStages = 3;  // calls of 2 and 3 stages
+struct Bands {
+    uint32_t on;  // stages of the calls they are for; 0: the edges mean nothing, the first pass only forms the fit's sums
+    float lo[kBandStages], hi[kBandStages];
+};
+
 // Device-resident state of one call.  Stage m's kernel reads the entries stage m-1 wrote and
 // writes its own, so no entry is read and written inside one kernel.
 struct DevState {
@@ -78,6 +86,11 @@ struct DevState {
     // of someone else fell into the current window of the controller's count
     unsigned long long owner;
     uint32_t disturbed;
+    // Bands of the call in flight (copied by its first pass) and of the next one (written by the last stage); whether
+    // stage m's threshold, and those before it, fell into their bands; the last call's thresholds and half-widths
+    Bands band, band_next;
+    uint32_t band_live[kBandStages + 1];
+    float band_eta[kBandStages], band_w[kBandStages];
 };
 
 // Kernel arguments (passed by value).
@@ -123,7 +136,13 @@ struct Params {
     float* out_eta;
     int64_t out_cap;
     uint32_t* status_out;   // NULL, or a device word that receives the call's status bits as well
+    int bands;              // kBands*
+    float band_w[kBandStages];  // least half-widths of the bands; the last stage's 0 if it reads no lists
+    double* band_part;      // [3 * (kBandStages - 1)][kMaxBlocks] sums of y, y^2 and 1 above each band's upper edge
+    uint32_t* band_cnt;     // [kMaxWaves] lengths of the lists of a first pass with bands
+    int2* band_seg;         // the lists themselves
 };
+constexpr int kBandsNone = 0, kBandsRecord = 1, kBandsUse = 2;
 
 // ---- exact Top-k comparator (sidco_topk.hip) ----
 constexpr int kTopkBins = 2048;  // digit 0 = magnitude bits 30..20; digits 1 and 2 have 1024 bins
@@ -306,6 +325,10 @@ constexpr int kSmallBlock = 1024;
 constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
 void launch_small(const Params& p, hipStream_t s);
 void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s);
+// A call that repeats a shape but has no bands (its thresholds jump) sweeps past the caches from this length on, where
+// they hold less than half of the vector anyway.
+constexpr int64_t kBandPastMinD = 100000000;
+void launch_fit_bands(const Params& p, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s);

@@ -9,6 +9,8 @@
 //                folds the per-block sums into the 512 slots the next kernel expects (long vectors, and from a
 //                lower length on calls that clear much of the residual; see fit_uses_flat).
 //                The gradient may be fp16 / bf16; it is widened as it is read.
+//   k_fit_bands  the same for a call that repeats a shape: it also sums up and lists what the stages will ask for if
+//                the thresholds fall near the last call's.
 //   stage m      m = 1..M, one kernel each.  Prologue: every block reduces the previous kernel's partial
 //                sums in a fixed order and its first wave evaluates the closed-form threshold eta_m in
 //                fp64 (the same arithmetic, hence identical bits, in every block).
@@ -171,6 +173,7 @@ struct StageEta {
     float eta;      // eta_m: the stage's threshold (statistics of the next fit; selection in the last stage)
     float eta_w;    // the lists this kernel writes hold every entry above eta_w (eta_w >= eta)
     bool lists_ok;  // the producer's lists hold every entry above eta: they can stand in for the dense vector
+    bool hit;       // eta fell into the stage's band: the first pass's sums and lists serve the stage
 };
 
 // Prologue of every stage kernel: reduce the producer's per-block partial sums (fixed order) and
@@ -200,6 +203,13 @@ struct PrologueLoads {
     float list_eta;     // the producer's lists hold every entry above this
     float seen;         // where the next stage's threshold fell last time (hint), NaN if unknown
     FitRecord prev_fit; // the producer's candidate fit (block 0, thread 0 only)
+};
+
+// Whether all thresholds so far fell into their bands (see k_fit_bands), and then the stage's own band; the last stage's
+// has no upper edge.
+struct BandEdges {
+    bool live;
+    float lo, hi;
 };
 
 template <bool FLAT = false>
@@ -276,7 +286,8 @@ __device__ __forceinline__ void flat_sums(const FlatPart& fp, const FlatLoads& f
 
 // Evaluates eta for stage p.stage from the reduced sums in g.v; called by the first wave of a block, and block 0's
 // thread 0 records the stage in the diagnostics.  g.status and g.frozen leave with what this stage adds to them.
-__device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto_src, PrologueLoads& g)
+__device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto_src, PrologueLoads& g,
+                                               const BandEdges& band = BandEdges{})
 {
     const int m = p.stage;  // 1-based
     const uint32_t t = threadIdx.x;
@@ -298,6 +309,7 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
     unsigned long long n;
     r.eta = r.eta_w = 0.0f;
     r.lists_ok = false;
+    r.hit = false;
     if (m == 1) {
         n = (unsigned long long)p.d;
         const double d = (double)p.d;
@@ -353,8 +365,10 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
             }
         }
     }
-    r.lists_ok = auto_src && (r.eta >= g.list_eta);  // false for a NaN threshold, which selects nothing anyway
-    if (auto_src && !r.lists_ok) status |= kStFallback;
+    // both false for a NaN threshold, which selects nothing anyway
+    r.hit = band.live && r.eta >= band.lo && r.eta <= band.hi;
+    r.lists_ok = auto_src && !band.live && r.eta >= g.list_eta;
+    if (auto_src && !r.lists_ok && !r.hit) status |= kStFallback;
     if (b.id == 0 && t == 0) {
         p.st->diag.eta[m - 1] = r.eta;
         p.st->diag.n[m - 1] = (int64_t)n;
@@ -390,23 +404,25 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
 
 // Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
 // in every thread of every block.  Block 0 records the stage in the diagnostics.
-__device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, PrologueLoads& g, double (*sh)[4])
+__device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, PrologueLoads& g, double (*sh)[4],
+                                    const BandEdges& band = BandEdges{})
 {
     const uint32_t t = threadIdx.x;
     StageEta r;
     r.eta = r.eta_w = 0.0f;
-    r.lists_ok = false;
+    r.lists_ok = r.hit = false;
     block_sum<3>(g.v, sh);
     // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
     // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
     // arithmetic and the prologue lasts that much longer (measured).
-    if (t < 64) r = stage_eval(p, b, auto_src, g);
+    if (t < 64) r = stage_eval(p, b, auto_src, g, band);
     __syncthreads();  // every thread has left block_sum: sh is free
     if (t == 0) {
         float* out = reinterpret_cast<float*>(&sh[0][0]);
         out[0] = r.eta;
         out[1] = r.eta_w;
         out[2] = r.lists_ok ? 1.0f : 0.0f;
+        out[3] = r.hit ? 1.0f : 0.0f;
     }
     __syncthreads();
     {
@@ -414,15 +430,17 @@ __device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, Prolo
         r.eta = in[0];
         r.eta_w = in[1];
         r.lists_ok = in[2] != 0.0f;
+        r.hit = in[3] != 0.0f;
     }
     return r;
 }
 
 // both halves back to back, for kernels whose body loads little before the threshold is known
-__device__ __forceinline__ StageEta stage_prologue(const Params& p, Blk b, bool auto_src, double (*sh)[4])
+__device__ __forceinline__ StageEta stage_prologue(const Params& p, Blk b, bool auto_src, double (*sh)[4],
+                                                   const BandEdges& band = BandEdges{})
 {
     PrologueLoads g = prologue_load(p, b, auto_src);
-    return prologue_finish(p, b, auto_src, g, sh);
+    return prologue_finish(p, b, auto_src, g, sh, band);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -469,6 +487,7 @@ __device__ __forceinline__ void fit_reset_state(const Params& p)
     p.st->overflow = 0;
     if (p.out_count) *p.out_count = 0;
     if (p.status_out) *p.status_out = 0;
+    if (p.bands == kBandsUse) p.st->band = p.st->band_next;
 }
 
 // one element through the guarded scalar path
@@ -500,14 +519,14 @@ struct FitSums {
     __device__ __forceinline__ void end() {}
 };
 
-template <int DIST, bool EC, int GT>
-__device__ __forceinline__ void fit_body(const Params& p, Blk b)
+template <int DIST, bool EC, int GT, bool PAST = false>
+__device__ __forceinline__ void fit_body(const Params& p, Blk b, const AccTile* first = nullptr)
 {
     __shared__ double sh[kWavesPerBlock][4];
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
     const uint32_t w = b.id * kWavesPerBlock + wib;
     FitSums<DIST> f;
-    if (w < p.nwaves) acc_sweep<EC, fit_writes<EC, GT>(), GT>(p, w, lane, f);
+    if (w < p.nwaves) acc_sweep<EC, fit_writes<EC, GT>(), GT, PAST>(p, w, lane, f, first);
     double v[3] = {f.s1, f.s2, f.sl + (double)f.se};
     v[0] = wave_sum(v[0]);
     v[1] = wave_sum(v[1]);
@@ -598,6 +617,183 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
         p.part_out[2 * kBatchBlocks + slot] = v[2];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) fit_reset_state(p);
+}
+
+// ---------------------------------------------------------------------------------------------
+// k_fit_bands: the first pass of a call that repeats the call before it in shape.  That call's thresholds, plus and
+// minus a few times what they moved by between the calls before, are a band in which each of this call's thresholds is
+// expected.  Besides the sums of the fit this pass forms, for every stage but the last, the sums of y = |x| - hi over the
+// magnitudes above the band, and lists the entries inside the bands and above the last stage's lower edge.  If the stage's
+// threshold then falls into its band - the stage's kernel checks - the exceedances are those sums, shifted to the
+// threshold, and the band's entries above it: the vector is not read again.  If not, the kernel reads the vector as it
+// would without bands.  The thresholds come from exact sums either way.
+// Bound by HBM: the ten or so instructions more per element hide behind 12 bytes.  Since nothing reads the vector again
+// soon, the residual goes past the caches, loads and stores: 25.6 M elements, three stages, three vectors in turn, first
+// pass alone 50.7 us against 57.0 (with the loads or the stores alone 58.2 and 57.0), 66 M 135 against 142; a dense stage
+// after such a pass would lose more than that (25.6 M, a call without bands 84.5 and 89.5).  A training step without and
+// with bands, us: 14.7 M, 2 stages, ratio 0.001 55.5 and 46.3; 25.6 M, 3 stages 84.2 and 75.5, bf16 77.4 and 67.1; 30 M,
+// fp16, 2 stages, 0.01 96.8 and 68.5; 66 M, gamma 171 and 148; 138 M, 3 stages, 0.01 518 and 409.  A call whose
+// thresholds fall out of the bands pays for them: 138 M 562 and 604, 100 M, 2 stages 381 and 410.
+// ---------------------------------------------------------------------------------------------
+// A band's half-width is the least one (see band_width in the host code) or, where that is more, kBandDrift times the
+// threshold's last relative change, which later calls let shrink by kBandDecay each: what moves by 10 % every third
+// call stays inside.  Beyond kBandMaxWidth the next call goes without bands - a tenth of the vector in lists costs what
+// the dense pass does - for 8 calls at most (kBandRest) once the thresholds keep still.
+constexpr float kBandDrift = 1.5f, kBandDecay = 0.87f, kBandMaxWidth = 0.15f, kBandRest = 0.4f;
+
+// One thread of the last stage's kernel: bands for the next call from this one's thresholds.
+__device__ void bands_record(const Params& p, float eta_last)
+{
+    if (p.bands == kBandsNone) return;
+    DevState* st = p.st;
+    Bands b;
+    b.on = (uint32_t)p.M;
+    float below = 0.0f;
+#pragma unroll
+    for (int m = 0; m < kBandStages; ++m) {
+        b.lo[m] = b.hi[m] = __builtin_inff();
+        if (m >= p.M) continue;
+        const bool last = m + 1 == p.M;
+        const float eta = last ? eta_last : st->diag.eta[m];
+        float w = p.band_w[m];
+        if (p.bands == kBandsUse) {
+            float moved = kBandDrift * __builtin_fabsf(eta - st->band_eta[m]) / st->band_eta[m];
+            if (!(moved <= kBandRest)) moved = kBandRest;
+            w = __builtin_fmaxf(w, __builtin_fmaxf(moved, kBandDecay * st->band_w[m]));
+        }
+        st->band_eta[m] = eta;
+        st->band_w[m] = w;
+        if (last && p.band_w[m] == 0.0f) continue;
+        const float lo = __builtin_fmaxf(eta * (1.0f - w), below), hi = last ? __builtin_inff() : eta * (1.0f + w);
+        if (!((last || w <= kBandMaxWidth) && eta > lo && eta < hi)) b.on = 0;  // also a threshold that is 0 or not finite
+        below = hi;
+        b.lo[m] = lo;
+        b.hi[m] = hi;
+    }
+    st->band_next = b;
+}
+
+__device__ __forceinline__ float uniform(float v)
+{
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+
+template <int DIST, int NB>
+struct FitBands {
+    static constexpr bool kSquares = DIST != kDistExp;  // the later stages' fits are GPD then
+    FitSums<DIST> f;
+    float lo[NB], hi[NB], last;
+    double y[NB], yy[NB];
+    uint32_t n[NB];
+    ListWriter lw;
+    int lane;
+    uint32_t shift;
+    __device__ __forceinline__ void element(float x, int32_t idx)
+    {
+        const float a = __builtin_fabsf(x);
+        // edges ascend: an entry above lo and not above hi of one band, or above the last edge, is above an odd number
+        bool keep = a > last;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const bool above = a > hi[b];
+            keep = keep != ((a > lo[b]) != above);
+            n[b] += (uint32_t)__popcll(__ballot(above));
+            const double v = (double)(above ? a : hi[b]) - (double)hi[b];
+            y[b] += v;
+            if (kSquares) yy[b] = __builtin_fma(v, v, yy[b]);
+        }
+        list_push(lw, keep, idx, x, lane);
+    }
+    __device__ __forceinline__ void tile(f4 c, uint32_t t)
+    {
+        f.tile(c, t);
+        const int32_t i0 = (int32_t)(t * kTile + lane * 4 - shift);
+        element(c.x, i0 + 0);
+        element(c.y, i0 + 1);
+        element(c.z, i0 + 2);
+        element(c.w, i0 + 3);
+        list_flush(lw, lane);
+    }
+    __device__ __forceinline__ void one(bool valid, float c, int64_t i)
+    {
+        f.one(valid, c, i);
+        element(c, (int32_t)i);  // zero where invalid: above no edge
+    }
+    __device__ __forceinline__ void end() { list_flush(lw, lane); }
+};
+
+template <int DIST, bool EC, int GT, int NB>
+__device__ __forceinline__ void fit_bands_body(const Params& p, Blk b, const Bands& e, const AccTile* first)
+{
+    __shared__ double sh[kWavesPerBlock][3 + 3 * NB];
+    __shared__ int2 ring[kWavesPerBlock][kRingSize];
+    const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
+    const uint32_t w = b.id * kWavesPerBlock + wib;
+    FitBands<DIST, NB> f;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        f.lo[k] = uniform(e.lo[k]);
+        f.hi[k] = uniform(e.hi[k]);
+        f.y[k] = f.yy[k] = 0.0;
+        f.n[k] = 0;
+    }
+    f.last = uniform(e.lo[NB]);
+    f.lane = lane;
+    f.shift = p.shift;
+    f.lw.list = p.band_seg + seg_begin(p, w < p.nwaves ? w : 0);
+    f.lw.ring = ring[wib];
+    f.lw.run = f.lw.fill = 0;
+    if (w < p.nwaves) {
+        acc_sweep<EC, fit_writes<EC, GT>(), GT, EC>(p, w, lane, f, first);
+        const uint32_t n = list_finish(f.lw, lane);
+        if (lane == 0) p.band_cnt[w] = n;
+    }
+    double v[3 + 3 * NB];
+    v[0] = wave_sum(f.f.s1);
+    v[1] = DIST == kDistGpd ? wave_sum(f.f.s2) : 0.0;
+    v[2] = DIST == kDistGamma ? wave_sum(f.f.sl + (double)f.f.se) : 0.0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        v[3 + 3 * k] = wave_sum(f.y[k]);
+        v[4 + 3 * k] = DIST != kDistExp ? wave_sum(f.yy[k]) : 0.0;
+        v[5 + 3 * k] = (double)f.n[k];
+    }
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < 3 + 3 * NB; ++q) sh[wib][q] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 3 + 3 * NB) {
+        double tot = 0.0;
+#pragma unroll
+        for (int i = 0; i < kWavesPerBlock; ++i) tot += sh[i][threadIdx.x];
+        if (threadIdx.x < 3) p.part_out[threadIdx.x * kBatchBlocks + b.id] = tot;
+        else p.band_part[(threadIdx.x - 3) * kMaxBlocks + b.id] = tot;
+    }
+    if (b.id == 0 && threadIdx.x == 0) fit_reset_state(p);
+}
+
+template <bool BANDS>
+__device__ __forceinline__ BandEdges band_load(const Params& p)
+{
+    if constexpr (!BANDS) return BandEdges{};
+    const int m = p.stage;
+    return BandEdges{m == 1 ? p.st->band.on == (uint32_t)p.M : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1]};
+}
+
+// What a block of the first pass summed up above the band of this stage, shifted to the stage's threshold below it.
+struct BandAbove {
+    double y, yy, n;
+};
+__device__ __forceinline__ BandAbove band_above_load(const Params& p, Blk b)
+{
+    const double* q = p.band_part + (size_t)3 * (p.stage - 1) * kMaxBlocks + b.id;
+    return BandAbove{q[0], q[kMaxBlocks], q[2 * kMaxBlocks]};
+}
+__device__ __forceinline__ BandAbove band_above_shift(BandAbove a, float hi, float eta)
+{
+    const double s = (double)hi - (double)eta;
+    return BandAbove{a.y + a.n * s, a.yy + (2.0 * a.y + a.n * s) * s, a.n};
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -703,9 +899,10 @@ __device__ __forceinline__ void compact_slots(const int4 (&q)[U], uint32_t c, ui
 // End of a stage kernel: per block, the number of exceedances of eta_m (the n of the next fit) - or,
 // without statistics (dense last stage), the number of list entries (k_gather's prefix) - and the
 // block's partial sums of y and y^2, each in its fixed slot.
-template <bool STATS>
+// BANDS: `above` joins them.
+template <bool STATS, bool BANDS = false>
 __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane, int wib, uint32_t count, double sy,
-                                               double syy, double (*sh)[4], uint32_t* sh_cnt)
+                                               double syy, double (*sh)[4], uint32_t* sh_cnt, BandAbove above = BandAbove{})
 {
     if (lane == 0) sh_cnt[wib] = count;
     if (STATS) {
@@ -722,21 +919,54 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
         uint32_t tot = 0;
 #pragma unroll
         for (int i = 0; i < kWavesPerBlock; ++i) tot += sh_cnt[i];
+        if (BANDS) tot += (uint32_t)above.n;
         p.blk_out[b.id] = tot;
     }
     if (STATS && threadIdx.x < 2) {
         double tot = 0.0;
 #pragma unroll
         for (int i = 0; i < kWavesPerBlock; ++i) tot += sh[i][threadIdx.x];
+        if (BANDS) tot += threadIdx.x == 0 ? above.y : above.yy;
         p.part_out[threadIdx.x * kBatchBlocks + b.id] = tot;
+    }
+}
+
+// A stage whose threshold fell into its band: the band's entries above the threshold.  `q0` and `q1` hold the list's
+// first 64 slots and the 64 after them.
+template <int U>
+__device__ __forceinline__ void band_sums(const int4* __restrict__ src4, uint32_t cap2, uint32_t n, int4 q0, int4 q1, int lane,
+                                          float eta, float hi, uint32_t& ns, double& sy, double& syy)
+{
+    ListWriter none;
+    auto entry = [&](bool in, int v) {
+        const float x = __int_as_float(v);
+        emit<true, false>(in && __builtin_fabsf(x) <= hi, x, 0, eta, eta, none, lane, ns, sy, syy);
+    };
+    const uint32_t e = 2 * lane;
+    entry(e < n, q0.y);
+    entry(e + 1 < n, q0.w);
+    entry(e + 128 < n, q1.y);
+    entry(e + 129 < n, q1.w);
+#pragma unroll 1
+    for (uint32_t c = 128; c < (n + 1) / 2; c += 64 * U) {
+        int4 q[U];
+        load_slots<U>(q, src4, c, cap2, lane);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t f = 2 * (c + u * 64 + lane);
+            entry(f < n, q[u].y);
+            entry(f + 1 < n, q[u].w);
+        }
     }
 }
 
 // k_compact: a stage that reads the dense vector.  STATS: form the sums for the next stage's fit.
 // WRITE: append the entries above eta_w to this stage's lists (eta_w = eta_m, or a candidate threshold
 // above it); a stage whose candidates would still be a large fraction only counts and sums.  KEEP: with ordinary loads,
-// which leave the vector in the memory-side cache (see keeps_much in the host code).
-template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false>
+// which leave the vector in the memory-side cache (see keeps_much in the host code).  BANDS: behind a first pass with
+// bands, which this stage may be able to do with; the head of the wave's list is then requested beside its first tile,
+// since waiting to know which of them it will be costs more than reading both.
+template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false, bool BANDS = false>
 __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{})
 {
     __shared__ double sh[kWavesPerBlock][4];
@@ -758,12 +988,35 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     f4 a[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) a[u] = dense_load<KEEP>(d, u, lane);
+    const int4* src4 = nullptr;
+    int4 q0 = {}, q1 = {};
+    uint32_t n_in = 0;
+    BandAbove above = {};
+    BandEdges band = {};
+    if constexpr (BANDS) {
+        src4 = reinterpret_cast<const int4*>(p.band_seg + seg_begin(p, active ? w : 0));
+        q0 = src4[lane];
+        n_in = active ? p.band_cnt[w] : 0u;
+        above = band_above_load(p, b);
+        band = band_load<true>(p);
+        if (band.live) q1 = src4[64 + lane];  // a wave owns several tiles
+    }
     if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
 
-    const StageEta se = prologue_finish(p, b, false, g, sh);
+    const StageEta se = prologue_finish(p, b, false, g, sh, band);
 
     uint32_t run = 0, ns = 0;
     double sy = 0.0, syy = 0.0;
+    if constexpr (BANDS) {
+        if (b.id == 0 && threadIdx.x == 0) p.st->band_live[p.stage] = se.hit ? 1u : 0u;
+        if (se.hit) {
+            if (active)
+                band_sums<4>(src4, seg_slots(p, w) / 2, __builtin_amdgcn_readfirstlane(n_in), q0, q1, lane, se.eta, band.hi,
+                             ns, sy, syy);
+            stage_epilogue<STATS, true>(p, b, lane, wib, ns, sy, syy, sh, sh_cnt, band_above_shift(above, band.hi, se.eta));
+            return;
+        }
+    }
     if (active) {
         ListWriter lw;
         lw.list = p.seg_out + seg_begin(p, w);  // room for every element of the wave's tiles
@@ -783,6 +1036,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
 // by the launch itself: every wave takes the list of the same wave of the kernel before it, and its
 // first 128 entries are loaded before the prologue.
 // ---------------------------------------------------------------------------------------------
+template <bool BANDS = false>
 __device__ __forceinline__ void lists_body(const Params& p, Blk b)
 {
     __shared__ double sh[kWavesPerBlock][4];
@@ -793,16 +1047,37 @@ __device__ __forceinline__ void lists_body(const Params& p, Blk b)
     const uint32_t w = b.id * kWavesPerBlock + wib;
     const bool active = w < p.nwaves;
     const size_t seg = seg_begin(p, active ? w : 0);
-    const int4* __restrict__ src4 = reinterpret_cast<const int4*>(p.seg_in + seg);
+    const int2* src = p.seg_in;
+    const uint32_t* cnt = p.cnt_in;
+    const BandEdges band = band_load<BANDS>(p);
+    if (band.live) {
+        src = p.band_seg;
+        cnt = p.band_cnt;
+    }
+    const int4* __restrict__ src4 = reinterpret_cast<const int4*>(src + seg);
     const uint32_t cap2 = seg_slots(p, active ? w : 0) / 2;  // at least 128: a wave owns a tile
-    uint32_t n_in = active ? p.cnt_in[w] : 0u;
+    uint32_t n_in = active ? cnt[w] : 0u;
     const int4 q0 = src4[lane];
+    int4 q1 = {};
+    BandAbove above = {};
+    if constexpr (BANDS) {
+        if (band.live) q1 = src4[64 + lane];
+        above = band_above_load(p, b);
+    }
 
-    const StageEta se = stage_prologue(p, b, true, sh);
+    const StageEta se = stage_prologue(p, b, true, sh, band);
     const float eta = se.eta;
 
     uint32_t ns = 0;
     double sy = 0.0, syy = 0.0;
+    if constexpr (BANDS) {
+        if (b.id == 0 && threadIdx.x == 0) p.st->band_live[p.stage] = se.hit ? 1u : 0u;
+        if (se.hit) {
+            if (active) band_sums<U>(src4, cap2, __builtin_amdgcn_readfirstlane(n_in), q0, q1, lane, eta, band.hi, ns, sy, syy);
+            stage_epilogue<true, true>(p, b, lane, wib, ns, sy, syy, sh, sh_cnt, band_above_shift(above, band.hi, eta));
+            return;
+        }
+    }
     if (active) {
         ListWriter lw;
         lw.list = p.seg_out + seg;
@@ -855,13 +1130,13 @@ struct FinalList {
     uint32_t n;        // entries
 };
 
-__device__ __forceinline__ FinalList final_list(const Params& p, uint32_t sw, bool valid)
+__device__ __forceinline__ FinalList final_list(const Params& p, const int2* seg, const uint32_t* cnt, uint32_t sw, bool valid)
 {
     FinalList l;
     const uint32_t w = valid ? sw : 0;
-    l.src4 = reinterpret_cast<const int4*>(p.seg_in + seg_begin(p, w));
+    l.src4 = reinterpret_cast<const int4*>(seg + seg_begin(p, w));
     l.cap2 = seg_slots(p, w) / 2;
-    l.n = valid ? p.cnt_in[w] : 0u;
+    l.n = valid ? cnt[w] : 0u;
     return l;
 }
 
@@ -954,6 +1229,7 @@ __device__ __forceinline__ void final_emit_dense(const Params& p, uint32_t sw, i
     });
 }
 
+template <bool BANDS = false>
 __device__ __forceinline__ void final_body(const Params& p, Blk b)
 {
     __shared__ double sh[kWavesPerBlock][4];
@@ -967,30 +1243,41 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
     const uint32_t first = b.id * per_block + wib;
     const uint32_t last = min(p.nwaves, (b.id + 1) * per_block);
 
-    // first group of lists: counts and first 64 slots of each, all loads issued together and before
-    // the prologue (none depends on the threshold)
+    const BandEdges band = band_load<BANDS>(p);
+    const int2* seg = band.live ? p.band_seg : p.seg_in;
+    const uint32_t* cnt = band.live ? p.band_cnt : p.cnt_in;
+    // first group of lists: counts and first 64 slots of each (128 behind a first pass with bands, whose lists hold what
+    // the stages before needed as well), all loads issued together and before the threshold (none depends on it)
+    constexpr int H = BANDS ? 2 : 1;
     FinalList l0[K];
-    int4 q0[K];
+    int4 q0[K][H];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const uint32_t sw = first + k * kWavesPerBlock;
-        l0[k] = final_list(p, sw, sw < last);
-        q0[k] = (uint32_t)lane < l0[k].cap2 ? l0[k].src4[lane] : make_int4(0, 0, 0, 0);
+        l0[k] = final_list(p, seg, cnt, sw, sw < last);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const uint32_t i = h * 64 + lane;
+            q0[k][h] = i < l0[k].cap2 && (h == 0 || band.live) ? l0[k].src4[i] : make_int4(0, 0, 0, 0);
+        }
     }
 
-    const StageEta se = stage_prologue(p, b, true, sh);
+    const StageEta se = stage_prologue(p, b, true, sh, band);
     const float eta = se.eta;
+    const bool from_lists = se.lists_ok || se.hit;
 
     // pass A: count
     uint32_t mine = 0;
-    if (!se.lists_ok) {
+    if (!from_lists) {
         for (uint32_t sw = first; sw < last; sw += kWavesPerBlock) mine += final_count_dense(p, sw, lane, eta);
     } else {
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const uint32_t n = __builtin_amdgcn_readfirstlane(l0[k].n);
-        mine += final_count(q0[k], lane, n, eta);
-        for (uint32_t c = 64; c < (n + 1) / 2; c += 64) {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+            if (h == 0 || band.live) mine += final_count(q0[k][h], h * 64 + lane, n, eta);
+        for (uint32_t c = band.live ? 64 * H : 64; c < (n + 1) / 2; c += 64) {
             const uint32_t i = c + lane;
             const int4 q = i < l0[k].cap2 ? l0[k].src4[i] : make_int4(0, 0, 0, 0);
             mine += final_count(q, i, n, eta);
@@ -1020,21 +1307,24 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
             const uint32_t status = p.st->status_after[p.M];  // written by this thread in the prologue
             p.st->diag.status = status;
             if (p.status_out && status) atomicOr(p.status_out, status);
+            bands_record(p, eta);
         }
     }
     __syncthreads();
     unsigned long long pos = sh_base + off;
 
     // pass B: same traversal, now writing; the first group is still in registers
-    if (!se.lists_ok) {
+    if (!from_lists) {
         for (uint32_t sw = first; sw < last; sw += kWavesPerBlock) final_emit_dense(p, sw, lane, eta, cap, pos);
         return;
     }
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const uint32_t n = __builtin_amdgcn_readfirstlane(l0[k].n);
-        final_emit(p, q0[k], lane, n, eta, cap, pos);
-        for (uint32_t c = 64; c < (n + 1) / 2; c += 64) {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+            if (h == 0 || band.live) final_emit(p, q0[k][h], h * 64 + lane, n, eta, cap, pos);
+        for (uint32_t c = band.live ? 64 * H : 64; c < (n + 1) / 2; c += 64) {
             const uint32_t i = c + lane;
             const int4 q = i < l0[k].cap2 ? l0[k].src4[i] : make_int4(0, 0, 0, 0);
             final_emit(p, q, i, n, eta, cap, pos);
@@ -1061,6 +1351,7 @@ __global__ __launch_bounds__(kBlock) void k_eta(Params p)
         const uint32_t status = p.st->status_after[p.M];  // written by this thread in the prologue
         p.st->diag.status = status;
         if (p.status_out && status) *p.status_out = status;
+        bands_record(p, se.eta);
     }
 }
 
@@ -1522,10 +1813,27 @@ __device__ __forceinline__ void block_tiles(const Params& p, Blk b, uint32_t& T0
 
 template <int DIST, bool EC, int GT>
 __global__ __launch_bounds__(kBlock, 4) void k_fit(Params p) { fit_body<DIST, EC, GT>(p, whole_grid()); }
-template <bool STATS, bool WRITE, bool KEEP>
-__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p) { compact_body<STATS, WRITE, false, KEEP>(p, whole_grid()); }
-__global__ __launch_bounds__(kBlock, 4) void k_lists(Params p) { lists_body(p, whole_grid()); }
-__global__ __launch_bounds__(kBlock) void k_final_lists(Params p) { final_body(p, whole_grid()); }
+// PAST: the sweep goes past the caches without bands too (see launch_fit_bands)
+template <int DIST, bool EC, int GT, int NB, bool PAST>
+__global__ __launch_bounds__(kBlock, 4) void k_fit_bands(Params p)
+{
+    // the edges were written at the end of the call before: a round trip, and the first tile is requested ahead of it
+    // (from kBandMinD elements on every wave has several)
+    const AccTile first =
+        acc_first<EC, fit_writes<EC, GT>(), GT, EC>(p, blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), threadIdx.x & 63);
+    const Bands e = p.st->band_next;
+    if (e.on == (uint32_t)p.M) fit_bands_body<DIST, EC, GT, NB>(p, whole_grid(), e, &first);
+    else fit_body<DIST, EC, GT, PAST>(p, whole_grid(), &first);
+}
+template <bool STATS, bool WRITE, bool KEEP, bool BANDS>
+__global__ __launch_bounds__(kBlock, 4) void k_compact(Params p)
+{
+    compact_body<STATS, WRITE, false, KEEP, BANDS>(p, whole_grid());
+}
+template <bool BANDS>
+__global__ __launch_bounds__(kBlock, 4) void k_lists(Params p) { lists_body<BANDS>(p, whole_grid()); }
+template <bool BANDS>
+__global__ __launch_bounds__(kBlock) void k_final_lists(Params p) { final_body<BANDS>(p, whole_grid()); }
 __global__ __launch_bounds__(kBlock) void k_gather(Params p) { gather_body(p, whole_grid()); }
 
 template <int DIST, bool EC, int GT>
@@ -1725,6 +2033,42 @@ static void launch_fit_type(const Params& p, bool flat, double* scratch, hipStre
     else launch_fit_shape<false, GT>(p, flat, scratch, s);
 }
 
+template <bool EC, int GT, int NB, bool PAST>
+static void launch_fit_bands_as(const Params& p, hipStream_t s)
+{
+    const dim3 grid(p.nblocks), block(kBlock);
+    switch (p.dist) {
+        case kDistExp: hipLaunchKernelGGL((k_fit_bands<kDistExp, EC, GT, NB, PAST>), grid, block, 0, s, p); break;
+        case kDistGamma: hipLaunchKernelGGL((k_fit_bands<kDistGamma, EC, GT, NB, PAST>), grid, block, 0, s, p); break;
+        default: hipLaunchKernelGGL((k_fit_bands<kDistGpd, EC, GT, NB, PAST>), grid, block, 0, s, p); break;
+    }
+}
+
+template <bool EC, int GT, bool PAST>
+static void launch_fit_bands_stages(const Params& p, hipStream_t s)
+{
+    if (p.M == 2) launch_fit_bands_as<EC, GT, 1, PAST>(p, s);
+    else launch_fit_bands_as<EC, GT, 2, PAST>(p, s);
+}
+
+template <int GT>
+static void launch_fit_bands_type(const Params& p, hipStream_t s)
+{
+    if (!p.residual) launch_fit_bands_stages<false, GT, false>(p, s);
+    else if (p.d >= kBandPastMinD) launch_fit_bands_stages<true, GT, true>(p, s);
+    else launch_fit_bands_stages<true, GT, false>(p, s);
+}
+
+// p.M = 2 or 3
+void launch_fit_bands(const Params& p, hipStream_t s)
+{
+    switch (p.gt) {
+        case kGradF16: launch_fit_bands_type<kGradF16>(p, s); break;
+        case kGradBf16: launch_fit_bands_type<kGradBf16>(p, s); break;
+        default: launch_fit_bands_type<kGradF32>(p, s); break;
+    }
+}
+
 template <bool EC, int GT, int N>
 static void launch_small_as(const Params& p, hipStream_t s)
 {
@@ -1769,17 +2113,23 @@ void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s)
 void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s)
 {
     const dim3 grid(p.nblocks), block(kBlock);
-    if (stats && write && keep) hipLaunchKernelGGL((k_compact<true, true, true>), grid, block, 0, s, p);
-    else if (stats && write) hipLaunchKernelGGL((k_compact<true, true, false>), grid, block, 0, s, p);
-    else if (stats && keep) hipLaunchKernelGGL((k_compact<true, false, true>), grid, block, 0, s, p);
-    else if (stats) hipLaunchKernelGGL((k_compact<true, false, false>), grid, block, 0, s, p);
-    else if (keep) hipLaunchKernelGGL((k_compact<false, true, true>), grid, block, 0, s, p);
-    else hipLaunchKernelGGL((k_compact<false, true, false>), grid, block, 0, s, p);
+    if (p.bands == kBandsUse) {  // statistics always: a last stage on the dense vector is another kernel
+        if (write) hipLaunchKernelGGL((k_compact<true, true, false, true>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((k_compact<true, false, false, true>), grid, block, 0, s, p);
+        return;
+    }
+    if (stats && write && keep) hipLaunchKernelGGL((k_compact<true, true, true, false>), grid, block, 0, s, p);
+    else if (stats && write) hipLaunchKernelGGL((k_compact<true, true, false, false>), grid, block, 0, s, p);
+    else if (stats && keep) hipLaunchKernelGGL((k_compact<true, false, true, false>), grid, block, 0, s, p);
+    else if (stats) hipLaunchKernelGGL((k_compact<true, false, false, false>), grid, block, 0, s, p);
+    else if (keep) hipLaunchKernelGGL((k_compact<false, true, true, false>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_compact<false, true, false, false>), grid, block, 0, s, p);
 }
 
 void launch_lists(const Params& p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_lists, dim3(p.nblocks), dim3(kBlock), 0, s, p);
+    if (p.bands == kBandsUse) hipLaunchKernelGGL(k_lists<true>, dim3(p.nblocks), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL(k_lists<false>, dim3(p.nblocks), dim3(kBlock), 0, s, p);
 }
 
 void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
@@ -1787,7 +2137,8 @@ void launch_final_lists(const Params& p, uint32_t grid_blocks, hipStream_t s)
     // a block reads at most kFinalGroup lists per wave (see final_body)
     const uint32_t least = (p.nwaves + kFinalGroup * kWavesPerBlock - 1) / (kFinalGroup * kWavesPerBlock);
     if (grid_blocks < least) grid_blocks = least;
-    hipLaunchKernelGGL(k_final_lists, dim3(grid_blocks), dim3(kBlock), 0, s, p);
+    if (p.bands == kBandsUse) hipLaunchKernelGGL(k_final_lists<true>, dim3(grid_blocks), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL(k_final_lists<false>, dim3(grid_blocks), dim3(kBlock), 0, s, p);
 }
 
 void launch_select(const Params& p, bool keep, hipStream_t s)

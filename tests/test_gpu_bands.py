@@ -1,0 +1,186 @@
+"""Calls that repeat the call before them in shape: the first pass looks for the thresholds where they fell last time
+(k_fit_bands) and the stages do without the dense vector if it found them.  Whether they did is seen from the second list
+buffer of the workspace, which only a stage that read the vector writes; results must not depend on it."""
+import numpy as np
+import pytest
+
+from gpu_harness import check_parity, run_gpu
+
+pytestmark = pytest.mark.gpu
+
+D = 10_000_037  # such calls take bands from 10 M elements
+
+
+class Workspace:
+    """A workspace of the test's own, to see what a call wrote."""
+
+    def __init__(self, d):
+        import torch
+        import paper_2101_10761_amd as sidco
+        size = sidco.sidco_workspace_bytes(d)
+        seg = (d + 31 + 255) // 256 * 256 * 8
+        self.ws = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
+        self.second = self.ws[size - seg:]
+
+    def __enter__(self):
+        import paper_2101_10761_amd as sidco
+        sidco.sidco_set_workspace(self.ws)
+        return self
+
+    def __exit__(self, *_):
+        import paper_2101_10761_amd as sidco
+        sidco.sidco_set_workspace(None)
+
+    def run(self, *args, **kw):
+        """The call's result and whether its first stage did without the dense vector."""
+        self.second.fill_(0x5A)
+        out = run_gpu(*args, **kw)
+        return out, bool((self.second == 0x5A).all())
+
+
+def _vector(law, d, seed, scale=1e-3):
+    rng = np.random.default_rng(seed)
+    if law == "laplace":
+        return rng.laplace(0, scale, size=d).astype(np.float32)
+    if law == "student":
+        return (rng.standard_t(5.0, size=d) * scale).astype(np.float32)
+    parts = rng.laplace(0, 1.0, size=d)  # tensors of very different scale one after the other
+    return (parts * np.repeat(scale * 10.0 ** np.linspace(-2, 1, 16), -(-d // 16))[:d]).astype(np.float32)
+
+
+@pytest.mark.parametrize("dist,law", [(0, "laplace"), (1, "scales"), (2, "student")])
+@pytest.mark.parametrize("stages,delta,residual,offset", [(2, 0.001, True, 0), (3, 0.01, True, 3), (3, 0.001, False, 1),
+                                                          (2, 0.03, True, 1)])
+def test_thresholds_found_where_they_fell_last_time(oracle, dist, law, stages, delta, residual, offset):
+    d = D + stages
+    ratios = oracle.schedule(delta, stages, 0.25)
+    r = _vector(law, d, 1, 3e-4) if residual else None
+    with Workspace(d) as ws:
+        routes = []
+        for call in range(4):
+            g = _vector(law, d, 10 + call)
+            out, without = ws.run(g, r, dist, ratios, grad_offset=offset, res_offset=(offset + 1) % 4 if offset else 0)
+            check_parity(oracle, g, r, dist, ratios, out, label=f"call {call} {law} dist={dist} M={stages}")
+            routes.append(without)
+        assert routes == [False, True, True, True]
+
+
+def _moved_tail(g, eta, factor):
+    """The same mean magnitude with the entries above 1.5 eta scaled by `factor`."""
+    a = np.abs(g.astype(np.float64))
+    tail, low = a > 1.5 * eta, a < 0.5 * eta
+    fix = 1.0 - (factor - 1.0) * a[tail].sum() / a[low].sum()
+    return np.where(tail, g * factor, np.where(low, g * fix, g)).astype(np.float32)
+
+
+@pytest.mark.parametrize("stages", [2, 3])
+@pytest.mark.parametrize("factor", [0.6, 1.2])
+def test_a_later_threshold_outside_its_band(oracle, stages, factor):
+    """The first threshold stays, the second moves: down out of the lists, or up."""
+    ratios = oracle.schedule(0.005, stages, 0.25)
+    zero = np.zeros(D, np.float32)
+    with Workspace(D) as ws:
+        for call in range(3):
+            g = _vector("laplace", D, call)
+            out, without = ws.run(g, zero, 0, ratios)
+        assert without
+        g = _moved_tail(g, float(out.etas[0]), factor)
+        moved, without = ws.run(g, zero, 0, ratios)
+        check_parity(oracle, g, zero, 0, ratios, moved, label=f"moved M={stages} {factor}")
+        assert without and bool(moved.status & 64) == (stages == 3 or factor < 1)  # two stages: the lists reach up, not down
+        again, without = ws.run(g, zero, 0, ratios)
+        check_parity(oracle, g, zero, 0, ratios, again, label="after the miss")
+
+
+@pytest.mark.parametrize("stages", [2, 3])
+def test_buffers_of_different_scale_in_turn(oracle, stages):
+    """Neither the jump of the first threshold nor the calls after it change a result; such calls go without bands."""
+    ratios = oracle.schedule(0.01, stages, 0.25)
+    zero = np.zeros(D, np.float32)
+    with Workspace(D) as ws:
+        for call, scale in enumerate([1e-3, 1e-3, 2e-3, 1e-3, 2e-3, 1e-3]):
+            g = _vector("laplace", D, call, scale)
+            out, without = ws.run(g, zero, 0, ratios)
+            check_parity(oracle, g, zero, 0, ratios, out, label=f"call {call}")
+            assert without == (call == 1)
+
+
+@pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
+def test_special_inputs_behind_bands(oracle, kind):
+    zero = np.zeros(D, np.float32)
+    for dist, ratios in ((0, [0.25, 0.04]), (2, [0.25, 0.2, 0.2]), (1, [0.25, 0.04])):
+        for call in range(3):
+            run_gpu(_vector("laplace", D, call), zero, dist, ratios)
+        g = _vector("laplace", D, 9)
+        if kind == "nan":
+            g[D // 2] = np.nan
+        elif kind == "zero":
+            g[:] = 0.0
+        else:
+            g = np.copysign(np.float32(1e-3), g)
+        for _ in range(2):
+            out = run_gpu(g, zero, dist, ratios)
+            check_parity(oracle, g, zero, dist, ratios, out, label=f"{kind} dist={dist}")
+
+
+def test_capacity_behind_bands(oracle):
+    zero, ratios = np.zeros(D, np.float32), [0.25, 0.04]
+    for call in range(3):
+        g = _vector("laplace", D, call)
+        out = run_gpu(g, zero, 0, ratios, cap=5000)
+        check_parity(oracle, g, zero, 0, ratios, out, capacity=5000, label=f"call {call}")
+
+
+@pytest.mark.parametrize("ratios", [[0.25, 0.4], [0.25, 0.64, 0.64]])
+def test_a_dense_last_stage_behind_bands(oracle, ratios):
+    d = 62_000_003
+    for call in range(3):
+        rng = np.random.default_rng(call)
+        g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+        r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+        out = run_gpu(g, r, 0, ratios)
+    check_parity(oracle, g, r, 0, ratios, out, label=f"{ratios}")
+
+
+@pytest.mark.parametrize("kind", ["f16", "bf16"])
+@pytest.mark.parametrize("residual", [True, False])
+def test_16_bit_gradients_behind_bands(oracle, kind, residual):
+    from test_gpu_typed import narrow, run_typed
+    r = _vector("laplace", D, 1, 3e-3) if residual else None
+    for dist, stages in ((2, 3), (1, 2), (0, 2)):
+        for call in range(4):
+            g16, g = narrow(_vector("student", D, 20 + call, 1e-2), kind)
+            out = run_typed(g16, r, dist, 0.005, stages, grad_offset=1, res_offset=2)
+        check_parity(oracle, g, r, dist, oracle.schedule(0.005, stages, 0.25), out, label=f"{kind} dist={dist} M={stages}")
+
+
+def test_replays_of_a_captured_call_with_bands(oracle):
+    """A call that uses bands, captured and replayed with new data; eager calls in between leave bands of another kind."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    from gpu_harness import GpuCall
+    ratios, other = oracle.schedule(0.01, 3, 0.25), oracle.schedule(0.01, 2, 0.25)
+    zero = np.zeros(D, np.float32)
+    side = torch.cuda.Stream()
+    for call in range(2):
+        GpuCall(_vector("laplace", D, call), zero, 0, ratios).launch(side).collect(side)
+    held = GpuCall(_vector("laplace", D, 2), zero, 0, ratios)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        graph.capture_begin()
+        held.launch(side)
+        graph.capture_end()
+    for it in range(4):
+        held.g = _vector("laplace", D, 10 + it)
+        held.gt.copy_(torch.from_numpy(held.g))
+        held.rt.zero_()
+        held.out_idx.fill_(-7)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check_parity(oracle, held.g, zero, 0, ratios, held.collect(side), label=f"replay {it}")
+        if it < 3:
+            g = _vector("laplace", D, 20 + it)
+            out = GpuCall(g, zero, 0, other).launch(side).collect(side)
+            check_parity(oracle, g, zero, 0, other, out, label=f"eager {it}")
+    sidco.sidco_release(stream=side)
