@@ -468,6 +468,16 @@ __device__ __forceinline__ void fit_accum(float x, double& s1, double& s2, doubl
 template <bool EC, int GT>
 constexpr bool fit_writes() { return EC || GT != kGradF32; }
 
+// Whether edges are for calls of M stages.  They ascend in every record; memory that holds none is refused here, and what
+// ascends by chance serves a call as well as any.
+__device__ __forceinline__ bool bands_usable(const Bands& e, int M)
+{
+    const float inf = __builtin_inff();
+    const bool first = e.on == (uint32_t)M && e.lo[0] > 0.0f && e.lo[0] < e.hi[0] && e.hi[0] <= e.lo[1] && e.hi[0] < inf;
+    const bool rest = M == 2 ? e.hi[1] == inf : e.lo[1] < e.hi[1] && e.hi[1] <= e.lo[2] && e.hi[1] < inf && e.hi[2] == inf;
+    return first && rest;
+}
+
 // start of a call: per-call device state, by one thread
 __device__ __forceinline__ void fit_reset_state(const Params& p)
 {
@@ -487,7 +497,10 @@ __device__ __forceinline__ void fit_reset_state(const Params& p)
     p.st->overflow = 0;
     if (p.out_count) *p.out_count = 0;
     if (p.status_out) *p.status_out = 0;
-    if (p.bands == kBandsUse) p.st->band = p.st->band_next;
+    if (p.bands == kBandsUse) {
+        p.st->band = p.st->band_next;
+        if (!bands_usable(p.st->band_next, p.M)) p.st->band.on = 0;
+    }
 }
 
 // one element through the guarded scalar path
@@ -778,7 +791,7 @@ __device__ __forceinline__ BandEdges band_load(const Params& p)
 {
     if constexpr (!BANDS) return BandEdges{};
     const int m = p.stage;
-    return BandEdges{m == 1 ? p.st->band.on == (uint32_t)p.M : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1]};
+    return BandEdges{m == 1 ? p.st->band.on != 0 : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1]};
 }
 
 // What a block of the first pass summed up above the band of this stage, shifted to the stage's threshold below it.
@@ -1822,7 +1835,7 @@ __global__ __launch_bounds__(kBlock, 4) void k_fit_bands(Params p)
     const AccTile first =
         acc_first<EC, fit_writes<EC, GT>(), GT, EC>(p, blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), threadIdx.x & 63);
     const Bands e = p.st->band_next;
-    if (e.on == (uint32_t)p.M) fit_bands_body<DIST, EC, GT, NB>(p, whole_grid(), e, &first);
+    if (bands_usable(e, NB + 1)) fit_bands_body<DIST, EC, GT, NB>(p, whole_grid(), e, &first);
     else fit_body<DIST, EC, GT, PAST>(p, whole_grid(), &first);
 }
 template <bool STATS, bool WRITE, bool KEEP, bool BANDS>
