@@ -56,6 +56,7 @@ struct WsCtx {
     const char* prof_name[kMaxKernels] = {};
     int64_t dgc_n_s = 0, dgc_k_s = 0;  // sizes of the last sidco_dgc call
     bool bad_cleared = false;  // the scatter kernels' bad-index flag has been initialised in this workspace
+    bool topk_clear = false;   // digit 0's histograms are clear: the workspace's last Top-k call left them so
     int64_t last_cap = 0;      // output capacity of the last compress call
     uint32_t* status_out = nullptr;  // device word that receives the status bits of every call (sidco_set_status_word)
     // shape of the last compress call: a call that repeats it may use the device's record of where the
@@ -83,6 +84,7 @@ struct WsCtx {
     {
         sig_d = 0;
         bad_cleared = false;
+        topk_clear = false;
         dgc_n_s = 0;
         batch_cur = -1;
         fit_nblocks = 0;
@@ -1236,6 +1238,14 @@ int sidco_read_diag_batched(void* stream, int t, sidco_diag* host_out)
     return SIDCO_OK;
 }
 
+static bool is_capturing(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // the default stream while another one captures
+    return true;
+}
+
 int sidco_topk(void* stream, const float* grad, float* residual, int64_t d, int64_t k, int32_t* out_idx, float* out_val,
                int32_t* out_count, float* out_kth)
 {
@@ -1283,6 +1293,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     p.hist0 = h->topk_hist;
     p.hist1 = p.hist0 + kTopkCopies * kTopkBins;
     p.hist2 = p.hist1 + kTopkBins;
+    p.clear0 = kTopkHist - kTopkLater;
     p.st = &h->topk;
     p.cnt = h->cnt[0];
     p.seg = (int2*)((char*)c.ws + head_bytes());
@@ -1304,9 +1315,13 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
         (void)hipEventRecord(c.ev[kn], s);
     };
     mark(nullptr);
-    launch_topk_zero(p, s);
-    ++kn;
-    mark("k_topk_zero");
+    // a captured call runs later, or never, and every time on whatever the calls before it left; a profile lists every kernel
+    const bool captured = is_capturing(s);
+    if (!c.topk_clear || captured || prof) {
+        launch_topk_zero(p, s);
+        ++kn;
+        mark("k_topk_zero");
+    }
     launch_topk_hist(p, s);
     ++kn;
     mark("k_topk_hist");
@@ -1326,6 +1341,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     mark("k_topk_final");
     c.prof_n = prof ? kn : 0;
     hipError_t e = hipGetLastError();
+    c.topk_clear = e == hipSuccess && (c.topk_clear || !captured);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return SIDCO_OK;
 }

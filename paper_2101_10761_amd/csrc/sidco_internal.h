@@ -153,6 +153,7 @@ constexpr int kTopkBins = 2048;  // digit 0 = magnitude bits 30..20; digits 1 an
 // line grid 12 M 106.7 -> 64.0, 60 M 380.1 -> 222.3.
 constexpr int kTopkCopies = 8;
 constexpr int kTopkHist = (kTopkCopies + 2) * kTopkBins;  // words of all digits
+constexpr int kTopkLater = 2 * kTopkBins;                 // those of digits 1 and 2
 
 struct TopkState {
     uint32_t prefix[3];            // bin of the k-th largest key in digit 0, 1, 2
@@ -173,6 +174,7 @@ struct TopkParams {
     int64_t d;
     int64_t k;
     int k_from_state;       // the last kernel takes k from st->k_eff (may be 0) instead of `k`
+    uint32_t clear0;        // words of hist0 that the last kernel clears for the next call
     uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
     uint32_t* hist0;        // [kTopkCopies][kTopkBins]
     uint32_t* hist1;        // [1024]

@@ -7,7 +7,8 @@
 // itself; NaN patterns lie above infinity and therefore count as the largest entries), most
 // significant digit first, digits of 11 + 10 + 10 bits.  Only the first digit needs the whole vector:
 //
-//   k_topk_zero      clears the three digit histograms and the output counters
+//   k_topk_zero      clears the histograms of digit 0, for a workspace's first call: the last kernel of a call leaves
+//                    them clear, and the first one clears what only later kernels use
 //   k_topk_hist      acc = g + residual (App. B.2), stored back; histogram of digit 0 of |acc|
 //                    (per-block histogram in LDS, merged into the global one with atomics on 2048
 //                    distinct addresses)                                         [12 B / element]
@@ -35,15 +36,7 @@ namespace sidco {
 __global__ __launch_bounds__(kBlock) void k_topk_zero(TopkParams p)
 {
     const uint32_t i = blockIdx.x * kBlock + threadIdx.x;
-    if (i < (uint32_t)kTopkHist) p.hist0[i] = 0;  // all digits, one piece
-    if (i == 0) {
-        p.st->gt_ctr = 0;
-        p.st->eq_ctr = 0;
-        p.st->prefix[0] = p.st->prefix[1] = p.st->prefix[2] = 0;
-        p.st->k_rem[0] = p.st->k_rem[1] = p.st->k_rem[2] = 0;
-        p.st->kth_key = 0;
-        p.st->k_eff = 0;
-    }
+    if (i < (uint32_t)(kTopkHist - kTopkLater)) p.hist0[i] = 0;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -72,6 +65,17 @@ __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
     constexpr bool WRITE = EC || GT != kGradF32;
     __shared__ uint32_t sh_hist[kTopkBins];
     for (int i = threadIdx.x; i < kTopkBins; i += kBlock) sh_hist[i] = 0;
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < kTopkLater; i += kBlock) p.hist1[i] = 0;  // digits 1 and 2, one piece
+        if (threadIdx.x == 0) {
+            p.st->gt_ctr = 0;
+            p.st->eq_ctr = 0;
+            p.st->prefix[0] = p.st->prefix[1] = p.st->prefix[2] = 0;
+            p.st->k_rem[0] = p.st->k_rem[1] = p.st->k_rem[2] = 0;
+            p.st->kth_key = 0;
+            p.st->k_eff = 0;
+        }
+    }
     __syncthreads();
     const uint32_t w = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     DigitHist h{sh_hist};
@@ -181,6 +185,8 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
     __shared__ uint32_t sh_gt[kWavesPerBlock], sh_eq[kWavesPerBlock];
     __shared__ unsigned long long sh_base[2];
     const ListGroup lists = load_lists(p);
+    // digit 0's histograms are done with: a kernel of its own before every call took 4.7 us
+    for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < p.clear0; i += gridDim.x * kBlock) p.hist0[i] = 0;
     const uint32_t b0 = p.st->prefix[0], b1 = p.st->prefix[1];
     const uint32_t k2 = p.st->k_rem[1];
     uint32_t b2, need;

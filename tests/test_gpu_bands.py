@@ -184,3 +184,33 @@ def test_replays_of_a_captured_call_with_bands(oracle):
             out = GpuCall(g, zero, 0, other).launch(side).collect(side)
             check_parity(oracle, g, zero, 0, other, out, label=f"eager {it}")
     sidco.sidco_release(stream=side)
+
+
+def test_top_k_captured_before_the_first_eager_call(oracle):
+    """A call that is captured and not yet run leaves nothing for the next call to rely on."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    d, k = 300_007, 500
+    dev = torch.device("cuda:0")
+    side = torch.cuda.Stream()
+    g = torch.from_numpy(_vector("student", d, 1)).to(dev)
+    out = [torch.zeros(k, dtype=torch.int32, device=dev), torch.zeros(k, dtype=torch.float32, device=dev),
+           torch.zeros(1, dtype=torch.int32, device=dev), torch.zeros(1, dtype=torch.float32, device=dev)]
+    ws = torch.full((sidco.sidco_workspace_bytes(d) // 4,), 3, dtype=torch.int32, device=dev).view(torch.uint8)
+    sidco.sidco_set_workspace(ws)
+    try:
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            graph.capture_begin()
+            sidco.sidco_topk(g, None, k, *out, stream=side)
+            graph.capture_end()
+        want = np.sort(np.abs(g.cpu().numpy()))[-k:]
+        for step in (lambda: sidco.sidco_topk(g, None, k, *out), graph.replay, lambda: sidco.sidco_topk(g, None, k, *out), graph.replay):
+            out[1].zero_()
+            torch.cuda.synchronize()
+            step()
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(np.sort(np.abs(out[1].cpu().numpy())), want)
+    finally:
+        sidco.sidco_set_workspace(None)
