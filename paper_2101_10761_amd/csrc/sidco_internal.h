@@ -56,6 +56,7 @@ struct FitRecord {
     double s, c, a, b;
 };
 
+constexpr int kBandsNone = 0, kBandsRecord = 1, kBandsUse = 2;
 // Bands of a first pass (see k_fit_bands): what it looks for besides the sums of the fit.  Stage m < M: magnitudes in
 // (lo[m-1], hi[m-1]] are listed, those above hi[m-1] summed up; the last stage: everything above lo[M-1] is listed.
 constexpr int kBandStages = 3;  // calls of 2 and 3 stages
@@ -142,7 +143,6 @@ struct Params {
     uint32_t* band_cnt;     // [kMaxWaves] lengths of the lists of a first pass with bands
     int2* band_seg;         // the lists themselves
 };
-constexpr int kBandsNone = 0, kBandsRecord = 1, kBandsUse = 2;
 
 // ---- exact Top-k comparator (sidco_topk.hip) ----
 constexpr int kTopkBins = 2048;  // digit 0 = magnitude bits 30..20; digits 1 and 2 have 1024 bins
@@ -162,7 +162,12 @@ struct TopkState {
     uint32_t k_eff;                // k when the device decides it (TopkParams::k_from_state)
     unsigned long long gt_ctr;     // output places reserved for entries above the k-th key
     unsigned long long eq_ctr;     // entries equal to the k-th key seen so far
+    // Survive from call to call: the first pass lists the entries whose key is `edge` or more (of this call; the next one;
+    // kNoEdge: none); the last k-th magnitude, and the share that the next one may fall below it
+    uint32_t edge, edge_next;
+    float last_kth, margin;
 };
+constexpr uint32_t kNoEdge = 0xffffffffu;
 
 struct TopkParams {
     const void* grad;       // d elements of type `gt`
@@ -175,6 +180,7 @@ struct TopkParams {
     int64_t k;
     int k_from_state;       // the last kernel takes k from st->k_eff (may be 0) instead of `k`
     uint32_t clear0;        // words of hist0 that the last kernel clears for the next call
+    int bands;              // kBands*: whether the call leaves an edge for the next one, and whether it has one itself
     uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
     uint32_t* hist0;        // [kTopkCopies][kTopkBins]
     uint32_t* hist1;        // [1024]

@@ -12,6 +12,7 @@
 //   k_topk_hist      acc = g + residual (App. B.2), stored back; histogram of digit 0 of |acc|
 //                    (per-block histogram in LDS, merged into the global one with atomics on 2048
 //                    distinct addresses)                                         [12 B / element]
+//                    A call that repeats a shape also lists the entries above an edge under the last k-th key
 //   k_topk_compact   prologue: every block finds the digit-0 bin b0 that holds the k-th largest key
 //                    (suffix sums of the histogram).  Body: entries with digit 0 >= b0 go to per-wave
 //                    lists; those with digit 0 == b0 are binned by digit 1       [4 B / element]
@@ -58,13 +59,44 @@ struct DigitHist {
     __device__ __forceinline__ void end() {}
 };
 
-template <bool EC, int GT>
+// The same behind a call of the same shape: also lists the entries at or above the edge that call left.
+struct DigitHistLists {
+    DigitHist h;
+    ListWriter lw;
+    uint32_t edge;
+    int lane;
+    uint32_t shift;
+    __device__ __forceinline__ void tile(f4 c, uint32_t t)
+    {
+        h.tile(c, t);
+        const int32_t i0 = (int32_t)(t * kTile + lane * 4 - shift);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) list_push(lw, mag_key(c[j]) >= edge, i0 + j, c[j], lane);
+        list_flush(lw, lane);
+    }
+    __device__ __forceinline__ void one(bool valid, float c, int64_t i)
+    {
+        h.one(valid, c, i);
+        list_push(lw, valid && mag_key(c) >= edge, (int32_t)i, c, lane);
+    }
+    __device__ __forceinline__ void end() { list_flush(lw, lane); }
+};
+
+// BANDS: behind a call of the same shape (see k_topk_compact); the residual goes past the caches then, as nothing reads
+// the vector again if the k-th magnitude falls where it is expected.
+template <bool EC, int GT, bool BANDS>
 __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
 {
     // a 16-bit gradient is widened as it is read, and acc is always stored then (every later kernel reads fp32)
     constexpr bool WRITE = EC || GT != kGradF32;
     __shared__ uint32_t sh_hist[kTopkBins];
     for (int i = threadIdx.x; i < kTopkBins; i += kBlock) sh_hist[i] = 0;
+    AccTile first;
+    uint32_t edge = kNoEdge;
+    if constexpr (BANDS) {
+        first = acc_first<EC, WRITE, GT, EC>(p, blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6), threadIdx.x & 63);
+        edge = __builtin_amdgcn_readfirstlane(p.st->edge_next);
+    }
     if (blockIdx.x == 0) {
         for (int i = threadIdx.x; i < kTopkLater; i += kBlock) p.hist1[i] = 0;  // digits 1 and 2, one piece
         if (threadIdx.x == 0) {
@@ -74,12 +106,35 @@ __global__ __launch_bounds__(kBlock) void k_topk_hist(TopkParams p)
             p.st->k_rem[0] = p.st->k_rem[1] = p.st->k_rem[2] = 0;
             p.st->kth_key = 0;
             p.st->k_eff = 0;
+            p.st->edge = edge;
         }
     }
     __syncthreads();
     const uint32_t w = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
     DigitHist h{sh_hist};
-    if (w < p.nwaves) acc_sweep<EC, WRITE, GT>(p, w, threadIdx.x & 63, h);
+    if constexpr (BANDS) {
+        __shared__ int2 ring[kWavesPerBlock][kRingSize];
+        if (edge != kNoEdge) {
+            DigitHistLists v;
+            v.h = h;
+            v.lw.list = p.seg + seg_begin(p, w < p.nwaves ? w : 0);
+            v.lw.ring = ring[threadIdx.x >> 6];
+            v.lw.run = v.lw.fill = 0;
+            v.edge = edge;
+            v.lane = lane;
+            v.shift = p.shift;
+            if (w < p.nwaves) {
+                acc_sweep<EC, WRITE, GT, EC>(p, w, lane, v, &first);
+                const uint32_t n = list_finish(v.lw, lane);
+                if (lane == 0) p.cnt[w] = n;
+            }
+        } else if (w < p.nwaves) {
+            acc_sweep<EC, WRITE, GT>(p, w, lane, h, &first);
+        }
+    } else if (w < p.nwaves) {
+        acc_sweep<EC, WRITE, GT>(p, w, lane, h);
+    }
     __syncthreads();
     merge_hist(sh_hist, p.hist0 + (blockIdx.x % kTopkCopies) * kTopkBins, kTopkBins);
 }
@@ -97,6 +152,11 @@ __device__ __forceinline__ void topk_emit(bool valid, float x, int32_t idx, uint
     if (valid && d0 == b0) atomicAdd(&sh_hist[(key >> 10) & 1023u], 1u);
 }
 
+// BANDS: the first pass has listed all entries from an edge on, below which the k-th magnitude of the last call was not,
+// less a margin.  If the boundary bin is not below the edge, the lists hold all that is asked for, and something more
+// that the kernels after this one pass over, and this kernel bins them instead of reading the vector; else it writes its
+// own lists in their place.
+template <bool BANDS>
 __global__ __launch_bounds__(kBlock, 4) void k_topk_compact(TopkParams p)
 {
     __shared__ uint32_t sh_hist[1024];
@@ -112,6 +172,15 @@ __global__ __launch_bounds__(kBlock, 4) void k_topk_compact(TopkParams p)
     const WaveTiles wt = wave_tiles(p, active ? w : 0);
     const DenseSweep ds = dense_sweep(p, wt, true, p.seg);
     f4 a = dense_load(ds, 0, lane);  // behind the histogram's loads, ahead of the search in it
+    const int2* list = p.seg + seg_begin(p, active ? w : 0);
+    int2 head[2];
+    uint32_t n_in = 0, edge = kNoEdge;
+    if constexpr (BANDS) {
+        head[0] = list[lane];  // a wave owns several tiles
+        head[1] = list[64 + lane];
+        n_in = active ? p.cnt[w] : 0u;
+        edge = p.st->edge;
+    }
     for (int i = threadIdx.x; i < 1024; i += kBlock) sh_hist[i] = 0;
     uint32_t b0, k1;
     pick_bin<kTopkBins / kBlock>(bins, (unsigned long long)p.k, sh_wave, sh_out, b0, k1);
@@ -119,7 +188,22 @@ __global__ __launch_bounds__(kBlock, 4) void k_topk_compact(TopkParams p)
         p.st->prefix[0] = b0;
         p.st->k_rem[0] = k1;
     }
-    if (active) {
+    if (BANDS && edge <= b0 << 20) {  // kNoEdge is above all bins
+        n_in = __builtin_amdgcn_readfirstlane(n_in);
+        auto entry = [&](bool in, int2 e) {
+            const uint32_t key = mag_key(__int_as_float(e.y));
+            if (in && key >> 20 == b0) atomicAdd(&sh_hist[(key >> 10) & 1023u], 1u);
+        };
+        entry((uint32_t)lane < n_in, head[0]);
+        entry((uint32_t)lane + 64 < n_in, head[1]);
+        for (uint32_t c = 128; c < n_in; c += 256) {
+            int2 e[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) e[u] = list[c + u * 64 + lane < n_in ? c + u * 64 + lane : 0u];
+#pragma unroll
+            for (uint32_t u = 0; u < 4; ++u) entry(c + u * 64 + lane < n_in, e[u]);
+        }
+    } else if (active) {
         ListWriter lw;
         lw.list = p.seg + seg_begin(p, w);
         lw.ring = ring[wib];
@@ -177,6 +261,22 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
     merge_hist(sh_hist, p.hist2, 1024);
 }
 
+// Edge for the next call: the bin that holds the k-th magnitude less a margin of at least 2 %, or one and a half times
+// its last change; none beyond 30 %, where the lists would grow long.
+__device__ void topk_record(const TopkParams& p, float kth)
+{
+    float m = 0.02f;
+    if (p.bands == kBandsUse) {
+        float moved = 0.02f + 1.5f * __builtin_fabsf(kth - p.st->last_kth) / p.st->last_kth;
+        if (!(moved <= 0.8f)) moved = 0.8f;
+        m = __builtin_fmaxf(moved, 0.87f * p.st->margin);
+    }
+    const float e = kth * (1.0f - m);
+    p.st->edge_next = m <= 0.3f && e > 0.0f && e < __builtin_inff() ? mag_key(e) & ~((1u << 20) - 1u) : kNoEdge;
+    p.st->last_kth = kth;
+    p.st->margin = m;
+}
+
 // k_topk_final: the k-th largest key, the output and the residual update
 __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
 {
@@ -227,6 +327,7 @@ __global__ __launch_bounds__(kBlock) void k_topk_final(TopkParams p)
             p.st->kth_key = kappa;
             *p.out_count = (int32_t)K;
             *p.out_kth = __int_as_float((int)kappa);
+            if (p.bands != kBandsNone) topk_record(p, __int_as_float((int)kappa));
         }
     }
     __syncthreads();
@@ -271,8 +372,12 @@ void launch_topk_zero(const TopkParams& p, hipStream_t s)
 template <int GT>
 static void launch_topk_hist_type(const TopkParams& p, hipStream_t s)
 {
-    if (p.residual) hipLaunchKernelGGL((k_topk_hist<true, GT>), dim3(p.nblocks), dim3(kBlock), 0, s, p);
-    else hipLaunchKernelGGL((k_topk_hist<false, GT>), dim3(p.nblocks), dim3(kBlock), 0, s, p);
+    const dim3 grid(p.nblocks), block(kBlock);
+    const bool bands = p.bands == kBandsUse;
+    if (p.residual && bands) hipLaunchKernelGGL((k_topk_hist<true, GT, true>), grid, block, 0, s, p);
+    else if (p.residual) hipLaunchKernelGGL((k_topk_hist<true, GT, false>), grid, block, 0, s, p);
+    else if (bands) hipLaunchKernelGGL((k_topk_hist<false, GT, true>), grid, block, 0, s, p);
+    else hipLaunchKernelGGL((k_topk_hist<false, GT, false>), grid, block, 0, s, p);
 }
 
 void launch_topk_hist(const TopkParams& p, hipStream_t s)
@@ -286,7 +391,8 @@ void launch_topk_hist(const TopkParams& p, hipStream_t s)
 
 void launch_topk_compact(const TopkParams& p, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_topk_compact, dim3(p.nblocks), dim3(kBlock), 0, s, p);
+    if (p.bands == kBandsUse) hipLaunchKernelGGL(k_topk_compact<true>, dim3(p.nblocks), dim3(kBlock), 0, s, p);
+    else hipLaunchKernelGGL(k_topk_compact<false>, dim3(p.nblocks), dim3(kBlock), 0, s, p);
 }
 
 void launch_topk_refine(const TopkParams& p, uint32_t grid, hipStream_t s)

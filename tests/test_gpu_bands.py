@@ -186,6 +186,20 @@ def test_replays_of_a_captured_call_with_bands(oracle):
     sidco.sidco_release(stream=side)
 
 
+@pytest.mark.parametrize("k,residual,offset", [(1, True, 0), (10_000, True, 3), (100_000, False, 1), (399_999, True, 2)])
+def test_top_k_behind_a_call_of_the_same_shape(oracle, k, residual, offset):
+    """The k-th magnitude where it was, far below it (the lists do not reach down), above it, among ties and zero."""
+    from test_gpu_topk import check_topk, run_topk
+    r = _vector("laplace", D, 1, 3e-4) if residual else None
+    few = np.zeros(D, np.float32)
+    few[::1000] = 1.0
+    for call, g in enumerate([_vector("student", D, 2), _vector("student", D, 3), _vector("laplace", D, 4, 2e-4),
+                              _vector("laplace", D, 5, 2e-4), _vector("student", D, 6), few, few, np.zeros(D, np.float32),
+                              _vector("student", D, 7), _vector("student", D, 8)]):
+        res = r if call < 5 or r is None else np.zeros(D, np.float32)
+        check_topk(oracle, g, res, k, run_topk(g, res, k, grad_offset=offset, res_offset=offset), label=f"call {call} k={k}")
+
+
 def test_top_k_captured_before_the_first_eager_call(oracle):
     """A call that is captured and not yet run leaves nothing for the next call to rely on."""
     import torch
