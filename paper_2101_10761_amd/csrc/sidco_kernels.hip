@@ -1353,7 +1353,9 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
 // lines that are written in part, and the pairs come in nearly ascending order, which the scatter that follows
 // profits from.  The set of pairs is deterministic, the order of the blocks' ranges is not.  Bound by HBM: at 138 M
 // elements and a ratio of 0.1 204 us for 1.22 GB, the scatter 243; k_final_lists took 235, the dense stage that wrote its
-// lists 30 more than one that only sums, and the scatter 270.
+// lists 30 more than one that only sums, and the scatter 270.  Loads that go past the caches want stores that do so as
+// well (all but those of a vector that the caches hold): a training step of 138 M, 3 stages, with ordinary and with such
+// stores 863 and 835 us, 90 M 576 and 547, 70 M, 2 stages 431 and 408.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_eta(Params p)
 {
@@ -1433,7 +1435,8 @@ __device__ __forceinline__ void select_body(const Params& p, uint32_t first, uin
         }
         if (p.residual) {
             if constexpr (WHOLE) {
-                *reinterpret_cast<f4*>(p.residual + i) = a[u];
+                if constexpr (KEEP) *reinterpret_cast<f4*>(p.residual + i) = a[u];
+                else __builtin_nontemporal_store(a[u], reinterpret_cast<f4*>(p.residual + i));
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
