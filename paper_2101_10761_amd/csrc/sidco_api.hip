@@ -76,6 +76,7 @@ struct WsCtx {
     int batch_cur = -1;
     double batch_delta = -1.0, batch_theta = -1.0;
     int batch_dist = -1, batch_M = 0, batch_n = 0;
+    bool batch_residual = false;
     std::vector<int64_t> batch_cap;
     uint32_t fit_nblocks = 0;  // grid, length and law of the last sidco_fit call
     int64_t fit_d = 0;
@@ -397,6 +398,30 @@ float band_width(const double* ratios, int M, int m)
     return (float)(w < most ? w : most);
 }
 
+// The same for a batch, whose bands serve its first stage alone, in the flat shape: that stage has to write lists, which
+// start where the second stage's threshold may fall, and an eighth of a chunk's elements is all there is room for
+// (kChunkList).  A call without and with bands, us: 66 M elements in 50 tensors, gamma, 2 stages, ratio 0.0001 182 and 147;
+// 25.6 M in 161, 2 stages, 0.01 82 and 77; 40 M in 50, 0.01 116 and 101, 0.02 129 and 116; 30 M in 300, GPD 91 and 84; 66 M
+// in 300, 3 stages, 0.0001 205 and 159.  Left without them: up to 15 M elements (12 M 50.2 and 51.8), fp16 and bf16 up to
+// 20 M (62.7 and 63.7); ratio 0.03 (40 M 145 and 161, 66 M 245 and 258), three stages at 0.01 (155 and 162), whose lists
+// overflow; the gamma law from 0.01 on, where the last stage often reads the vector again (313 and 339); three stages
+// whose second keeps more than 0.01 of short tensors, a few of which miss in most calls (50 M in 250, gamma 166 and 176; 25 M
+// in 280, GPD 92 and 95).  One tensor's miss is a block's sweep over its range, and what the call then loses: 40 M fp16
+// in 200 tensors of 64 elements up, GPD 106.7 and 108.5.
+constexpr int64_t kBandMinBatch = 20000000, kBandMinBatch16 = 25000000;
+constexpr double kBandMaxShareBatch = 0.04, kBandMaxGammaBatch = 0.005;
+constexpr double kBandMaxKeptShort = 0.01;
+constexpr int64_t kBandMinMean = 250000;
+bool batch_uses_bands(int64_t total, int n, int gt, int dist, const double* ratios, int M, double theta)
+{
+    if (total < (gt == kGradF32 ? kBandMinBatch : kBandMinBatch16) || !uses_bands(total, ratios, M, theta, false)) return false;
+    if (dist == kDistGamma && kept_ratio(ratios, M) > kBandMaxGammaBatch) return false;
+    if (list_fraction(ratios, 0, theta) > kMaterializeBelow) return false;
+    const double kept = kept_ratio(ratios, 2);
+    if (M > 2 && kept > kBandMaxKeptShort && total < (int64_t)n * kBandMinMean) return false;
+    return kBandShare + kept * exp(band_width(ratios, M, 1) * log(1.0 / kept)) <= kBandMaxShareBatch;
+}
+
 // the host's view of a call's device state
 void fill_diag(const DevState& st, int64_t cap, sidco_diag* host_out)
 {
@@ -477,6 +502,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     const bool banded = uses_bands(d, ratios, M, theta, select);
     p.bands = !banded ? kBandsNone : same_shape && c.sig_residual == (residual != nullptr) ? kBandsUse : kBandsRecord;
     for (int m = 0; banded && m < M; ++m) p.band_w[m] = m + 1 == M && select ? 0.0f : band_width(ratios, M, m);
+    p.band_max = kBandMaxWidth;
     p.band_part = h->band_part;
     p.band_cnt = h->band_cnt;
     p.band_seg = segbuf[0];  // free until a stage that could not use them writes lists of its own
@@ -1169,9 +1195,18 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     a.flat = (double*)a.seg[0];
     a.flat_gx = pl.flat_gx;
     a.flat_blocks = pl.blocks;
+    const int64_t total = offsets[n] - offsets[0];
+    const size_t nchunks = (size_t)pl.flat_gx * pl.blocks;
+    const size_t lists_at = (nchunks * (6 * sizeof(double) + sizeof(uint32_t)) + kAlign - 1) / kAlign * kAlign;
+    const bool banded = pl.flat_gx > 0 && lists_at + nchunks * kChunkList * sizeof(int2) <= seg &&
+                        batch_uses_bands(total, n, gt, dist, ratios, M, theta);
+    a.bands = !banded ? kBandsNone : same_shape && c.batch_residual == (residual != nullptr) ? kBandsUse : kBandsRecord;
+    for (int m = 0; banded && m < M; ++m) a.band_w[m] = band_width(ratios, M, m);
+    a.chunk_cnt = (uint32_t*)(a.flat + 6 * nchunks);
+    a.chunk_list = (int2*)((char*)a.flat + lists_at);
+    c.batch_residual = residual != nullptr;
     launch_fit_batched(a, residual != nullptr, pl.blocks, pl.flat_gx, pl.fold, s);
     const bool flat = pl.flat_gx > 0 && !pl.fold;
-    const int64_t total = offsets[n] - offsets[0];
     const bool much = residual && keeps_much(total, true, dist, ratios, M) &&
                       (M != 2 || (double)total * (4.0 + 8.0 * kept_ratio(ratios, M)) <= kKeepMaxBytesBatchTwo);
     bool lists = false, cand = false, reverse = true;

@@ -60,6 +60,10 @@ constexpr int kBandsNone = 0, kBandsRecord = 1, kBandsUse = 2;
 // Bands of a first pass (see k_fit_bands): what it looks for besides the sums of the fit.  Stage m < M: magnitudes in
 // (lo[m-1], hi[m-1]] are listed, those above hi[m-1] summed up; the last stage: everything above lo[M-1] is listed.
 constexpr int kBandStages = 3;  // calls of 2 and 3 stages
+// Widest band, of a stage before the last, that the next call goes by (see bands_record).  In a batch the lists have less
+// room (kChunkList), and with 0.15 for the first stage they overflowed on the first call after each rest (66 M elements in 50 tensors, gamma law, 3
+// stages, ratio 0.001: every tensor's).
+constexpr float kBandMaxWidth = 0.15f, kBandMaxWidthBatch = 0.08f;
 struct Bands {
     uint32_t on;  // stages of the calls they are for; 0: the edges mean nothing, the first pass only forms the fit's sums
     float lo[kBandStages], hi[kBandStages];
@@ -91,6 +95,7 @@ struct DevState {
     // stage m's threshold, and those before it, fell into their bands; the last call's thresholds and half-widths
     Bands band, band_next;
     uint32_t band_live[kBandStages + 1];
+    uint32_t band_over;     // a batch's first pass found more entries for a chunk's list than it has room for
     float band_eta[kBandStages], band_w[kBandStages];
 };
 
@@ -139,6 +144,7 @@ struct Params {
     uint32_t* status_out;   // NULL, or a device word that receives the call's status bits as well
     int bands;              // kBands*
     float band_w[kBandStages];  // least half-widths of the bands; the last stage's 0 if it reads no lists
+    float band_max;             // and the first one's widest
     double* band_part;      // [3 * (kBandStages - 1)][kMaxBlocks] sums of y, y^2 and 1 above each band's upper edge
     uint32_t* band_cnt;     // [kMaxWaves] lengths of the lists of a first pass with bands
     int2* band_seg;         // the lists themselves
@@ -288,7 +294,15 @@ struct BatchArgs {
     int use_hint, prev_cand;
     double* flat;           // partial sums of a flat first pass (see k_fit_flat_batched), chunks per block and blocks
     uint32_t flat_gx, flat_blocks;
+    int bands;              // as in Params, and if used: lengths of the chunks' lists, and the lists, kChunkList entries each
+    float band_w[kBandStages];
+    uint32_t* chunk_cnt;
+    int2* chunk_list;
 };
+// Room in a chunk's list: an eighth of its entries.  A stage's wave that takes the lists of its share of a block's chunks
+// never has more entries than the elements its own list has room for: of a block with n <= 8 waves of at most q + 1 and at
+// least q >= 1 tiles, chunks of 8 tiles shared out over the n, that is ceil((q + 1) / 8) lists of one tile's length.
+constexpr uint32_t kChunkList = kTile;
 
 void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s);
 void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, bool keep, uint32_t blocks, hipStream_t s);

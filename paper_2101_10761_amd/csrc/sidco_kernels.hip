@@ -210,6 +210,7 @@ struct PrologueLoads {
 struct BandEdges {
     bool live;
     float lo, hi;
+    float cand;  // > 0: what the stage's lists are to start from then (a batch's first stage)
 };
 
 template <bool FLAT = false>
@@ -368,6 +369,7 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
     // both false for a NaN threshold, which selects nothing anyway
     r.hit = band.live && r.eta >= band.lo && r.eta <= band.hi;
     r.lists_ok = auto_src && !band.live && r.eta >= g.list_eta;
+    if (r.hit && band.cand > 0.0f) r.eta_w = band.cand;
     if (auto_src && !r.lists_ok && !r.hit) status |= kStFallback;
     if (b.id == 0 && t == 0) {
         p.st->diag.eta[m - 1] = r.eta;
@@ -505,12 +507,13 @@ __device__ __forceinline__ void fit_reset_state(const Params& p)
 
 // one element through the guarded scalar path
 template <int DIST, bool EC, int GT>
-__device__ __forceinline__ void fit_one(const Params& p, int64_t i, double& s1, double& s2, double& sl, int& se)
+__device__ __forceinline__ float fit_one(const Params& p, int64_t i, double& s1, double& s2, double& sl, int& se)
 {
     float c = load_grad1<GT>(p.grad, i);
     if (EC) c = c + p.acc_w[i];
     if (fit_writes<EC, GT>()) p.acc_w[i] = c;
     fit_accum<DIST>(c, s1, s2, sl, se);
+    return c;
 }
 
 // the sums of one lane
@@ -652,7 +655,11 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
 // threshold's last relative change, which later calls let shrink by kBandDecay each: what moves by 10 % every third
 // call stays inside.  Beyond kBandMaxWidth the next call goes without bands - a tenth of the vector in lists costs what
 // the dense pass does - for 8 calls at most (kBandRest) once the thresholds keep still.
-constexpr float kBandDrift = 1.5f, kBandDecay = 0.87f, kBandMaxWidth = 0.15f, kBandRest = 0.4f;
+constexpr float kBandDrift = 1.5f, kBandDecay = 0.87f, kBandRest = 0.4f;
+// The least width for short vectors (in a batch), whose thresholds are noisy: 99 % of the changes from call to call,
+// relative and times the square root of the length, were within 4.4 (exponential) and 4 (GPD) for the first threshold and 6.6
+// and 7.8 for the second, 6 to 19 and 8 to 20 with the gamma law (12 M to 66 M elements in 50 to 300 tensors).
+constexpr float kBandNoise = 6.0f, kBandNoiseLater = 8.0f, kBandNoiseGamma = 3.0f;
 
 // One thread of the last stage's kernel: bands for the next call from this one's thresholds.
 __device__ void bands_record(const Params& p, float eta_last)
@@ -662,23 +669,28 @@ __device__ void bands_record(const Params& p, float eta_last)
     Bands b;
     b.on = (uint32_t)p.M;
     float below = 0.0f;
+    const bool over = p.bands == kBandsUse && st->band_over != 0;
+    st->band_over = 0;
 #pragma unroll
     for (int m = 0; m < kBandStages; ++m) {
         b.lo[m] = b.hi[m] = __builtin_inff();
         if (m >= p.M) continue;
         const bool last = m + 1 == p.M;
         const float eta = last ? eta_last : st->diag.eta[m];
-        float w = p.band_w[m];
+        const float spread = (m == 0 ? kBandNoise : kBandNoiseLater) * (p.dist == kDistGamma ? kBandNoiseGamma : 1.0f);
+        float w = spread / __builtin_sqrtf((float)p.d);
+        if (!last) w = __builtin_fminf(w, m == 0 ? kBandMaxWidthBatch : kBandMaxWidth);  // short vectors are a batch's
+        w = __builtin_fmaxf(p.band_w[m], w);
         if (p.bands == kBandsUse) {
             float moved = kBandDrift * __builtin_fabsf(eta - st->band_eta[m]) / st->band_eta[m];
-            if (!(moved <= kBandRest)) moved = kBandRest;
+            if (over || !(moved <= kBandRest)) moved = kBandRest;
             w = __builtin_fmaxf(w, __builtin_fmaxf(moved, kBandDecay * st->band_w[m]));
         }
         st->band_eta[m] = eta;
         st->band_w[m] = w;
         if (last && p.band_w[m] == 0.0f) continue;
         const float lo = __builtin_fmaxf(eta * (1.0f - w), below), hi = last ? __builtin_inff() : eta * (1.0f + w);
-        if (!((last || w <= kBandMaxWidth) && eta > lo && eta < hi)) b.on = 0;  // also a threshold that is 0 or not finite
+        if (!((last || w <= (m == 0 ? p.band_max : kBandMaxWidth)) && eta > lo && eta < hi)) b.on = 0;  // also a threshold that is 0 or not finite
         below = hi;
         b.lo[m] = lo;
         b.hi[m] = hi;
@@ -791,7 +803,7 @@ __device__ __forceinline__ BandEdges band_load(const Params& p)
 {
     if constexpr (!BANDS) return BandEdges{};
     const int m = p.stage;
-    return BandEdges{m == 1 ? p.st->band.on != 0 : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1]};
+    return BandEdges{m == 1 ? p.st->band.on != 0 : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1], 0.0f};
 }
 
 // What a block of the first pass summed up above the band of this stage, shifted to the stage's threshold below it.
@@ -973,14 +985,24 @@ __device__ __forceinline__ void band_sums(const int4* __restrict__ src4, uint32_
     }
 }
 
+// What a batch's first pass with bands left for a block of the first stage's kernel (see k_fit_flat_batched).
+struct ChunkPart {
+    const double* above;  // sums of y, y^2 and 1 above the band, `stride` apart, one of each for every chunk
+    uint32_t stride, n;   // chunks of the block
+    const uint32_t* cnt;
+    const int2* list;
+};
+
 // k_compact: a stage that reads the dense vector.  STATS: form the sums for the next stage's fit.
 // WRITE: append the entries above eta_w to this stage's lists (eta_w = eta_m, or a candidate threshold
 // above it); a stage whose candidates would still be a large fraction only counts and sums.  KEEP: with ordinary loads,
 // which leave the vector in the memory-side cache (see keeps_much in the host code).  BANDS: behind a first pass with
 // bands, which this stage may be able to do with; the head of the wave's list is then requested beside its first tile,
-// since waiting to know which of them it will be costs more than reading both.
-template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false, bool BANDS = false>
-__device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{})
+// since waiting to know which of them it will be costs more than reading both.  CHUNKS: the same for a batch, whose first
+// pass leaves a list for every chunk of the block's range.
+template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false, bool BANDS = false, bool CHUNKS = false>
+__device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{},
+                                             const ChunkPart& cp = ChunkPart{})
 {
     __shared__ double sh[kWavesPerBlock][4];
     __shared__ uint32_t sh_cnt[kWavesPerBlock];
@@ -1014,6 +1036,29 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         band = band_load<true>(p);
         if (band.live) q1 = src4[64 + lane];  // a wave owns several tiles
     }
+    constexpr int U = CHUNKS ? 8 : 1;  // lists a wave has requested when the threshold is known
+    int2 head[U];
+    uint32_t len[U];
+    uint32_t step = 1;
+    if constexpr (CHUNKS) {
+        step = p.nwaves - b.id * kWavesPerBlock;  // the block's waves that have a list to write to
+        if (step > kWavesPerBlock) step = kWavesPerBlock;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t x = wib + u * step;
+            const bool have = active && x < cp.n;
+            len[u] = have ? cp.cnt[x] : 0u;
+            head[u] = cp.list[(have ? x : 0u) * kChunkList + lane];
+        }
+        for (uint32_t x = threadIdx.x; x < cp.n; x += kBlock) {
+            above.y += cp.above[x];
+            above.yy += cp.above[x + cp.stride];
+            above.n += cp.above[x + 2 * (size_t)cp.stride];
+        }
+        band = band_load<true>(p);
+        band.live = band.live && p.st->band_over == 0;
+        band.cand = p.st->band.lo[1];
+    }
     if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
 
     const StageEta se = prologue_finish(p, b, false, g, sh, band);
@@ -1027,6 +1072,36 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
                 band_sums<4>(src4, seg_slots(p, w) / 2, __builtin_amdgcn_readfirstlane(n_in), q0, q1, lane, se.eta, band.hi,
                              ns, sy, syy);
             stage_epilogue<STATS, true>(p, b, lane, wib, ns, sy, syy, sh, sh_cnt, band_above_shift(above, band.hi, se.eta));
+            return;
+        }
+    }
+    if constexpr (CHUNKS) {
+        if (se.hit) {
+            if (active) {
+                ListWriter lw;
+                lw.list = p.seg_out + seg_begin(p, w);
+                lw.ring = ring[wib];
+                lw.run = lw.fill = 0;
+                auto entry = [&](bool in, int2 e) {
+                    const float x = __int_as_float(e.y), m = __builtin_fabsf(x);
+                    list_push(lw, in && m > se.eta_w, e.x, x, lane);
+                    emit<true, false>(in && m <= band.hi, x, 0, se.eta, se.eta, lw, lane, ns, sy, syy);
+                };
+                auto chunk = [&](uint32_t x, uint32_t n, int2 first) {
+                    n = __builtin_amdgcn_readfirstlane(n);
+                    entry((uint32_t)lane < n, first);
+                    for (uint32_t c = 64; c < n; c += 64) entry(c + lane < n, cp.list[x * kChunkList + c + lane]);
+                    list_flush(lw, lane);
+                };
+#pragma unroll
+                for (int u = 0; u < U; ++u) chunk(wib + u * step, len[u], head[u]);
+                for (uint32_t x = wib + U * step; x < cp.n; x += step) chunk(x, cp.cnt[x], cp.list[x * kChunkList + lane]);
+                const uint32_t n = list_finish(lw, lane);
+                if (lane == 0) p.cnt_out[w] = n;
+            }
+            above = band_above_shift(above, band.hi, se.eta);
+            ns += (uint32_t)wave_sum(above.n);  // counts: exact
+            stage_epilogue<STATS>(p, b, lane, wib, ns, sy + above.y, syy + above.yy, sh, sh_cnt);
             return;
         }
     }
@@ -1813,6 +1888,10 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.out_count = a.out_counts + ds.index;
     p.out_eta = a.out_etas + ds.index;
     p.out_cap = ds.out_cap;
+    p.bands = a.bands;
+#pragma unroll
+    for (int m = 0; m < kBandStages; ++m) p.band_w[m] = a.band_w[m];
+    p.band_max = kBandMaxWidthBatch;
     b.id = gb - (final_grid ? ds.first_final : ds.first_block);
     b.n = final_grid ? ds.nfinal : ds.nblocks;
     return p;
@@ -1865,10 +1944,18 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // ahead of its data; 161 tensors, 25.6 M elements, with one, two and four tiles per wave: 86.1, 84.1 and 87.5 us).  Blocks run in the order x first, then y: address
 // order.  Chunks past the end of a y's tiles leave zeros and exit (the host launches the flat shape only when few
 // are).
-template <int DIST, bool EC, int GT>
+// BANDS: behind a call of the same layout (see k_fit_bands).  Every chunk also leaves the sums above the first stage's band
+// and a list of the band's entries and of all that the second stage may ask for; the first stage's kernel writes its lists
+// from that, and the later stages are those of any batch.  The per-wave shape with bands was slower (66 M elements in 50
+// tensors 185 us for the pass against 128, 161 tensors, 25.6 M 72 against 52).  With ordinary loads and stores of the
+// residual: 66 M 167 us a call against 146, 40 M in 50 tensors 119 against 101, 25.6 M in 161 79 against 76.
+template <int DIST, bool EC, int GT, bool BANDS>
 __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
 {
-    __shared__ double sh[kFlatBlock / 64][4];
+    constexpr int Q = BANDS ? 6 : 3;  // sums
+    __shared__ double sh[kFlatBlock / 64][Q];
+    __shared__ int2 sh_list[BANDS ? kFlatBlock / 64 : 1][BANDS ? kFlatTiles * kTile : 1];
+    __shared__ uint32_t sh_len[kFlatBlock / 64];
     Blk b;
     const Params p = batch_params(a, false, b, blockIdx.y);
     uint32_t T0, T1;
@@ -1877,13 +1964,36 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
     const size_t stride = (size_t)gridDim.y * gridDim.x, slot = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
     if (b.id == 0 && blockIdx.x == 0 && threadIdx.x == 0) fit_reset_state(p);
     if (first >= T1) {  // the whole block
-        if (threadIdx.x < 3) a.flat[threadIdx.x * stride + slot] = 0.0;
+        if (threadIdx.x < Q) a.flat[threadIdx.x * stride + slot] = 0.0;
+        if (BANDS && threadIdx.x == 0) a.chunk_cnt[slot] = 0;
         return;
     }
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    double s1 = 0.0, s2 = 0.0, sl = 0.0;
+    double s1 = 0.0, s2 = 0.0, sl = 0.0, by = 0.0, byy = 0.0;
     int se = 0;
-    constexpr bool WRITE = fit_writes<EC, GT>();
+    uint32_t bn = 0, len = 0;
+    float lo = __builtin_inff(), hi = lo, cand = lo;  // nothing is above these
+    if constexpr (BANDS) {
+        const Bands e = p.st->band_next;
+        if (bands_usable(e, p.M)) {
+            lo = uniform(e.lo[0]);
+            hi = uniform(e.hi[0]);
+            cand = uniform(e.lo[1]);
+        }
+    }
+    // the wave together; idx is the element's
+    auto look = [&](float x, int32_t idx) {
+        const float m = __builtin_fabsf(x);
+        const bool above = m > hi, keep = (m > lo && !above) || m > cand;
+        bn += (uint32_t)__popcll(__ballot(above));
+        const double y = (double)(above ? m : hi) - (double)hi;
+        by += y;
+        if (DIST != kDistExp) byy = __builtin_fma(y, y, byy);
+        const unsigned long long mask = __ballot(keep);
+        if (keep) sh_list[wib][len + lane_prefix(mask)] = make_int2(idx, __float_as_int(x));
+        len += (uint32_t)__popcll(mask);
+    };
+    constexpr bool WRITE = fit_writes<EC, GT>(), PAST = EC && BANDS;
     auto add_up = [&](f4 c) {
         fit_accum<DIST>(c.x, s1, s2, sl, se);
         fit_accum<DIST>(c.y, s1, s2, sl, se);
@@ -1897,13 +2007,18 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
 #pragma unroll
         for (int u = 0; u < kFlatTiles; ++u) {
             c[u] = load_grad4<GT, WRITE>(p.grad, i + u * step);
-            if (EC) r[u] = *reinterpret_cast<const f4*>(p.acc_w + i + u * step);
+            if constexpr (EC && PAST) r[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.acc_w + i + u * step));
+            else if constexpr (EC) r[u] = *reinterpret_cast<const f4*>(p.acc_w + i + u * step);
         }
 #pragma unroll
         for (int u = 0; u < kFlatTiles; ++u) {
             if (EC) c[u] = c[u] + r[u];
-            if (WRITE) *reinterpret_cast<f4*>(p.acc_w + i + u * step) = c[u];
+            if (WRITE) acc_store<PAST>(p.acc_w, i + u * step, c[u]);
             add_up(c[u]);
+            if constexpr (BANDS) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) look(c[u][j], (int32_t)(i + u * step) + j);
+            }
         }
     } else {
         const uint32_t end = first + kFlatChunk < T1 ? first + kFlatChunk : T1;
@@ -1914,30 +2029,58 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
                 if (EC) c = c + *reinterpret_cast<const f4*>(p.acc_w + i);
                 if (WRITE) *reinterpret_cast<f4*>(p.acc_w + i) = c;
                 add_up(c);
+                if constexpr (BANDS) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) look(c[j], (int32_t)i + j);
+                }
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
-                    if (i >= 0 && i < p.d) fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+                    float x = 0.0f;  // above no edge
+                    if (i >= 0 && i < p.d) x = fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
+                    if constexpr (BANDS) look(x, (int32_t)i);
                 }
             }
         }
     }
-    double v[3] = {s1, s2, sl + (double)se};
+    double v[Q];
+    v[0] = s1;
+    v[1] = s2;
+    v[2] = sl + (double)se;
     v[0] = wave_sum(v[0]);
     v[1] = wave_sum(v[1]);
     v[2] = wave_sum(v[2]);
+    if constexpr (BANDS) {
+        v[3] = wave_sum(by);
+        v[4] = DIST != kDistExp ? wave_sum(byy) : 0.0;
+        v[5] = (double)bn;
+    }
     if (lane == 0) {
-        sh[wib][0] = v[0];
-        sh[wib][1] = v[1];
-        sh[wib][2] = v[2];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) sh[wib][q] = v[q];
+        sh_len[wib] = len;
     }
     __syncthreads();
-    if (threadIdx.x < 3) {
+    if (threadIdx.x < Q) {
         double tot = 0.0;
 #pragma unroll
         for (int w = 0; w < kFlatBlock / 64; ++w) tot += sh[w][threadIdx.x];
         a.flat[threadIdx.x * stride + slot] = tot;
+    }
+    if constexpr (BANDS) {
+        uint32_t at = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < kFlatBlock / 64; ++w) {
+            at += w < wib ? sh_len[w] : 0u;
+            all += sh_len[w];
+        }
+        int2* list = a.chunk_list + slot * kChunkList;
+        for (uint32_t q = lane; q < len && at + q < kChunkList; q += 64) list[at + q] = sh_list[wib][q];
+        if (threadIdx.x == 0) {
+            a.chunk_cnt[slot] = all < kChunkList ? all : kChunkList;
+            if (all > kChunkList) p.st->band_over = 1;
+        }
     }
 }
 
@@ -1968,7 +2111,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
     }
 }
 
-template <bool STATS, bool WRITE, bool FLAT, bool KEEP>
+template <bool STATS, bool WRITE, bool FLAT, bool KEEP, bool CHUNKS = false>
 __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
 {
     Blk b;
@@ -1979,7 +2122,16 @@ __global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
         fp.n = p.nblocks * a.flat_gx;
         fp.stride = a.flat_blocks * a.flat_gx;
     }
-    compact_body<STATS, WRITE, FLAT, KEEP>(p, b, fp);
+    ChunkPart cp = {};
+    if (CHUNKS) {
+        const size_t first = (size_t)blockIdx.x * a.flat_gx;
+        cp.n = a.flat_gx;
+        cp.stride = a.flat_blocks * a.flat_gx;
+        cp.above = a.flat + 3 * (size_t)cp.stride + first;
+        cp.cnt = a.chunk_cnt + first;
+        cp.list = a.chunk_list + first * kChunkList;
+    }
+    compact_body<STATS, WRITE, FLAT, KEEP, false, CHUNKS>(p, b, fp, cp);
 }
 __global__ __launch_bounds__(kBlock, 4) void k_lists_batched(BatchArgs a)
 {
@@ -2174,16 +2326,16 @@ void launch_gather(const Params& p, hipStream_t s)
 
 // batched: `blocks` is the sum of the vectors' grids (the last stage's own, smaller sum for launch_final).
 // `flat_gx` > 0: the first pass in the flat shape, `flat_gx` chunks of 8 tiles per block of the dense grid, with
-// a.flat holding 3 * flat_gx * blocks doubles; `fold`: a second kernel folds them.
-template <bool EC, int GT>
+// a.flat holding 3 * flat_gx * blocks doubles (6 with bands); `fold`: a second kernel folds them.
+template <bool EC, int GT, bool BANDS>
 static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
 {
     if (flat_gx > 0) {
         const dim3 grid(flat_gx, blocks), block(kFlatBlock);
         switch (a.dist) {
-            case kDistExp: hipLaunchKernelGGL((k_fit_flat_batched<kDistExp, EC, GT>), grid, block, 0, s, a); break;
-            case kDistGamma: hipLaunchKernelGGL((k_fit_flat_batched<kDistGamma, EC, GT>), grid, block, 0, s, a); break;
-            default: hipLaunchKernelGGL((k_fit_flat_batched<kDistGpd, EC, GT>), grid, block, 0, s, a); break;
+            case kDistExp: hipLaunchKernelGGL((k_fit_flat_batched<kDistExp, EC, GT, BANDS>), grid, block, 0, s, a); break;
+            case kDistGamma: hipLaunchKernelGGL((k_fit_flat_batched<kDistGamma, EC, GT, BANDS>), grid, block, 0, s, a); break;
+            default: hipLaunchKernelGGL((k_fit_flat_batched<kDistGpd, EC, GT, BANDS>), grid, block, 0, s, a); break;
         }
         if (fold)
             hipLaunchKernelGGL(k_fit_reduce_batched, dim3((blocks + kWavesPerBlock - 1) / kWavesPerBlock), dim3(kBlock), 0, s,
@@ -2201,8 +2353,11 @@ static void launch_fit_batched_as(const BatchArgs& a, uint32_t blocks, uint32_t 
 template <int GT>
 static void launch_fit_batched_type(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
 {
-    if (ec) launch_fit_batched_as<true, GT>(a, blocks, flat_gx, fold, s);
-    else launch_fit_batched_as<false, GT>(a, blocks, flat_gx, fold, s);
+    const bool bands = a.bands == kBandsUse;
+    if (ec && bands) launch_fit_batched_as<true, GT, true>(a, blocks, flat_gx, fold, s);
+    else if (ec) launch_fit_batched_as<true, GT, false>(a, blocks, flat_gx, fold, s);
+    else if (bands) launch_fit_batched_as<false, GT, true>(a, blocks, flat_gx, fold, s);
+    else launch_fit_batched_as<false, GT, false>(a, blocks, flat_gx, fold, s);
 }
 
 void launch_fit_batched(const BatchArgs& a, bool ec, uint32_t blocks, uint32_t flat_gx, bool fold, hipStream_t s)
@@ -2226,6 +2381,12 @@ static void launch_compact_batched_as(const BatchArgs& a, bool stats, bool write
 // `flat`: the first stage, behind a flat first pass whose partial sums have not been folded.  `keep`: ordinary loads
 void launch_compact_batched(const BatchArgs& a, bool stats, bool write, bool flat, bool keep, uint32_t blocks, hipStream_t s)
 {
+    if (a.bands == kBandsUse && a.stage == 1) {  // such a stage writes lists, and no call that keeps the vector has bands
+        const dim3 grid(blocks), block(kBlock);
+        if (flat) hipLaunchKernelGGL((k_compact_batched<true, true, true, false, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_compact_batched<true, true, false, false, true>), grid, block, 0, s, a);
+        return;
+    }
     if (flat && keep) launch_compact_batched_as<true, true>(a, stats, write, blocks, s);
     else if (flat) launch_compact_batched_as<true, false>(a, stats, write, blocks, s);
     else if (keep) launch_compact_batched_as<false, true>(a, stats, write, blocks, s);

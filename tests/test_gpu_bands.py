@@ -228,3 +228,31 @@ def test_top_k_captured_before_the_first_eager_call(oracle):
             np.testing.assert_array_equal(np.sort(np.abs(out[1].cpu().numpy())), want)
     finally:
         sidco.sidco_set_workspace(None)
+
+
+@pytest.mark.parametrize("kind,dist,stages,delta,residual", [("f32", 0, 2, 0.01, True), ("f32", 2, 3, 0.0002, True),
+                                                             ("f32", 1, 2, 0.001, False), ("bf16", 2, 2, 0.01, True),
+                                                             ("f16", 0, 3, 0.001, False)])
+def test_batches_behind_a_call_of_the_same_layout(oracle, kind, dist, stages, delta, residual):
+    """Tensors of a few entries to millions, with bands of their own; one of the long ones jumps in every other call."""
+    from test_gpu_batched import check_batched, run_batched
+    from test_gpu_typed import narrow
+    sizes = [1, 63, 257, 4_000_001, 64, 0, 300_007, 255, 33, 2_500_000, 2_048, 70_001, 511]
+    sizes[5] = 25_345_678 - sum(sizes)  # a batch takes bands from 20 M elements, 25 M of 16 bits
+    offsets = [0, *np.cumsum(sizes).tolist()]
+    r = _vector("student", offsets[-1], 1, 3e-3) if residual else None
+    for call in range(5):
+        g = _vector("student", offsets[-1], 50 + call, 1e-2)
+        if call % 2:
+            g[offsets[9]:offsets[10]] *= np.float32(3.0)
+        if call == 3:
+            g[offsets[3] + 100_000:offsets[3] + 104_000] = 1.0  # more in a chunk than its list has room for
+        if call == 4:
+            g[offsets[3] + 17] = np.inf
+            g[offsets[6]:offsets[7]] = 0.0
+        given = g
+        if kind != "f32":
+            given, g = narrow(g, kind)
+        results = run_batched(given, r, offsets, delta, dist, stages, base_offset=call % 4)
+        if call:
+            check_batched(oracle, g, r, offsets, delta, dist, stages, results, f"call {call} {kind} dist={dist} M={stages}")
