@@ -413,7 +413,12 @@ size_t sidco_workspace_bytes(int64_t d);
 /* Give the library a caller-owned device workspace (256-byte aligned) for the
  * current device instead of letting it allocate; NULL/0 returns to library
  * allocation.  The buffer must outlive every call that uses it; it serves the
- * calls of every stream, which therefore must not overlap.                    */
+ * calls of every stream, which therefore must not overlap.  Between two calls it
+ * may serve other ends: no result depends on what a call left in it, except that
+ * batched calls keep the tables of their layout there, the controller its count,
+ * sidco_scatter_check its flag, and the diagnostics calls report what they find.
+ * A caller that writes to it and makes batched calls sets it again afterwards
+ * (the library then takes nothing in it for known).                           */
 int sidco_set_workspace(void *device_ptr, size_t bytes);
 
 /* Make sure that the library's own workspace of `stream` on the current device

@@ -56,7 +56,7 @@ struct WsCtx {
     const char* prof_name[kMaxKernels] = {};
     int64_t dgc_n_s = 0, dgc_k_s = 0;  // sizes of the last sidco_dgc call
     bool bad_cleared = false;  // the scatter kernels' bad-index flag has been initialised in this workspace
-    bool topk_clear = false;   // digit 0's histograms are clear: the workspace's last Top-k call left them so
+    bool topk_clear = false;   // digit 0's histograms are clear: the last Top-k call left them so, and the memory is the library's
     int64_t topk_d = 0, topk_k = 0;  // shape of the last Top-k call
     bool topk_residual = false;
     int64_t last_cap = 0;      // output capacity of the last compress call
@@ -1366,7 +1366,8 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
         (void)hipEventRecord(c.ev[kn], s);
     };
     mark(nullptr);
-    // a captured call runs later, or never, and every time on whatever the calls before it left; a profile lists every kernel
+    // a captured call runs later, or never, and every time on whatever the calls before it left; the caller may write to a
+    // workspace of its own between two calls; a profile lists every kernel
     const bool captured = is_capturing(s);
     if (!c.topk_clear || captured || prof) {
         launch_topk_zero(p, s);
@@ -1392,7 +1393,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     mark("k_topk_final");
     c.prof_n = prof ? kn : 0;
     hipError_t e = hipGetLastError();
-    c.topk_clear = e == hipSuccess && (c.topk_clear || !captured);
+    c.topk_clear = e == hipSuccess && c.ws_owned && (c.topk_clear || !captured);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     return SIDCO_OK;
 }

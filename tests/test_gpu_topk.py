@@ -161,3 +161,21 @@ def test_edges_of_the_tile_split_off_the_line_grid(oracle, d, goff, roff):
     for residual in (r, None):
         out = run_topk(g16, residual, k, grad_offset=goff, res_offset=roff)
         check_topk(oracle, g16.to(torch.float32).numpy(), residual, k, out, label=f"bf16 d={d} offsets {goff},{roff} ec={residual is not None}")
+
+
+@pytest.mark.parametrize("d", [70_001, 10_000_037])
+def test_a_caller_workspace_written_between_calls(oracle, d):
+    """A workspace of the caller's may serve other ends between two calls: nothing a call left in it is relied upon."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    g, r = _inputs(d, 61)
+    k = d // 100
+    ws = torch.zeros(sidco.sidco_workspace_bytes(d) // 4, dtype=torch.int32, device="cuda:0")
+    sidco.sidco_set_workspace(ws)
+    try:
+        for call, left in enumerate([None, 1, -1, 0x3f800000, None]):
+            if left is not None:
+                ws.fill_(left)
+            check_topk(oracle, g, r, k, run_topk(g, r, k), label=f"d={d} call {call}, workspace words {left}")
+    finally:
+        sidco.sidco_set_workspace(None)
