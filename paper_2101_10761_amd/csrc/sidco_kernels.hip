@@ -684,7 +684,8 @@ __device__ void bands_record(const Params& p, float eta_last)
         if (p.bands == kBandsUse) {
             float moved = kBandDrift * __builtin_fabsf(eta - st->band_eta[m]) / st->band_eta[m];
             if (over || !(moved <= kBandRest)) moved = kBandRest;
-            w = __builtin_fmaxf(w, __builtin_fmaxf(moved, kBandDecay * st->band_w[m]));
+            // no more than a jump leaves: a captured call that has not run yet may have left no width at all
+            w = __builtin_fmaxf(w, __builtin_fmaxf(moved, kBandDecay * __builtin_fminf(st->band_w[m], kBandRest)));
         }
         st->band_eta[m] = eta;
         st->band_w[m] = w;

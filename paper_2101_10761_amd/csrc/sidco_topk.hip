@@ -269,7 +269,8 @@ __device__ void topk_record(const TopkParams& p, float kth)
     if (p.bands == kBandsUse) {
         float moved = 0.02f + 1.5f * __builtin_fabsf(kth - p.st->last_kth) / p.st->last_kth;
         if (!(moved <= 0.8f)) moved = 0.8f;
-        m = __builtin_fmaxf(moved, 0.87f * p.st->margin);
+        // no more than a jump leaves: a captured call that has not run yet may have left no margin at all
+        m = __builtin_fmaxf(moved, 0.87f * __builtin_fminf(p.st->margin, 0.8f));
     }
     const float e = kth * (1.0f - m);
     p.st->edge_next = m <= 0.3f && e > 0.0f && e < __builtin_inff() ? mag_key(e) & ~((1u << 20) - 1u) : kNoEdge;

@@ -20,7 +20,7 @@ class Workspace:
         size = sidco.sidco_workspace_bytes(d)
         seg = (d + 31 + 255) // 256 * 256 * 8
         self.ws = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
-        self.second = self.ws[size - seg:]
+        self.first, self.second = self.ws[size - 2 * seg:size - seg], self.ws[size - seg:]
 
     def __enter__(self):
         import paper_2101_10761_amd as sidco
@@ -36,6 +36,23 @@ class Workspace:
         self.second.fill_(0x5A)
         out = run_gpu(*args, **kw)
         return out, bool((self.second == 0x5A).all())
+
+    def run_topk(self, g, r, k, **kw):
+        """The same for the exact Top-k: whether its first pass listed entries.  Without, the lists hold no entry below the
+        bin (the upper 12 bits of a float) of the k-th magnitude, which `_above_a_bin` puts at the bin's lower end."""
+        import torch
+        from test_gpu_topk import run_topk
+        self.first.fill_(0x5A)
+        out = run_topk(g, r, k, **kw)
+        pairs = self.first.view(torch.int32).view(-1, 2)
+        values = pairs[pairs[:, 0] != 0x5A5A5A5A][:, 1].cpu().numpy().view(np.uint32) & 0x7FFFFFFF
+        return out, bool((values >> 20 < np.float32(out[3]).view(np.uint32) >> 20).any())
+
+
+def _above_a_bin(g, k):
+    """`g` scaled so that its k-th magnitude is 1 % above a bin of the radix select: an edge below it is in the bin before."""
+    kth = np.partition(np.abs(g), g.size - k)[g.size - k]
+    return (g * np.float32(1.01 * 2.0 ** -7 / kth)).astype(np.float32)
 
 
 def _vector(law, d, seed, scale=1e-3):
@@ -228,6 +245,46 @@ def test_top_k_captured_before_the_first_eager_call(oracle):
             np.testing.assert_array_equal(np.sort(np.abs(out[1].cpu().numpy())), want)
     finally:
         sidco.sidco_set_workspace(None)
+
+
+def test_a_record_that_was_never_written_is_forgotten(oracle):
+    """A call that was captured and not run is taken for one that left a record; what stands in its place may not keep the
+    calls after it from looking for their thresholds (nor the k-th magnitude) in the first pass for longer than a jump."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    from gpu_harness import GpuCall
+    ratios, zero = oracle.schedule(0.01, 2, 0.25), np.zeros(D, np.float32)
+    side = torch.cuda.Stream()
+    with Workspace(D) as ws:
+        ws.ws.fill_(0x7F)  # floats of 3e38
+        held = GpuCall(_vector("laplace", D, 1), zero, 0, ratios)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            graph.capture_begin()
+            held.launch(side)
+            graph.capture_end()
+        routes = []
+        for call in range(10):
+            g = _vector("laplace", D, 2 + call % 3)
+            out, without = ws.run(g, zero, 0, ratios)
+            routes.append(without)
+        check_parity(oracle, g, zero, 0, ratios, out, label="after the record")
+        assert not routes[0] and routes[-1]
+    k = 10_000
+    vectors = [_above_a_bin(_vector("student", D, 5 + call), k) for call in range(3)]
+    with Workspace(D) as ws:
+        ws.ws.fill_(0x7F)
+        g = torch.from_numpy(vectors[0]).to("cuda:0")
+        out = [torch.zeros(k, dtype=t, device="cuda:0") for t in (torch.int32, torch.float32)]
+        out += [torch.zeros(1, dtype=t, device="cuda:0") for t in (torch.int32, torch.float32)]
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            graph.capture_begin()
+            sidco.sidco_topk(g, None, k, *out, stream=side)
+            graph.capture_end()
+        routes = [ws.run_topk(vectors[call % 3], None, k)[1] for call in range(14)]
+        assert routes[-1]
 
 
 @pytest.mark.parametrize("kind,dist,stages,delta,residual", [("f32", 0, 2, 0.01, True), ("f32", 2, 3, 0.0002, True),
