@@ -92,9 +92,9 @@ extern "C" {
 #define SIDCO_ST_OVERFLOW     (1u << 5) /* more pairs selected than the output capacity; the excess
                                            stays in the residual and is not reported                  */
 #define SIDCO_ST_FALLBACK     (1u << 6) /* performance only: a stage found the lists of the stage before it,
-                                           or of the first pass, too short for its threshold and read
-                                           the dense vector again (see sidco_set_speculation); the
-                                           result is the same either way                              */
+                                           or those that the first pass of a call that repeats a shape
+                                           left, too short for its threshold and read the dense vector
+                                           (see sidco_set_speculation); the result is the same either way */
 
 /* Per-call diagnostics, filled on the device by the kernels of the last call. */
 typedef struct sidco_diag {

@@ -209,6 +209,7 @@ struct PrologueLoads {
 // has no upper edge.
 struct BandEdges {
     bool live;
+    bool over;   // they did, but the first pass found more entries than its lists have room for
     float lo, hi;
     float cand;  // > 0: what the stage's lists are to start from then (a batch's first stage)
 };
@@ -370,7 +371,7 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
     r.hit = band.live && r.eta >= band.lo && r.eta <= band.hi;
     r.lists_ok = auto_src && !band.live && r.eta >= g.list_eta;
     if (r.hit && band.cand > 0.0f) r.eta_w = band.cand;
-    if (auto_src && !r.lists_ok && !r.hit) status |= kStFallback;
+    if (!r.hit && (band.live || band.over || (auto_src && !r.lists_ok))) status |= kStFallback;
     if (b.id == 0 && t == 0) {
         p.st->diag.eta[m - 1] = r.eta;
         p.st->diag.n[m - 1] = (int64_t)n;
@@ -804,7 +805,8 @@ __device__ __forceinline__ BandEdges band_load(const Params& p)
 {
     if constexpr (!BANDS) return BandEdges{};
     const int m = p.stage;
-    return BandEdges{m == 1 ? p.st->band.on != 0 : p.st->band_live[m - 1] != 0, p.st->band.lo[m - 1], p.st->band.hi[m - 1], 0.0f};
+    return BandEdges{m == 1 ? p.st->band.on != 0 : p.st->band_live[m - 1] != 0, false, p.st->band.lo[m - 1], p.st->band.hi[m - 1],
+                     0.0f};
 }
 
 // What a block of the first pass summed up above the band of this stage, shifted to the stage's threshold below it.
@@ -1057,7 +1059,8 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
             above.n += cp.above[x + 2 * (size_t)cp.stride];
         }
         band = band_load<true>(p);
-        band.live = band.live && p.st->band_over == 0;
+        band.over = band.live && p.st->band_over != 0;
+        band.live = band.live && !band.over;
         band.cand = p.st->band.lo[1];
     }
     if constexpr (FLAT) flat_sums(fp, f, p.dist, g);

@@ -122,6 +122,40 @@ def test_buffers_of_different_scale_in_turn(oracle, stages):
             assert without == (call == 1)
 
 
+FALLBACK = 64
+
+
+@pytest.mark.parametrize("stages,select", [(2, False), (3, False), (3, True)])
+def test_a_first_threshold_outside_its_band_is_reported(oracle, stages, select):
+    """Also where the stages before a dense last one only sum."""
+    d = 62_000_003 if select else D
+    ratios, zero = [0.25, 0.64, 0.64] if select else oracle.schedule(0.01, stages, 0.25), np.zeros(d, np.float32)
+    g = _vector("laplace", d, 1)
+    status = []
+    for scale in (1.0, 1.0, 2.0):
+        x = g * np.float32(scale)
+        out = run_gpu(x, zero, 0, ratios, cap=d // 4)
+        status.append(out.status & FALLBACK)
+    check_parity(oracle, x, zero, 0, ratios, out, label=f"M={stages} select={select}")
+    assert status == [0, 0, FALLBACK]
+
+
+def test_a_batch_reports_the_tensors_outside_their_bands(oracle):
+    """A tensor whose first threshold jumps, and one with more candidates in a chunk of eight tiles than a list holds."""
+    from test_gpu_batched import check_batched, run_batched
+    sizes = [4_000_001, 2_500_000, 18_000_000]
+    offsets = [0, *np.cumsum(sizes).tolist()]
+    g = _vector("laplace", offsets[-1], 7, 1e-2)
+    jump, crowd = g.copy(), g.copy()
+    jump[offsets[1]:offsets[2]] *= np.float32(2.0)
+    crowd[offsets[2] + 50_000:offsets[2] + 54_000] = 0.05  # a little above the second threshold, the first one stays
+    for x, want in ((g, [0, 0, 0]), (g, [0, 0, 0]), (jump, [0, FALLBACK, 0]), (g, None), (crowd, [0, None, FALLBACK])):
+        results = run_batched(x, None, offsets, 0.01, 0, 2)
+        check_batched(oracle, x, None, offsets, 0.01, 0, 2, results, f"{want}")
+        if want:
+            assert all(w is None or r.status & FALLBACK == w for r, w in zip(results, want)), [r.status for r in results]
+
+
 @pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
 def test_special_inputs_behind_bands(oracle, kind):
     zero = np.zeros(D, np.float32)
