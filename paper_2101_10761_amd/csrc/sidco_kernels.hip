@@ -1022,6 +1022,13 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     PrologueLoads g = prologue_load<FLAT>(p, b, false);
     FlatLoads f;
     if constexpr (FLAT) f = flat_load(fp, p.dist);
+    BandEdges band = {};
+    if constexpr (CHUNKS) {
+        band = band_load<true>(p);
+        band.over = band.live && p.st->band_over != 0;
+        band.live = band.live && !band.over;
+        band.cand = p.st->band.lo[1];
+    }
     const DenseSweep d = dense_sweep(p, wt, p.reverse != 0, p.seg_out);
     f4 a[kAhead];
 #pragma unroll
@@ -1030,7 +1037,6 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     int4 q0 = {}, q1 = {};
     uint32_t n_in = 0;
     BandAbove above = {};
-    BandEdges band = {};
     if constexpr (BANDS) {
         src4 = reinterpret_cast<const int4*>(p.band_seg + seg_begin(p, active ? w : 0));
         q0 = src4[lane];
@@ -1039,29 +1045,30 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         band = band_load<true>(p);
         if (band.live) q1 = src4[64 + lane];  // a wave owns several tiles
     }
-    constexpr int U = CHUNKS ? 8 : 1;  // lists a wave has requested when the threshold is known
+    constexpr int U = CHUNKS ? 4 : 1;  // lists a wave has requested when the threshold is known
     int2 head[U];
     uint32_t len[U];
     uint32_t step = 1;
-    if constexpr (CHUNKS) {
-        step = p.nwaves - b.id * kWavesPerBlock;  // the block's waves that have a list to write to
-        if (step > kWavesPerBlock) step = kWavesPerBlock;
+    auto chunk_heads = [&](uint32_t x0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const uint32_t x = wib + u * step;
+            const uint32_t x = x0 + u * step;
             const bool have = active && x < cp.n;
             len[u] = have ? cp.cnt[x] : 0u;
             head[u] = cp.list[(have ? x : 0u) * kChunkList + lane];
         }
-        for (uint32_t x = threadIdx.x; x < cp.n; x += kBlock) {
-            above.y += cp.above[x];
-            above.yy += cp.above[x + cp.stride];
-            above.n += cp.above[x + 2 * (size_t)cp.stride];
+    };
+    if constexpr (CHUNKS) {
+        step = p.nwaves - b.id * kWavesPerBlock;  // the block's waves that have a list to write to
+        if (step > kWavesPerBlock) step = kWavesPerBlock;
+        if (band.live) {
+            chunk_heads(wib);
+            for (uint32_t x = threadIdx.x; x < cp.n; x += kBlock) {
+                above.y += cp.above[x];
+                above.yy += cp.above[x + cp.stride];
+                above.n += cp.above[x + 2 * (size_t)cp.stride];
+            }
         }
-        band = band_load<true>(p);
-        band.over = band.live && p.st->band_over != 0;
-        band.live = band.live && !band.over;
-        band.cand = p.st->band.lo[1];
     }
     if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
 
@@ -1097,9 +1104,13 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
                     for (uint32_t c = 64; c < n; c += 64) entry(c + lane < n, cp.list[x * kChunkList + c + lane]);
                     list_flush(lw, lane);
                 };
+                for (uint32_t x = wib;;) {
 #pragma unroll
-                for (int u = 0; u < U; ++u) chunk(wib + u * step, len[u], head[u]);
-                for (uint32_t x = wib + U * step; x < cp.n; x += step) chunk(x, cp.cnt[x], cp.list[x * kChunkList + lane]);
+                    for (int u = 0; u < U; ++u) chunk(x + u * step, len[u], head[u]);
+                    x += U * step;
+                    if (x >= cp.n) break;
+                    chunk_heads(x);
+                }
                 const uint32_t n = list_finish(lw, lane);
                 if (lane == 0) p.cnt_out[w] = n;
             }
@@ -1953,6 +1964,78 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // from that, and the later stages are those of any batch.  The per-wave shape with bands was slower (66 M elements in 50
 // tensors 185 us for the pass against 128, 161 tensors, 25.6 M 72 against 52).  With ordinary loads and stores of the
 // residual: 66 M 167 us a call against 146, 40 M in 50 tensors 119 against 101, 25.6 M in 161 79 against 76.
+// What a lane of such a pass looks for with bands.
+template <int DIST>
+struct FlatBands {
+    float lo, hi, cand;
+    double y = 0.0, yy = 0.0;
+    uint32_t n = 0, len = 0;
+    int2* list;  // the wave's, in LDS: room for all of its elements
+    // the wave together; idx is the element's
+    __device__ __forceinline__ void look(float x, int32_t idx)
+    {
+        const float m = __builtin_fabsf(x);
+        const bool above = m > hi, keep = (m > lo && !above) || m > cand;
+        n += (uint32_t)__popcll(__ballot(above));
+        const double v = (double)(above ? m : hi) - (double)hi;
+        y += v;
+        if (DIST != kDistExp) yy = __builtin_fma(v, v, yy);
+        const unsigned long long mask = __ballot(keep);
+        if (keep) list[len + lane_prefix(mask)] = make_int2(idx, __float_as_int(x));
+        len += (uint32_t)__popcll(mask);
+    }
+};
+
+// A wave's two tiles of the chunk that starts at tile `first`.
+template <int DIST, bool EC, int GT, bool LOOK>
+__device__ __forceinline__ void flat_chunk(const Params& p, uint32_t first, uint32_t T1, int wib, int lane, FitSums<DIST>& f,
+                                           FlatBands<DIST>& fb)
+{
+    constexpr bool WRITE = fit_writes<EC, GT>(), PAST = EC && LOOK;
+    if (first + kFlatChunk <= T1 && first + kFlatChunk <= p.nfull && (first > 0 || p.shift == 0)) {
+        AccTile a[kFlatTiles];
+        const size_t i = (size_t)(first + wib) * kTile + lane * 4 - p.shift;
+        constexpr size_t step = (size_t)(kFlatBlock / 64) * kTile;
+#pragma unroll
+        for (int u = 0; u < kFlatTiles; ++u) a[u] = acc_load<EC, WRITE, GT, PAST>(p, i + u * step);
+#pragma unroll
+        for (int u = 0; u < kFlatTiles; ++u) {
+            f4 c = a[u].g;
+            if (EC) c = c + a[u].r;
+            if (WRITE) acc_store<PAST>(p.acc_w, i + u * step, c);
+            f.tile(c, 0);
+            if constexpr (LOOK) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) fb.look(c[j], (int32_t)(i + u * step) + j);
+            }
+        }
+        return;
+    }
+    const uint32_t end = first + kFlatChunk < T1 ? first + kFlatChunk : T1;
+    for (uint32_t t = first + wib; t < end; t += kFlatBlock / 64) {
+        if (t < p.nfull && (t > 0 || p.shift == 0)) {
+            const size_t i = (size_t)t * kTile + lane * 4 - p.shift;
+            const AccTile a = acc_load<EC, WRITE, GT, false>(p, i);
+            f4 c = a.g;
+            if (EC) c = c + a.r;
+            if (WRITE) acc_store<false>(p.acc_w, i, c);
+            f.tile(c, 0);
+            if constexpr (LOOK) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) fb.look(c[j], (int32_t)i + j);
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
+                float x = 0.0f;  // above no edge
+                if (i >= 0 && i < p.d) x = fit_one<DIST, EC, GT>(p, i, f.s1, f.s2, f.sl, f.se);
+                if constexpr (LOOK) fb.look(x, (int32_t)i);
+            }
+        }
+    }
+}
+
 template <int DIST, bool EC, int GT, bool BANDS>
 __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
 {
@@ -1962,6 +2045,8 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
     __shared__ uint32_t sh_len[kFlatBlock / 64];
     Blk b;
     const Params p = batch_params(a, false, b, blockIdx.y);
+    Bands e;
+    if constexpr (BANDS) e = p.st->band_next;  // beside the descriptor, ahead of all stores: not a round trip of its own
     uint32_t T0, T1;
     block_tiles(p, b, T0, T1);
     const uint32_t first = T0 + blockIdx.x * kFlatChunk;
@@ -1973,97 +2058,34 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
         return;
     }
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    double s1 = 0.0, s2 = 0.0, sl = 0.0, by = 0.0, byy = 0.0;
-    int se = 0;
-    uint32_t bn = 0, len = 0;
-    float lo = __builtin_inff(), hi = lo, cand = lo;  // nothing is above these
+    FitSums<DIST> f;
+    FlatBands<DIST> fb;
     if constexpr (BANDS) {
-        const Bands e = p.st->band_next;
         if (bands_usable(e, p.M)) {
-            lo = uniform(e.lo[0]);
-            hi = uniform(e.hi[0]);
-            cand = uniform(e.lo[1]);
-        }
-    }
-    // the wave together; idx is the element's
-    auto look = [&](float x, int32_t idx) {
-        const float m = __builtin_fabsf(x);
-        const bool above = m > hi, keep = (m > lo && !above) || m > cand;
-        bn += (uint32_t)__popcll(__ballot(above));
-        const double y = (double)(above ? m : hi) - (double)hi;
-        by += y;
-        if (DIST != kDistExp) byy = __builtin_fma(y, y, byy);
-        const unsigned long long mask = __ballot(keep);
-        if (keep) sh_list[wib][len + lane_prefix(mask)] = make_int2(idx, __float_as_int(x));
-        len += (uint32_t)__popcll(mask);
-    };
-    constexpr bool WRITE = fit_writes<EC, GT>(), PAST = EC && BANDS;
-    auto add_up = [&](f4 c) {
-        fit_accum<DIST>(c.x, s1, s2, sl, se);
-        fit_accum<DIST>(c.y, s1, s2, sl, se);
-        fit_accum<DIST>(c.z, s1, s2, sl, se);
-        fit_accum<DIST>(c.w, s1, s2, sl, se);
-    };
-    if (first + kFlatChunk <= T1 && first + kFlatChunk <= p.nfull && (first > 0 || p.shift == 0)) {
-        f4 c[kFlatTiles], r[kFlatTiles];
-        const size_t i = (size_t)(first + wib) * kTile + lane * 4 - p.shift;
-        constexpr size_t step = (size_t)(kFlatBlock / 64) * kTile;
-#pragma unroll
-        for (int u = 0; u < kFlatTiles; ++u) {
-            c[u] = load_grad4<GT, WRITE>(p.grad, i + u * step);
-            if constexpr (EC && PAST) r[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(p.acc_w + i + u * step));
-            else if constexpr (EC) r[u] = *reinterpret_cast<const f4*>(p.acc_w + i + u * step);
-        }
-#pragma unroll
-        for (int u = 0; u < kFlatTiles; ++u) {
-            if (EC) c[u] = c[u] + r[u];
-            if (WRITE) acc_store<PAST>(p.acc_w, i + u * step, c[u]);
-            add_up(c[u]);
-            if constexpr (BANDS) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) look(c[u][j], (int32_t)(i + u * step) + j);
-            }
+            fb.lo = uniform(e.lo[0]);
+            fb.hi = uniform(e.hi[0]);
+            fb.cand = uniform(e.lo[1]);
+            fb.list = sh_list[wib];
+            flat_chunk<DIST, EC, GT, true>(p, first, T1, wib, lane, f, fb);
+        } else {
+            flat_chunk<DIST, EC, GT, false>(p, first, T1, wib, lane, f, fb);
         }
     } else {
-        const uint32_t end = first + kFlatChunk < T1 ? first + kFlatChunk : T1;
-        for (uint32_t t = first + wib; t < end; t += kFlatBlock / 64) {
-            if (t < p.nfull && (t > 0 || p.shift == 0)) {
-                const size_t i = (size_t)t * kTile + lane * 4 - p.shift;
-                f4 c = load_grad4<GT, WRITE>(p.grad, i);
-                if (EC) c = c + *reinterpret_cast<const f4*>(p.acc_w + i);
-                if (WRITE) *reinterpret_cast<f4*>(p.acc_w + i) = c;
-                add_up(c);
-                if constexpr (BANDS) {
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) look(c[j], (int32_t)i + j);
-                }
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
-                    float x = 0.0f;  // above no edge
-                    if (i >= 0 && i < p.d) x = fit_one<DIST, EC, GT>(p, i, s1, s2, sl, se);
-                    if constexpr (BANDS) look(x, (int32_t)i);
-                }
-            }
-        }
+        flat_chunk<DIST, EC, GT, false>(p, first, T1, wib, lane, f, fb);
     }
     double v[Q];
-    v[0] = s1;
-    v[1] = s2;
-    v[2] = sl + (double)se;
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    v[2] = wave_sum(v[2]);
+    v[0] = wave_sum(f.s1);
+    v[1] = wave_sum(f.s2);
+    v[2] = wave_sum(f.sl + (double)f.se);
     if constexpr (BANDS) {
-        v[3] = wave_sum(by);
-        v[4] = DIST != kDistExp ? wave_sum(byy) : 0.0;
-        v[5] = (double)bn;
+        v[3] = wave_sum(fb.y);
+        v[4] = DIST != kDistExp ? wave_sum(fb.yy) : 0.0;
+        v[5] = (double)fb.n;
     }
     if (lane == 0) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) sh[wib][q] = v[q];
-        sh_len[wib] = len;
+        sh_len[wib] = fb.len;
     }
     __syncthreads();
     if (threadIdx.x < Q) {
@@ -2080,7 +2102,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
             all += sh_len[w];
         }
         int2* list = a.chunk_list + slot * kChunkList;
-        for (uint32_t q = lane; q < len && at + q < kChunkList; q += 64) list[at + q] = sh_list[wib][q];
+        for (uint32_t q = lane; q < fb.len && at + q < kChunkList; q += 64) list[at + q] = sh_list[wib][q];
         if (threadIdx.x == 0) {
             a.chunk_cnt[slot] = all < kChunkList ? all : kChunkList;
             if (all > kChunkList) p.st->band_over = 1;
@@ -2116,7 +2138,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
 }
 
 template <bool STATS, bool WRITE, bool FLAT, bool KEEP, bool CHUNKS = false>
-__global__ __launch_bounds__(kBlock, 4) void k_compact_batched(BatchArgs a)
+__global__ __launch_bounds__(kBlock, CHUNKS ? 6 : 4) void k_compact_batched(BatchArgs a)
 {
     Blk b;
     const Params p = batch_params(a, false, b);

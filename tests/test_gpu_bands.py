@@ -156,6 +156,23 @@ def test_a_batch_reports_the_tensors_outside_their_bands(oracle):
             assert all(w is None or r.status & FALLBACK == w for r, w in zip(results, want)), [r.status for r in results]
 
 
+@pytest.mark.parametrize("dist,stages,delta", [(0, 2, 0.005), (2, 3, 0.0002), (1, 2, 0.001)])
+def test_long_batches_behind_a_call_of_the_same_layout(oracle, dist, stages, delta):
+    """More chunks for each of a block's waves than it asks for at once; then thresholds that jump and bands that rest."""
+    from test_gpu_batched import check_batched, run_batched
+    sizes = [300, 38_000_001, 4_097, 12_000_000, 64]
+    offsets = [0, *np.cumsum(sizes).tolist()]
+    g = _vector("laplace", offsets[-1], 3, 1e-3)
+    status = []
+    for call, scale in enumerate((1.0, 1.0, 1.0, 1.7, 1.7)):
+        x = g * np.float32(scale)
+        results = run_batched(x, None, offsets, delta, dist, stages)
+        status.append([results[t].status & FALLBACK for t in (1, 3)])
+        if call in (1, 3, 4):
+            check_batched(oracle, x, None, offsets, delta, dist, stages, results, f"call {call} dist={dist} M={stages}")
+    assert status[1] == status[2] == [0, 0] and status[3] == [FALLBACK, FALLBACK], status
+
+
 @pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
 def test_special_inputs_behind_bands(oracle, kind):
     zero = np.zeros(D, np.float32)
