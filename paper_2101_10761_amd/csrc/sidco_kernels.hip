@@ -1002,7 +1002,8 @@ struct ChunkPart {
 // which leave the vector in the memory-side cache (see keeps_much in the host code).  BANDS: behind a first pass with
 // bands, which this stage may be able to do with; the head of the wave's list is then requested beside its first tile,
 // since waiting to know which of them it will be costs more than reading both.  CHUNKS: the same for a batch, whose first
-// pass leaves a list for every chunk of the block's range.
+// pass leaves a list for every chunk of the block's range; their heads are requested only if the tensor has bands, which
+// the wave knows by the time its first tiles are on their way.
 template <bool STATS, bool WRITE, bool FLAT = false, bool KEEP = false, bool BANDS = false, bool CHUNKS = false>
 __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatPart& fp = FlatPart{},
                                              const ChunkPart& cp = ChunkPart{})
@@ -1045,7 +1046,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         band = band_load<true>(p);
         if (band.live) q1 = src4[64 + lane];  // a wave owns several tiles
     }
-    constexpr int U = CHUNKS ? 4 : 1;  // lists a wave has requested when the threshold is known
+    constexpr int U = CHUNKS ? 4 : 1;  // lists a wave requests at once, the first ones before the threshold is known
     int2 head[U];
     uint32_t len[U];
     uint32_t step = 1;
@@ -1963,7 +1964,10 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // and a list of the band's entries and of all that the second stage may ask for; the first stage's kernel writes its lists
 // from that, and the later stages are those of any batch.  The per-wave shape with bands was slower (66 M elements in 50
 // tensors 185 us for the pass against 128, 161 tensors, 25.6 M 72 against 52).  With ordinary loads and stores of the
-// residual: 66 M 167 us a call against 146, 40 M in 50 tensors 119 against 101, 25.6 M in 161 79 against 76.
+// residual: 66 M 167 us a call against 146, 40 M in 50 tensors 119 against 101, 25.6 M in 161 79 against 76.  A tensor that
+// has no bands (yet, or while its thresholds jump) is read again by the first stage: its blocks take the plain pass, whose
+// residual stays in the caches.
+
 // What a lane of such a pass looks for with bands.
 template <int DIST>
 struct FlatBands {
@@ -2137,6 +2141,10 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
     }
 }
 
+// CHUNKS: three blocks per CU, as without.  A batch's grid is up to 1024 blocks; with the 104 registers of eight lists asked
+// for at once 512 of them ran first and the rest after them.  With that, and the heads requested in any case, 25.6 M
+// elements in 161 tensors took 40.5 us and now 26.6 where the thresholds jump (15.0 and 12.7 where they keep still), 66 M in
+// 50 87.7 and 63.1 (20.0 and 16.4); without bands 26.5 and 63.5.
 template <bool STATS, bool WRITE, bool FLAT, bool KEEP, bool CHUNKS = false>
 __global__ __launch_bounds__(kBlock, CHUNKS ? 6 : 4) void k_compact_batched(BatchArgs a)
 {
