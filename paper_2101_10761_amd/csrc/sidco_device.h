@@ -47,6 +47,13 @@ __device__ __forceinline__ T wave_total(T v)
 __device__ __forceinline__ double wave_sum(double v) { return wave_total(v); }
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) { return wave_total(v); }
 
+__device__ __forceinline__ Calm calm_after(Calm c, bool jumped)
+{
+    if (jumped) return Calm{0, c.run};
+    return Calm{c.run < kCalmMost ? c.run + 1 : kCalmMost, c.last};
+}
+__device__ __forceinline__ bool calm_enough(Calm c) { return c.run >= (c.last >= kCalmRun ? 1u : kCalmMost); }
+
 // Four consecutive gradient elements as fp32, from element e on: one 16-byte load of an fp32 buffer, one 8-byte
 // load of an fp16 / bf16 buffer (widening either type is exact).  The address need only be aligned for one
 // element: tiles follow the alignment of the accumulated vector, the gradient's may be another one (the load

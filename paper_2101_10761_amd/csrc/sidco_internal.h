@@ -69,6 +69,17 @@ struct Bands {
     float lo[kBandStages], hi[kBandStages];
 };
 
+// Calls since the thresholds last jumped, and calls between the two jumps before.  After a jump the next call goes
+// without bands (or Top-k's edge); after one that came less than kCalmRun calls behind the one before it so do
+// kCalmMost calls: bands that serve two calls and then miss gain nothing.  A training step, us, without bands, with eight
+// calls without them after any jump, and so.  Jumps in every 8th call: 25.6 M elements, 3 stages 84.4, 86.5 and 79.3; 40 M,
+// ratio 0.01 116.6, 118.7 and 110.8; 100 M 258, 273 and 243; 138 M 515, 535 and 445; 66 M in 50 tensors 187, 190 and 161.
+// In every 5th, without and so: 25.6 M 84.6 and 81.6, 40 M 117 and 115, 138 M 515 and 470, 161 tensors 84.2 and 84.3.
+constexpr uint32_t kCalmRun = 4, kCalmMost = 8;
+struct Calm {
+    uint32_t run, last;
+};
+
 // Device-resident state of one call.  Stage m's kernel reads the entries stage m-1 wrote and
 // writes its own, so no entry is read and written inside one kernel.
 struct DevState {
@@ -97,6 +108,7 @@ struct DevState {
     uint32_t band_live[kBandStages + 1];
     uint32_t band_over;     // a batch's first pass found more entries for a chunk's list than it has room for
     float band_eta[kBandStages], band_w[kBandStages];
+    Calm band_calm;
 };
 
 // Kernel arguments (passed by value).
@@ -172,6 +184,7 @@ struct TopkState {
     // kNoEdge: none); the last k-th magnitude, and the share that the next one may fall below it
     uint32_t edge, edge_next;
     float last_kth, margin;
+    Calm calm;
 };
 constexpr uint32_t kNoEdge = 0xffffffffu;
 
@@ -347,9 +360,10 @@ constexpr int kSmallBlock = 1024;
 constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
 void launch_small(const Params& p, hipStream_t s);
 void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s);
-// A call that repeats a shape but has no bands (its thresholds jump) sweeps past the caches from this length on, where
-// they hold less than half of the vector anyway.
-constexpr int64_t kBandPastMinD = 100000000;
+// A call that repeats a shape but has no bands (its thresholds jump) sweeps past the caches from this length on.  A training
+// step of that kind with ordinary accesses and past the caches, us: 100 M elements, 2 stages 276 and 284, 120 M 339 and 342,
+// 138 M, 3 stages, ratio 0.01 559 and 541, 0.1 965 and 943.
+constexpr int64_t kBandPastMinD = 130000000;
 void launch_fit_bands(const Params& p, hipStream_t s);
 void launch_compact(const Params& p, bool stats, bool write, bool keep, hipStream_t s);
 void launch_lists(const Params& p, hipStream_t s);

@@ -654,9 +654,10 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
 // ---------------------------------------------------------------------------------------------
 // A band's half-width is the least one (see band_width in the host code) or, where that is more, kBandDrift times the
 // threshold's last relative change, which later calls let shrink by kBandDecay each: what moves by 10 % every third
-// call stays inside.  Beyond kBandMaxWidth the next call goes without bands - a tenth of the vector in lists costs what
-// the dense pass does - for 8 calls at most (kBandRest) once the thresholds keep still.
-constexpr float kBandDrift = 1.5f, kBandDecay = 0.87f, kBandRest = 0.4f;
+// call stays inside.  What would take more than kBandMaxWidth - a tenth of the vector in lists costs what the dense pass
+// does, kBandLastWidest for the last stage, whose band has no upper edge - is a jump: the next call goes without bands (see
+// Calm), and the widths do not grow by it.
+constexpr float kBandDrift = 1.5f, kBandDecay = 0.87f, kBandLastWidest = 0.4f;
 // The least width for short vectors (in a batch), whose thresholds are noisy: 99 % of the changes from call to call,
 // relative and times the square root of the length, were within 4.4 (exponential) and 4 (GPD) for the first threshold and 6.6
 // and 7.8 for the second, 6 to 19 and 8 to 20 with the gamma law (12 M to 66 M elements in 50 to 300 tensors).
@@ -672,31 +673,47 @@ __device__ void bands_record(const Params& p, float eta_last)
     float below = 0.0f;
     const bool over = p.bands == kBandsUse && st->band_over != 0;
     st->band_over = 0;
+    float eta_now[kBandStages], moved[kBandStages], most[kBandStages];
+    bool jumped = false;
+#pragma unroll
+    for (int m = 0; m < kBandStages; ++m) {
+        if (m >= p.M) continue;
+        const bool last = m + 1 == p.M;
+        eta_now[m] = last ? eta_last : st->diag.eta[m];
+        most[m] = last ? kBandLastWidest : m == 0 ? p.band_max : kBandMaxWidth;
+        moved[m] = 0.0f;
+        if (p.bands == kBandsUse) moved[m] = kBandDrift * __builtin_fabsf(eta_now[m] - st->band_eta[m]) / st->band_eta[m];
+        if (!(moved[m] <= most[m])) jumped = true;  // also what is not a number
+    }
 #pragma unroll
     for (int m = 0; m < kBandStages; ++m) {
         b.lo[m] = b.hi[m] = __builtin_inff();
         if (m >= p.M) continue;
         const bool last = m + 1 == p.M;
-        const float eta = last ? eta_last : st->diag.eta[m];
+        const float eta = eta_now[m];
         const float spread = (m == 0 ? kBandNoise : kBandNoiseLater) * (p.dist == kDistGamma ? kBandNoiseGamma : 1.0f);
         float w = spread / __builtin_sqrtf((float)p.d);
         if (!last) w = __builtin_fminf(w, m == 0 ? kBandMaxWidthBatch : kBandMaxWidth);  // short vectors are a batch's
         w = __builtin_fmaxf(p.band_w[m], w);
         if (p.bands == kBandsUse) {
-            float moved = kBandDrift * __builtin_fabsf(eta - st->band_eta[m]) / st->band_eta[m];
-            if (over || !(moved <= kBandRest)) moved = kBandRest;
-            // no more than a jump leaves: a captured call that has not run yet may have left no width at all
-            w = __builtin_fmaxf(w, __builtin_fmaxf(moved, kBandDecay * __builtin_fminf(st->band_w[m], kBandRest)));
+            if (!jumped) w = __builtin_fmaxf(w, moved[m]);
+            // a captured call that has not run yet may have left no width at all
+            w = __builtin_fmaxf(w, kBandDecay * __builtin_fminf(st->band_w[m], most[m]));
         }
         st->band_eta[m] = eta;
         st->band_w[m] = w;
         if (last && p.band_w[m] == 0.0f) continue;
         const float lo = __builtin_fmaxf(eta * (1.0f - w), below), hi = last ? __builtin_inff() : eta * (1.0f + w);
-        if (!((last || w <= (m == 0 ? p.band_max : kBandMaxWidth)) && eta > lo && eta < hi)) b.on = 0;  // also a threshold that is 0 or not finite
+        if (!((last || w <= most[m]) && eta > lo && eta < hi)) b.on = 0;  // also a threshold that is 0 or not finite
         below = hi;
         b.lo[m] = lo;
         b.hi[m] = hi;
     }
+    Calm calm = {kCalmMost, kCalmMost};
+    if (p.bands == kBandsUse) calm = calm_after(st->band_calm, jumped);
+    if (over) calm = Calm{0, 0};
+    if (!calm_enough(calm)) b.on = 0;
+    st->band_calm = calm;
     st->band_next = b;
 }
 

@@ -261,21 +261,26 @@ __global__ __launch_bounds__(kBlock) void k_topk_refine(TopkParams p)
     merge_hist(sh_hist, p.hist2, 1024);
 }
 
-// Edge for the next call: the bin that holds the k-th magnitude less a margin of at least 2 %, or one and a half times
-// its last change; none beyond 30 %, where the lists would grow long.
+// Edge for the next call: the k-th magnitude less a margin of 2 % and one and a half times its last change (which later
+// calls let shrink by 13 % each), down to the start of its bin of digit 0 (an eighth of an octave at most).  Beyond
+// kTopkMargin the lists would grow long: that is a jump, and the next call goes without an edge (see Calm).
+constexpr float kTopkMargin = 0.3f;
 __device__ void topk_record(const TopkParams& p, float kth)
 {
     float m = 0.02f;
+    Calm calm = {kCalmMost, kCalmMost};
     if (p.bands == kBandsUse) {
-        float moved = 0.02f + 1.5f * __builtin_fabsf(kth - p.st->last_kth) / p.st->last_kth;
-        if (!(moved <= 0.8f)) moved = 0.8f;
-        // no more than a jump leaves: a captured call that has not run yet may have left no margin at all
-        m = __builtin_fmaxf(moved, 0.87f * __builtin_fminf(p.st->margin, 0.8f));
+        const float moved = 0.02f + 1.5f * __builtin_fabsf(kth - p.st->last_kth) / p.st->last_kth;
+        if (moved <= kTopkMargin) m = moved;
+        // a captured call that has not run yet may have left no margin at all
+        m = __builtin_fmaxf(m, 0.87f * __builtin_fminf(p.st->margin, kTopkMargin));
+        calm = calm_after(p.st->calm, !(moved <= kTopkMargin));
     }
     const float e = kth * (1.0f - m);
-    p.st->edge_next = m <= 0.3f && e > 0.0f && e < __builtin_inff() ? mag_key(e) & ~((1u << 20) - 1u) : kNoEdge;
+    p.st->edge_next = calm_enough(calm) && e > 0.0f && e < __builtin_inff() ? mag_key(e) & ~((1u << 20) - 1u) : kNoEdge;
     p.st->last_kth = kth;
     p.st->margin = m;
+    p.st->calm = calm;
 }
 
 // k_topk_final: the k-th largest key, the output and the residual update

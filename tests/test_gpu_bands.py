@@ -12,13 +12,14 @@ D = 10_000_037  # such calls take bands from 10 M elements
 
 
 class Workspace:
-    """A workspace of the test's own, to see what a call wrote."""
+    """A workspace of the test's own, to see what a call wrote.  `sizes`: the length of a vector, or those of a batch."""
 
-    def __init__(self, d):
+    def __init__(self, sizes):
         import torch
         import paper_2101_10761_amd as sidco
-        size = sidco.sidco_workspace_bytes(d)
-        seg = (d + 31 + 255) // 256 * 256 * 8
+        self.sizes = [sizes] if isinstance(sizes, int) else list(sizes)
+        size = sidco.sidco_workspace_bytes_batched([0, *np.cumsum(self.sizes).tolist()])
+        seg = sum((d + 31 + 255) // 256 * 256 * 8 for d in self.sizes)
         self.ws = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
         self.first, self.second = self.ws[size - 2 * seg:size - seg], self.ws[size - seg:]
 
@@ -36,6 +37,15 @@ class Workspace:
         self.second.fill_(0x5A)
         out = run_gpu(*args, **kw)
         return out, bool((self.second == 0x5A).all())
+
+    def run_batched(self, *args, **kw):
+        """The results of a batch and how many pairs stand in the first list buffer, which the first pass borrows for its
+        sums and, with bands, its lists; the stages of a batch of two stages leave it alone."""
+        import torch
+        from test_gpu_batched import run_batched
+        self.first.fill_(0x5A)
+        out = run_batched(*args, **kw)
+        return out, int((self.first.view(torch.int32).view(-1, 2)[:, 0] != 0x5A5A5A5A).sum())
 
     def run_topk(self, g, r, k, **kw):
         """The same for the exact Top-k: whether its first pass listed entries.  Without, the lists hold no entry below the
@@ -171,6 +181,32 @@ def test_long_batches_behind_a_call_of_the_same_layout(oracle, dist, stages, del
         if call in (1, 3, 4):
             check_batched(oracle, x, None, offsets, delta, dist, stages, results, f"call {call} dist={dist} M={stages}")
     assert status[1] == status[2] == [0, 0] and status[3] == [FALLBACK, FALLBACK], status
+
+
+def test_bands_return_after_a_jump(oracle):
+    """One call without them, for a vector, the exact Top-k and a batch; none between jumps that come too often."""
+    scales = (1.0, 1.0, 0.5, 0.5, 0.5, 0.5, 0.5, 1.0, 1.0, 0.5, 0.5, 0.5)
+    want = [False, True, False, False, True, True, True, False, False, False, False, False]
+    ratios, zero, k = oracle.schedule(0.01, 2, 0.25), np.zeros(D, np.float32), 10_000
+    g = _vector("laplace", D, 1)
+    with Workspace(D) as ws:
+        routes = []
+        for scale in scales:
+            x = g * np.float32(scale)
+            out, without = ws.run(x, zero, 0, ratios)
+            routes.append(without)
+        check_parity(oracle, x, zero, 0, ratios, out, label="after the jumps")
+        assert routes == want
+    g = _above_a_bin(_vector("student", D, 2), k)
+    with Workspace(D) as ws:
+        assert [ws.run_topk(g * np.float32(scale), None, k)[1] for scale in scales[:5]] == want[:5]
+    sizes = [12_000_000, 9_000_001]
+    offsets = [0, *np.cumsum(sizes).tolist()]
+    g = _vector("laplace", offsets[-1], 3)
+    with Workspace(sizes) as ws:
+        pairs = [ws.run_batched(g * np.float32(scale), None, offsets, 0.001, 0, 2)[1] for scale in scales]
+    missed = (2, 7, 9)  # with lists, but for nothing
+    assert [n > pairs[0] + 0.005 * offsets[-1] for n in pairs] == [w or call in missed for call, w in enumerate(want)], pairs
 
 
 @pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
