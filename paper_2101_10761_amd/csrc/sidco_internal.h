@@ -106,7 +106,8 @@ struct DevState {
     // stage m's threshold, and those before it, fell into their bands; the last call's thresholds and half-widths
     Bands band, band_next;
     uint32_t band_live[kBandStages + 1];
-    uint32_t band_over;     // a batch's first pass found more entries for a chunk's list than it has room for
+    uint32_t band_over;     // a batch's first pass found more entries for a chunk's list than it has room for, or another's
+                            // more than are worth listing
     float band_eta[kBandStages], band_w[kBandStages];
     Calm band_calm;
 };

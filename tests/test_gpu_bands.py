@@ -41,11 +41,14 @@ class Workspace:
     def run_batched(self, *args, **kw):
         """The results of a batch and how many pairs stand in the first list buffer, which the first pass borrows for its
         sums and, with bands, its lists; the stages of a batch of two stages leave it alone."""
-        import torch
         from test_gpu_batched import run_batched
         self.first.fill_(0x5A)
         out = run_batched(*args, **kw)
-        return out, int((self.first.view(torch.int32).view(-1, 2)[:, 0] != 0x5A5A5A5A).sum())
+        return out, self.pairs()
+
+    def pairs(self):
+        import torch
+        return int((self.first.view(torch.int32).view(-1, 2)[:, 0] != 0x5A5A5A5A).sum())
 
     def run_topk(self, g, r, k, **kw):
         """The same for the exact Top-k: whether its first pass listed entries.  Without, the lists hold no entry below the
@@ -207,6 +210,23 @@ def test_bands_return_after_a_jump(oracle):
         pairs = [ws.run_batched(g * np.float32(scale), None, offsets, 0.001, 0, 2)[1] for scale in scales]
     missed = (2, 7, 9)  # with lists, but for nothing
     assert [n > pairs[0] + 0.005 * offsets[-1] for n in pairs] == [w or call in missed for call, w in enumerate(want)], pairs
+
+
+def test_crowded_bands_are_given_up(oracle):
+    """Most entries have the one magnitude that the first threshold lies just below: what falls into the band is most of
+    the vector, which then goes without."""
+    share = 0.99 / np.log(4.0)
+    rng = np.random.default_rng(5)
+    g = np.where(rng.random(D) < share, np.copysign(np.float32(1e-3), rng.standard_normal(D)), 0.0).astype(np.float32)
+    ratios = [0.25, 0.1]
+    with Workspace(D) as ws:
+        crowded = []
+        for call in range(4):
+            ws.first.fill_(0x5A)
+            out, _ = ws.run(g, None, 0, ratios)
+            crowded.append(ws.pairs() > D / 2)
+        check_parity(oracle, g, None, 0, ratios, out, label="crowded")
+    assert crowded == [False, True, False, False]
 
 
 @pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
