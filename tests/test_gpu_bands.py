@@ -1,6 +1,7 @@
 """Calls that repeat the call before them in shape: the first pass looks for the thresholds where they fell last time
-(k_fit_bands) and the stages do without the dense vector if it found them.  Whether they did is seen from the second list
-buffer of the workspace, which only a stage that read the vector writes; results must not depend on it."""
+(k_fit_bands) and the stages do without the dense vector if it found them.  Whether it looked is seen from the first list
+buffer of the workspace, where its lists stand; whether a stage did without from the second one, which only a stage that
+read the vector writes, and from the status bit that reports those which could not.  Results must not depend on it."""
 import numpy as np
 import pytest
 
@@ -18,10 +19,12 @@ class Workspace:
         import torch
         import paper_2101_10761_amd as sidco
         self.sizes = [sizes] if isinstance(sizes, int) else list(sizes)
-        size = sidco.sidco_workspace_bytes_batched([0, *np.cumsum(self.sizes).tolist()])
+        offsets = [0, *np.cumsum(self.sizes).tolist()]
+        size = sidco.sidco_workspace_bytes_batched(offsets)
         seg = sum((d + 31 + 255) // 256 * 256 * 8 for d in self.sizes)
-        self.ws = torch.zeros(size, dtype=torch.uint8, device="cuda:0")
-        self.first, self.second = self.ws[size - 2 * seg:size - seg], self.ws[size - seg:]
+        widened = sidco.sidco_workspace_bytes_batched_typed(offsets, sidco.GRAD_F16, False)  # a copy behind the lists
+        self.ws = torch.zeros(widened, dtype=torch.uint8, device="cuda:0")
+        self.first, self.second = self.ws[size - 2 * seg:size - seg], self.ws[size - seg:size]
 
     def __enter__(self):
         import paper_2101_10761_amd as sidco
@@ -32,10 +35,10 @@ class Workspace:
         import paper_2101_10761_amd as sidco
         sidco.sidco_set_workspace(None)
 
-    def run(self, *args, **kw):
+    def run(self, *args, call=run_gpu, **kw):
         """The call's result and whether its first stage did without the dense vector."""
         self.second.fill_(0x5A)
-        out = run_gpu(*args, **kw)
+        out = call(*args, **kw)
         return out, bool((self.second == 0x5A).all())
 
     def run_batched(self, *args, **kw):
@@ -50,16 +53,19 @@ class Workspace:
         import torch
         return int((self.first.view(torch.int32).view(-1, 2)[:, 0] != 0x5A5A5A5A).sum())
 
+    def magnitudes(self):
+        """Of the pairs in the first list buffer."""
+        import torch
+        pairs = self.first.view(torch.int32).view(-1, 2)
+        return np.abs(pairs[pairs[:, 0] != 0x5A5A5A5A][:, 1].cpu().numpy().view(np.float32))
+
     def run_topk(self, g, r, k, **kw):
         """The same for the exact Top-k: whether its first pass listed entries.  Without, the lists hold no entry below the
         bin (the upper 12 bits of a float) of the k-th magnitude, which `_above_a_bin` puts at the bin's lower end."""
-        import torch
         from test_gpu_topk import run_topk
         self.first.fill_(0x5A)
         out = run_topk(g, r, k, **kw)
-        pairs = self.first.view(torch.int32).view(-1, 2)
-        values = pairs[pairs[:, 0] != 0x5A5A5A5A][:, 1].cpu().numpy().view(np.uint32) & 0x7FFFFFFF
-        return out, bool((values >> 20 < np.float32(out[3]).view(np.uint32) >> 20).any())
+        return out, bool((self.magnitudes().view(np.uint32) >> 20 < np.float32(out[3]).view(np.uint32) >> 20).any())
 
 
 def _above_a_bin(g, k):
@@ -231,38 +237,48 @@ def test_crowded_bands_are_given_up(oracle):
 
 @pytest.mark.parametrize("kind", ["nan", "zero", "constant"])
 def test_special_inputs_behind_bands(oracle, kind):
+    """They fall out of the bands, the constant vector (of the mean magnitude before) at the latest behind the first stage."""
     zero = np.zeros(D, np.float32)
     for dist, ratios in ((0, [0.25, 0.04]), (2, [0.25, 0.2, 0.2]), (1, [0.25, 0.04])):
-        for call in range(3):
-            run_gpu(_vector("laplace", D, call), zero, dist, ratios)
-        g = _vector("laplace", D, 9)
-        if kind == "nan":
-            g[D // 2] = np.nan
-        elif kind == "zero":
-            g[:] = 0.0
-        else:
-            g = np.copysign(np.float32(1e-3), g)
-        for _ in range(2):
-            out = run_gpu(g, zero, dist, ratios)
-            check_parity(oracle, g, zero, dist, ratios, out, label=f"{kind} dist={dist}")
+        with Workspace(D) as ws:
+            for call in range(3):
+                out, without = ws.run(_vector("laplace", D, call), zero, dist, ratios)
+            assert without and not out.status & FALLBACK
+            g = _vector("laplace", D, 9)
+            if kind == "nan":
+                g[D // 2] = np.nan
+            elif kind == "zero":
+                g[:] = 0.0
+            else:
+                g = np.copysign(np.float32(1e-3), g)
+            for call in range(2):
+                out = run_gpu(g, zero, dist, ratios)
+                check_parity(oracle, g, zero, dist, ratios, out, label=f"{kind} dist={dist}")
+                assert call or out.status & FALLBACK
 
 
 def test_capacity_behind_bands(oracle):
     zero, ratios = np.zeros(D, np.float32), [0.25, 0.04]
-    for call in range(3):
-        g = _vector("laplace", D, call)
-        out = run_gpu(g, zero, 0, ratios, cap=5000)
-        check_parity(oracle, g, zero, 0, ratios, out, capacity=5000, label=f"call {call}")
+    with Workspace(D) as ws:
+        for call in range(3):
+            g = _vector("laplace", D, call)
+            out, without = ws.run(g, zero, 0, ratios, cap=5000)
+            check_parity(oracle, g, zero, 0, ratios, out, capacity=5000, label=f"call {call}")
+            assert without == (call > 0)
 
 
 @pytest.mark.parametrize("ratios", [[0.25, 0.4], [0.25, 0.64, 0.64]])
 def test_a_dense_last_stage_behind_bands(oracle, ratios):
+    """Such a call writes no lists but those of its first pass."""
     d = 62_000_003
-    for call in range(3):
-        rng = np.random.default_rng(call)
-        g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
-        r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
-        out = run_gpu(g, r, 0, ratios)
+    with Workspace(d) as ws:
+        for call in range(3):
+            rng = np.random.default_rng(call)
+            g = rng.standard_normal(d, dtype=np.float32) * np.float32(1e-3)
+            r = rng.standard_normal(d, dtype=np.float32) * np.float32(3e-4)
+            ws.first.fill_(0x5A)
+            out = run_gpu(g, r, 0, ratios)
+            assert not out.status & FALLBACK and (ws.pairs() > 0.005 * d) == (call > 0)
     check_parity(oracle, g, r, 0, ratios, out, label=f"{ratios}")
 
 
@@ -272,10 +288,34 @@ def test_16_bit_gradients_behind_bands(oracle, kind, residual):
     from test_gpu_typed import narrow, run_typed
     r = _vector("laplace", D, 1, 3e-3) if residual else None
     for dist, stages in ((2, 3), (1, 2), (0, 2)):
-        for call in range(4):
-            g16, g = narrow(_vector("student", D, 20 + call, 1e-2), kind)
-            out = run_typed(g16, r, dist, 0.005, stages, grad_offset=1, res_offset=2)
+        with Workspace(D) as ws:
+            routes = []
+            for call in range(4):
+                g16, g = narrow(_vector("student", D, 20 + call, 1e-2), kind)
+                out, without = ws.run(g16, r, dist, 0.005, stages, grad_offset=1, res_offset=2, call=run_typed)
+                routes.append(without)
         check_parity(oracle, g, r, dist, oracle.schedule(0.005, stages, 0.25), out, label=f"{kind} dist={dist} M={stages}")
+        assert routes == [False, True, True, True]
+
+
+@pytest.mark.parametrize("factor", [0.6, 1.2])
+def test_a_first_stage_that_only_sums_and_a_second_outside_its_band(oracle, factor):
+    """The first stage would keep too much to list it; its threshold stays, the second one moves."""
+    ratios, zero = [0.64, 0.2, 0.25], np.zeros(D, np.float32)
+    with Workspace(D) as ws:
+        for call in range(3):
+            g = _vector("laplace", D, call)
+            ws.first.fill_(0x5A)
+            out, without = ws.run(g, zero, 0, ratios)
+            assert without and not out.status & FALLBACK
+            # entries by the first threshold: the second stage lists none
+            assert bool((ws.magnitudes() < 1.1 * out.etas[0]).any()) == (call > 0)
+        g = _moved_tail(g, 2.0 * float(out.etas[1]) / 3.0, factor)  # what is above the second threshold
+        moved = run_gpu(g, zero, 0, ratios)
+        check_parity(oracle, g, zero, 0, ratios, moved, label=f"moved {factor}")
+        assert moved.status & FALLBACK
+        again = run_gpu(g, zero, 0, ratios)
+        check_parity(oracle, g, zero, 0, ratios, again, label="after the miss")
 
 
 def test_replays_of_a_captured_call_with_bands(oracle):
@@ -286,28 +326,35 @@ def test_replays_of_a_captured_call_with_bands(oracle):
     ratios, other = oracle.schedule(0.01, 3, 0.25), oracle.schedule(0.01, 2, 0.25)
     zero = np.zeros(D, np.float32)
     side = torch.cuda.Stream()
-    for call in range(2):
-        GpuCall(_vector("laplace", D, call), zero, 0, ratios).launch(side).collect(side)
-    held = GpuCall(_vector("laplace", D, 2), zero, 0, ratios)
-    graph = torch.cuda.CUDAGraph()
-    with torch.cuda.stream(side):
-        graph.capture_begin()
-        held.launch(side)
-        graph.capture_end()
-    for it in range(4):
-        held.g = _vector("laplace", D, 10 + it)
-        held.gt.copy_(torch.from_numpy(held.g))
-        held.rt.zero_()
-        held.out_idx.fill_(-7)
-        torch.cuda.synchronize()
-        graph.replay()
-        torch.cuda.synchronize()
-        check_parity(oracle, held.g, zero, 0, ratios, held.collect(side), label=f"replay {it}")
-        if it < 3:
-            g = _vector("laplace", D, 20 + it)
-            out = GpuCall(g, zero, 0, other).launch(side).collect(side)
-            check_parity(oracle, g, zero, 0, other, out, label=f"eager {it}")
-    sidco.sidco_release(stream=side)
+    routes = []
+    with Workspace(D) as ws:
+        for call in range(2):
+            GpuCall(_vector("laplace", D, call), zero, 0, ratios).launch(side).collect(side)
+        held = GpuCall(_vector("laplace", D, 2), zero, 0, ratios)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            graph.capture_begin()
+            held.launch(side)
+            graph.capture_end()
+        for it in range(13):
+            held.g = _vector("laplace", D, 10 + it)
+            held.gt.copy_(torch.from_numpy(held.g))
+            held.rt.zero_()
+            held.out_idx.fill_(-7)
+            ws.second.fill_(0x5A)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            routes.append(bool((ws.second == 0x5A).all()))
+            if it < 6 or it == 12:
+                check_parity(oracle, held.g, zero, 0, ratios, held.collect(side), label=f"replay {it}")
+            if it < 3:
+                g = _vector("laplace", D, 20 + it)
+                out = GpuCall(g, zero, 0, other).launch(side).collect(side)
+                check_parity(oracle, g, zero, 0, other, out, label=f"eager {it}")
+    # the bands of the eager calls are not a replay's, and their thresholds jump to the replay's and back: a rest of eight
+    # calls behind the last jump, which is replay 3's
+    assert routes == [True] + 11 * [False] + [True]
 
 
 @pytest.mark.parametrize("k,residual,offset", [(1, True, 0), (10_000, True, 3), (100_000, False, 1), (399_999, True, 2)])
@@ -324,11 +371,28 @@ def test_top_k_behind_a_call_of_the_same_shape(oracle, k, residual, offset):
         check_topk(oracle, g, res, k, run_topk(g, res, k, grad_offset=offset, res_offset=offset), label=f"call {call} k={k}")
 
 
-def test_top_k_captured_before_the_first_eager_call(oracle):
-    """A call that is captured and not yet run leaves nothing for the next call to rely on."""
+@pytest.mark.parametrize("kind", ["f32", "bf16"])
+@pytest.mark.parametrize("residual", [True, False])
+def test_top_k_reads_the_lists_of_its_first_pass(oracle, kind, residual):
+    from test_gpu_topk import check_topk
+    from test_gpu_typed import narrow
+    k = 20_000
+    r = np.zeros(D, np.float32) if residual else None
+    with Workspace(D) as ws:
+        for call in range(3):
+            given = g = _above_a_bin(_vector("student", D, 30 + call), k)
+            if kind != "f32":
+                given, g = narrow(g, kind)
+            out, listed = ws.run_topk(given, r, k, grad_offset=1, res_offset=2)
+            check_topk(oracle, g, r, k, out, label=f"call {call} {kind}")
+            assert listed == (call > 0)
+
+
+@pytest.mark.parametrize("d,k", [(300_007, 500), (D, 10_000)])
+def test_top_k_captured_before_the_first_eager_call(oracle, d, k):
+    """A call that is captured and not yet run leaves nothing for the next call to rely on; nor does a later one."""
     import torch
     import paper_2101_10761_amd as sidco
-    d, k = 300_007, 500
     dev = torch.device("cuda:0")
     side = torch.cuda.Stream()
     g = torch.from_numpy(_vector("student", d, 1)).to(dev)
@@ -344,7 +408,19 @@ def test_top_k_captured_before_the_first_eager_call(oracle):
             sidco.sidco_topk(g, None, k, *out, stream=side)
             graph.capture_end()
         want = np.sort(np.abs(g.cpu().numpy()))[-k:]
-        for step in (lambda: sidco.sidco_topk(g, None, k, *out), graph.replay, lambda: sidco.sidco_topk(g, None, k, *out), graph.replay):
+        eager = lambda: sidco.sidco_topk(g, None, k, *out)
+        repeated = torch.cuda.CUDAGraph()
+
+        def capture_a_call_that_repeats_the_shape():
+            eager()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(side):
+                repeated.capture_begin()
+                sidco.sidco_topk(g, None, k, *out, stream=side)
+                repeated.capture_end()
+
+        for step in (eager, graph.replay, eager, graph.replay, capture_a_call_that_repeats_the_shape, repeated.replay, eager,
+                     repeated.replay, graph.replay, repeated.replay):
             out[1].zero_()
             torch.cuda.synchronize()
             step()
@@ -405,18 +481,23 @@ def test_batches_behind_a_call_of_the_same_layout(oracle, kind, dist, stages, de
     sizes[5] = 25_345_678 - sum(sizes)  # a batch takes bands from 20 M elements, 25 M of 16 bits
     offsets = [0, *np.cumsum(sizes).tolist()]
     r = _vector("student", offsets[-1], 1, 3e-3) if residual else None
-    for call in range(5):
-        g = _vector("student", offsets[-1], 50 + call, 1e-2)
-        if call % 2:
-            g[offsets[9]:offsets[10]] *= np.float32(3.0)
-        if call == 3:
-            g[offsets[3] + 100_000:offsets[3] + 104_000] = 1.0  # more in a chunk than its list has room for
-        if call == 4:
-            g[offsets[3] + 17] = np.inf
-            g[offsets[6]:offsets[7]] = 0.0
-        given = g
-        if kind != "f32":
-            given, g = narrow(g, kind)
-        results = run_batched(given, r, offsets, delta, dist, stages, base_offset=call % 4)
-        if call:
-            check_batched(oracle, g, r, offsets, delta, dist, stages, results, f"call {call} {kind} dist={dist} M={stages}")
+    pairs = []
+    with Workspace(sizes) as ws:
+        for call in range(5):
+            g = _vector("student", offsets[-1], 50 + call, 1e-2)
+            if call % 2:
+                g[offsets[9]:offsets[10]] *= np.float32(3.0)
+            if call == 3:
+                g[offsets[3] + 100_000:offsets[3] + 104_000] = 1.0  # more in a chunk than its list has room for
+            if call == 4:
+                g[offsets[3] + 17] = np.inf
+                g[offsets[6]:offsets[7]] = 0.0
+            given = g
+            if kind != "f32":
+                given, g = narrow(g, kind)
+            results, n = ws.run_batched(given, r, offsets, delta, dist, stages, base_offset=call % 4)
+            pairs.append(n)
+            if call:
+                check_batched(oracle, g, r, offsets, delta, dist, stages, results, f"call {call} {kind} dist={dist} M={stages}")
+    # the first pass looked for the thresholds: of three stages, the second one's lists stand there in any case
+    assert all(n > pairs[0] + 0.002 * offsets[-1] for n in pairs[1:]), pairs
