@@ -33,7 +33,9 @@
  * threshold that differs in its last bit.  Across
  * different histories the exceedance statistics of the stages after the first
  * are summed in a different order (the lists follow the previous calls'
- * thresholds, see sidco_set_speculation), so a threshold can differ in
+ * thresholds, see sidco_set_speculation), and so are the first one's sums of a
+ * single vector of 58 million elements or more, whose first pass has another
+ * shape in a call that repeats the one before it, so a threshold can differ in
  * its last bit, far inside the 1e-5 the fitted values are specified to; given
  * the threshold, the selected set, its values and the residual are exact.  The
  * order of the output pairs is fixed for a single-stage call and may vary
@@ -450,7 +452,9 @@ int sidco_set_status_word(void *stream, uint32_t *device_word);
  * to the calls that follow, on every device.  With theta > 0 a call that repeats
  * the call before it on the workspace in shape (length, law, ratios, with or
  * without a residual) may also look for its thresholds near that call's while it
- * forms acc, and read the vector again only where one fell elsewhere.
+ * forms acc, and read the vector again only where one fell elsewhere
+ * (SIDCO_ST_FALLBACK).  sidco_topk does the same with its k-th magnitude,
+ * whatever theta is; what it returns does not depend on it.
  */
 int sidco_set_speculation(double theta);
 
