@@ -101,6 +101,25 @@ def test_thresholds_found_where_they_fell_last_time(oracle, dist, law, stages, d
         assert routes == [False, True, True, True]
 
 
+@pytest.mark.parametrize("residual", [True, False])
+def test_thresholds_closer_together_than_their_bands(oracle, residual):
+    """Magnitudes up to 1 and a light tail: the second and third threshold differ by 5 %, less than the second band's width."""
+    ratios = oracle.schedule(0.001, 3, 0.25)
+    zero = np.zeros(D, np.float32) if residual else None
+    with Workspace(D) as ws:
+        routes = []
+        for call in range(4):
+            rng = np.random.default_rng(call)
+            g = ((rng.random(D) + rng.exponential(0.02, D)) * rng.choice([-1.0, 1.0], D)).astype(np.float32)
+            out, without = ws.run(g, zero, 0, ratios)
+            check_parity(oracle, g, zero, 0, ratios, out, label=f"call {call}")
+            assert 1.0 < out.etas[2] / out.etas[1] < 1.057
+            routes.append((without, bool(out.status & FALLBACK)))
+        assert routes[1:] == [(True, False)] * 3  # the first call's candidate threshold is above all entries
+        out, _ = ws.run(g * np.float32(1.02), zero, 0, ratios)  # out of the narrowed bands or not, the result holds
+        check_parity(oracle, g * np.float32(1.02), zero, 0, ratios, out, label="moved")
+
+
 def _moved_tail(g, eta, factor):
     """The same mean magnitude with the entries above 1.5 eta scaled by `factor`."""
     a = np.abs(g.astype(np.float64))
