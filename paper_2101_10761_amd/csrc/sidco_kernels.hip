@@ -650,7 +650,8 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
 // after such a pass would lose more than that (25.6 M, a call without bands 84.5 and 89.5).  A training step without and
 // with bands, us: 14.7 M, 2 stages, ratio 0.001 55.5 and 46.3; 25.6 M, 3 stages 84.2 and 75.5, bf16 77.4 and 67.1; 30 M,
 // fp16, 2 stages, 0.01 96.8 and 68.5; 66 M, gamma 171 and 148; 138 M, 3 stages, 0.01 518 and 409.  A call whose
-// thresholds fall out of the bands pays for them: 138 M 562 and 604, 100 M, 2 stages 381 and 410.
+// thresholds fall out of the bands pays for them, the more the longer the lists get; where the thresholds double or halve
+// 25.6 M 88 and 100, 66 M 173 and 203, 100 M, 2 stages, 0.01 295 and 359, 138 M, 3 stages, 0.01 515 and 645, 0.001 405 and 461.
 // ---------------------------------------------------------------------------------------------
 // A band's half-width is the least one (see band_width in the host code) or, where that is more, kBandDrift times the
 // threshold's last relative change, which later calls let shrink by kBandDecay each: what moves by 10 % every third
