@@ -65,7 +65,7 @@ def scope_formula_bytes(d, ec, n_stage, khat, fit_bpe=None):
 
 
 def moved_bytes_min(d, ec, n_stage, khat, fit_bpe=None):
-    """The least this design can move in a call: the first pass, ONE further pass over the accumulated vector
+    """The least a call moves that does not find its thresholds in the first pass: that pass, ONE further pass over the accumulated vector
     (whatever the number of stages: the dense stage only sums over the exceedances of eta_1 and writes
     candidates for the stage after it), the lists behind the dense stage - candidates that must at least hold
     the next stage's exceedances, then each later stage's exceedances, all written once and read once - and the
@@ -404,8 +404,9 @@ def main():
         "bytes_moved_min": moved, "bytes_per_elem": round(moved / d, 2),
         "achieved": round(moved / secs / 1e9, 1), "unit": "GB/s",
         "frac": round(moved / secs / 1e9 / HBM_PEAK_GBPS, 4),
-        "note": "frac prices the step against the bytes this design must move (the exceedances of eta_1 are never "
-                "written as pairs); frac_scope_formula prices it against the scope table's formula, which charges them",
+        "note": "frac prices the step against the bytes of a call that reads the vector a second time (4 B per element; one "
+                "that finds its thresholds in the first pass does without), the exceedances of eta_1 never written as pairs; "
+                "frac_scope_formula prices it against the scope table's formula, which charges them",
         "scope_formula_bytes": formula, "frac_scope_formula": round(formula / secs / 1e9 / HBM_PEAK_GBPS, 4),
         "counter_bytes": None if not counters else {k: v for k, v in counters.items()},
         "counter_source": None if not counters else "profiles/hbm_traffic.json, not measured in this run",
