@@ -556,12 +556,12 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     double list_frac = 1;  // expected fraction of the vector in the current lists
     int sel = 0;           // which half of the double buffers the last kernel wrote
     bool reverse = true;   // direction of the next dense pass: k_fit walked forward, so the first one walks back
-    bool cand = false;     // the current lists are candidate lists
     auto bind = [&](int m) {
         const int in = sel, out = sel ^ 1;
         p.stage = m;
+        p.L_stage = p.L[m - 1];
+        p.L_next = m < M ? p.L[m] : 0.0;
         p.theta = 0.0f;
-        p.prev_cand = cand ? 1 : 0;
         p.part_in = h->part[in];
         p.part_out = h->part[out];
         p.cnt_in = h->cnt[in];
@@ -591,14 +591,13 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
             if (write) {
                 lists = true;
                 list_frac = frac;
-                cand = theta > 0.0;
+                if (theta > 0.0) p.cand_stage = m;
             }
         } else {
             launch_lists(p, s);
             ++k;
             mark("k_lists");
             list_frac = cum * ratios[m - 1];
-            cand = false;
         }
         cum *= ratios[m - 1];
     }
@@ -1209,7 +1208,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     const bool flat = pl.flat_gx > 0 && !pl.fold;
     const bool much = residual && keeps_much(total, true, dist, ratios, M) &&
                       (M != 2 || (double)total * (4.0 + 8.0 * kept_ratio(ratios, M)) <= kKeepMaxBytesBatchTwo);
-    bool lists = false, cand = false, reverse = true;
+    bool lists = false, reverse = true;
     double cum = 1.0;
     int sel = 0;
     auto bind = [&](int m) {
@@ -1217,8 +1216,9 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
         a.out = sel ^ 1;
         sel ^= 1;
         a.stage = m;
+        a.L_stage = a.L[m - 1];
+        a.L_next = m < M ? a.L[m] : 0.0;
         a.theta = 0.0f;
-        a.prev_cand = cand ? 1 : 0;
     };
     for (int m = 1; m < M; ++m) {
         bind(m);
@@ -1234,11 +1234,10 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
             launch_compact_batched(a, /*stats=*/true, write, flat && m == 1, much, pl.blocks, s);
             if (write) {
                 lists = true;
-                cand = theta > 0.0;
+                if (theta > 0.0) a.cand_stage = m;
             }
         } else {
             launch_lists_batched(a, pl.blocks, s);
-            cand = false;
         }
         cum *= ratios[m - 1];
     }

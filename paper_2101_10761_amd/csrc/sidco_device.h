@@ -25,23 +25,40 @@ __device__ __forceinline__ T dpp_or_zero(T v)
     return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
 }
 
-// Sum over the wave in a fixed order, the same in every lane.  Six DPP moves and adds: a shuffle through LDS costs
+// Sums over the wave in a fixed order, the same in every lane.  Six DPP moves and adds: a shuffle through LDS costs
 // several times the latency, and these sums stand in the serial chain of every kernel's prologue and epilogue
 // (25.6 M elements, three stages: dense stage 21.6 -> 20.8 us, the two list stages 8.6 -> 6.8 and 7.7 -> 7.0;
-// 14.7 M, two stages: dense stage 16.1 -> 14.7, last stage 10.1 -> 9.4).
+// 14.7 M, two stages: dense stage 16.1 -> 14.7, last stage 10.1 -> 9.4).  Several values take every step together: one
+// value's moves fill the wait for the adds of the others.
+template <int CTRL, int ROWS, int Q, typename T>
+__device__ __forceinline__ void wave_step(T (&v)[Q])
+{
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] += dpp_or_zero<CTRL, ROWS>(v[q]);
+}
+template <int Q, typename T>
+__device__ __forceinline__ void wave_totals(T (&v)[Q])
+{
+    wave_step<0x111, 0xf>(v);
+    wave_step<0x112, 0xf>(v);
+    wave_step<0x114, 0xf>(v);
+    wave_step<0x118, 0xf>(v);  // lane 15 of each row: the row's sum
+    wave_step<0x142, 0xa>(v);
+    wave_step<0x143, 0xc>(v);  // lane 63: the wave's sum
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint64_t u = __builtin_bit_cast(uint64_t, v[q]);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
+        v[q] = __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
+    }
+}
 template <typename T>
 __device__ __forceinline__ T wave_total(T v)
 {
-    v += dpp_or_zero<0x111, 0xf>(v);
-    v += dpp_or_zero<0x112, 0xf>(v);
-    v += dpp_or_zero<0x114, 0xf>(v);
-    v += dpp_or_zero<0x118, 0xf>(v);  // lane 15 of each row: the row's sum
-    v += dpp_or_zero<0x142, 0xa>(v);
-    v += dpp_or_zero<0x143, 0xc>(v);  // lane 63: the wave's sum
-    const uint64_t u = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, 63);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), 63);
-    return __builtin_bit_cast(T, (uint64_t)hi << 32 | lo);
+    T a[1] = {v};
+    wave_totals(a);
+    return a[0];
 }
 
 __device__ __forceinline__ double wave_sum(double v) { return wave_total(v); }

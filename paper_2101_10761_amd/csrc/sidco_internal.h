@@ -112,43 +112,50 @@ struct DevState {
     Calm band_calm;
 };
 
-// Kernel arguments (passed by value).
 // element type of the gradient buffer (the accumulated vector and the residual are always fp32)
 constexpr int kGradF32 = 0, kGradF16 = 1, kGradBf16 = 2;
 
+// Kernel arguments: the first three 64-byte lines are what a stage's kernel asks for before its threshold, in the order of
+// need.  A line that is not in the scalar cache yet, and after a kernel's start none is, costs 0.2 us and more.
 struct Params {
-    const void* grad;       // d elements of type `gt`
-    int gt;                 // kGrad*
-    float* residual;        // NULL: memoryless
-    float* acc_w;           // where k_fit stores acc: residual; for a 16-bit gradient without residual a
-                            // workspace buffer; NULL when acc is the fp32 gradient itself
-    const float* acc;       // dense working vector read by stage 1's compaction: acc_w, else grad
-    int64_t d;
-    uint32_t shift;         // elements between the 128-byte boundary before acc[0] and acc[0] (see WaveTiles)
-    uint32_t nfull;         // (d + shift) / kTile: tiles below this index are complete (tile 0 only if shift = 0)
-    uint32_t nwaves;        // waves that own tiles
-    uint32_t tq, tr;        // T / nwaves and T % nwaves, T = ceil((d + shift) / kTile) tiles (see WaveTiles)
-    uint32_t nblocks;       // grid size of the kernels that read the dense vector or write partial sums
-    int reverse;            // a dense stage kernel walks the tiles from the last to the first
-    int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
-    unsigned long long owner;  // id of the stage controller that makes the call, 0 otherwise
-    int dist;
-    int M;
-    int stage;              // 1-based stage a k_compact launch works for
-    double L[SIDCO_MAX_STAGES];  // log(1/delta_m)
-    float theta;            // > 0: the lists of this kernel are candidate lists (see stage_prologue); else 0
-    float theta_min;        // lowest theta a hint may lead to: below it the lists would exceed kMaterializeBelow
-    int use_hint;           // the previous call on the device had this call's shape: theta_seen applies
-    int prev_cand;          // the producer of this kernel's source lists wrote candidate lists
     DevState* st;
     const double* part_in;  // [4][kBatchBlocks] partial sums written by the previous kernel
-    double* part_out;
-    const uint32_t* cnt_in; // [kMaxWaves] survivor-list lengths written by the previous kernel
-    uint32_t* cnt_out;
     const uint32_t* blk_in; // [kMaxBlocks] per-block sums of cnt
-    uint32_t* blk_out;
+    double* band_part;      // [3 * (kBandStages - 1)][kMaxBlocks] sums of y, y^2 and 1 above each band's upper edge
+    int stage;              // 1-based stage a k_compact launch works for
+    uint32_t nblocks;       // grid size of the kernels that read the dense vector or write partial sums
+    int dist;
+    uint32_t nwaves;        // waves that own tiles
+    uint32_t tq, tr;        // T / nwaves and T % nwaves, T = ceil((d + shift) / kTile) tiles (see WaveTiles)
+    float theta;            // > 0: the lists of this kernel are candidate lists (see stage_prologue); else 0
+    int use_hint;           // the previous call on the device had this call's shape: theta_seen applies
+
+    int2* band_seg;         // lists of a first pass with bands
+    uint32_t* band_cnt;     // [kMaxWaves] their lengths
     const int2* seg_in;     // survivor lists (index, value bits); wave w's list starts at seg_begin(w)
+    const uint32_t* cnt_in; // [kMaxWaves] survivor-list lengths written by the previous kernel
     int2* seg_out;
+    const float* acc;       // dense working vector read by stage 1's compaction: acc_w, else grad
+    uint32_t shift;         // elements between the 128-byte boundary before acc[0] and acc[0] (see WaveTiles)
+    uint32_t nfull;         // (d + shift) / kTile: tiles below this index are complete (tile 0 only if shift = 0)
+    int reverse;            // a dense stage kernel walks the tiles from the last to the first
+    int M;
+
+    double L_stage, L_next; // log(1/delta_m) of the stage and of the next one
+    int64_t d;
+    float theta_min;        // lowest theta a hint may lead to: below it the lists would exceed kMaterializeBelow
+    int cand_stage;         // the stage of this call that wrote candidate lists; 0: none so far
+    double* part_out;
+    uint32_t* cnt_out;
+    uint32_t* blk_out;
+    float* residual;        // NULL: memoryless
+
+    const void* grad;       // d elements of type `gt`
+    float* acc_w;           // where k_fit stores acc: residual; for a 16-bit gradient without residual a
+                            // workspace buffer; NULL when acc is the fp32 gradient itself
+    int gt;                 // kGrad*
+    int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
+    unsigned long long owner;  // id of the stage controller that makes the call, 0 otherwise
     int32_t* out_idx;
     float* out_val;
     int32_t* out_count;
@@ -158,9 +165,7 @@ struct Params {
     int bands;              // kBands*
     float band_w[kBandStages];  // least half-widths of the bands; the last stage's 0 if it reads no lists
     float band_max;             // and the first one's widest
-    double* band_part;      // [3 * (kBandStages - 1)][kMaxBlocks] sums of y, y^2 and 1 above each band's upper edge
-    uint32_t* band_cnt;     // [kMaxWaves] lengths of the lists of a first pass with bands
-    int2* band_seg;         // the lists themselves
+    double L[SIDCO_MAX_STAGES];  // log(1/delta_m)
 };
 
 // ---- exact Top-k comparator (sidco_topk.hip) ----
@@ -259,6 +264,7 @@ void launch_dgc_lists(const DgcParams& p, uint32_t grid, hipStream_t s);
 struct Blk {
     uint32_t id;  // block index within the vector's grid
     uint32_t n;   // size of that grid
+    uint32_t none;  // 0 (see stage_grid)
 };
 
 // ---- batched calls: several vectors (the tensors of one flat buffer) in one launch sequence ----
@@ -304,8 +310,9 @@ struct BatchArgs {
     int in, out;            // which half of the double buffers the kernel reads / writes
     int dist, M, stage, reverse;
     double L[SIDCO_MAX_STAGES];
+    double L_stage, L_next;
     float theta, theta_min;
-    int use_hint, prev_cand;
+    int use_hint, cand_stage;
     double* flat;           // partial sums of a flat first pass (see k_fit_flat_batched), chunks per block and blocks
     uint32_t flat_gx, flat_blocks;
     int bands;              // as in Params, and if used: lengths of the chunks' lists, and the lists, kChunkList entries each

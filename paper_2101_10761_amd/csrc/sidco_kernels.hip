@@ -11,8 +11,8 @@
 //                The gradient may be fp16 / bf16; it is widened as it is read.
 //   k_fit_bands  the same for a call that repeats a shape: it also sums up and lists what the stages will ask for if
 //                the thresholds fall near the last call's.
-//   stage m      m = 1..M, one kernel each.  Prologue: every block reduces the previous kernel's partial
-//                sums in a fixed order and its first wave evaluates the closed-form threshold eta_m in
+//   stage m      m = 1..M, one kernel each.  Prologue: the first wave of every block reduces the previous kernel's
+//                partial sums in a fixed order and evaluates the closed-form threshold eta_m in
 //                fp64 (the same arithmetic, hence identical bits, in every block).
 //                k_compact: the stage whose source is the dense acc (m = 1; also later stages while the
 //                exceedances are still a large part of the vector).  It forms n and the sums of
@@ -57,8 +57,7 @@ template <int Q>
 __device__ __forceinline__ void block_sum(double (&v)[Q], double (*sh)[4])
 {
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-#pragma unroll
-    for (int q = 0; q < Q; ++q) v[q] = wave_sum(v[q]);
+    wave_totals(v);
     __syncthreads();  // protects sh against a previous use
     if (lane == 0) {
 #pragma unroll
@@ -166,7 +165,21 @@ __device__ __forceinline__ double stage_L(const Params& p, int i)
     return v;
 }
 
-__device__ __forceinline__ Blk whole_grid() { return Blk{blockIdx.x, gridDim.x}; }
+__device__ __forceinline__ Blk whole_grid() { return Blk{blockIdx.x, gridDim.x, 0u}; }
+// The same for a stage's kernel.  `none` is zero, but the compiler does not know: it comes with the arguments that the
+// kernel needs ahead of its threshold, and what is loaded with it waits for all of them at once.  Fetched one by one as
+// they come up they are a chain of round trips, 0.2 us each.
+__device__ __forceinline__ Blk stage_grid(const Params& p)
+{
+    uint32_t none;
+    asm("s_mov_b32 %0, 0"
+        : "=s"(none)
+        : "s"(p.st), "s"(p.part_in), "s"(p.blk_in), "s"(p.band_part), "s"(p.stage), "s"(p.nblocks), "s"(p.dist), "s"(p.nwaves),
+          "s"(p.tq), "s"(p.tr), "s"(p.theta), "s"(p.use_hint), "s"(p.band_seg), "s"(p.band_cnt), "s"(p.seg_in), "s"(p.cnt_in),
+          "s"(p.seg_out), "s"(p.acc), "s"(p.shift), "s"(p.nfull), "s"(p.reverse), "s"(p.M), "s"(p.L_stage), "s"(p.L_next),
+          "s"(p.d), "s"(p.theta_min));
+    return Blk{blockIdx.x, gridDim.x, none};
+}
 
 // What the prologue of a stage's kernel hands to its body.
 struct StageEta {
@@ -176,9 +189,8 @@ struct StageEta {
     bool hit;       // eta fell into the stage's band: the first pass's sums and lists serve the stage
 };
 
-// Prologue of every stage kernel: reduce the producer's per-block partial sums (fixed order) and
-// evaluate eta for stage p.stage.  Returns the same values in every thread of every block.
-// Block 0 records the stage in the diagnostics.
+// Prologue of every stage kernel (prologue_load, prologue_finish): reduce the producer's per-block partial sums (fixed
+// order) and evaluate eta for stage p.stage.
 //
 // Speculative candidate lists.  A stage that reads the dense vector and keeps a large fraction
 // (delta_1 = 0.25) would have to write a quarter of it as 8-byte pairs, or make the next stage read the
@@ -195,14 +207,23 @@ struct StageEta {
 // What a stage's prologue reads from memory: issued as early as possible, and BEFORE any bulk loads of
 // the kernel's body - the wave's memory counter retires in order, so a wait for these few values would
 // otherwise also wait for every load issued ahead of them.
+// The partial sums are the first wave's: it adds them up alone, eight of each kind per lane, and goes on to the closed
+// form without waiting for the rest of the block.  A prologue is a chain of latencies - arguments, partial sums, the sums,
+// the closed form - and sets the time of every stage that reads only lists.  With a value per thread, a sum over the block,
+// arguments and state fetched as they came up, the lists' loads ahead of the partial sums' and the bookkeeping of block 0
+// ahead of the threshold's way to the other waves, a training step took, us, and so: 2.6 M elements, 2 stages 22.7 and 21.5;
+// 14.7 M, 2 stages 46.8 and 44.8; 25.6 M, 3 stages 76.0 and 72.4, with a bf16 gradient 67.9 and 64.8.
+typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(4)));
+constexpr int kPartLoads = kMaxBlocks / 128;
 struct PrologueLoads {
-    double v[3];        // this thread's share of the producer's partial sums (and counts)
+    d2 a[kPartLoads], b[kPartLoads];  // the lane's share of the producer's partial sums: the first quantity's, the second's
+    u2 n[kPartLoads];                 // and of the counts
     float eta_prev;     // eta_{m-1}
     uint32_t status;    // status bits accumulated up to stage m-1
     bool frozen;        // an empty exceedance set has stopped the refinement
     float list_eta;     // the producer's lists hold every entry above this
     float seen;         // where the next stage's threshold fell last time (hint), NaN if unknown
-    FitRecord prev_fit; // the producer's candidate fit (block 0, thread 0 only)
 };
 
 // Whether all thresholds so far fell into their bands (see k_fit_bands), and then the stage's own band; the last stage's
@@ -214,37 +235,63 @@ struct BandEdges {
     float cand;  // > 0: what the stage's lists are to start from then (a batch's first stage)
 };
 
+// The quantity that the law adds to the plain sum: rows of the partial sums of the first pass and of a stage.
+__device__ __forceinline__ int second_row(int dist, int m)
+{
+    if (dist == kDistExp) return 0;  // none: the first once more
+    return m == 1 && dist == kDistGamma ? 2 : 1;
+}
+
 template <bool FLAT = false>
 __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, bool auto_src)
 {
     const int m = p.stage;  // 1-based
-    const uint32_t t = threadIdx.x;
-    const bool have = t < p.nblocks;  // one thread per block of the kernel that produced the partial sums
     PrologueLoads g;
+    if (!FLAT && threadIdx.x < 64) {
+        const double* first = p.part_in;
+        const double* second = p.part_in + (size_t)second_row(p.dist, m) * kBatchBlocks;
+        const uint32_t most = ((p.nblocks - 1) & ~1u) + b.none;  // pairs past the last block's are that one's again: an unused value at most
+#pragma unroll
+        for (int k = 0; k < kPartLoads; ++k) {
+            const uint32_t i = min((uint32_t)(128 * k) + 2 * threadIdx.x, most);
+            g.a[k] = *reinterpret_cast<const d2*>(first + i);
+            g.b[k] = *reinterpret_cast<const d2*>(second + i);
+            g.n[k] = *reinterpret_cast<const u2*>(p.blk_in + i);
+        }
+    }
     g.seen = (p.theta > 0.0f && p.use_hint) ? p.st->theta_seen[m] : __builtin_nanf("");
-    g.prev_fit.gpd = 0;
-    g.prev_fit.loc = 0.0f;
-    g.prev_fit.s = g.prev_fit.c = g.prev_fit.a = g.prev_fit.b = 0.0;
-    if (auto_src && p.prev_cand && b.id == 0 && t == 0) g.prev_fit = p.st->cand_fit[m - 1];
     g.list_eta = auto_src ? p.st->list_eta[m - 1] : 0.0f;
     g.eta_prev = 0.0f;
     g.status = 0;
     g.frozen = false;
-    if (FLAT) {
-        g.v[0] = g.v[1] = g.v[2] = 0.0;  // flat_sums
-    } else if (m == 1) {
-        g.v[0] = have ? p.part_in[0 * kBatchBlocks + t] : 0.0;
-        g.v[1] = (have && p.dist == kDistGpd) ? p.part_in[1 * kBatchBlocks + t] : 0.0;
-        g.v[2] = (have && p.dist == kDistGamma) ? p.part_in[2 * kBatchBlocks + t] : 0.0;
-    } else {
-        g.v[0] = have ? p.part_in[0 * kBatchBlocks + t] : 0.0;
-        g.v[1] = (have && p.dist != kDistExp) ? p.part_in[1 * kBatchBlocks + t] : 0.0;
-        g.v[2] = have ? (double)p.blk_in[t] : 0.0;  // counts < 2^31: exact in fp64
+    if (m > 1) {
         g.eta_prev = p.st->diag.eta[m - 2];
         g.status = p.st->status_after[m - 1];
         g.frozen = p.st->frozen_after[m - 1] != 0;
     }
     return g;
+}
+
+// What the stage's fit is made from, by the first wave: sums of |x| (stage 1) or y = |x| - eta_{m-1} over the exceedances,
+// the law's second quantity, and the exceedances' number (0 in stage 1).
+struct StageSums {
+    double first, second, n;
+};
+__device__ __forceinline__ StageSums prologue_sums(const Params& p, const PrologueLoads& g)
+{
+    double v[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kPartLoads; ++k) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const bool have = (uint32_t)(128 * k + j) + 2 * threadIdx.x < p.nblocks;
+            v[0] += have ? g.a[k][j] : 0.0;
+            v[1] += have ? g.b[k][j] : 0.0;
+            v[2] += have ? (double)g.n[k][j] : 0.0;  // counts < 2^31: exact in fp64
+        }
+    }
+    wave_totals(v);
+    return StageSums{v[0], v[1], v[2]};
 }
 
 // Behind an unfolded flat first pass (stage 1 of a batch) a thread's share of the partial sums is several values:
@@ -271,7 +318,8 @@ __device__ __forceinline__ FlatLoads flat_load(const FlatPart& fp, int dist)
     }
     return f;
 }
-__device__ __forceinline__ void flat_sums(const FlatPart& fp, const FlatLoads& f, int dist, PrologueLoads& g)
+// the thread's share: of the sum of magnitudes, of the second quantity, and 0 exceedances
+__device__ __forceinline__ void flat_sums(const FlatPart& fp, const FlatLoads& f, double (&v)[3])
 {
     double a = 0.0, b = 0.0;
 #pragma unroll
@@ -281,27 +329,34 @@ __device__ __forceinline__ void flat_sums(const FlatPart& fp, const FlatLoads& f
             b += f.b[k];
         }
     }
-    g.v[0] = a;
-    g.v[1] = dist == kDistGpd ? b : 0.0;
-    g.v[2] = dist == kDistGamma ? b : 0.0;
+    v[0] = a;
+    v[1] = b;
+    v[2] = 0.0;
 }
 
-// Evaluates eta for stage p.stage from the reduced sums in g.v; called by the first wave of a block, and block 0's
-// thread 0 records the stage in the diagnostics.  g.status and g.frozen leave with what this stage adds to them.
-__device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto_src, PrologueLoads& g,
-                                               const BandEdges& band = BandEdges{})
+// What block 0 keeps of a stage.
+struct StageRecord {
+    double stats[3];
+    unsigned long long n;
+    uint32_t status;  // accumulated, this stage's bits among them
+    bool frozen;
+    Fit fit;
+    float loc;
+};
+
+// Evaluates eta for stage p.stage from the reduced sums; called by the first wave of a block.
+__device__ __forceinline__ StageEta stage_eval(const Params& p, bool auto_src, const PrologueLoads& g, const StageSums& sums,
+                                               StageRecord& rec, const BandEdges& band = BandEdges{})
 {
     const int m = p.stage;  // 1-based
-    const uint32_t t = threadIdx.x;
-    const double L = stage_L(p, m - 1);
+    const double L = p.L_stage;
     // candidate threshold of this kernel's lists: log-ratio Lw > L, or none
     double Lw = 0.0;
     if (p.theta > 0.0f) {
         float theta = p.theta;
         if (g.seen == g.seen) theta = fminf(fmaxf(g.seen - kHintMargin, p.theta_min), kHintMax);
-        Lw = L + (double)theta * stage_L(p, m);
+        Lw = L + (double)theta * p.L_next;
     }
-    const FitRecord prev_fit = g.prev_fit;
     Fit fit = fit_linear(0.0, 0.0);
     float loc = 0.0f;
     uint32_t status = g.status;
@@ -315,14 +370,14 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
     if (m == 1) {
         n = (unsigned long long)p.d;
         const double d = (double)p.d;
-        const double mu = g.v[0] / d;
+        const double mu = sums.first / d;
         double var = 0.0, mulog = 0.0;
         bool finite = isfinite(mu);
         if (p.dist == kDistGpd) {
-            var = g.v[1] / d - mu * mu;
+            var = sums.second / d - mu * mu;
             finite = finite && isfinite(var);
         } else if (p.dist == kDistGamma) {
-            mulog = (g.v[2] / d) * 0.6931471805599453094;  // log2 -> natural log
+            mulog = (sums.second / d) * 0.6931471805599453094;  // log2 -> natural log
             finite = finite && isfinite(mulog);
         }
         stats[0] = mu;
@@ -346,15 +401,15 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
         }
     } else {
         const float eta_prev = g.eta_prev;
-        n = (unsigned long long)g.v[2];
+        n = (unsigned long long)sums.n;
         r.eta = r.eta_w = eta_prev;
         if (!frozen) {
             if (n == 0) {  // nothing exceeds eta_prev: keep it for all later stages
                 frozen = true;
                 status |= kStStopped;
             } else {
-                const double ybar = g.v[0] / (double)n;
-                const double yvar = p.dist == kDistExp ? 0.0 : g.v[1] / (double)n - ybar * ybar;
+                const double ybar = sums.first / (double)n;
+                const double yvar = p.dist == kDistExp ? 0.0 : sums.second / (double)n - ybar * ybar;
                 stats[0] = ybar;
                 stats[1] = yvar;
                 fit = pot_fit(p.dist, ybar, yvar, status);
@@ -372,69 +427,104 @@ __device__ __forceinline__ StageEta stage_eval(const Params& p, Blk b, bool auto
     r.lists_ok = auto_src && !band.live && r.eta >= g.list_eta;
     if (r.hit && band.cand > 0.0f) r.eta_w = band.cand;
     if (!r.hit && (band.live || band.over || (auto_src && !r.lists_ok))) status |= kStFallback;
-    if (b.id == 0 && t == 0) {
-        p.st->diag.eta[m - 1] = r.eta;
-        p.st->diag.n[m - 1] = (int64_t)n;
-        p.st->diag.stats[m - 1][0] = stats[0];
-        p.st->diag.stats[m - 1][1] = stats[1];
-        p.st->diag.stats[m - 1][2] = stats[2];
-        p.st->status_after[m] = status;
-        p.st->frozen_after[m] = frozen ? 1u : 0u;
-        p.st->list_eta[m] = r.eta_w;
-        if (p.theta > 0.0f) {
-            FitRecord rec;
-            rec.gpd = fit.gpd ? 1 : 0;
-            rec.loc = loc;
-            rec.s = fit.s;
-            rec.c = fit.c;
-            rec.a = fit.a;
-            rec.b = fit.b;
-            p.st->cand_fit[m] = rec;
-        }
-        if (auto_src && p.prev_cand) {
-            // invert the producer's quantile function at this stage's threshold:
-            // eta = loc + Q(L_{m-1} + theta * L_m)  ->  theta
-            const double tq = (double)r.eta - (double)prev_fit.loc;
-            const double Lq = prev_fit.gpd ? log1p(tq * prev_fit.a / prev_fit.b) / prev_fit.a : (tq - prev_fit.c) / prev_fit.s;
-            const float seen = (float)((Lq - stage_L(p, m - 2)) / L);
-            p.st->theta_seen[m - 1] = (frozen || !(fabsf(seen) < 1.0e6f)) ? __builtin_nanf("") : seen;
-        }
-    }
-    g.status = status;
-    g.frozen = frozen;
+    rec.stats[0] = stats[0];
+    rec.stats[1] = stats[1];
+    rec.stats[2] = stats[2];
+    rec.n = n;
+    rec.status = status;
+    rec.frozen = frozen;
+    rec.fit = fit;
+    rec.loc = loc;
     return r;
 }
 
-// Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
-// in every thread of every block.  Block 0 records the stage in the diagnostics.
-__device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, PrologueLoads& g, double (*sh)[4],
-                                    const BandEdges& band = BandEdges{})
+// Block 0's first thread: the stage in the diagnostics and for the stages behind it.
+__device__ __forceinline__ void stage_record(const Params& p, const StageEta& r, const StageRecord& rec)
 {
+    const int m = p.stage;
+    p.st->diag.eta[m - 1] = r.eta;
+    p.st->diag.n[m - 1] = (int64_t)rec.n;
+    p.st->diag.stats[m - 1][0] = rec.stats[0];
+    p.st->diag.stats[m - 1][1] = rec.stats[1];
+    p.st->diag.stats[m - 1][2] = rec.stats[2];
+    p.st->status_after[m] = rec.status;
+    p.st->frozen_after[m] = rec.frozen ? 1u : 0u;
+    p.st->list_eta[m] = r.eta_w;
+    if (p.theta > 0.0f) {
+        FitRecord f;
+        f.gpd = rec.fit.gpd ? 1 : 0;
+        f.loc = rec.loc;
+        f.s = rec.fit.s;
+        f.c = rec.fit.c;
+        f.a = rec.fit.a;
+        f.b = rec.fit.b;
+        p.st->cand_fit[m] = f;
+    }
+}
+
+// One thread of the last stage's kernel: where the threshold fell for which stage p.cand_stage wrote candidate lists, for
+// the next call.  Inverts that stage's quantile function at the next one's threshold: eta = loc + Q(L_s + theta L_{s+1}).
+// Here, beside the reservation's round trip, and not where the threshold is evaluated: a logarithm and two divisions more
+// than the other blocks have, 0.6 us in the chain of block 0.
+__device__ __forceinline__ void hint_record(const Params& p, float eta_last)
+{
+    const int s = p.cand_stage;
+    if (s == 0) return;
+    const FitRecord f = p.st->cand_fit[s];
+    const float eta = s + 1 == p.M ? eta_last : p.st->diag.eta[s];
+    const bool frozen = p.st->frozen_after[s + 1] != 0;
+    const double tq = (double)eta - (double)f.loc;
+    const double Lq = f.gpd ? log1p(tq * f.a / f.b) / f.a : (tq - f.c) / f.s;
+    const float seen = (float)((Lq - stage_L(p, s - 1)) / stage_L(p, s));
+    p.st->theta_seen[s] = (frozen || !(fabsf(seen) < 1.0e6f)) ? __builtin_nanf("") : seen;
+}
+
+template <typename T>
+__device__ __forceinline__ void present(T x) { asm volatile("" ::"v"(x)); }
+
+// Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
+// in every thread of every block.  Block 0 records the stage in the diagnostics.  FLAT: `v` is the thread's share of the
+// sums (see flat_sums), which the whole block adds up.
+template <bool FLAT = false>
+__device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, const PrologueLoads& g, double (*sh)[4],
+                                                    const BandEdges& band = BandEdges{}, double (*v)[3] = nullptr)
+{
+    __shared__ float sh_eta[4];
     const uint32_t t = threadIdx.x;
-    StageEta r;
-    r.eta = r.eta_w = 0.0f;
-    r.lists_ok = r.hit = false;
-    block_sum<3>(g.v, sh);
+    // have what the closed form asks for loaded by now: the compiler would put the loads where it is used, a round trip
+    // behind the sums
+    present(g.eta_prev);
+    present(g.list_eta);
+    present(g.seen);
+    present(g.status);
+    present(g.frozen ? 1u : 0u);
+    present(band.lo);
+    present(band.hi);
+    present(band.cand);
+    if constexpr (FLAT) block_sum<3>(*v, sh);
     // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
     // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
     // arithmetic and the prologue lasts that much longer (measured).
-    if (t < 64) r = stage_eval(p, b, auto_src, g, band);
-    __syncthreads();  // every thread has left block_sum: sh is free
-    if (t == 0) {
-        float* out = reinterpret_cast<float*>(&sh[0][0]);
-        out[0] = r.eta;
-        out[1] = r.eta_w;
-        out[2] = r.lists_ok ? 1.0f : 0.0f;
-        out[3] = r.hit ? 1.0f : 0.0f;
+    StageEta r;
+    StageRecord rec;
+    if (t < 64) {
+        StageSums sums;
+        if constexpr (FLAT) sums = StageSums{(*v)[0], (*v)[1], (*v)[2]};
+        else sums = prologue_sums(p, g);
+        r = stage_eval(p, auto_src, g, sums, rec, band);
+        if (t == 0) {
+            sh_eta[0] = r.eta;
+            sh_eta[1] = r.eta_w;
+            sh_eta[2] = r.lists_ok ? 1.0f : 0.0f;
+            sh_eta[3] = r.hit ? 1.0f : 0.0f;
+        }
     }
     __syncthreads();
-    {
-        const float* in = reinterpret_cast<const float*>(&sh[0][0]);
-        r.eta = in[0];
-        r.eta_w = in[1];
-        r.lists_ok = in[2] != 0.0f;
-        r.hit = in[3] != 0.0f;
-    }
+    if (b.id == 0 && t == 0) stage_record(p, r, rec);
+    r.eta = sh_eta[0];
+    r.eta_w = sh_eta[1];
+    r.lists_ok = sh_eta[2] != 0.0f;
+    r.hit = sh_eta[3] != 0.0f;
     return r;
 }
 
@@ -442,7 +532,7 @@ __device__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, Prolo
 __device__ __forceinline__ StageEta stage_prologue(const Params& p, Blk b, bool auto_src, double (*sh)[4],
                                                    const BandEdges& band = BandEdges{})
 {
-    PrologueLoads g = prologue_load(p, b, auto_src);
+    const PrologueLoads g = prologue_load(p, b, auto_src);
     return prologue_finish(p, b, auto_src, g, sh, band);
 }
 
@@ -545,9 +635,7 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b, const AccTile* 
     FitSums<DIST> f;
     if (w < p.nwaves) acc_sweep<EC, fit_writes<EC, GT>(), GT, PAST>(p, w, lane, f, first);
     double v[3] = {f.s1, f.s2, f.sl + (double)f.se};
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    v[2] = wave_sum(v[2]);
+    wave_totals(v);
     if (lane == 0) {
         sh[wib][0] = v[0];
         sh[wib][1] = v[1];
@@ -594,9 +682,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat(Params p, double* __res
             if (i + j >= 0 && i + j < p.d) fit_one<DIST, EC, GT>(p, i + j, s1, s2, sl, se);
     }
     double v[3] = {s1, s2, sl + (double)se};
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    v[2] = wave_sum(v[2]);
+    wave_totals(v);
     if (lane == 0) {
         sh[wib][0] = v[0];
         sh[wib][1] = v[1];
@@ -625,9 +711,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce(Params p, const double* _
         if (p.dist == kDistGpd) v[1] += flat_part[(size_t)nflat + b];
         if (p.dist == kDistGamma) v[2] += flat_part[2 * (size_t)nflat + b];
     }
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    v[2] = wave_sum(v[2]);
+    wave_totals(v);
     if (lane == 0 && slot < (uint32_t)kMaxBlocks) {
         p.part_out[0 * kBatchBlocks + slot] = v[0];
         p.part_out[1 * kBatchBlocks + slot] = v[1];
@@ -815,14 +899,26 @@ __device__ __forceinline__ void fit_bands_body(const Params& p, Blk b, const Ban
             if (n > seg_slots(p, w) / kBandCrowd) p.st->band_over = 1;
         }
     }
-    double v[3 + 3 * NB];
-    v[0] = wave_sum(f.f.s1);
-    v[1] = DIST == kDistGpd ? wave_sum(f.f.s2) : 0.0;
-    v[2] = DIST == kDistGamma ? wave_sum(f.f.sl + (double)f.f.se) : 0.0;
+    // per band y and y^2, and |x| with the law's second quantity
+    constexpr int S = DIST == kDistExp ? 1 : 2;
+    double w_sum[S * (NB + 1)];
+    w_sum[0] = f.f.s1;
+    if constexpr (DIST == kDistGpd) w_sum[1] = f.f.s2;
+    if constexpr (DIST == kDistGamma) w_sum[1] = f.f.sl + (double)f.f.se;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
-        v[3 + 3 * k] = wave_sum(f.y[k]);
-        v[4 + 3 * k] = DIST != kDistExp ? wave_sum(f.yy[k]) : 0.0;
+        w_sum[S * (k + 1)] = f.y[k];
+        if constexpr (S > 1) w_sum[S * (k + 1) + 1] = f.yy[k];
+    }
+    wave_totals(w_sum);
+    double v[3 + 3 * NB];
+    v[0] = w_sum[0];
+    v[1] = DIST == kDistGpd ? w_sum[S - 1] : 0.0;
+    v[2] = DIST == kDistGamma ? w_sum[S - 1] : 0.0;
+#pragma unroll
+    for (int k = 0; k < NB; ++k) {
+        v[3 + 3 * k] = w_sum[S * (k + 1)];
+        v[4 + 3 * k] = S > 1 ? w_sum[S * (k + 1) + S - 1] : 0.0;
         v[5 + 3 * k] = (double)f.n[k];
     }
     if (lane == 0) {
@@ -974,12 +1070,11 @@ __device__ __forceinline__ void stage_epilogue(const Params& p, Blk b, int lane,
 {
     if (lane == 0) sh_cnt[wib] = count;
     if (STATS) {
-        sy = wave_sum(sy);
-        syy = wave_sum(syy);
-        __syncthreads();  // the prologue's reads of sh are done
-        if (lane == 0) {
-            sh[wib][0] = sy;
-            sh[wib][1] = syy;
+        double v[2] = {sy, syy};
+        wave_totals(v);
+        if (lane == 0) {  // the prologue is done with sh
+            sh[wib][0] = v[0];
+            sh[wib][1] = v[1];
         }
     }
     __syncthreads();
@@ -1060,12 +1155,12 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     // prologue's go first (the memory counter retires in order: behind the tiles they would wait for
     // them), then the first tiles, so that the stream runs while the partial sums are reduced and the
     // closed form is evaluated.
-    PrologueLoads g = prologue_load<FLAT>(p, b, false);
+    BandEdges band = {};
+    if constexpr (BANDS || CHUNKS) band = band_load<true>(p);
+    const PrologueLoads g = prologue_load<FLAT>(p, b, false);
     FlatLoads f;
     if constexpr (FLAT) f = flat_load(fp, p.dist);
-    BandEdges band = {};
     if constexpr (CHUNKS) {
-        band = band_load<true>(p);
         band.over = band.live && p.st->band_over != 0;
         band.live = band.live && !band.over;
         band.cand = p.st->band.lo[1];
@@ -1082,9 +1177,8 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         src4 = reinterpret_cast<const int4*>(p.band_seg + seg_begin(p, active ? w : 0));
         q0 = src4[lane];
         n_in = active ? p.band_cnt[w] : 0u;
+        q1 = src4[64 + lane];  // a wave owns several tiles
         above = band_above_load(p, b);
-        band = band_load<true>(p);
-        if (band.live) q1 = src4[64 + lane];  // a wave owns several tiles
     }
     constexpr int U = CHUNKS ? 4 : 1;  // lists a wave requests at once, the first ones before the threshold is known
     int2 head[U];
@@ -1111,9 +1205,10 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
             }
         }
     }
-    if constexpr (FLAT) flat_sums(fp, f, p.dist, g);
+    double share[3];
+    if constexpr (FLAT) flat_sums(fp, f, share);
 
-    const StageEta se = prologue_finish(p, b, false, g, sh, band);
+    const StageEta se = prologue_finish<FLAT>(p, b, false, g, sh, band, &share);
 
     uint32_t run = 0, ns = 0;
     double sy = 0.0, syy = 0.0;
@@ -1193,7 +1288,8 @@ __device__ __forceinline__ void lists_body(const Params& p, Blk b)
     const size_t seg = seg_begin(p, active ? w : 0);
     const int2* src = p.seg_in;
     const uint32_t* cnt = p.cnt_in;
-    const BandEdges band = band_load<BANDS>(p);
+    const BandEdges band = band_load<BANDS>(p);  // names the lists: the first round trip, beside the prologue's
+    const PrologueLoads g = prologue_load(p, b, true);
     if (band.live) {
         src = p.band_seg;
         cnt = p.band_cnt;
@@ -1205,11 +1301,11 @@ __device__ __forceinline__ void lists_body(const Params& p, Blk b)
     int4 q1 = {};
     BandAbove above = {};
     if constexpr (BANDS) {
-        if (band.live) q1 = src4[64 + lane];
+        q1 = src4[64 + lane];
         above = band_above_load(p, b);
     }
 
-    const StageEta se = stage_prologue(p, b, true, sh, band);
+    const StageEta se = prologue_finish(p, b, true, g, sh, band);
     const float eta = se.eta;
 
     uint32_t ns = 0;
@@ -1387,7 +1483,8 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
     const uint32_t first = b.id * per_block + wib;
     const uint32_t last = min(p.nwaves, (b.id + 1) * per_block);
 
-    const BandEdges band = band_load<BANDS>(p);
+    const BandEdges band = band_load<BANDS>(p);  // names the lists: the first round trip, beside the prologue's
+    const PrologueLoads g = prologue_load(p, b, true);
     const int2* seg = band.live ? p.band_seg : p.seg_in;
     const uint32_t* cnt = band.live ? p.band_cnt : p.cnt_in;
     // first group of lists: counts and first 64 slots of each (128 behind a first pass with bands, whose lists hold what
@@ -1406,7 +1503,7 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
         }
     }
 
-    const StageEta se = stage_prologue(p, b, true, sh, band);
+    const StageEta se = prologue_finish(p, b, true, g, sh, band);
     const float eta = se.eta;
     const bool from_lists = se.lists_ok || se.hit;
 
@@ -1455,6 +1552,7 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
     }
     // by another wave, beside the round trip of the reservation: behind it 25.6 M elements, 3 stages took 76.1 us a call, so 75.5
     if (b.id == 0 && threadIdx.x == kBlock - 64) bands_record(p, eta);
+    if (b.id == 0 && threadIdx.x == kBlock - 128) hint_record(p, eta);
     __syncthreads();
     unsigned long long pos = sh_base + off;
 
@@ -1663,8 +1761,7 @@ constexpr int kSmallWaves = kSmallBlock / 64;
 template <int Q>
 __device__ __forceinline__ void small_sum(double (&v)[Q], double (*sh)[4], int lane, int wib)
 {
-#pragma unroll
-    for (int q = 0; q < Q; ++q) v[q] = wave_sum(v[q]);
+    wave_totals(v);
     if (lane == 0) {
 #pragma unroll
         for (int q = 0; q < Q; ++q) sh[wib][q] = v[q];
@@ -1695,8 +1792,8 @@ __device__ __forceinline__ void small_fit(const float* x, int32_t t, int32_t d, 
         if (DIST != kDistGamma || i + 3 < d) fit_accum<DIST>(c.w, s1, s2, sl, se);
     }
     v[0] = s1;
-    v[1] = s2;
-    v[2] = sl + (double)se;
+    v[1] = DIST == kDistGamma ? sl + (double)se : s2;
+    v[2] = 0.0;
 }
 
 // N: float4s per thread, 4 * 1024 * N >= d
@@ -1751,20 +1848,24 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 
     PrologueLoads g = {};
     g.seen = __builtin_nanf("");
+    double v[3];
     switch (p.dist) {
-        case kDistExp: small_fit<kDistExp>(x, t, d, g.v); break;
-        case kDistGamma: small_fit<kDistGamma>(x, t, d, g.v); break;
-        default: small_fit<kDistGpd>(x, t, d, g.v); break;
+        case kDistExp: small_fit<kDistExp>(x, t, d, v); break;
+        case kDistGamma: small_fit<kDistGamma>(x, t, d, v); break;
+        default: small_fit<kDistGpd>(x, t, d, v); break;
     }
     auto evaluate = [&](int m) {  // the sums of all threads -> eta_m, the same in every thread
-        small_sum<3>(g.v, sh, lane, wib);
+        small_sum<3>(v, sh, lane, wib);
         if (wib == 0) {
             p.stage = m;
-            const StageEta r = stage_eval(p, Blk{0, 1}, false, g);
+            p.L_stage = stage_L(p, m - 1);
+            StageRecord rec;
+            const StageEta r = stage_eval(p, false, g, StageSums{v[0], v[1], v[2]}, rec);
             if (lane == 0) {
                 sh_eta = r.eta;
-                sh_status = g.status;
-                sh_frozen = g.frozen ? 1u : 0u;
+                sh_status = rec.status;
+                sh_frozen = rec.frozen ? 1u : 0u;
+                stage_record(p, r, rec);
             }
         }
         __syncthreads();
@@ -1793,9 +1894,9 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
                 syy = __builtin_fma(y, y, syy);
             }
         }
-        g.v[0] = sy;
-        g.v[1] = syy;
-        g.v[2] = (double)ns;
+        v[0] = sy;
+        v[1] = syy;
+        v[2] = (double)ns;
         evaluate(m);
     }
 
@@ -1927,10 +2028,12 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.stage = a.stage;
 #pragma unroll
     for (int m = 0; m < SIDCO_MAX_STAGES; ++m) p.L[m] = a.L[m];
+    p.L_stage = a.L_stage;
+    p.L_next = a.L_next;
     p.theta = a.theta;
     p.theta_min = a.theta_min;
     p.use_hint = a.use_hint;
-    p.prev_cand = a.prev_cand;
+    p.cand_stage = a.cand_stage;
     p.st = &a.tb->st[t];
     p.part_in = a.part[a.in] + ds.first_block;
     p.part_out = a.part[a.out] + ds.first_block;
@@ -1951,6 +2054,7 @@ __device__ __forceinline__ Params batch_params(const BatchArgs& a, bool final_gr
     p.band_max = kBandMaxWidthBatch;
     b.id = gb - (final_grid ? ds.first_final : ds.first_block);
     b.n = final_grid ? ds.nfinal : ds.nblocks;
+    b.none = 0;
     return p;
 }
 
@@ -1980,12 +2084,18 @@ __global__ __launch_bounds__(kBlock, 4) void k_fit_bands(Params p)
 template <bool STATS, bool WRITE, bool KEEP, bool BANDS>
 __global__ __launch_bounds__(kBlock, 4) void k_compact(Params p)
 {
-    compact_body<STATS, WRITE, false, KEEP, BANDS>(p, whole_grid());
+    compact_body<STATS, WRITE, false, KEEP, BANDS>(p, stage_grid(p));
 }
 template <bool BANDS>
-__global__ __launch_bounds__(kBlock, 4) void k_lists(Params p) { lists_body<BANDS>(p, whole_grid()); }
+__global__ __launch_bounds__(kBlock, 4) void k_lists(Params p)
+{
+    lists_body<BANDS>(p, stage_grid(p));
+}
 template <bool BANDS>
-__global__ __launch_bounds__(kBlock) void k_final_lists(Params p) { final_body<BANDS>(p, whole_grid()); }
+__global__ __launch_bounds__(kBlock) void k_final_lists(Params p)
+{
+    final_body<BANDS>(p, stage_grid(p));
+}
 __global__ __launch_bounds__(kBlock) void k_gather(Params p) { gather_body(p, whole_grid()); }
 
 template <int DIST, bool EC, int GT>
@@ -2119,13 +2229,21 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
         flat_chunk<DIST, EC, GT, false>(p, first, T1, wib, lane, f, fb);
     }
     double v[Q];
-    v[0] = wave_sum(f.s1);
-    v[1] = wave_sum(f.s2);
-    v[2] = wave_sum(f.sl + (double)f.se);
-    if constexpr (BANDS) {
-        v[3] = wave_sum(fb.y);
-        v[4] = DIST != kDistExp ? wave_sum(fb.yy) : 0.0;
-        v[5] = (double)fb.n;
+    {
+        double w_sum[BANDS ? 4 : 2] = {f.s1, DIST == kDistGamma ? f.sl + (double)f.se : f.s2};
+        if constexpr (BANDS) {
+            w_sum[2] = fb.y;
+            w_sum[3] = fb.yy;
+        }
+        wave_totals(w_sum);
+        v[0] = w_sum[0];
+        v[1] = DIST == kDistGpd ? w_sum[1] : 0.0;
+        v[2] = DIST == kDistGamma ? w_sum[1] : 0.0;
+        if constexpr (BANDS) {
+            v[3] = w_sum[2];
+            v[4] = w_sum[3];
+            v[5] = (double)fb.n;
+        }
     }
     if (lane == 0) {
 #pragma unroll
@@ -2172,9 +2290,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
         if (p.dist == kDistGpd) v[1] += part[stride + c];
         if (p.dist == kDistGamma) v[2] += part[2 * stride + c];
     }
-    v[0] = wave_sum(v[0]);
-    v[1] = wave_sum(v[1]);
-    v[2] = wave_sum(v[2]);
+    wave_totals(v);
     if (lane == 0) {
         p.part_out[0 * kBatchBlocks + b.id] = v[0];
         p.part_out[1 * kBatchBlocks + b.id] = v[1];
