@@ -361,11 +361,15 @@ inline uint32_t fit_flat_blocks(int64_t d, uint32_t shift)
 {
     return (uint32_t)(((d + shift + 3) / 4 + kFlatBlock - 1) / kFlatBlock);
 }
-// k_small's block, and the longest vector that goes through it: 144 KB of the 160 KB of LDS.  A training step's call
-// and its scatter, one kernel against three to five: 64 elements 29.4 -> 19.3 us, 20000 28.4 -> 19.5, 36000
-// 30.2 -> 21.6 (three stages), 30011 27.1 -> 20.3 (one stage).
-constexpr int kSmallBlock = 1024;
-constexpr int kSmallMaxD = 9 * 4 * kSmallBlock;
+// k_small's block, its threads that hold data, the longest vector that goes through it, and the pairs that a data wave's
+// list has room for with N float4s per lane: all and a step of the wave more, or what 150 of the 160 KB of LDS hold.  A
+// training step's call and its scatter, one kernel against the kernels of a longer vector, us: 64 elements, three stages 12.8
+// and 20.3 (the host's launches), 20000 13.1 and 20.4, 36000 16.4 and 20.7, 36864, two stages, ratio 0.1 16.0 and 18.1; the
+// gamma law at 36000 and 0.1, of which it keeps 31 %, 22.8 and 19.6.
+constexpr int kSmallBlock = 1024, kSmallWaves = kSmallBlock / 64, kSmallData = kSmallBlock - 64;
+constexpr int kSmallMaxD = 36864;
+template <int N>
+constexpr uint32_t kSmallList = 256 * N + 64 < 1280 ? 256 * N + 64 : 1280;
 void launch_small(const Params& p, hipStream_t s);
 void launch_fit(const Params& p, bool flat, double* scratch, hipStream_t s);
 // A call that repeats a shape but has no bands (its thresholds jump) sweeps past the caches from this length on.  A training

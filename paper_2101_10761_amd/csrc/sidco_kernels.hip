@@ -1749,211 +1749,320 @@ __device__ __forceinline__ void gather_body(const Params& p, Blk b)
 }
 
 // ---------------------------------------------------------------------------------------------
-// k_small: a whole call in one block of 1024 threads, for a vector short enough to stay in the LDS of one CU.  A call
-// of several kernels on such a vector is all launches, prologues and drains; here a stage is a sweep over LDS, a
-// block sum and the closed form.  All loads of a thread are in flight at once: one round trip to HBM.  What bounds it
-// is a serial chain on one CU: at 64 elements and three stages 9 us, all latency; at 30011 elements 16.5 us against
-// 20.6 for the four kernels and the three launches between them.  It pays as far as the LDS reaches.
+// k_small: a whole call in one block of 1024 threads, for a vector short enough for one CU.  A call
+// of several kernels on such a vector is all launches, prologues and drains; here a stage is a sweep over registers or
+// LDS, a sum over the block and the closed form.  All loads of a thread are in flight at once: one round trip to HBM.
+// Fifteen waves hold the vector in registers.  Once the first threshold
+// is known a wave lists what exceeds it in LDS, and everything after that reads the lists: their sums, the later stages,
+// the selection.  (A wave whose exceedances outgrow its list goes on with the registers.)  The sixteenth wave evaluates
+// the closed forms; while the data are on their way it runs through them twice for nothing, so that their code is in the
+// instruction cache when the sums arrive.
+// What bounds it is a serial chain on one CU.  At 30011 elements, GPD, three stages, with the vector in LDS, every sweep and
+// the selection over all of it, and one wave of the sixteen evaluating, the kernel took 16.4 us; now 12.9 (a training step 18.2 and
+// 15.2).  With the residual stored as it was formed the last wave had its data 2700 cycles later; with a branch around every
+// element's way to the list the lists took 6300 cycles, 5500 without.
 // The sums, the thresholds and the order of the output are fixed.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSmallWaves = kSmallBlock / 64;
 
-template <int Q>
-__device__ __forceinline__ void small_sum(double (&v)[Q], double (*sh)[4], int lane, int wib)
-{
-    wave_totals(v);
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < Q; ++q) sh[wib][q] = v[q];
-    }
-    __syncthreads();
-    if (wib == 0) {  // the wave that evaluates the closed form
-#pragma unroll
-        for (int q = 0; q < Q; ++q) {
-            double t = 0.0;
-#pragma unroll
-            for (int i = 0; i < kSmallWaves; ++i) t += sh[i][q];
-            v[q] = t;
-        }
-    }
-}
+// A data wave's share of the vector: N float4s per lane.
+template <int DIST, int N>
+struct SmallShare {
+    f4 c[N];  // zeros past the end of the vector
 
-template <int DIST>
-__device__ __forceinline__ void small_fit(const float* x, int32_t t, int32_t d, double (&v)[3])
-{
-    double s1 = 0.0, s2 = 0.0, sl = 0.0;
-    int se = 0;
-#pragma unroll 1
-    for (int32_t i = 4 * t; i < d; i += 4 * kSmallBlock) {
-        const f4 c = *reinterpret_cast<const f4*>(x + i);  // past the end zeros, which leave s1 and s2 alone
-        fit_accum<DIST>(c.x, s1, s2, sl, se);
-        if (DIST != kDistGamma || i + 1 < d) fit_accum<DIST>(c.y, s1, s2, sl, se);
-        if (DIST != kDistGamma || i + 2 < d) fit_accum<DIST>(c.z, s1, s2, sl, se);
-        if (DIST != kDistGamma || i + 3 < d) fit_accum<DIST>(c.w, s1, s2, sl, se);
-    }
-    v[0] = s1;
-    v[1] = DIST == kDistGamma ? sl + (double)se : s2;
-    v[2] = 0.0;
-}
-
-// N: float4s per thread, 4 * 1024 * N >= d
-template <bool EC, int GT, int N>
-__global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
-{
-    extern __shared__ __align__(16) float x[];  // 4 * kSmallBlock * N
-    __shared__ double sh[kSmallWaves][4];
-    __shared__ uint32_t sh_cnt[kSmallWaves];
-    __shared__ float sh_eta;
-    __shared__ uint32_t sh_status, sh_frozen;
-    const int32_t t = (int32_t)threadIdx.x, d = (int32_t)p.d;
-    const int lane = t & 63, wib = t >> 6;
-    p.theta = 0.0f;  // no candidate lists
-
-    if (d >= 4) {
-        // whole float4s, wherever the buffers start; past the end the last one again: the loads stay unconditional
-        f4 c[N];
+    // f(valid, value, index), the wave together
+    template <typename F>
+    __device__ __forceinline__ void each(int32_t t, int32_t d, F f) const
+    {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            const int32_t i = 4 * (u * kSmallBlock + t);
-            c[u] = load_grad4<GT, true>(p.grad, (size_t)(i + 4 <= d ? i : d - 4));
+            const int32_t i = 4 * (u * kSmallData + t);
+            if (4 * u * kSmallData < d) {  // uniform
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f(i + j < d, c[u][j], i + j);
+            }
+        }
+    }
+};
+
+// Sums of y = |x| - eta and y^2 over what exceeds eta, and their number, of one wave.
+template <int DIST>
+struct SmallSums {
+    double y = 0.0, yy = 0.0;
+    uint32_t n = 0;  // wave-uniform
+    __device__ __forceinline__ void add(bool valid, float x, float eta)
+    {
+        const float a = __builtin_fabsf(x);
+        const bool sel = valid && a > eta;
+        n += (uint32_t)__popcll(__ballot(sel));
+        const double v = (double)(sel ? a : eta) - (double)eta;
+        y += v;
+        if constexpr (DIST != kDistExp) yy = __builtin_fma(v, v, yy);
+    }
+};
+
+// The wave that evaluates the closed forms.  `sh`: the data waves' sums.
+template <int DIST>
+__device__ __forceinline__ void small_evaluate(Params& p, int lane, const double (*sh)[4], const uint32_t* sh_cnt, float* sh_eta)
+{
+    const double d = (double)p.d;
+    PrologueLoads g = {};
+    g.seen = __builtin_nanf("");
+    __builtin_amdgcn_s_setprio(3);  // the others wait for it
+    StageEta r = {};
+    auto stage = [&](int m, bool dry) {
+        StageSums sums = {d, DIST == kDistGamma ? -d : 3.0 * d, d};  // mean 1, variance 2
+        g.eta_prev = dry ? 1.0f : r.eta;
+        if (!dry) {
+            __syncthreads();
+            double v[3];
+#pragma unroll
+            for (int q = 0; q < 3; ++q) v[q] = lane < kSmallWaves - 1 ? sh[lane][q] : 0.0;
+            wave_totals(v);
+            sums = StageSums{v[0], v[1], v[2]};
+        }
+        p.stage = m;
+        p.L_stage = stage_L(p, m - 1);
+        StageRecord rec;
+        r = stage_eval(p, false, g, sums, rec);
+        if (dry) return;
+        if (lane == 0) *sh_eta = r.eta;
+        __syncthreads();
+        if (m == 1 && lane == 0) fit_reset_state(p);
+        g.status = rec.status;
+        g.frozen = rec.frozen;
+        if (lane == 0) stage_record(p, r, rec);
+    };
+    if constexpr (DIST == kDistGamma) {
+        // lgamma's constants, hoisted out of a loop, would not fit the registers: the first stage on its own, no dry runs
+        stage(1, false);
+#pragma unroll 1
+        for (int m = 2; m <= p.M; ++m) {
+            __builtin_assume(m >= 2);
+            stage(m, false);
+        }
+    } else {
+#pragma unroll 1
+        for (int it = p.M > 1 ? -1 : 0; it <= p.M; ++it) {
+            int m = it > 0 ? it : (it < 0 ? 2 : 1);  // ahead of the stages the second one's form and the first one's
+            asm volatile("" : "+s"(m));
+            stage(m, it <= 0);
+        }
+    }
+    __syncthreads();  // the data waves' counts
+    uint32_t total = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallWaves - 1; ++i) total += sh_cnt[i];
+    const uint32_t cap = (uint32_t)p.out_cap;
+    if (lane == 0) {
+        *p.out_count = (int32_t)(total > cap ? cap : total);
+        *p.out_eta = r.eta;
+        p.st->selected_ctr = total;
+        p.st->overflow = total > cap ? 1u : 0u;
+        p.st->diag.status = g.status;
+        if (p.status_out) *p.status_out = g.status | (total > cap ? kStOverflow : 0u);
+    }
+}
+
+constexpr uint32_t kSmallMuch = 8;
+
+// A data wave.  `list`: room for kSmallList<N> pairs
+template <int DIST, bool EC, int GT, int N>
+__device__ __forceinline__ void small_data(const Params& p, int lane, int wib, int2* list, double (*sh)[4], uint32_t* sh_cnt,
+                                           const float* sh_eta)
+{
+    const int32_t t = wib * 64 + lane, d = (int32_t)p.d;
+    SmallShare<DIST, N> x;
+    // the last, incomplete float4 is its owner's, element by element; past the end the last element again
+    const int32_t tail = d & ~3;
+    const bool owner = tail < d && (tail >> 2) % kSmallData == t;
+    float rest[3], rest_r[3];
+    if (owner) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+            const int32_t i = tail + j < d ? tail + j : d - 1;
+            rest[j] = load_grad1<GT>(p.grad, i);
+            rest_r[j] = EC ? p.residual[i] : 0.0f;
+        }
+    }
+    if (d >= 4) {
+        // whole float4s, wherever the buffers start; past the end the last one again: the loads stay unconditional
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const int32_t i = 4 * (u * kSmallData + t);
+            x.c[u] = load_grad4<GT, true>(p.grad, (size_t)(i + 4 <= d ? i : d - 4));
         }
         if constexpr (EC) {
             typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
             f4 r[N];
 #pragma unroll
             for (int u = 0; u < N; ++u) {
-                const int32_t i = 4 * (u * kSmallBlock + t);
+                const int32_t i = 4 * (u * kSmallData + t);
                 r[u] = *reinterpret_cast<const f4u*>(p.residual + (i + 4 <= d ? i : d - 4));
             }
 #pragma unroll
-            for (int u = 0; u < N; ++u) c[u] = c[u] + r[u];
+            for (int u = 0; u < N; ++u) x.c[u] = x.c[u] + r[u];
         }
+    }
+    f4 end = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (owner) {
 #pragma unroll
-        for (int u = 0; u < N; ++u) {
-            const int32_t i = 4 * (u * kSmallBlock + t);
-            if (i + 4 <= d) *reinterpret_cast<f4*>(x + i) = c[u];
-        }
-    }
-    if (t < 4 && (d & ~3) + t < 4 * kSmallBlock * N) {  // the last incomplete float4, zeros behind it
-        const int32_t i = (d & ~3) + t;
-        float c = 0.0f;
-        if (i < d) {
-            c = load_grad1<GT>(p.grad, i);
-            if (EC) c = c + p.residual[i];
-        }
-        x[i] = c;
-    }
-    if (t == 64) fit_reset_state(p);  // not in the wave that evaluates the closed form
-    __syncthreads();
-
-    PrologueLoads g = {};
-    g.seen = __builtin_nanf("");
-    double v[3];
-    switch (p.dist) {
-        case kDistExp: small_fit<kDistExp>(x, t, d, v); break;
-        case kDistGamma: small_fit<kDistGamma>(x, t, d, v); break;
-        default: small_fit<kDistGpd>(x, t, d, v); break;
-    }
-    auto evaluate = [&](int m) {  // the sums of all threads -> eta_m, the same in every thread
-        small_sum<3>(v, sh, lane, wib);
-        if (wib == 0) {
-            p.stage = m;
-            p.L_stage = stage_L(p, m - 1);
-            StageRecord rec;
-            const StageEta r = stage_eval(p, false, g, StageSums{v[0], v[1], v[2]}, rec);
-            if (lane == 0) {
-                sh_eta = r.eta;
-                sh_status = rec.status;
-                sh_frozen = rec.frozen ? 1u : 0u;
-                stage_record(p, r, rec);
+        for (int j = 0; j < 3; ++j) {
+            if (tail + j >= d) continue;
+            end[j] = rest[j];
+            if constexpr (EC) {
+                end[j] = rest[j] + rest_r[j];
+                p.residual[tail + j] = end[j];
             }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int32_t i = 4 * (u * kSmallData + t);
+        if (i + 4 > d) x.c[u] = i < d ? end : f4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+    auto sums_out = [&](double a, double b, double n) {
+        double v[2] = {a, b};
+        wave_totals(v);
+        if (lane == 0) {
+            sh[wib][0] = v[0];
+            sh[wib][1] = v[1];
+            sh[wib][2] = n;
         }
         __syncthreads();
-        g.eta_prev = sh_eta;
-        g.status = sh_status;
-        g.frozen = sh_frozen != 0;
     };
-    evaluate(1);
-#pragma unroll 1
-    for (int m = 2; m <= p.M; ++m) {
-        __builtin_assume(m >= 2);
-        // exceedances of eta_{m-1}: their number and the sums of y = |x| - eta_{m-1} (see emit)
-        const float eta = g.eta_prev;
-        uint32_t ns = 0;
-        double sy = 0.0, syy = 0.0;
-#pragma unroll 1
-        for (int32_t i = 4 * t; i < d; i += 4 * kSmallBlock) {
-            const f4 c = *reinterpret_cast<const f4*>(x + i);
+    {
+        double s1 = 0.0, s2 = 0.0, sl = 0.0;
+        int se = 0;
+        x.each(t, d, [&](bool valid, float v, int32_t) {
+            if (DIST != kDistGamma || valid) fit_accum<DIST>(v, s1, s2, sl, se);  // zeros leave s1 and s2 alone
+        });
+        sums_out(s1, DIST == kDistGamma ? sl + (double)se : s2, 0.0);
+    }
+    if constexpr (EC) {  // while the closed form is evaluated: ahead of that the stores would hold other waves' loads back
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float a = __builtin_fabsf(c[j]);  // past the end zero, never above eta
-                const bool sel = a > eta;
-                ns += sel ? 1u : 0u;
-                const double y = (double)(sel ? a : eta) - (double)eta;
-                sy += y;
-                syy = __builtin_fma(y, y, syy);
-            }
+        for (int u = 0; u < N; ++u) {
+            const int32_t i = 4 * (u * kSmallData + t);
+            if (i + 4 <= d) *reinterpret_cast<f4u*>(p.residual + i) = x.c[u];
         }
-        v[0] = sy;
-        v[1] = syy;
-        v[2] = (double)ns;
-        evaluate(m);
     }
-
-    // selection: wave w takes the elements of its threads' float4s, in address order
-    const float eta = g.eta_prev;
-    const int32_t last = 4 * (t - lane);  // lanes of a wave stay together
-    uint32_t mine = 0;
-#pragma unroll 1
-    for (int32_t b = last; b < d; b += 4 * kSmallBlock) {
-        const int32_t i = b + 4 * lane;
-        const f4 c = i < d ? *reinterpret_cast<const f4*>(x + i) : f4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) mine += (uint32_t)__popcll(__ballot(__builtin_fabsf(c[j]) > eta));
-    }
-    if (lane == 0) sh_cnt[wib] = mine;
     __syncthreads();
-    uint32_t pos = 0, total = 0;
+    // what exceeds the first threshold
+    float eta = *sh_eta;
+    uint32_t len = 0;
+    constexpr uint32_t kRoom = kSmallList<N> - 64;
 #pragma unroll
-    for (int i = 0; i < kSmallWaves; ++i) {
-        if (i < wib) pos += sh_cnt[i];
-        total += sh_cnt[i];
-    }
-    const uint32_t cap = (uint32_t)p.out_cap;
-    if (t == 64) {
-        *p.out_count = (int32_t)(total > cap ? cap : total);
-        *p.out_eta = eta;
-        p.st->selected_ctr = total;
-        p.st->overflow = total > cap ? 1u : 0u;
-        p.st->diag.status = g.status;
-        if (p.status_out) *p.status_out = g.status | (total > cap ? kStOverflow : 0u);
-    }
-#pragma unroll 1
-    for (int32_t b = last; b < d; b += 4 * kSmallBlock) {
-        const int32_t i = b + 4 * lane;
-        f4 c = i < d ? *reinterpret_cast<const f4*>(x + i) : f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int u = 0; u < N; ++u) {
+        const int32_t i = 4 * (u * kSmallData + t);
+        if (4 * u * kSmallData >= d || len > kRoom) continue;  // uniform; a list that is too short is none
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const bool sel = __builtin_fabsf(c[j]) > eta;
+            const bool sel = __builtin_fabsf(x.c[u][j]) > eta;
             const unsigned long long mask = __ballot(sel);
-            const uint32_t at = pos + lane_prefix(mask);
-            if (sel && at < cap) {  // pairs beyond the capacity stay in the residual
-                p.out_idx[at] = i + j;
-                p.out_val[at] = c[j];
-                c[j] = 0.0f;
-            }
-            pos += (uint32_t)__popcll(mask);
+            // every lane writes, without a branch: what is not selected, or does not fit, to the places behind the list
+            const uint32_t at = min(len, kRoom) + lane_prefix(mask);
+            list[sel ? at : kSmallList<N> - 1] = make_int2(i + j, __float_as_int(x.c[u][j]));
+            len += (uint32_t)__popcll(mask);
         }
+    }
+    const bool listed = len <= kRoom;
+    // the lane's entries among the first 64 * kHead of the list stay in registers; stale past the list's end
+    constexpr int kHead = 8;
+    int2 head[kHead];
+#pragma unroll
+    for (int u = 0; u < kHead; ++u) head[u] = list[u * 64 + lane];
+    // f(valid, value, index) for those, the wave together: from the list, or, if it is too short, from all elements
+    auto exceeding = [&](auto f) {
+        if (listed) {
+#pragma unroll
+            for (uint32_t u = 0; u < kHead; ++u)
+                if (u * 64 < len) f(u * 64 + lane < len, __int_as_float(head[u].y), head[u].x);
+#pragma unroll 1
+            for (uint32_t k = 64 * kHead; k < len; k += 128) {
+                const int2 e = list[k + lane], g = list[k + 64 + lane];
+                f(k + lane < len, __int_as_float(e.y), e.x);
+                f(k + 64 + lane < len, __int_as_float(g.y), g.x);
+            }
+        } else {
+            x.each(t, d, [&](bool, float v, int32_t i) { f(true, v, i); });
+        }
+    };
+#pragma unroll 1
+    for (int m = 2; m <= p.M; ++m) {
+        SmallSums<DIST> q;
+        exceeding([&](bool in, float v, int32_t) { q.add(in, v, eta); });
+        sums_out(q.y, q.yy, (double)q.n);
+        __syncthreads();
+        eta = *sh_eta;
+    }
+
+    uint32_t mine = len;
+    if (p.M > 1 || !listed) {
+        mine = 0;
+        exceeding([&](bool in, float v, int32_t) { mine += (uint32_t)__popcll(__ballot(in && __builtin_fabsf(v) > eta)); });
+    }
+    if (lane == 0) sh_cnt[wib] = mine;
+    __syncthreads();  // also between the residual's stores and the clearing
+    uint32_t pos = 0;
+#pragma unroll
+    for (int i = 0; i < kSmallWaves - 1; ++i) pos += i < wib ? sh_cnt[i] : 0u;
+    const uint32_t cap = (uint32_t)p.out_cap;
+    // writes what is selected of 64 entries; whether the lane's was
+    auto emit_pairs = [&](bool in, float v, int32_t i) {
+        const bool sel = in && __builtin_fabsf(v) > eta;
+        const unsigned long long mask = __ballot(sel);
+        const uint32_t at = pos + lane_prefix(mask);
+        const bool out = sel && at < cap;  // pairs beyond the capacity stay in the residual
+        if (out) {
+            p.out_idx[at] = i;
+            p.out_val[at] = v;
+        }
+        pos += (uint32_t)__popcll(mask);
+        return out;
+    };
+    // A wave that selects much of its share, or has no list, goes through its elements once more and stores whole float4s: one
+    // by one the cleared entries of 12000 elements, gamma law, of which it keeps 31 %, cost 3 us more.
+    if (listed && mine * kSmallMuch <= (uint32_t)(d / (kSmallWaves - 1))) {
+        exceeding([&](bool in, float v, int32_t i) {
+            if (emit_pairs(in, v, i) && EC) p.residual[i] = 0.0f;
+        });
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        const int32_t i = 4 * (u * kSmallData + t);
+        if (4 * u * kSmallData >= d) continue;  // uniform
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (emit_pairs(true, x.c[u][j], i + j)) x.c[u][j] = 0.0f;
         if constexpr (EC) {
             typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-            if (i + 4 <= d) *reinterpret_cast<f4u*>(p.residual + i) = c;
-            else {
+            if (i + 4 <= d) {
+                *reinterpret_cast<f4u*>(p.residual + i) = x.c[u];
+            } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (i + j < d) p.residual[i + j] = c[j];
+                for (int j = 0; j < 3; ++j)
+                    if (i + j < d) p.residual[i + j] = x.c[u][j];
             }
         }
     }
+}
+
+// N: float4s per lane of a data wave, 4 * kSmallData * N >= d
+template <int DIST, bool EC, int GT, int N>
+__global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
+{
+    extern __shared__ __align__(16) int2 lists[];  // kSmallList<N> for each data wave
+    __shared__ double sh[kSmallWaves - 1][4];
+    __shared__ uint32_t sh_cnt[kSmallWaves - 1];
+    __shared__ float sh_eta;
+    const int lane = threadIdx.x & 63, wib = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    p.theta = 0.0f;  // no candidate lists
+    p.dist = DIST;
+    // Both sides pass the same barriers: two for every stage, one ahead of the output.
+    if (wib == kSmallWaves - 1) small_evaluate<DIST>(p, lane, sh, sh_cnt, &sh_eta);
+    else small_data<DIST, EC, GT, N>(p, lane, wib, lists + wib * kSmallList<N>, sh, sh_cnt, &sh_eta);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2428,17 +2537,29 @@ void launch_fit_bands(const Params& p, hipStream_t s)
     }
 }
 
-template <bool EC, int GT, int N>
+template <int DIST, bool EC, int GT, int N>
 static void launch_small_as(const Params& p, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_small<EC, GT, N>), dim3(1), dim3(kSmallBlock), 4 * kSmallBlock * N * sizeof(float), s, p);
+    constexpr size_t lds = (kSmallWaves - 1) * kSmallList<N> * sizeof(int2);
+    hipLaunchKernelGGL((k_small<DIST, EC, GT, N>), dim3(1), dim3(kSmallBlock), lds, s, p);
+}
+
+template <bool EC, int GT, int N>
+static void launch_small_dist(const Params& p, hipStream_t s)
+{
+    switch (p.dist) {
+        case kDistExp: launch_small_as<kDistExp, EC, GT, N>(p, s); break;
+        case kDistGamma: launch_small_as<kDistGamma, EC, GT, N>(p, s); break;
+        default: launch_small_as<kDistGpd, EC, GT, N>(p, s); break;
+    }
 }
 
 template <bool EC, int GT>
 static void launch_small_size(const Params& p, hipStream_t s)
 {
-    if (p.d <= 3 * 4 * kSmallBlock) launch_small_as<EC, GT, 3>(p, s);
-    else launch_small_as<EC, GT, kSmallMaxD / (4 * kSmallBlock)>(p, s);
+    constexpr int kShort = 4, kLong = (kSmallMaxD + 4 * kSmallData - 1) / (4 * kSmallData);
+    if (p.d <= 4 * kSmallData * kShort) launch_small_dist<EC, GT, kShort>(p, s);
+    else launch_small_dist<EC, GT, kLong>(p, s);
 }
 
 template <int GT>
