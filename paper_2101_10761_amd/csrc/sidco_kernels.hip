@@ -2071,6 +2071,11 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 // distinct, so plain read-modify-write needs no atomics and the result is deterministic; lists of
 // several workers are added by consecutive launches.  Two roundings per element (product, then sum),
 // as a plain fp32 loop does.
+// Bound by the lines that long lists touch.  The pairs are read past the caches, whose room the dense lines need, and the
+// grid is several times what runs at once, so that blocks that fall behind do not end last: 13.8 M pairs in 138 M elements,
+// alone, 1024 blocks and ordinary loads 282 us, non-temporal ones 271, 8192 blocks 268, both 258 (4096 259, 65536 with
+// ordinary loads 281); 1.4 M pairs 80 and 78; a training step of 138 M elements, ratio 0.1 834 and 823.  Non-temporal loads or stores of the dense lines are slower (390, 268 at 8192
+// blocks), and four pairs per thread change nothing.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_scatter_add(float* __restrict__ dense, int64_t d, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, const int32_t* __restrict__ count,
@@ -2080,12 +2085,12 @@ __global__ __launch_bounds__(kBlock) void k_scatter_add(float* __restrict__ dens
     if (n > capacity) n = capacity;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
-        const int64_t j = (int64_t)idx[i];
+        const int64_t j = (int64_t)__builtin_nontemporal_load(idx + i);
         if (j < 0 || j >= d) {  // never written; reported
             atomicOr(bad, 1u);
             continue;
         }
-        dense[j] = __fadd_rn(dense[j], __fmul_rn(scale, val[i]));
+        dense[j] = __fadd_rn(dense[j], __fmul_rn(scale, __builtin_nontemporal_load(val + i)));
     }
 }
 
@@ -2094,6 +2099,7 @@ __global__ void k_clear_u32(uint32_t* p) { *p = 0; }
 // a fill kernel rather than a memset: callers may record the stream into a HIP graph
 void launch_clear_u32(uint32_t* p, hipStream_t s) { hipLaunchKernelGGL(k_clear_u32, dim3(1), dim3(1), 0, s, p); }
 
+constexpr int64_t kScatterBlocks = 8192;  // see k_scatter_add
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s)
 {
@@ -2102,7 +2108,7 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
     // a chain of four updates: 7.1 us, against 4.0 for as many pairs in four times the capacity.
     int64_t blocks = (capacity + kBlock - 1) / kBlock;
     if (blocks < 1) blocks = 1;
-    if (blocks > 2 * kMaxBlocks) blocks = 2 * kMaxBlocks;
+    if (blocks > kScatterBlocks) blocks = kScatterBlocks;
     hipLaunchKernelGGL(k_scatter_add, dim3((uint32_t)blocks), dim3(kBlock), 0, s, dense, d, idx, val, count, capacity,
                        scale, bad);
 }
