@@ -177,6 +177,21 @@ __device__ __forceinline__ size_t seg_begin(const P& p, uint32_t w) { return (si
 template <typename P>
 __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
 
+// Number of the wave's k-th tile in the sweep that forms acc; they ascend.  In vectors of kTurnRows rows of W tiles and more
+// the waves' places move on by a block's 8 tiles from row to row.  A block stays on its XCD, and a row is 4 MB: without that an
+// XCD has the same 8 KB of every 64 KB, that is the same share of the memory channels, all the way, and the waves of the
+// channels that fall behind are never relieved.  First pass of 138 M elements 292 us and so 281, its waves 275 and 262 on
+// average.  A training step, places that stay and that move on, us: 25.6 M elements, 3 stages 72.2 and 72.6, 40 M, 2 stages 94.9
+// and 94.1, 3 stages 123.2 and 122.1, 52 M 119.3 and 118.2, 66 M, gamma 148.0 and 146.5, 90 M 203.1 and 200.5, 138 M, 3 stages
+// 407.6 and 396.6.  The lists and sums are the wave's whichever its tiles are.
+constexpr uint32_t kTurnRows = 30;
+template <typename P>
+__device__ __forceinline__ uint32_t acc_tile(const P& p, uint32_t w, uint32_t k)
+{
+    const bool turn = p.nwaves == (uint32_t)kMaxWaves && p.tq >= kTurnRows && k < p.tq;
+    return k * p.nwaves + (turn ? (w + k * kWavesPerBlock) & (uint32_t)(kMaxWaves - 1) : w);
+}
+
 // One wave's share of the sweep that forms acc = g + residual (EC; else acc = g) and stores it (WRITE) to p.acc_w.
 // The wave requests its next tile before it works on the one it has: one tile (1 KB of each operand) per wave in
 // flight is what 16 waves per CU need to keep HBM busy, and more only widens the window of addresses that the chip
@@ -206,36 +221,40 @@ __device__ __forceinline__ void acc_store(float* acc, size_t i, f4 c)
 template <bool EC, bool WRITE, int GT, bool PAST, typename P>
 __device__ __forceinline__ AccTile acc_first(const P& p, uint32_t w, int lane)
 {
-    const uint32_t t = w + ((w == 0 && p.shift > 0) ? p.nwaves : 0u);
+    const uint32_t t = acc_tile(p, w, (w == 0 && p.shift > 0) ? 1u : 0u);
     return acc_load<EC, WRITE, GT, PAST>(p, (size_t)t * kTile + lane * 4 - p.shift);
 }
 // `first`: NULL, or that tile
 template <bool EC, bool WRITE, int GT, bool PAST = false, typename P, typename V>
 __device__ __forceinline__ void acc_sweep(const P& p, uint32_t w, int lane, V& v, const AccTile* first = nullptr)
 {
-    const WaveTiles wt = wave_tiles(p, w);
+    w = __builtin_amdgcn_readfirstlane(w);
+    WaveTiles wt = wave_tiles(p, w);
+    // the wave with the vector's last, incomplete tile may be another one than in the other sweeps
+    wt.nb = wt.n - wt.k0 - (wt.n > wt.k0 && acc_tile(p, w, wt.n - 1) >= p.nfull ? 1u : 0u);
     if (wt.nb > 0) {
         float* acc = p.acc_w;
-        uint32_t t = w + wt.k0 * wt.W;
+        uint32_t t = acc_tile(p, w, wt.k0);
         size_t i = (size_t)t * kTile + lane * 4 - p.shift;
-        const size_t step = (size_t)wt.W * kTile;
         AccTile a = first ? *first : acc_load<EC, WRITE, GT, PAST>(p, i);
 #pragma unroll 1
         for (uint32_t k = 1; k < wt.nb; ++k) {
             f4 c = a.g;
             if (EC) c = a.g + a.r;
-            a = acc_load<EC, WRITE, GT, PAST>(p, i + step);
+            const uint32_t t1 = acc_tile(p, w, wt.k0 + k);
+            const size_t i1 = (size_t)t1 * kTile + lane * 4 - p.shift;
+            a = acc_load<EC, WRITE, GT, PAST>(p, i1);
             if (WRITE) acc_store<PAST>(acc, i, c);
             v.tile(c, t);
-            t += wt.W;
-            i += step;
+            t = t1;
+            i = i1;
         }
         if (EC) a.g = a.g + a.r;
         if (WRITE) acc_store<PAST>(acc, i, a.g);
         v.tile(a.g, t);
     }
     for (uint32_t k = 0; k < wt.n - wt.nb; ++k) {
-        const uint32_t t = w + guarded_tile(wt, k) * wt.W;
+        const uint32_t t = acc_tile(p, w, guarded_tile(wt, k));
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int64_t i = (int64_t)t * kTile + lane * 4 + j - p.shift;
