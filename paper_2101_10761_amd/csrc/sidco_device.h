@@ -178,18 +178,21 @@ template <typename P>
 __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
 
 // Number of the wave's k-th tile in the sweep that forms acc; they ascend.  In vectors of kTurnRows rows of W tiles and more
-// the waves' places move on by a block's 8 tiles from row to row.  A block stays on its XCD, and a row is 4 MB: without that an
-// XCD has the same 8 KB of every 64 KB, that is the same share of the memory channels, all the way, and the waves of the
-// channels that fall behind are never relieved.  First pass of 138 M elements 292 us and so 281, its waves 275 and 262 on
-// average.  A training step, places that stay and that move on, us: 25.6 M elements, 3 stages 72.2 and 72.6, 40 M, 2 stages 94.9
-// and 94.1, 3 stages 123.2 and 122.1, 52 M 119.3 and 118.2, 66 M, gamma 148.0 and 146.5, 90 M 203.1 and 200.5, 138 M, 3 stages
-// 407.6 and 396.6.  The lists and sums are the wave's whichever its tiles are.
-constexpr uint32_t kTurnRows = 30;
+// the two halves of the waves change places from row to row.  Blocks b and b + 256 share a CU and the later one is served
+// behind the other, by 1.5 % of the sweep, while even and odd blocks run on XCDs of which every other one is 5 % slower: with
+// places that stay, what a wave falls behind adds up at the same addresses, row by row.  A training step, us, places that
+// stay, that move on by one block a row, and halves that change: 14.7 M elements, 2 stages 45.3, 45.4 and 45.3; 25.6 M, 3 stages
+// 72.3, 72.5 and 71.9; 40 M, 2 stages 94.4, 93.8 and 93.5; 66 M, gamma 146.5, 145.0 and 144.0; 138 M, 3 stages 405.8, 394.0 and
+// 392.5 (its first pass 292, 281 and 279).  Moving on by 8 blocks, on the same XCD, gains nothing (405), by 2 or 4, or by
+// half a row and some more, less than half a row at one length or another.  Shorter vectors gain nothing, and those that the
+// caches serve lose (12 M 40.4 and 40.4, one stage on 8 M 27.8 and 28.4).  The lists and sums are the wave's whichever its
+// tiles are.
+constexpr uint32_t kTurnRows = 18;
 template <typename P>
 __device__ __forceinline__ uint32_t acc_tile(const P& p, uint32_t w, uint32_t k)
 {
     const bool turn = p.nwaves == (uint32_t)kMaxWaves && p.tq >= kTurnRows && k < p.tq;
-    return k * p.nwaves + (turn ? (w + k * kWavesPerBlock) & (uint32_t)(kMaxWaves - 1) : w);
+    return k * p.nwaves + (turn ? w ^ (k & 1u) * (uint32_t)(kMaxWaves / 2) : w);
 }
 
 // One wave's share of the sweep that forms acc = g + residual (EC; else acc = g) and stores it (WRITE) to p.acc_w.

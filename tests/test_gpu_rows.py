@@ -1,4 +1,4 @@
-"""The first pass's tiles where the waves' places begin to move on from row to row: whole rows, one tile more or less, an
+"""The first pass's tiles where the halves of the waves begin to change places from row to row: whole rows, one tile more or less, an
 incomplete last tile and an incomplete first one (a vector that starts inside a line), without and with bands."""
 import numpy as np
 import pytest
@@ -10,8 +10,8 @@ pytestmark = pytest.mark.gpu
 ROW = 4096 * 256  # elements of a row of tiles
 
 
-@pytest.mark.parametrize("d,offset,residual", [(30 * ROW - 1, 0, True), (30 * ROW, 0, True), (30 * ROW, 5, True), (30 * ROW + 257, 31, True),
-                                               (31 * ROW - 256, 0, False), (31 * ROW + 8 * 256 + 2, 1, True)])
+@pytest.mark.parametrize("d,offset,residual", [(18 * ROW - 1, 0, True), (18 * ROW, 0, True), (18 * ROW, 5, True), (18 * ROW + 257, 31, True),
+                                               (19 * ROW - 256, 0, False), (19 * ROW + 2048 * 256 + 2, 1, True)])
 def test_first_pass_on_both_sides_of_the_line(oracle, d, offset, residual):
     rng = np.random.default_rng(d + offset)
     g = rng.standard_normal(d, dtype=np.float32)
