@@ -178,21 +178,26 @@ template <typename P>
 __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
 
 // Number of the wave's k-th tile in the sweep that forms acc; they ascend.  In vectors of kTurnRows rows of W tiles and more
-// the two halves of the waves change places from row to row.  Blocks b and b + 256 share a CU and the later one is served
-// behind the other, by 1.5 % of the sweep, while even and odd blocks run on XCDs of which every other one is 5 % slower: with
-// places that stay, what a wave falls behind adds up at the same addresses, row by row.  A training step, us, places that
-// stay, that move on by one block a row, and halves that change: 14.7 M elements, 2 stages 45.3, 45.4 and 45.3; 25.6 M, 3 stages
-// 72.3, 72.5 and 71.9; 40 M, 2 stages 94.4, 93.8 and 93.5; 66 M, gamma 146.5, 145.0 and 144.0; 138 M, 3 stages 405.8, 394.0 and
-// 392.5 (its first pass 292, 281 and 279).  Moving on by 8 blocks, on the same XCD, gains nothing (405), by 2 or 4, or by
-// half a row and some more, less than half a row at one length or another.  Shorter vectors gain nothing, and those that the
-// caches serve lose (12 M 40.4 and 40.4, one stage on 8 M 27.8 and 28.4).  The lists and sums are the wave's whichever its
-// tiles are.
+// the waves do not keep their place in the row.  Blocks go to the eight XCDs in turn, b and b + 256 share a CU and the later
+// one ends 1.5 % behind the other, and every other XCD ends 5 % behind its neighbours; where places stay, an XCD has the same
+// 8 KB of every 64 KB all the way.  Here the halves of the waves change places from row to row, and in each half of a
+// row an XCD has 256 KB in one piece, the piece behind its last one.  A training step, us, places that stay, halves that
+// change and this: 14.7 M elements, 2 stages 45.3, 45.3 and 45.1; 25.6 M, 3 stages 72.3, 72.0 and 71.9; 32 M, 2 stages -, 78.1
+// and 77.1; 40 M 94.4, 93.6 and 92.3; 66 M, gamma 146.5, 143.8 and 142.0; 78 M, 3 stages -, 188.5 and 186.7; 90 M, 2 stages
+// 203, 198.8 and 195.9; 138 M, 3 stages 405.8, 393.0 and 392.2 (first pass 292 and 278).  Pieces of 128 and of 64 KB or that
+// move on every other row are slower (66 M 142.7, 147.6, 145.1), and so are places that move on by one, two, four or eight
+// blocks a row (138 M 394, 401, 405, 405).  Shorter vectors gain nothing, and those that the caches serve lose (halves that
+// change: one stage on 8 M 27.8 and 28.4).  The lists and sums are the wave's whichever its tiles are.
 constexpr uint32_t kTurnRows = 18;
 template <typename P>
 __device__ __forceinline__ uint32_t acc_tile(const P& p, uint32_t w, uint32_t k)
 {
-    const bool turn = p.nwaves == (uint32_t)kMaxWaves && p.tq >= kTurnRows && k < p.tq;
-    return k * p.nwaves + (turn ? w ^ (k & 1u) * (uint32_t)(kMaxWaves / 2) : w);
+    static_assert(kMaxBlocks == 512 && kWavesPerBlock == 8, "halves of 8 pieces of 32 blocks");
+    if (p.nwaves == (uint32_t)kMaxWaves && p.tq >= kTurnRows && k < p.tq) {
+        const uint32_t b = w / kWavesPerBlock, half = (b >> 8) ^ (k & 1u), piece = (b + k) & 7u;
+        w = ((half * 8 + piece) * 32 + (b >> 3 & 31u)) * kWavesPerBlock + w % kWavesPerBlock;
+    }
+    return k * p.nwaves + w;
 }
 
 // One wave's share of the sweep that forms acc = g + residual (EC; else acc = g) and stores it (WRITE) to p.acc_w.

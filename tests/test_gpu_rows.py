@@ -1,4 +1,4 @@
-"""The first pass's tiles where the halves of the waves begin to change places from row to row: whole rows, one tile more or less, an
+"""The first pass's tiles where the waves begin to change places from row to row: whole rows, one tile more or less, an
 incomplete last tile and an incomplete first one (a vector that starts inside a line), without and with bands."""
 import numpy as np
 import pytest
