@@ -655,15 +655,27 @@ __device__ __forceinline__ void fit_body(const Params& p, Blk b, const AccTile* 
 // k_fit_flat + k_fit_reduce: the same pass for large vectors.  One float4 per thread and a grid that
 // covers the vector in address order: the blocks in flight at any time touch one narrow window of each
 // buffer, however long the vector is (see kFlatMinD for both shapes' times).
+// Of every 2 MB an XCD has 256 KB in one piece, the piece behind its last one (piece_order; see acc_tile).  A training step
+// with blocks in address order and so, us: 1 stage, 66 M elements 167.2 and 162.8, 138 M 373 and 361.5; 2 stages, 40 M, ratio 0.1
+// 257.0 and 254.4; 3 stages, 25 M, 0.1 180.9 and 180.3; 4 stages, 66 M 274.1 and 271.9.  Pieces that stay 138 M 376, of 32 KB 389.
 // The price is one partial sum per 256-thread block - far too many for every block of the next
 // kernel to add up - so a second, small kernel folds them into the usual 512 slots, in a fixed order.
 // ---------------------------------------------------------------------------------------------
+// Place in address order of block i of n, GROUP of which cover 2 MB.
+template <uint32_t GROUP>
+__device__ __forceinline__ uint32_t piece_order(uint32_t i, uint32_t n)
+{
+    if ((i | (GROUP - 1)) >= n) return i;  // the last ones, which do not fill 2 MB
+    return (i & ~(GROUP - 1)) + ((i + i / GROUP) & 7u) * (GROUP / 8) + (i & (GROUP - 1)) / 8;
+}
+
 template <int DIST, bool EC, int GT>
 __global__ __launch_bounds__(kFlatBlock) void k_fit_flat(Params p, double* __restrict__ flat_part, uint32_t nflat)
 {
     __shared__ double sh[kFlatBlock / 64][4];
     const int lane = threadIdx.x & 63, wib = threadIdx.x >> 6;
-    const int64_t i = ((int64_t)blockIdx.x * kFlatBlock + threadIdx.x) * 4 - p.shift;  // first of the thread's 4 elements
+    const uint32_t place = piece_order<512>(blockIdx.x, nflat);
+    const int64_t i = ((int64_t)place * kFlatBlock + threadIdx.x) * 4 - p.shift;  // first of the thread's 4 elements
     double s1 = 0.0, s2 = 0.0, sl = 0.0;
     int se = 0;
     if (i >= 0 && i + 4 <= p.d) {
@@ -693,7 +705,7 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat(Params p, double* __res
         double tot = 0.0;
 #pragma unroll
         for (int w = 0; w < kFlatBlock / 64; ++w) tot += sh[w][threadIdx.x];
-        flat_part[(size_t)threadIdx.x * nflat + blockIdx.x] = tot;
+        flat_part[(size_t)threadIdx.x * nflat + place] = tot;
     }
 }
 
