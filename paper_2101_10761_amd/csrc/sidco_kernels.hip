@@ -1597,7 +1597,8 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
 // elements and a ratio of 0.1 204 us for 1.22 GB, the scatter 243; k_final_lists took 235, the dense stage that wrote its
 // lists 30 more than one that only sums, and the scatter 270.  Loads that go past the caches want stores that do so as
 // well (all but those of a vector that the caches hold): a training step of 138 M, 3 stages, with ordinary and with such
-// stores 863 and 835 us, 90 M 576 and 547, 70 M, 2 stages 431 and 408.
+// stores 863 and 835 us, 90 M 576 and 547, 70 M, 2 stages 431 and 408.  XCDs have pieces of 256 KB (piece_order): 138 M 812 and
+// 808, 66 M, 2 stages 385.2 and 383.5.
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_eta(Params p)
 {
@@ -1694,7 +1695,8 @@ __global__ __launch_bounds__(kSelectBlock) void k_select(Params p)
     __shared__ uint32_t sh_cnt[kSelectBlock / 64];
     __shared__ uint32_t sh_base;
     constexpr uint32_t kTiles = kSelectBlock / 64 * kSelectTiles;
-    const uint32_t first = (p.reverse ? gridDim.x - 1 - blockIdx.x : blockIdx.x) * kTiles;
+    const uint32_t place = piece_order<32>(blockIdx.x, gridDim.x);
+    const uint32_t first = (p.reverse ? gridDim.x - 1 - place : place) * kTiles;
     if (first + kTiles <= p.nfull && (first > 0 || p.shift == 0)) select_body<true, KEEP>(p, first, sh_cnt, &sh_base);
     else select_body<false, KEEP>(p, first, sh_cnt, &sh_base);
 }
