@@ -1195,6 +1195,7 @@ int sidco_compress_batched_typed(void* stream, const void* grad, int grad_dtype,
     a.flat_gx = pl.flat_gx;
     a.flat_blocks = pl.blocks;
     const int64_t total = offsets[n] - offsets[0];
+    a.pieces = total >= kPiecesMinBatch ? 1 : 0;
     const size_t nchunks = (size_t)pl.flat_gx * pl.blocks;
     const size_t lists_at = (nchunks * (6 * sizeof(double) + sizeof(uint32_t)) + kAlign - 1) / kAlign * kAlign;
     const bool banded = pl.flat_gx > 0 && lists_at + nchunks * kChunkList * sizeof(int2) <= seg &&

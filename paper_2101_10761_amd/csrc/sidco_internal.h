@@ -315,6 +315,7 @@ struct BatchArgs {
     int use_hint, cand_stage;
     double* flat;           // partial sums of a flat first pass (see k_fit_flat_batched), chunks per block and blocks
     uint32_t flat_gx, flat_blocks;
+    int pieces;             // k_fit_flat_batched: whether blocks go by piece_order
     int bands;              // as in Params, and if used: lengths of the chunks' lists, and the lists, kChunkList entries each
     float band_w[kBandStages];
     uint32_t* chunk_cnt;
@@ -352,6 +353,11 @@ constexpr int64_t kFlatMinMuch = 20000000;
 // A batch's waves walk the tiles of their own vector, so that its window is as many as it has vectors, and the flat
 // shape pays earlier: 25.6 M elements in 161 tensors 96.6 us per wave and 90.6 flat, 66 M in 50 tensors 236.6 and 204.
 constexpr int64_t kFlatMinBatch = 12000000;
+// From this length on the blocks of that shape go by piece_order; shorter batches with many tensors, of whose chunks some are
+// empty, lose by it.  A call in address order and so, us: 66 M elements in 50 tensors 145.4 and 143.2, in 20 of 64 elements
+// up 150.7 and 148.5, in 300 208.4 and 206.2, in 161 of 64 elements up 151.8 and 151.7; 40 M in 50 99.3 and 98.8, in 100 of 64
+// up 100.5 and 101.7; 25.6 M in 161 72.6 and 75.5, in 50 70.5 and 70.5; 14 M in 20 50.0 and 51.0.
+constexpr int64_t kPiecesMinBatch = 60000000;
 // A batch whose longest vector has at most this many flat partial sums leaves them to the prologue of the first
 // stage's kernel, 4 loads per thread and quantity; beyond it a kernel folds them first, 4.8 us against 1 to 2.5 in that
 // prologue: 161 tensors, 25.6 M elements 83.5 -> 81.6 us, 200 tensors, 14 M 49.0 -> 47.0.

@@ -2240,6 +2240,7 @@ __global__ __launch_bounds__(kBlock) void k_fit_batched(BatchArgs a)
 // ahead of its data; 161 tensors, 25.6 M elements, with one, two and four tiles per wave: 86.1, 84.1 and 87.5 us).  Blocks run in the order x first, then y: address
 // order.  Chunks past the end of a y's tiles leave zeros and exit (the host launches the flat shape only when few
 // are).
+// `pieces`: of every 256 blocks an XCD has 32 that follow each other (see piece_order).
 // BANDS: behind a call of the same layout (see k_fit_bands).  Every chunk also leaves the sums above the first stage's band
 // and a list of the band's entries and of all that the second stage may ask for; the first stage's kernel writes its lists
 // from that, and the later stages are those of any batch.  The per-wave shape with bands was slower (66 M elements in 50
@@ -2328,14 +2329,20 @@ __global__ __launch_bounds__(kFlatBlock) void k_fit_flat_batched(BatchArgs a)
     __shared__ int2 sh_list[BANDS ? kFlatBlock / 64 : 1][BANDS ? kFlatTiles * kTile : 1];
     __shared__ uint32_t sh_len[kFlatBlock / 64];
     Blk b;
-    const Params p = batch_params(a, false, b, blockIdx.y);
+    uint32_t x = blockIdx.x, y = blockIdx.y;
+    if (a.pieces) {
+        const uint32_t place = piece_order<256>(y * gridDim.x + x, gridDim.y * gridDim.x);
+        y = place / gridDim.x;
+        x = place - y * gridDim.x;
+    }
+    const Params p = batch_params(a, false, b, y);
     Bands e;
     if constexpr (BANDS) e = p.st->band_next;  // beside the descriptor, ahead of all stores: not a round trip of its own
     uint32_t T0, T1;
     block_tiles(p, b, T0, T1);
-    const uint32_t first = T0 + blockIdx.x * kFlatChunk;
-    const size_t stride = (size_t)gridDim.y * gridDim.x, slot = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    if (b.id == 0 && blockIdx.x == 0 && threadIdx.x == 0) fit_reset_state(p);
+    const uint32_t first = T0 + x * kFlatChunk;
+    const size_t stride = (size_t)gridDim.y * gridDim.x, slot = (size_t)y * gridDim.x + x;
+    if (b.id == 0 && x == 0 && threadIdx.x == 0) fit_reset_state(p);
     if (first >= T1) {  // the whole block
         if (threadIdx.x < Q) a.flat[threadIdx.x * stride + slot] = 0.0;
         if (BANDS && threadIdx.x == 0) a.chunk_cnt[slot] = 0;
