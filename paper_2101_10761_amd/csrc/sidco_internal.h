@@ -265,6 +265,7 @@ struct Blk {
     uint32_t id;  // block index within the vector's grid
     uint32_t n;   // size of that grid
     uint32_t none;  // 0 (see stage_grid)
+    bool records;   // the block that keeps what the vector's call leaves in its state
 };
 
 // ---- batched calls: several vectors (the tensors of one flat buffer) in one launch sequence ----
@@ -340,7 +341,8 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
 // flat shape's blocks start in address order, but it needs a kernel that folds its partial sums.  A two-stage call
 // in the per-wave shape and in the flat one, us: 25.6 M elements 84.3 and 87.5, 41 M 111.2 and 113.7, 50 M 133.2
 // and 135.0, 58 M 154.2 and 155.1, 62 M 164.5 and 161.2, 80 M 217.0 and 205.7; with a bf16 gradient 50 M 120.1 and
-// 126.8, 62 M 148.7 and 150.8, 80 M 193.3 and 191.2.  The shapes meet between 58 and 62 M with fp32 gradients and
+// 126.8, 62 M 148.7 and 150.8, 80 M 193.3 and 191.2; one stage, with both shapes' tiles in pieces (acc_tile, piece_order), 40 M
+// 100.7 and 101.2, 50 M 123.9 and 123.8, 58 M 147.7 and 146.9, 66 M 164.9 and 163.0, 80 M 202.5 and 197.5.  The shapes meet between 58 and 62 M with fp32 gradients and
 // between 62 and 80 M with 16-bit ones, which share the line: it costs them at most 1.4 % of a call around 62 M.
 constexpr int kFlatBlock = 256;
 constexpr int kFlatTiles = 2;                                // tiles per wave of a batch's flat first pass
