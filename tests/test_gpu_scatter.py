@@ -51,3 +51,27 @@ def test_count_is_read_on_the_device_and_bad_indices_are_skipped(oracle):
         np.testing.assert_array_equal(got.cpu().numpy(), want)
         assert sidco.sidco_scatter_check() == (bad > 0)
         assert not sidco.sidco_scatter_check()      # the flag is cleared by the check
+
+
+@pytest.mark.parametrize("capacity,count", [(524_289, 524_289), (2_100_000, 2_097_151), (2_100_000, 2_097_152), (9_000_000, 100),
+                                            (9_000_000, 4_194_305), (9_000_000, 9_000_000)])
+def test_long_lists(capacity, count):
+    """More pairs than threads, so that a thread goes on to a second one; lists on both sides of what is read past the
+    caches, and buffers on both sides of what takes more blocks than run at once.  The device fuses product and sum: one
+    rounding, which the 64 bits of a long double's mantissa leave to the last step."""
+    import torch
+    import paper_2101_10761_amd as sidco
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(capacity + count)
+    d = 12_000_017
+    idx = rng.permutation(d)[:capacity].astype(np.int32)
+    val = rng.standard_normal(capacity, dtype=np.float32)
+    want = rng.standard_normal(d, dtype=np.float32)
+    got = torch.from_numpy(want).to(dev)
+    sidco.sidco_scatter_add(got, torch.from_numpy(idx).to(dev), torch.from_numpy(val).to(dev),
+                            torch.tensor([count], dtype=torch.int32, device=dev), -0.1)
+    assert np.finfo(np.longdouble).nmant >= 63
+    at = idx[:count]
+    want[at] = (want[at].astype(np.longdouble) + np.longdouble(np.float32(-0.1)) * val[:count].astype(np.longdouble)).astype(np.float32)
+    np.testing.assert_array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32))
+    assert not sidco.sidco_scatter_check()
