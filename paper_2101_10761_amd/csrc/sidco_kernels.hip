@@ -242,12 +242,12 @@ __device__ __forceinline__ int second_row(int dist, int m)
     return m == 1 && dist == kDistGamma ? 2 : 1;
 }
 
-template <bool FLAT = false>
+template <bool SHARED = false>  // the partial sums are not the first wave's
 __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, bool auto_src)
 {
     const int m = p.stage;  // 1-based
     PrologueLoads g;
-    if (!FLAT && threadIdx.x < 64) {
+    if (!SHARED && threadIdx.x < 64) {
         const double* first = p.part_in;
         const double* second = p.part_in + (size_t)second_row(p.dist, m) * kBatchBlocks;
         const uint32_t most = ((p.nblocks - 1) & ~1u) + b.none;  // pairs past the last block's are that one's again: an unused value at most
@@ -483,9 +483,9 @@ template <typename T>
 __device__ __forceinline__ void present(T x) { asm volatile("" ::"v"(x)); }
 
 // Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
-// in every thread of every block.  Block 0 records the stage in the diagnostics.  FLAT: `v` is the thread's share of the
-// sums (see flat_sums), which the whole block adds up.
-template <bool FLAT = false>
+// in every thread of every block.  Block 0 records the stage in the diagnostics.  SHARED: `v` is the thread's share of the
+// sums (see compact_body), which the whole block adds up.
+template <bool SHARED = false>
 __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, const PrologueLoads& g, double (*sh)[4],
                                                     const BandEdges& band = BandEdges{}, double (*v)[3] = nullptr)
 {
@@ -501,7 +501,7 @@ __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool
     present(band.lo);
     present(band.hi);
     present(band.cand);
-    if constexpr (FLAT) block_sum<3>(*v, sh);
+    if constexpr (SHARED) block_sum<3>(*v, sh);
     // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
     // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
     // arithmetic and the prologue lasts that much longer (measured).
@@ -509,7 +509,7 @@ __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool
     StageRecord rec;
     if (t < 64) {
         StageSums sums;
-        if constexpr (FLAT) sums = StageSums{(*v)[0], (*v)[1], (*v)[2]};
+        if constexpr (SHARED) sums = StageSums{(*v)[0], (*v)[1], (*v)[2]};
         else sums = prologue_sums(p, g);
         r = stage_eval(p, auto_src, g, sums, rec, band);
         if (t == 0) {
@@ -1169,9 +1169,18 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     // closed form is evaluated.
     BandEdges band = {};
     if constexpr (BANDS || CHUNKS) band = band_load<true>(p);
-    const PrologueLoads g = prologue_load<FLAT>(p, b, false);
+    // CHUNKS: registers are short (see k_compact_batched), and the first wave's share of the partial sums would take 40
+    constexpr bool SHARED = FLAT || CHUNKS;  // the block adds the partial sums up together
+    const PrologueLoads g = prologue_load<SHARED>(p, b, false);
     FlatLoads f;
     if constexpr (FLAT) f = flat_load(fp, p.dist);
+    double share[3] = {0.0, 0.0, 0.0};
+    if constexpr (SHARED && !FLAT) {
+        if (threadIdx.x < p.nblocks) {
+            share[0] = p.part_in[threadIdx.x];
+            share[1] = p.part_in[(size_t)second_row(p.dist, 1) * kBatchBlocks + threadIdx.x];
+        }
+    }
     if constexpr (CHUNKS) {
         band.over = band.live && p.st->band_over != 0;
         band.live = band.live && !band.over;
@@ -1217,10 +1226,9 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
             }
         }
     }
-    double share[3];
     if constexpr (FLAT) flat_sums(fp, f, share);
 
-    const StageEta se = prologue_finish<FLAT>(p, b, false, g, sh, band, &share);
+    const StageEta se = prologue_finish<SHARED>(p, b, false, g, sh, band, &share);
 
     uint32_t run = 0, ns = 0;
     double sy = 0.0, syy = 0.0;
@@ -2466,7 +2474,9 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
 // CHUNKS: three blocks per CU, as without.  A batch's grid is up to 1024 blocks; with the 104 registers of eight lists asked
 // for at once 512 of them ran first and the rest after them.  With that, and the heads requested in any case, 25.6 M
 // elements in 161 tensors took 40.5 us and now 26.6 where the thresholds jump (15.0 and 12.7 where they keep still), 66 M in
-// 50 87.7 and 63.1 (20.0 and 16.4); without bands 26.5 and 63.5.
+// 50 87.7 and 63.1 (20.0 and 16.4); without bands 26.5 and 63.5.  Where the partial sums are folded the block adds them up
+// together: with the first wave's way, whose 40 registers went to scratch here (46 spilled, now 17), a call of 25.6 M
+// elements in 3 tensors took 84.9 us and now 81.4, 66 M in 8 193.7 and 176.2, in 15 198.6 and 183.
 template <bool STATS, bool WRITE, bool FLAT, bool KEEP, bool CHUNKS = false>
 __global__ __launch_bounds__(kBlock, CHUNKS ? 6 : 4) void k_compact_batched(BatchArgs a)
 {
