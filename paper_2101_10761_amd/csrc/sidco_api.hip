@@ -530,6 +530,8 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     mark(nullptr);
 
     if (d <= kSmallMaxD) {
+        p.stage = 1;
+        p.L_stage = p.L[0];
         launch_small(p, s);
         ++k;
         mark("k_small");

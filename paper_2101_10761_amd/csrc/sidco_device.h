@@ -71,6 +71,28 @@ __device__ __forceinline__ Calm calm_after(Calm c, bool jumped)
 }
 __device__ __forceinline__ bool calm_enough(Calm c) { return c.run >= (c.last >= kCalmRun ? 1u : kCalmMost); }
 
+// Four elements of 16 bits in two words as fp32 (widening either type is exact).
+template <int GT, typename W>
+__device__ __forceinline__ f4 widen4(W w)
+{
+    const uint32_t w0 = w.x, w1 = w.y;  // elements 0,1 and 2,3
+    f4 c;
+    if constexpr (GT == kGradBf16) {
+        c.x = __uint_as_float(w0 << 16);
+        c.y = __uint_as_float(w0 & 0xffff0000u);
+        c.z = __uint_as_float(w1 << 16);
+        c.w = __uint_as_float(w1 & 0xffff0000u);
+    } else {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        const h2 lo = __builtin_bit_cast(h2, w0), hi = __builtin_bit_cast(h2, w1);
+        c.x = (float)lo.x;
+        c.y = (float)lo.y;
+        c.z = (float)hi.x;
+        c.w = (float)hi.y;
+    }
+    return c;
+}
+
 // Four consecutive gradient elements as fp32, from element e on: one 16-byte load of an fp32 buffer, one 8-byte
 // load of an fp16 / bf16 buffer (widening either type is exact).  The address need only be aligned for one
 // element: tiles follow the alignment of the accumulated vector, the gradient's may be another one (the load
@@ -91,22 +113,7 @@ __device__ __forceinline__ f4 load_grad4(const void* __restrict__ g, size_t e)
         u2 w;
         if constexpr (STREAM) w = __builtin_nontemporal_load(q);
         else w = *q;
-        const uint32_t w0 = w.x, w1 = w.y;  // elements 0,1 and 2,3
-        f4 c;
-        if constexpr (GT == kGradBf16) {
-            c.x = __uint_as_float(w0 << 16);
-            c.y = __uint_as_float(w0 & 0xffff0000u);
-            c.z = __uint_as_float(w1 << 16);
-            c.w = __uint_as_float(w1 & 0xffff0000u);
-        } else {
-            typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-            const h2 lo = __builtin_bit_cast(h2, w0), hi = __builtin_bit_cast(h2, w1);
-            c.x = (float)lo.x;
-            c.y = (float)lo.y;
-            c.z = (float)hi.x;
-            c.w = (float)hi.y;
-        }
-        return c;
+        return widen4<GT>(w);
     }
 }
 

@@ -47,6 +47,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "sidco_internal.h"
 #include "sidco_device.h"
 
@@ -1796,14 +1798,20 @@ __device__ __forceinline__ void gather_body(const Params& p, Blk b)
 // LDS, a sum over the block and the closed form.  All loads of a thread are in flight at once: one round trip to HBM.
 // Fifteen waves hold the vector in registers.  Once the first threshold
 // is known a wave lists what exceeds it in LDS, and everything after that reads the lists: their sums, the later stages,
-// the selection.  (A wave whose exceedances outgrow its list goes on with the registers.)  The sixteenth wave evaluates
-// the closed forms; while the data are on their way it runs through them twice for nothing, so that their code is in the
-// instruction cache when the sums arrive.
-// What bounds it is a serial chain on one CU.  At 30011 elements, GPD, three stages, with the vector in LDS, every sweep and
-// the selection over all of it, and one wave of the sixteen evaluating, the kernel took 16.4 us; now 12.9 (a training step 18.2 and
-// 15.2).  With the residual stored as it was formed the last wave had its data 2700 cycles later; with a branch around every
-// element's way to the list the lists took 6300 cycles, 5500 without.
+// the selection.  (A wave whose exceedances are many or outgrow its list goes on with all of its elements.)  The sixteenth
+// wave evaluates the closed forms; while the data are on their way it runs through the first stage's for nothing, and ahead
+// of it, if there are several stages, through a later stage's, so that their code is in the instruction cache when the sums
+// arrive (not for the gamma law, see small_evaluate).
+// What bounds it is a serial chain on one CU, and instructions that are not in the cache: code that a call does not run
+// through costs it nothing, but what it does run through costs more unrolled than as a loop, and so do rows of registers that
+// a short vector does not fill.  In a graph, us, with the vector in LDS, every sweep and the selection over all of it and one wave
+// of sixteen evaluating; with registers and lists; and so: 30011 elements, GPD, 3 stages, ratio 0.01 16.5, 13.4 and 13.2; 1000
+// elements, exponential law, 1 stage 3.93, 4.18 and 3.40; 12000, gamma, 2 stages, 0.1 10.2, 11.0 and 10.5; 36000, exponential, 1
+// stage, 0.5 12.1, 13.8 and 10.9.  With the residual stored as it was formed the last wave had its data 2700 cycles later;
+// with a branch around every element's way to the list the lists took 6300 cycles, 5500 without.
 // The sums, the thresholds and the order of the output are fixed.
+// 24 kernels: the law; 16 bits or 32 (a kernel of its own for each 16-bit type and for calls without residual made 36, and a process's first
+// call took 7.0 ms, now 4.4); N of 1, 4 and 10, and for the longest vectors WHOLE.
 // ---------------------------------------------------------------------------------------------
 
 // A data wave's share of the vector: N float4s per lane.
@@ -1905,44 +1913,75 @@ __device__ __forceinline__ void small_evaluate(Params& p, int lane, const double
     }
 }
 
-constexpr uint32_t kSmallMuch = 8;
+// A list pays for a selection of up to a quarter of the wave's share (36000 elements, exponential law, 2 stages, ratio 0.15 with
+// an eighth 16.3 us, so 13.1, a third the same), and for the sums of a later stage while up to 96 of the
+// first row's 256 elements exceed the first threshold (the gamma law keeps more than it is asked for: 20000 elements, 2 stages,
+// ratio 0.1 with lists of whatever length 16.0 us, so 14.6; up to 144 of 256 the same).
+constexpr uint32_t kSmallMuch = 4, kSmallMost = 96;
+// A call of one stage with a ratio above 0.15 makes no lists at all and stores the residual once, when it has selected: 36000
+// elements, exponential law, with lists and without, ratio 0.16 10.2 us and 10.9, 0.2 10.7 and 10.9, 0.25 13.7 and 10.9; 0.5, with
+// lists that are given up, 12.6 and 10.9.
+constexpr double kSmallWhole = 1.9;  // log(1 / 0.15)
 
-// A data wave.  `list`: room for kSmallList<N> pairs
-template <int DIST, bool EC, int GT, int N>
+// A data wave.  `list`: room for kSmallList<N> pairs.  HALF: the gradient is of 16 bits.  WHOLE: a call without lists; where N
+// <= 4 one kernel does both.
+template <int DIST, bool HALF, int N, bool WHOLE>
 __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, int2* list, double (*sh)[4], uint32_t* sh_cnt,
                                            const float* sh_eta)
 {
     const int32_t t = wib * 64 + lane, d = (int32_t)p.d;
+    const bool ec = p.residual != nullptr;
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
     SmallShare<DIST, N> x;
     // the last, incomplete float4 is its owner's, element by element; past the end the last element again
     const int32_t tail = d & ~3;
     const bool owner = tail < d && (tail >> 2) % kSmallData == t;
-    float rest[3], rest_r[3];
+    const bool f16 = HALF && p.gt == kGradF16;
+    float rest[3], rest_r[3] = {0.0f, 0.0f, 0.0f};
     if (owner) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
             const int32_t i = tail + j < d ? tail + j : d - 1;
-            rest[j] = load_grad1<GT>(p.grad, i);
-            rest_r[j] = EC ? p.residual[i] : 0.0f;
+            if constexpr (HALF) rest[j] = f16 ? load_grad1<kGradF16>(p.grad, i) : load_grad1<kGradBf16>(p.grad, i);
+            else rest[j] = load_grad1<kGradF32>(p.grad, i);
+            if (ec) rest_r[j] = p.residual[i];
         }
     }
     if (d >= 4) {
         // whole float4s, wherever the buffers start; past the end the last one again: the loads stay unconditional
+        typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(2)));
+        typedef std::conditional_t<HALF, u2, f4u> Raw;
+        Raw raw[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int32_t i = 4 * (u * kSmallData + t);
-            x.c[u] = load_grad4<GT, true>(p.grad, (size_t)(i + 4 <= d ? i : d - 4));
+            const size_t at = (size_t)(i + 4 <= d ? i : d - 4) * (HALF ? 2 : 4);
+            raw[u] = __builtin_nontemporal_load(reinterpret_cast<const Raw*>(reinterpret_cast<const char*>(p.grad) + at));
         }
-        if constexpr (EC) {
-            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        auto widen = [&] {
+            if constexpr (!HALF) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) x.c[u] = raw[u];
+            } else if (f16) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) x.c[u] = widen4<kGradF16>(raw[u]);
+            } else {
+#pragma unroll
+                for (int u = 0; u < N; ++u) x.c[u] = widen4<kGradBf16>(raw[u]);
+            }
+        };
+        if (ec) {
             f4 r[N];
 #pragma unroll
             for (int u = 0; u < N; ++u) {
                 const int32_t i = 4 * (u * kSmallData + t);
                 r[u] = *reinterpret_cast<const f4u*>(p.residual + (i + 4 <= d ? i : d - 4));
             }
+            widen();
 #pragma unroll
             for (int u = 0; u < N; ++u) x.c[u] = x.c[u] + r[u];
+        } else {
+            widen();
         }
     }
     f4 end = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -1951,7 +1990,7 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
         for (int j = 0; j < 3; ++j) {
             if (tail + j >= d) continue;
             end[j] = rest[j];
-            if constexpr (EC) {
+            if (ec) {
                 end[j] = rest[j] + rest_r[j];
                 p.residual[tail + j] = end[j];
             }
@@ -1981,8 +2020,8 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
         });
         sums_out(s1, DIST == kDistGamma ? sl + (double)se : s2, 0.0);
     }
-    if constexpr (EC) {  // while the closed form is evaluated: ahead of that the stores would hold other waves' loads back
-        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const bool whole = N > 4 ? WHOLE : p.M == 1 && p.L_stage < kSmallWhole;
+    if (ec && !whole) {  // while the closed form is evaluated: ahead of that the stores would hold other waves' loads back
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int32_t i = 4 * (u * kSmallData + t);
@@ -1990,14 +2029,61 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
         }
     }
     __syncthreads();
-    // what exceeds the first threshold
     float eta = *sh_eta;
-    uint32_t len = 0;
+    uint32_t pos = 0;  // the wave's next place in the output
+    auto positions = [&](uint32_t mine) {
+        if (lane == 0) sh_cnt[wib] = mine;
+        __syncthreads();  // also between the residual's stores and the clearing
+#pragma unroll
+        for (int i = 0; i < kSmallWaves - 1; ++i) pos += i < wib ? sh_cnt[i] : 0u;
+    };
+    const uint32_t cap = (uint32_t)p.out_cap;
+    // writes what is selected of 64 entries; whether the lane's was
+    auto emit_pairs = [&](bool in, float v, int32_t i) {
+        const bool sel = in && __builtin_fabsf(v) > eta;
+        const unsigned long long mask = __ballot(sel);
+        const uint32_t at = pos + lane_prefix(mask);
+        const bool out = sel && at < cap;  // pairs beyond the capacity stay in the residual
+        if (out) {
+            p.out_idx[at] = i;
+            p.out_val[at] = v;
+        }
+        pos += (uint32_t)__popcll(mask);
+        return out;
+    };
+    // the float4 `c`, of whose entries those that are selected go to the output and become zero
+    auto emit_row = [&](f4 c, int32_t i) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (emit_pairs(true, c[j], i + j)) c[j] = 0.0f;
+        if (!ec) return;
+        if (i + 4 <= d) {
+            *reinterpret_cast<f4u*>(p.residual + i) = c;
+        } else {
+#pragma unroll
+            for (int j = 0; j < 3; ++j)
+                if (i + j < d) p.residual[i + j] = c[j];
+        }
+    };
+    if (__builtin_expect(whole, 0)) {
+        uint32_t n = 0;
+        x.each(t, d, [&](bool, float v, int32_t) { n += (uint32_t)__popcll(__ballot(__builtin_fabsf(v) > eta)); });
+        positions(n);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (4 * u * kSmallData < d) emit_row(x.c[u], 4 * (u * kSmallData + t));  // uniform
+        return;
+    }
+    // what exceeds the first threshold
     constexpr uint32_t kRoom = kSmallList<N> - 64;
+    // where all of a wave's share has room and the law keeps to its ratio no list is given up: 15360 elements 5.20 us, 5.28 with
+    // the code for it
+    constexpr bool kMayGiveUp = N > 4 || (N > 1 && DIST == kDistGamma);
+    uint32_t len = 0;
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         const int32_t i = 4 * (u * kSmallData + t);
-        if (4 * u * kSmallData >= d || len > kRoom) continue;  // uniform; a list that is too short is none
+        if (4 * u * kSmallData >= d || (kMayGiveUp && len > kRoom)) continue;  // uniform; a list that is too short is none
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const bool sel = __builtin_fabsf(x.c[u][j]) > eta;
@@ -2007,14 +2093,24 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
             list[sel ? at : kSmallList<N> - 1] = make_int2(i + j, __float_as_int(x.c[u][j]));
             len += (uint32_t)__popcll(mask);
         }
+        if (kMayGiveUp && u == 0 && len > kSmallMost) len = kRoom + 1;
     }
-    const bool listed = len <= kRoom;
+    const bool listed = !kMayGiveUp || len <= kRoom;
+    // Where the list does not serve the elements take its room, the lane's own in rows: what goes through them is a loop then
+    // (30011 elements, GPD, 3 stages, with that code unrolled over the registers 13.5 us, so 13.2)
+    static_assert(kSmallList<N> * sizeof(int2) >= N * 64 * sizeof(f4), "room for the wave's share");
+    f4* const rows = reinterpret_cast<f4*>(list) + lane;
+    auto rows_store = [&] {
+#pragma unroll
+        for (int u = 0; u < N; ++u) rows[u * 64] = x.c[u];
+    };
+    if (!listed) rows_store();
     // the lane's entries among the first 64 * kHead of the list stay in registers; stale past the list's end
-    constexpr int kHead = 8;
+    constexpr int kHead = N > 1 ? 8 : 4;
     int2 head[kHead];
 #pragma unroll
     for (int u = 0; u < kHead; ++u) head[u] = list[u * 64 + lane];
-    // f(valid, value, index) for those, the wave together: from the list, or, if it is too short, from all elements
+    // f(valid, value, index) for those, the wave together: from the list, or, if it is none, from all elements
     auto exceeding = [&](auto f) {
         if (listed) {
 #pragma unroll
@@ -2027,7 +2123,12 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
                 f(k + 64 + lane < len, __int_as_float(g.y), g.x);
             }
         } else {
-            x.each(t, d, [&](bool, float v, int32_t i) { f(true, v, i); });
+#pragma unroll 1
+            for (int u = 0; 4 * u * kSmallData < d; ++u) {
+                const f4 c = rows[u * 64];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) f(true, c[j], 4 * (u * kSmallData + t) + j);
+            }
         }
     };
 #pragma unroll 1
@@ -2044,55 +2145,22 @@ __device__ __forceinline__ void small_data(const Params& p, int lane, int wib, i
         mine = 0;
         exceeding([&](bool in, float v, int32_t) { mine += (uint32_t)__popcll(__ballot(in && __builtin_fabsf(v) > eta)); });
     }
-    if (lane == 0) sh_cnt[wib] = mine;
-    __syncthreads();  // also between the residual's stores and the clearing
-    uint32_t pos = 0;
-#pragma unroll
-    for (int i = 0; i < kSmallWaves - 1; ++i) pos += i < wib ? sh_cnt[i] : 0u;
-    const uint32_t cap = (uint32_t)p.out_cap;
-    // writes what is selected of 64 entries; whether the lane's was
-    auto emit_pairs = [&](bool in, float v, int32_t i) {
-        const bool sel = in && __builtin_fabsf(v) > eta;
-        const unsigned long long mask = __ballot(sel);
-        const uint32_t at = pos + lane_prefix(mask);
-        const bool out = sel && at < cap;  // pairs beyond the capacity stay in the residual
-        if (out) {
-            p.out_idx[at] = i;
-            p.out_val[at] = v;
-        }
-        pos += (uint32_t)__popcll(mask);
-        return out;
-    };
+    positions(mine);
     // A wave that selects much of its share, or has no list, goes through its elements once more and stores whole float4s: one
-    // by one the cleared entries of 12000 elements, gamma law, of which it keeps 31 %, cost 3 us more.
+    // by one the cleared entries of 12000 elements, gamma law, of which it keeps 31 %, cost 3 us more (see kSmallMuch).
     if (listed && mine * kSmallMuch <= (uint32_t)(d / (kSmallWaves - 1))) {
         exceeding([&](bool in, float v, int32_t i) {
-            if (emit_pairs(in, v, i) && EC) p.residual[i] = 0.0f;
+            if (emit_pairs(in, v, i) && ec) p.residual[i] = 0.0f;
         });
         return;
     }
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-        const int32_t i = 4 * (u * kSmallData + t);
-        if (4 * u * kSmallData >= d) continue;  // uniform
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (emit_pairs(true, x.c[u][j], i + j)) x.c[u][j] = 0.0f;
-        if constexpr (EC) {
-            typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-            if (i + 4 <= d) {
-                *reinterpret_cast<f4u*>(p.residual + i) = x.c[u];
-            } else {
-#pragma unroll
-                for (int j = 0; j < 3; ++j)
-                    if (i + j < d) p.residual[i + j] = x.c[u][j];
-            }
-        }
-    }
+    if (listed) rows_store();
+#pragma unroll 1
+    for (int u = 0; 4 * u * kSmallData < d; ++u) emit_row(rows[u * 64], 4 * (u * kSmallData + t));
 }
 
 // N: float4s per lane of a data wave, 4 * kSmallData * N >= d
-template <int DIST, bool EC, int GT, int N>
+template <int DIST, bool HALF, int N, bool WHOLE>
 __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 {
     extern __shared__ __align__(16) int2 lists[];  // kSmallList<N> for each data wave
@@ -2104,7 +2172,7 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
     p.dist = DIST;
     // Both sides pass the same barriers: two for every stage, one ahead of the output.
     if (wib == kSmallWaves - 1) small_evaluate<DIST>(p, lane, sh, sh_cnt, &sh_eta);
-    else small_data<DIST, EC, GT, N>(p, lane, wib, lists + wib * kSmallList<N>, sh, sh_cnt, &sh_eta);
+    else small_data<DIST, HALF, N, WHOLE>(p, lane, wib, lists + wib * kSmallList<N>, sh, sh_cnt, &sh_eta);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2603,46 +2671,33 @@ void launch_fit_bands(const Params& p, hipStream_t s)
     }
 }
 
-template <int DIST, bool EC, int GT, int N>
+template <bool HALF, int N, bool WHOLE = false>
 static void launch_small_as(const Params& p, hipStream_t s)
 {
     constexpr size_t lds = (kSmallWaves - 1) * kSmallList<N> * sizeof(int2);
-    hipLaunchKernelGGL((k_small<DIST, EC, GT, N>), dim3(1), dim3(kSmallBlock), lds, s, p);
-}
-
-template <bool EC, int GT, int N>
-static void launch_small_dist(const Params& p, hipStream_t s)
-{
+    const dim3 grid(1), block(kSmallBlock);
     switch (p.dist) {
-        case kDistExp: launch_small_as<kDistExp, EC, GT, N>(p, s); break;
-        case kDistGamma: launch_small_as<kDistGamma, EC, GT, N>(p, s); break;
-        default: launch_small_as<kDistGpd, EC, GT, N>(p, s); break;
+        case kDistExp: hipLaunchKernelGGL((k_small<kDistExp, HALF, N, WHOLE>), grid, block, lds, s, p); break;
+        case kDistGamma: hipLaunchKernelGGL((k_small<kDistGamma, HALF, N, WHOLE>), grid, block, lds, s, p); break;
+        default: hipLaunchKernelGGL((k_small<kDistGpd, HALF, N, WHOLE>), grid, block, lds, s, p); break;
     }
 }
 
-template <bool EC, int GT>
+template <bool HALF>
 static void launch_small_size(const Params& p, hipStream_t s)
 {
     constexpr int kShort = 4, kLong = (kSmallMaxD + 4 * kSmallData - 1) / (4 * kSmallData);
-    if (p.d <= 4 * kSmallData * kShort) launch_small_dist<EC, GT, kShort>(p, s);
-    else launch_small_dist<EC, GT, kLong>(p, s);
-}
-
-template <int GT>
-static void launch_small_type(const Params& p, hipStream_t s)
-{
-    if (p.residual) launch_small_size<true, GT>(p, s);
-    else launch_small_size<false, GT>(p, s);
+    if (p.d <= 4 * kSmallData) launch_small_as<HALF, 1>(p, s);
+    else if (p.d <= 4 * kSmallData * kShort) launch_small_as<HALF, kShort>(p, s);
+    else if (p.M > 1 || p.L_stage >= kSmallWhole) launch_small_as<HALF, kLong>(p, s);
+    else launch_small_as<HALF, kLong, true>(p, s);
 }
 
 // needs p.d <= kSmallMaxD
 void launch_small(const Params& p, hipStream_t s)
 {
-    switch (p.gt) {
-        case kGradF16: launch_small_type<kGradF16>(p, s); break;
-        case kGradBf16: launch_small_type<kGradBf16>(p, s); break;
-        default: launch_small_type<kGradF32>(p, s); break;
-    }
+    if (p.gt == kGradF32) launch_small_size<false>(p, s);
+    else launch_small_size<true>(p, s);
 }
 
 // `flat`: the launch shape (see fit_uses_flat).  `scratch`: device memory for 3 * fit_flat_blocks(d, shift) doubles in

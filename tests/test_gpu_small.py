@@ -34,3 +34,28 @@ def test_lists_that_are_too_short(oracle, d, dist, ratios):
     for cap in (None, d // 7):  # the second: the output is full long before the end
         out = run_gpu(g, r, dist, ratios, cap=cap)
         check_parity(oracle, g, r, dist, ratios, out, capacity=cap, label=f"d={d} law {dist} ratios {ratios} cap {cap}")
+
+
+@pytest.mark.parametrize("kind", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("d", [3839, 3841, 15359, 15361, 26_001, 36_863])
+def test_mild_ratios(oracle, kind, d):
+    """One stage with and without lists (the line is 0.15) for each number of rows, the types that share a kernel, and calls with
+    and without a residual, which do."""
+    import paper_2101_10761_amd as sidco
+    from test_gpu_typed import narrow, run_typed
+    rng = np.random.default_rng(3 * d)
+    g = (rng.standard_t(3.0, d) * 1e-3).astype(np.float32)
+    r = rng.laplace(0, 1e-3, d).astype(np.float32)
+    for dist in (0, 1, 2):
+        for delta, stages in ((0.14, 1), (0.16, 1), (0.6, 1), (0.1, 2)):
+            ratios = sidco.sidco_stage_ratios(delta, stages)
+            for res in (r, None):
+                label = f"{kind} d={d} law {dist} delta {delta} M={stages} ec={res is not None}"
+                if kind == "f32":
+                    cap = None
+                    out, seen = run_gpu(g, res, dist, ratios, grad_offset=1, res_offset=2), g
+                else:
+                    cap = sidco.sidco_out_capacity(d, delta)
+                    given, seen = narrow(g, kind)
+                    out = run_typed(given, res, dist, delta, stages, grad_offset=1, res_offset=2)
+                check_parity(oracle, seen, res, dist, ratios, out, capacity=cap, label=label)
