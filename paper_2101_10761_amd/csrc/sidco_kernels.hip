@@ -2179,14 +2179,14 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 // k_scatter_add: the step after the sparsifier in Algorithm 2 - a worker's (index, value) pairs are
 // added into the dense aggregate, dense[idx[i]] += scale * val[i].  The indices of one list are
 // distinct, so plain read-modify-write needs no atomics and the result is deterministic; lists of
-// several workers are added by consecutive launches.  Two roundings per element (product, then sum),
-// as a plain fp32 loop does.
-// Bound by the lines that long lists touch.  The pairs are read past the caches, whose room the dense lines need, and the
-// grid is several times what runs at once, so that blocks that fall behind do not end last: 13.8 M pairs in 138 M elements,
-// alone, 1024 blocks and ordinary loads 282 us, non-temporal ones 271, 8192 blocks 268, both 258 (4096 259, 65536 with
-// ordinary loads 281); 1.4 M pairs 80 and 78; a training step of 138 M elements, ratio 0.1 834 and 823.  Non-temporal loads or stores of the dense lines are slower (390, 268 at 8192
-// blocks), and four pairs per thread change nothing.
+// several workers are added by consecutive launches.  Product and sum are fused: one rounding per element.
+// Bound by the lines that long lists touch.  Pairs that fill the L2 caches (half of their 32 MB) are read past them, as the dense lines
+// need the room: 13.8 M pairs in 138 M elements, alone, 1024 blocks, ordinary and non-temporal loads 270 and 267 us, 4096
+// blocks 263 and 259; 4 M 127 and 114, 3.5 M 98 and 90; but a list that the caches may still hold 1.4 M 46 and 50, 0.3 M 9.4 and
+// 13.3.  Non-temporal loads or stores of the dense lines are slower (390, 268 at 8192 blocks), and four pairs per thread change
+// nothing.
 // ---------------------------------------------------------------------------------------------
+constexpr int64_t kScatterStream = 1 << 21;  // pairs
 __global__ __launch_bounds__(kBlock) void k_scatter_add(float* __restrict__ dense, int64_t d, const int32_t* __restrict__ idx,
                                                         const float* __restrict__ val, const int32_t* __restrict__ count,
                                                         int64_t capacity, float scale, uint32_t* __restrict__ bad)
@@ -2194,14 +2194,19 @@ __global__ __launch_bounds__(kBlock) void k_scatter_add(float* __restrict__ dens
     int64_t n = (int64_t)*count;
     if (n > capacity) n = capacity;
     const int64_t stride = (int64_t)gridDim.x * kBlock;
-    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
-        const int64_t j = (int64_t)__builtin_nontemporal_load(idx + i);
-        if (j < 0 || j >= d) {  // never written; reported
-            atomicOr(bad, 1u);
-            continue;
+    auto add = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
+        for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) {
+            const int64_t j = (int64_t)(STREAM ? __builtin_nontemporal_load(idx + i) : idx[i]);
+            if (j < 0 || j >= d) {  // never written; reported
+                atomicOr(bad, 1u);
+                continue;
+            }
+            dense[j] = fmaf(scale, STREAM ? __builtin_nontemporal_load(val + i) : val[i], dense[j]);
         }
-        dense[j] = __fadd_rn(dense[j], __fmul_rn(scale, __builtin_nontemporal_load(val + i)));
-    }
+    };
+    if (n >= kScatterStream) add(std::true_type());
+    else add(std::false_type());
 }
 
 __global__ void k_clear_u32(uint32_t* p) { *p = 0; }
@@ -2209,7 +2214,11 @@ __global__ void k_clear_u32(uint32_t* p) { *p = 0; }
 // a fill kernel rather than a memset: callers may record the stream into a HIP graph
 void launch_clear_u32(uint32_t* p, hipStream_t s) { hipLaunchKernelGGL(k_clear_u32, dim3(1), dim3(1), 0, s, p); }
 
-constexpr int64_t kScatterBlocks = 8192;  // see k_scatter_add
+// Blocks: as many as run at once, or, where the buffers have room for a list that is long enough to gain by it, several times as
+// many, so that blocks that fall behind do not end last.  With 1024, 4096 and 8192 blocks 13.8 M pairs take 267, 259 and 254 us, a
+// training step of 138 M elements, ratio 0.1 859, 851 and 846; 4 M pairs 114, 113 and 113; but 100 pairs in long buffers
+// 2.1, 3.3 and 5.0, and 138000 4.7, 4.7 and 6.3.
+constexpr int64_t kScatterBlocks = 2 * kMaxBlocks, kScatterBlocksLong = 8 * kMaxBlocks, kScatterLong = 8000000;
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s)
 {
@@ -2218,7 +2227,8 @@ void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float
     // a chain of four updates: 7.1 us, against 4.0 for as many pairs in four times the capacity.
     int64_t blocks = (capacity + kBlock - 1) / kBlock;
     if (blocks < 1) blocks = 1;
-    if (blocks > kScatterBlocks) blocks = kScatterBlocks;
+    const int64_t most = capacity < kScatterLong ? kScatterBlocks : kScatterBlocksLong;
+    if (blocks > most) blocks = most;
     hipLaunchKernelGGL(k_scatter_add, dim3((uint32_t)blocks), dim3(kBlock), 0, s, dense, d, idx, val, count, capacity,
                        scale, bad);
 }
