@@ -175,9 +175,9 @@ int ensure_workspace(WsCtx& c, size_t need)
 }
 
 // Launch geometry of a sweep (see WaveTiles): `base` is the vector whose lines the tiles sit on, NULL if its alignment
-// does not matter.
+// does not matter.  `turn_rows`: see kTurnRows.
 template <typename P>
-void fill_sweep(P& p, const float* base, int64_t d)
+void fill_sweep(P& p, const float* base, int64_t d, uint32_t turn_rows = kTurnRows)
 {
     p.shift = (uint32_t)((uintptr_t)base >> 2) & (uint32_t)(kGrid - 1);
     const uint32_t ntiles = (uint32_t)((d + p.shift + kTile - 1) / kTile);
@@ -185,6 +185,7 @@ void fill_sweep(P& p, const float* base, int64_t d)
     p.nwaves = ntiles < (uint32_t)kMaxWaves ? ntiles : (uint32_t)kMaxWaves;
     p.tq = ntiles / p.nwaves;
     p.tr = ntiles % p.nwaves;
+    p.turn = p.nwaves == (uint32_t)kMaxWaves && p.tq >= turn_rows ? 1u : 0u;
     p.nblocks = (p.nwaves + kWavesPerBlock - 1) / kWavesPerBlock;
 }
 
@@ -498,6 +499,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     Params p;
     fill_common(p, h, grad, residual, d, dist, gt, own_acc ? (float*)((char*)c.ws + head_bytes() + 2 * seg) : nullptr);
     p.M = M;
+    if (M == 1) p.turn = 0;
     for (int m = 0; m < M; ++m) p.L[m] = log(1.0 / ratios[m]);
     p.out_idx = out_idx;
     p.out_val = out_val;
@@ -1348,7 +1350,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     p.acc = q.acc;
     p.d = d;
     p.k = k;
-    fill_sweep(p, p.acc, d);
+    fill_sweep(p, p.acc, d, kTurnRowsTopk);
     p.hist0 = h->topk_hist;
     p.hist1 = p.hist0 + kTopkCopies * kTopkBins;
     p.hist2 = p.hist1 + kTopkBins;

@@ -184,7 +184,7 @@ __device__ __forceinline__ size_t seg_begin(const P& p, uint32_t w) { return (si
 template <typename P>
 __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (p.tq + (w < p.tr ? 1u : 0u)) * kTile; }
 
-// Number of the wave's k-th tile in the sweep that forms acc; they ascend.  In vectors of kTurnRows rows of W tiles and more
+// Number of the wave's k-th tile in the sweep that forms acc; they ascend.  In long vectors (`turn`, see kTurnRows)
 // the waves do not keep their place in the row.  Blocks go to the eight XCDs in turn, b and b + 256 share a CU and the later
 // one ends 1.5 % behind the other, and every other XCD ends 5 % behind its neighbours; where places stay, an XCD has the same
 // 8 KB of every 64 KB all the way.  Here the halves of the waves change places from row to row, and in each half of a
@@ -193,14 +193,12 @@ __device__ __forceinline__ uint32_t seg_slots(const P& p, uint32_t w) { return (
 // and 77.1; 40 M 94.4, 93.6 and 92.3; 66 M, gamma 146.5, 143.8 and 142.0; 78 M, 3 stages -, 188.5 and 186.7; 90 M, 2 stages
 // 203, 198.8 and 195.9; 138 M, 3 stages 405.8, 393.0 and 392.2 (first pass 292 and 278).  Pieces of 128 and of 64 KB or that
 // move on every other row are slower (66 M 142.7, 147.6, 145.1), and so are places that move on by one, two, four or eight
-// blocks a row (138 M 394, 401, 405, 405).  Shorter vectors gain nothing, and those that the caches serve lose (halves that
-// change: one stage on 8 M 27.8 and 28.4).  The lists and sums are the wave's whichever its tiles are.
-constexpr uint32_t kTurnRows = 18;
+// blocks a row (138 M 394, 401, 405, 405).  The lists and sums are the wave's whichever its tiles are.
 template <typename P>
 __device__ __forceinline__ uint32_t acc_tile(const P& p, uint32_t w, uint32_t k)
 {
     static_assert(kMaxBlocks == 512 && kWavesPerBlock == 8, "halves of 8 pieces of 32 blocks");
-    if (p.nwaves == (uint32_t)kMaxWaves && p.tq >= kTurnRows && k < p.tq) {
+    if (p.turn && k < p.tq) {
         const uint32_t b = w / kWavesPerBlock, half = (b >> 8) ^ (k & 1u), piece = (b + k) & 7u;
         w = ((half * 8 + piece) * 32 + (b >> 3 & 31u)) * kWavesPerBlock + w % kWavesPerBlock;
     }

@@ -112,6 +112,15 @@ struct DevState {
     Calm band_calm;
 };
 
+// Rows of kMaxWaves tiles from which on the waves of a first pass change places (see acc_tile).  Shorter vectors gain nothing, and those
+// that the caches serve lose (one stage on 8 M 27.8 and 28.4 us).  Calls without it and with it, us: 2 stages 19 M 59.3 and 59.2,
+// 25.6 M 74.1 and 73.5, 3 stages 82.1 and 81.5, calls that do not repeat a shape, 25.6 M 83.5 and 82.1, 40 M 122 and 118.7; DGC 19 M
+// 77.1 and 76.5, 25.6 M 93.0 and 92.9, 40 M 133 and 129.  A call of one stage reads the vector again at its own places, and 19 M take
+// 50.8 and 52.3, 25.6 M 65.9 and 67.1, 40 M 98.3 and 99.8, and longer ones have the flat shape: it never does.  Top-k, whose first pass
+// lists as well or is read again: 19 M 62.7 and 63.7, bf16 25.6 M 73.1 and 74.0, fp32 79.4 and 79.7, 40 M 113.4 and 114.3, not
+// repeated 109.6 and 110.4, 60 M 164.2 and 162.4, not repeated 162.1 and 159.1, 100 M 277 and 269.
+constexpr uint32_t kTurnRows = 18, kTurnRowsTopk = 40;
+
 // element type of the gradient buffer (the accumulated vector and the residual are always fp32)
 constexpr int kGradF32 = 0, kGradF16 = 1, kGradBf16 = 2;
 
@@ -154,6 +163,7 @@ struct Params {
     float* acc_w;           // where k_fit stores acc: residual; for a 16-bit gradient without residual a
                             // workspace buffer; NULL when acc is the fp32 gradient itself
     int gt;                 // kGrad*
+    uint32_t turn;          // k_fit: the waves change places from row to row (see acc_tile)
     int acc_reset;          // k_fit: start the controller's count of reported pairs over instead of adding to it
     unsigned long long owner;  // id of the stage controller that makes the call, 0 otherwise
     int32_t* out_idx;
@@ -206,7 +216,7 @@ struct TopkParams {
     int k_from_state;       // the last kernel takes k from st->k_eff (may be 0) instead of `k`
     uint32_t clear0;        // words of hist0 that the last kernel clears for the next call
     int bands;              // kBands*: whether the call leaves an edge for the next one, and whether it has one itself
-    uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
+    uint32_t shift, nfull, nwaves, tq, tr, nblocks, turn;  // see Params
     uint32_t* hist0;        // [kTopkCopies][kTopkBins]
     uint32_t* hist1;        // [1024]
     uint32_t* hist2;        // [1024]
@@ -242,7 +252,7 @@ struct DgcParams {
     float* acc_w;     // where the dense pass stores acc: residual, or nowhere
     int64_t d;
     int64_t k;        // target number of entries
-    uint32_t shift, nfull, nwaves, tq, tr, nblocks;  // see Params
+    uint32_t shift, nfull, nwaves, tq, tr, nblocks, turn;  // see Params
     uint64_t seed;
     uint32_t n_s, k_s;  // subset size, rank of the threshold in it
     uint32_t* keys;     // [n_s] magnitude keys of the subset

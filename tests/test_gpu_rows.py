@@ -20,3 +20,28 @@ def test_first_pass_on_both_sides_of_the_line(oracle, d, offset, residual):
     for call in range(2):  # the second goes by the first one's thresholds
         out = run_gpu(g, r, 0, ratios, grad_offset=offset, res_offset=offset)
         check_parity(oracle, g, r, 0, ratios, out, label=f"d={d} offset={offset} ec={residual} call {call}")
+
+
+@pytest.mark.parametrize("d,offset,residual", [(40 * ROW - 1, 0, True), (40 * ROW + 257, 31, True), (41 * ROW - 256, 0, False)])
+def test_first_pass_of_top_k(oracle, d, offset, residual):
+    from test_gpu_topk import check_topk, run_topk
+    rng = np.random.default_rng(d + offset)
+    g = rng.standard_normal(d, dtype=np.float32)
+    r = rng.standard_normal(d, dtype=np.float32) if residual else None
+    k = d // 1000
+    for call in range(2):  # the second lists what is above an edge under the first one's k-th magnitude
+        out = run_topk(g, r, k, grad_offset=offset, res_offset=offset)
+        check_topk(oracle, g, r, k, out, label=f"d={d} offset={offset} ec={residual} call {call}")
+
+
+@pytest.mark.parametrize("d,offset", [(18 * ROW - 1, 0), (18 * ROW + 257, 31)])
+def test_calls_of_one_stage_and_dgc(oracle, d, offset):
+    """The first, which reads the vector at its waves' own places again, does not change places; the second does."""
+    from test_gpu_dgc import check_dgc, run_dgc
+    rng = np.random.default_rng(d + offset)
+    g = rng.standard_normal(d, dtype=np.float32)
+    r = rng.standard_normal(d, dtype=np.float32)
+    out = run_gpu(g, r, 0, [0.001], grad_offset=offset, res_offset=offset)
+    check_parity(oracle, g, r, 0, [0.001], out, label=f"d={d} one stage")
+    out = run_dgc(g, r, 0.001, 0.01, 3, grad_offset=offset, res_offset=offset)
+    check_dgc(oracle, g, r, 0.001, 0.01, 3, out, label=f"d={d} DGC")
