@@ -133,7 +133,8 @@ __device__ __forceinline__ uint32_t lane_prefix(unsigned long long mask)
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-// The tiles of one wave of the sparsifier's sweeps: wave w of W takes the tiles w, w + W, w + 2W, ...  All waves
+// The tiles of one wave of the sparsifier's sweeps: wave w of W takes the tiles w, w + W, w + 2W, ... (in long vectors the sweep
+// that forms acc takes others, see acc_tile, as many).  All waves
 // then work in one narrow window of the vector that moves through it in address order, which DRAM and the
 // memory-side cache serve better than thousands of separate streams (a statistics-only sweep right after k_fit,
 // contiguous ranges against this: 16.2 and 13.0 us at 25.6 M elements, 38 and 29 us at 66 M, 106 and 88 us at

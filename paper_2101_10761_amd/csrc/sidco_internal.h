@@ -35,7 +35,7 @@ constexpr double kSpeculation = 0.5;
 // next, so the candidate lists shrink to a little more than the next stage's exceedances.
 constexpr float kHintMargin = 0.1f;
 constexpr float kHintMax = 0.95f;
-static_assert(kMaxBlocks <= kBlock, "one thread per producer block in the prologue reductions");
+static_assert(kMaxBlocks <= kBlock, "a thread for every producer block, in gather_body and for compact_body's folded sums");
 
 constexpr int kDistExp = SIDCO_DIST_EXP;
 constexpr int kDistGamma = SIDCO_DIST_GAMMA_GPD;

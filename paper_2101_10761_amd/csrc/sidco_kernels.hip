@@ -218,6 +218,7 @@ struct StageEta {
 typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef uint32_t u2 __attribute__((ext_vector_type(2), aligned(4)));
 constexpr int kPartLoads = kMaxBlocks / 128;
+static_assert(kMaxBlocks % 128 == 0, "every partial sum is loaded");
 struct PrologueLoads {
     d2 a[kPartLoads], b[kPartLoads];  // the lane's share of the producer's partial sums: the first quantity's, the second's
     u2 n[kPartLoads];                 // and of the counts
@@ -258,7 +259,7 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
             const uint32_t i = min((uint32_t)(128 * k) + 2 * threadIdx.x, most);
             g.a[k] = *reinterpret_cast<const d2*>(first + i);
             g.b[k] = *reinterpret_cast<const d2*>(second + i);
-            g.n[k] = *reinterpret_cast<const u2*>(p.blk_in + i);
+            g.n[k] = *reinterpret_cast<const u2*>(p.blk_in + i);  // in stage 1 too: under a condition 0.3 % of a call slower
         }
     }
     g.seen = (p.theta > 0.0f && p.use_hint) ? p.st->theta_seen[m] : __builtin_nanf("");
@@ -275,7 +276,7 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
 }
 
 // What the stage's fit is made from, by the first wave: sums of |x| (stage 1) or y = |x| - eta_{m-1} over the exceedances,
-// the law's second quantity, and the exceedances' number (0 in stage 1).
+// the law's second quantity, and the exceedances' number (anything in stage 1, where nothing asks for it).
 struct StageSums {
     double first, second, n;
 };
@@ -488,8 +489,8 @@ __device__ __forceinline__ void present(T x) { asm volatile("" ::"v"(x)); }
 // in every thread of every block.  Block 0 records the stage in the diagnostics.  SHARED: `v` is the thread's share of the
 // sums (see compact_body), which the whole block adds up.
 template <bool SHARED = false>
-__device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, const PrologueLoads& g, double (*sh)[4],
-                                                    const BandEdges& band = BandEdges{}, double (*v)[3] = nullptr)
+__device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, const PrologueLoads& g, const BandEdges& band = BandEdges{},
+                                                    double (*v)[3] = nullptr, double (*sh)[4] = nullptr)
 {
     __shared__ float sh_eta[4];
     const uint32_t t = threadIdx.x;
@@ -531,11 +532,10 @@ __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool
 }
 
 // both halves back to back, for kernels whose body loads little before the threshold is known
-__device__ __forceinline__ StageEta stage_prologue(const Params& p, Blk b, bool auto_src, double (*sh)[4],
-                                                   const BandEdges& band = BandEdges{})
+__device__ __forceinline__ StageEta stage_prologue(const Params& p, Blk b, bool auto_src, const BandEdges& band = BandEdges{})
 {
     const PrologueLoads g = prologue_load(p, b, auto_src);
-    return prologue_finish(p, b, auto_src, g, sh, band);
+    return prologue_finish(p, b, auto_src, g, band);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1230,7 +1230,7 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     }
     if constexpr (FLAT) flat_sums(fp, f, share);
 
-    const StageEta se = prologue_finish<SHARED>(p, b, false, g, sh, band, &share);
+    const StageEta se = prologue_finish<SHARED>(p, b, false, g, band, &share, sh);
 
     uint32_t run = 0, ns = 0;
     double sy = 0.0, syy = 0.0;
@@ -1327,7 +1327,7 @@ __device__ __forceinline__ void lists_body(const Params& p, Blk b)
         above = band_above_load(p, b);
     }
 
-    const StageEta se = prologue_finish(p, b, true, g, sh, band);
+    const StageEta se = prologue_finish(p, b, true, g, band);
     const float eta = se.eta;
 
     uint32_t ns = 0;
@@ -1507,9 +1507,8 @@ __device__ __forceinline__ void final_results(const Params& p, float eta)
 template <bool BANDS>
 __device__ __forceinline__ void final_record(const Params& p, Blk b)
 {
-    __shared__ double sh[kWavesPerBlock][4];
     const BandEdges band = band_load<BANDS>(p);
-    const float eta = stage_prologue(p, b, true, sh, band).eta;
+    const float eta = stage_prologue(p, b, true, band).eta;
     if (threadIdx.x == 0) final_results(p, eta);
     __syncthreads();
     if (threadIdx.x == kBlock - 64) bands_record(p, eta);
@@ -1519,7 +1518,6 @@ __device__ __forceinline__ void final_record(const Params& p, Blk b)
 template <bool BANDS = false>
 __device__ __forceinline__ void final_body(const Params& p, Blk b)
 {
-    __shared__ double sh[kWavesPerBlock][4];
     __shared__ uint32_t sh_cnt[kWavesPerBlock];
     __shared__ unsigned long long sh_base;
     constexpr int K = kFinalGroup;
@@ -1550,7 +1548,7 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
         }
     }
 
-    const StageEta se = prologue_finish(p, b, true, g, sh, band);
+    const StageEta se = prologue_finish(p, b, true, g, band);
     const float eta = se.eta;
     const bool from_lists = se.lists_ok || se.hit;
 
@@ -1632,8 +1630,7 @@ __device__ __forceinline__ void final_body(const Params& p, Blk b)
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(kBlock) void k_eta(Params p)
 {
-    __shared__ double sh[kWavesPerBlock][4];
-    const StageEta se = stage_prologue(p, whole_grid(), false, sh);
+    const StageEta se = stage_prologue(p, whole_grid(), false);
     if (threadIdx.x == 0) {
         *p.out_eta = se.eta;
         const uint32_t status = p.st->status_after[p.M];  // written by this thread in the prologue
