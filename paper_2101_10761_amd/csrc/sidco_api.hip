@@ -1350,7 +1350,7 @@ int sidco_topk_typed(void* stream, const void* grad, int grad_dtype, float* resi
     p.acc = q.acc;
     p.d = d;
     p.k = k;
-    fill_sweep(p, p.acc, d, kTurnRowsTopk);
+    fill_sweep(p, p.acc, d, gt == kGradF32 ? kTurnRowsTopk : kTurnRowsTopk16);
     p.hist0 = h->topk_hist;
     p.hist1 = p.hist0 + kTopkCopies * kTopkBins;
     p.hist2 = p.hist1 + kTopkBins;

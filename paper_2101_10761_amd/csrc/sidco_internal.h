@@ -117,9 +117,11 @@ struct DevState {
 // 25.6 M 74.1 and 73.5, 3 stages 82.1 and 81.5, calls that do not repeat a shape, 25.6 M 83.5 and 82.1, 40 M 122 and 118.7; DGC 19 M
 // 77.1 and 76.5, 25.6 M 93.0 and 92.9, 40 M 133 and 129.  A call of one stage reads the vector again at its own places, and 19 M take
 // 50.8 and 52.3, 25.6 M 65.9 and 67.1, 40 M 98.3 and 99.8, and longer ones have the flat shape: it never does.  Top-k, whose first pass
-// lists as well or is read again: 19 M 62.7 and 63.7, bf16 25.6 M 73.1 and 74.0, fp32 79.4 and 79.7, 40 M 113.4 and 114.3, not
-// repeated 109.6 and 110.4, 60 M 164.2 and 162.4, not repeated 162.1 and 159.1, 100 M 277 and 269.
-constexpr uint32_t kTurnRows = 18, kTurnRowsTopk = 40;
+// lists as well or is read again, with its scatter: fp32 19 M 66.2 and 67.1, 22.5 M 75.6 and 76.4, 25.6 M 73.1 and 72.2 (the training-step
+// case), 33 M, k of a hundredth 134.5 and 131.8, 38 M 154.6 and 149.4, a thousandth 113.2 and 113.3; bf16 25.6 M 73.3 and 74.2, 29 M 80.5
+// and 80.6, 38 M, a hundredth 129.0 and 126.6.
+constexpr uint32_t kTurnRowsTopk = 24, kTurnRowsTopk16 = 28;
+constexpr uint32_t kTurnRows = 18;
 
 // element type of the gradient buffer (the accumulated vector and the residual are always fp32)
 constexpr int kGradF32 = 0, kGradF16 = 1, kGradBf16 = 2;

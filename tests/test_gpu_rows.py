@@ -22,7 +22,7 @@ def test_first_pass_on_both_sides_of_the_line(oracle, d, offset, residual):
         check_parity(oracle, g, r, 0, ratios, out, label=f"d={d} offset={offset} ec={residual} call {call}")
 
 
-@pytest.mark.parametrize("d,offset,residual", [(40 * ROW - 1, 0, True), (40 * ROW + 257, 31, True), (41 * ROW - 256, 0, False)])
+@pytest.mark.parametrize("d,offset,residual", [(24 * ROW - 1, 0, True), (24 * ROW + 257, 31, True), (25 * ROW - 256, 0, False)])
 def test_first_pass_of_top_k(oracle, d, offset, residual):
     from test_gpu_topk import check_topk, run_topk
     rng = np.random.default_rng(d + offset)
