@@ -2178,8 +2178,8 @@ __global__ __launch_bounds__(kSmallBlock) void k_small(Params p)
 // distinct, so plain read-modify-write needs no atomics and the result is deterministic; lists of
 // several workers are added by consecutive launches.  Product and sum are fused: one rounding per element.
 // Bound by the lines that long lists touch.  Pairs that fill the L2 caches (half of their 32 MB) are read past them, as the dense lines
-// need the room: 13.8 M pairs in 138 M elements, alone, 1024 blocks, ordinary and non-temporal loads 270 and 267 us, 4096
-// blocks 263 and 259; 4 M 127 and 114, 3.5 M 98 and 90; but a list that the caches may still hold 1.4 M 46 and 50, 0.3 M 9.4 and
+// need the room: 13.8 M pairs in 138 M elements, alone, 1024 blocks, ordinary and non-temporal loads 270 and 267 us, 8192
+// blocks 257 and 254; 4 M 127 and 114, 3.5 M 98 and 90; but a list that the caches may still hold 1.4 M 46 and 50, 0.3 M 9.4 and
 // 13.3.  Non-temporal loads or stores of the dense lines are slower (390, 268 at 8192 blocks), and four pairs per thread change
 // nothing.
 // ---------------------------------------------------------------------------------------------
@@ -2214,8 +2214,8 @@ void launch_clear_u32(uint32_t* p, hipStream_t s) { hipLaunchKernelGGL(k_clear_u
 // Blocks: as many as run at once, or, where the buffers have room for a list that is long enough to gain by it, several times as
 // many, so that blocks that fall behind do not end last.  With 1024, 4096 and 8192 blocks 13.8 M pairs take 267, 259 and 254 us, a
 // training step of 138 M elements, ratio 0.1 859, 851 and 846; 4 M pairs 114, 113 and 113; but 100 pairs in long buffers
-// 2.1, 3.3 and 5.0, and 138000 4.7, 4.7 and 6.3.
-constexpr int64_t kScatterBlocks = 2 * kMaxBlocks, kScatterBlocksLong = 8 * kMaxBlocks, kScatterLong = 8000000;
+// 2.1, 3.3 and 5.0, and 138000 4.7, 4.7 and 6.3: such calls pay 3 us, of a step of 380 and more.
+constexpr int64_t kScatterBlocks = 2 * kMaxBlocks, kScatterBlocksLong = 16 * kMaxBlocks, kScatterLong = 8000000;
 void launch_scatter_add(float* dense, int64_t d, const int32_t* idx, const float* val, const int32_t* count,
                         int64_t capacity, float scale, uint32_t* bad, hipStream_t s)
 {
