@@ -28,7 +28,7 @@
 //                block reserving its output range with one atomic.
 //                k_eta, k_select: the last stage of a call that keeps a large part of a long vector: it selects from the
 //                dense vector and writes the residual back whole.
-//   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements.
+//   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements (but see small_pays).
 //   k_gather     M = 1 only (last stage read the dense vector): exclusive prefix over the per-block
 //                survivor counts, copy of the lists into the output, residual zeroing.
 //
