@@ -348,19 +348,6 @@ bool writes_lists(const double* ratios, int M, double theta)
     return false;
 }
 
-// Whether one block makes the whole call (k_small).  The gamma law at mild ratios exceeds its thresholds by far more than it is
-// asked for, its closed form is the longest, and from 26000 elements on the kernels of a longer vector are faster.  A training
-// step's call and its scatter, us, in one kernel and in several: 2 stages, ratio 0.1 24000 elements 18.9 and 20.0, 28000 20.5 and 19.9,
-// 32000 21.5 and 20.0, 36864 23.1 and 21.5; 3 stages 24000 21.3 and 21.0, 28000 22.7 and 21.1, 36864 25.8 and 23.8; ratio 0.03, 2 stages
-// 28000 17.4 and 18.5, 32000 19.2 and 18.7; 0.01 18.3 and 18.2, 28000 17.2 and 18.2; one stage, 0.1 36864 16.4 and 20.2.
-constexpr int64_t kSmallMaxGamma = 26000;
-constexpr double kSmallMaxGammaRatio = 0.05;
-bool small_pays(int64_t d, int dist, const double* ratios, int M)
-{
-    if (dist == kDistGamma && M > 1 && d > kSmallMaxGamma && kept_ratio(ratios, M) >= kSmallMaxGammaRatio) return false;
-    return d <= kSmallMaxD;
-}
-
 // Whether the last stage selects from the dense vector and writes the residual back whole (k_select) although a list
 // could serve it.  Reading and writing the vector again costs the same whatever is kept; the list's writes and reads
 // grow with it, and so does the clearing of the residual, whose lines are then written in part.  A training step
@@ -544,7 +531,7 @@ int run(void* stream, const void* grad, float* residual, int64_t d, int dist, co
     };
     mark(nullptr);
 
-    if (small_pays(d, dist, ratios, M)) {
+    if (d <= kSmallMaxD) {
         p.stage = 1;
         p.L_stage = p.L[0];
         launch_small(p, s);

@@ -59,23 +59,3 @@ def test_mild_ratios(oracle, kind, d):
                     given, seen = narrow(g, kind)
                     out = run_typed(given, res, dist, delta, stages, grad_offset=1, res_offset=2)
                 check_parity(oracle, seen, res, dist, ratios, out, capacity=cap, label=label)
-
-
-@pytest.mark.parametrize("d,delta,stages,one_kernel", [(26_000, 0.1, 2, True), (26_001, 0.1, 2, False), (36_864, 0.1, 3, False),
-                                                       (36_863, 0.051, 2, False), (36_864, 0.04, 2, True), (36_864, 0.1, 1, True)])
-def test_gamma_law_at_mild_ratios_leaves_the_one_kernel(oracle, d, delta, stages, one_kernel):
-    """On both sides of each of the rule's lines; the calls that go through the kernels of a longer vector, behind each other."""
-    import paper_2101_10761_amd as sidco
-    rng = np.random.default_rng(d + stages)
-    ratios = oracle.schedule(delta, stages, 0.25)
-    sidco.sidco_set_profiling(True)
-    try:
-        for call in range(3):
-            g = (rng.standard_t(3.0, d) * 1e-3).astype(np.float32)
-            r = rng.laplace(0, 1e-3, d).astype(np.float32) if call < 2 else None
-            cap = (None, d // 50, None)[call]  # the second: the output is full long before the end
-            out = run_gpu(g, r, 1, ratios, cap=cap, grad_offset=call, res_offset=call)
-            assert ([n for n, _ in sidco.sidco_get_profile()] == ["k_small"]) == one_kernel
-            check_parity(oracle, g, r, 1, ratios, out, capacity=cap, label=f"d={d} delta {delta} M={stages} call {call}")
-    finally:
-        sidco.sidco_set_profiling(False)
