@@ -28,7 +28,7 @@
 //                block reserving its output range with one atomic.
 //                k_eta, k_select: the last stage of a call that keeps a large part of a long vector: it selects from the
 //                dense vector and writes the residual back whole.
-//   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements (but see small_pays).
+//   k_small      the whole call in one block, for a vector of at most kSmallMaxD elements.
 //   k_gather     M = 1 only (last stage read the dense vector): exclusive prefix over the per-block
 //                survivor counts, copy of the lists into the output, residual zeroing.
 //
@@ -245,12 +245,16 @@ __device__ __forceinline__ int second_row(int dist, int m)
     return m == 1 && dist == kDistGamma ? 2 : 1;
 }
 
-template <bool SHARED = false>  // the partial sums are not the first wave's
+// How a block gets at the partial sums: its first wave loads them; every thread has a share, which the block adds up; or every
+// thread loads one, and the first wave adds them up from LDS, with the same bits as in the first way.
+constexpr int kSumsWave = 0, kSumsBlock = 1, kSumsStaged = 2;
+
+template <int SUMS = kSumsWave>
 __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, bool auto_src)
 {
     const int m = p.stage;  // 1-based
     PrologueLoads g;
-    if (!SHARED && threadIdx.x < 64) {
+    if (SUMS == kSumsWave && threadIdx.x < 64) {
         const double* first = p.part_in;
         const double* second = p.part_in + (size_t)second_row(p.dist, m) * kBatchBlocks;
         const uint32_t most = ((p.nblocks - 1) & ~1u) + b.none;  // pairs past the last block's are that one's again: an unused value at most
@@ -280,6 +284,20 @@ __device__ __forceinline__ PrologueLoads prologue_load(const Params& p, Blk b, b
 struct StageSums {
     double first, second, n;
 };
+__device__ __forceinline__ StageSums prologue_sums_staged(const double* staged)
+{
+    double v[2] = {0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < kPartLoads; ++k) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            v[0] += staged[128 * k + 2 * threadIdx.x + j];
+            v[1] += staged[kMaxBlocks + 128 * k + 2 * threadIdx.x + j];
+        }
+    }
+    wave_totals(v);
+    return StageSums{v[0], v[1], 0.0};
+}
 __device__ __forceinline__ StageSums prologue_sums(const Params& p, const PrologueLoads& g)
 {
     double v[3] = {0.0, 0.0, 0.0};
@@ -486,11 +504,11 @@ template <typename T>
 __device__ __forceinline__ void present(T x) { asm volatile("" ::"v"(x)); }
 
 // Reduces the partial sums (fixed order) and evaluates eta for stage p.stage.  Returns the same values
-// in every thread of every block.  Block 0 records the stage in the diagnostics.  SHARED: `v` is the thread's share of the
-// sums (see compact_body), which the whole block adds up.
-template <bool SHARED = false>
+// in every thread of every block.  Block 0 records the stage in the diagnostics.  `v`: the thread's share of the
+// sums, `staged`: LDS for kMaxBlocks of each kind (see kSumsWave).
+template <int SUMS = kSumsWave>
 __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool auto_src, const PrologueLoads& g, const BandEdges& band = BandEdges{},
-                                                    double (*v)[3] = nullptr, double (*sh)[4] = nullptr)
+                                                    double (*v)[3] = nullptr, double (*sh)[4] = nullptr, double* staged = nullptr)
 {
     __shared__ float sh_eta[4];
     const uint32_t t = threadIdx.x;
@@ -504,7 +522,13 @@ __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool
     present(band.lo);
     present(band.hi);
     present(band.cand);
-    if constexpr (SHARED) block_sum<3>(*v, sh);
+    if constexpr (SUMS == kSumsBlock) block_sum<3>(*v, sh);
+    if constexpr (SUMS == kSumsStaged) {
+        static_assert(kMaxBlocks == kBlock, "a place for every thread");
+        staged[t] = (*v)[0];
+        staged[kMaxBlocks + t] = (*v)[1];
+        __syncthreads();
+    }
     // One wave per block evaluates the closed form - a few hundred dependent fp64 instructions, more for
     // the gamma law - and the others wait: with every wave at it, four per SIMD take turns on the same
     // arithmetic and the prologue lasts that much longer (measured).
@@ -512,7 +536,8 @@ __device__ __forceinline__ StageEta prologue_finish(const Params& p, Blk b, bool
     StageRecord rec;
     if (t < 64) {
         StageSums sums;
-        if constexpr (SHARED) sums = StageSums{(*v)[0], (*v)[1], (*v)[2]};
+        if constexpr (SUMS == kSumsBlock) sums = StageSums{(*v)[0], (*v)[1], (*v)[2]};
+        else if constexpr (SUMS == kSumsStaged) sums = prologue_sums_staged(staged);
         else sums = prologue_sums(p, g);
         r = stage_eval(p, auto_src, g, sums, rec, band);
         if (t == 0) {
@@ -1171,13 +1196,12 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
     // closed form is evaluated.
     BandEdges band = {};
     if constexpr (BANDS || CHUNKS) band = band_load<true>(p);
-    // CHUNKS: registers are short (see k_compact_batched), and the first wave's share of the partial sums would take 40
-    constexpr bool SHARED = FLAT || CHUNKS;  // the block adds the partial sums up together
-    const PrologueLoads g = prologue_load<SHARED>(p, b, false);
+    constexpr int SUMS = FLAT ? kSumsBlock : CHUNKS ? kSumsStaged : kSumsWave;
+    const PrologueLoads g = prologue_load<SUMS>(p, b, false);
     FlatLoads f;
     if constexpr (FLAT) f = flat_load(fp, p.dist);
     double share[3] = {0.0, 0.0, 0.0};
-    if constexpr (SHARED && !FLAT) {
+    if constexpr (SUMS == kSumsStaged) {
         if (threadIdx.x < p.nblocks) {
             share[0] = p.part_in[threadIdx.x];
             share[1] = p.part_in[(size_t)second_row(p.dist, 1) * kBatchBlocks + threadIdx.x];
@@ -1229,8 +1253,10 @@ __device__ __forceinline__ void compact_body(const Params& p, Blk b, const FlatP
         }
     }
     if constexpr (FLAT) flat_sums(fp, f, share);
+    static_assert(!CHUNKS || (WRITE && sizeof(ring) >= 2 * kMaxBlocks * sizeof(double)), "room for the staged sums");
+    double* const staged = reinterpret_cast<double*>(ring);  // nobody's before the threshold is known
 
-    const StageEta se = prologue_finish<SHARED>(p, b, false, g, band, &share, sh);
+    const StageEta se = prologue_finish<SUMS>(p, b, false, g, band, &share, sh, staged);
 
     uint32_t run = 0, ns = 0;
     double sy = 0.0, syy = 0.0;
@@ -2549,9 +2575,9 @@ __global__ __launch_bounds__(kBlock) void k_fit_reduce_batched(BatchArgs a)
 // CHUNKS: three blocks per CU, as without.  A batch's grid is up to 1024 blocks; with the 104 registers of eight lists asked
 // for at once 512 of them ran first and the rest after them.  With that, and the heads requested in any case, 25.6 M
 // elements in 161 tensors took 40.5 us and now 26.6 where the thresholds jump (15.0 and 12.7 where they keep still), 66 M in
-// 50 87.7 and 63.1 (20.0 and 16.4); without bands 26.5 and 63.5.  Where the partial sums are folded the block adds them up
-// together: with the first wave's way, whose 40 registers went to scratch here (46 spilled, now 17), a call of 25.6 M
-// elements in 3 tensors took 84.9 us and now 81.4, 66 M in 8 193.7 and 176.2, in 15 198.6 and 183.
+// 50 87.7 and 63.1 (20.0 and 16.4); without bands 26.5 and 63.5.  Where the partial sums are folded they are staged in
+// LDS: loaded by the first wave they are 40 registers, which went to scratch here (46 spilled, now none), and a call of 25.6 M
+// elements in 3 tensors took 84.9 us and now 80.2, 66 M in 8 193.7 and 174.2, in 15 198.6 and 180.9.
 template <bool STATS, bool WRITE, bool FLAT, bool KEEP, bool CHUNKS = false>
 __global__ __launch_bounds__(kBlock, CHUNKS ? 6 : 4) void k_compact_batched(BatchArgs a)
 {

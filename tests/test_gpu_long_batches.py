@@ -34,3 +34,19 @@ def test_pieces_and_bands(oracle, sizes, kind, dist, delta, base_offset):
             pairs.append(n)
     check_batched(oracle, g, r, offsets, delta, dist, 2, results, f"{kind} law {dist}")
     assert pairs[1] > pairs[0] + 0.002 * offsets[-1], pairs  # the second call's first pass wrote lists
+
+
+@pytest.mark.parametrize("dist", [0, 1, 2])
+@pytest.mark.parametrize("sizes", [[300, 12_000_007, 9_500_003], [1_750_001] * 12 + [64] * 9], ids=["folded", "unfolded"])
+def test_the_first_threshold_does_not_depend_on_the_calls_before(sizes, dist):
+    """The first stage's sums are grouped in one way whether or not its first pass left lists: the same bits."""
+    from test_gpu_batched import run_batched
+    offsets = [0, *np.cumsum(sizes).tolist()]
+    rng = np.random.default_rng(5)
+    g = rng.standard_normal(offsets[-1], dtype=np.float32) * np.float32(1e-3)
+    run_batched(g[:1000], None, [0, 1000], 0.01, 0, 2)  # another layout before
+    first = run_batched(g, None, offsets, 0.002, dist, 2)
+    again = run_batched(g, None, offsets, 0.002, dist, 2)
+    for a, b in zip(first, again):
+        np.testing.assert_array_equal(a.stats[0].view(np.uint64), b.stats[0].view(np.uint64))
+        assert a.etas[0] == b.etas[0]

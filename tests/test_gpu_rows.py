@@ -45,3 +45,15 @@ def test_calls_of_one_stage_and_dgc(oracle, d, offset):
     check_parity(oracle, g, r, 0, [0.001], out, label=f"d={d} one stage")
     out = run_dgc(g, r, 0.001, 0.01, 3, grad_offset=offset, res_offset=offset)
     check_dgc(oracle, g, r, 0.001, 0.01, 3, out, label=f"d={d} DGC")
+
+
+@pytest.mark.parametrize("d,offset", [(10 * ROW + 3, 3), (18 * ROW + 257, 31)])
+@pytest.mark.parametrize("dist", [0, 1, 2])
+def test_the_first_threshold_does_not_depend_on_the_calls_before(d, offset, dist):
+    """With bands or without: the same sums, to the last bit."""
+    rng = np.random.default_rng(d)
+    g = rng.standard_normal(d, dtype=np.float32)
+    run_gpu(g[:1000], None, 0, [0.1])  # another shape before
+    first, again = (run_gpu(g, None, dist, [0.25, 0.004], grad_offset=offset) for _ in range(2))
+    np.testing.assert_array_equal(first.stats[0].view(np.uint64), again.stats[0].view(np.uint64))
+    assert first.etas[0] == again.etas[0]
